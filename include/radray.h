@@ -302,10 +302,14 @@ int rr_set_paths(rr_ctx *ctx, const rr_paths *src, int64_t n);
  *          channel and chirp; RR_SEPARABLE: the channel part of the length
  *          uses f0 and chirp 0 (a per-channel factor times a per-(chirp,
  *          sample) factor), which allows the complex-GEMM engine.
+ *   Paths whose every hit lies on an object of zero velocity add the same to
+ *   every chirp: each engine sums them once and adds the moving paths chirp
+ *   by chirp.
  *   engine RR_DIRECT_FP32 (either model), RR_GEMM_BF16X3 (separable only:
- *          split-bf16 hi+lo complex GEMM on MFMA, FP32 accumulation; each
- *          chirp's samples are computed in whole tiles of 64; relative error
- *          bar 1e-3), RR_GEMM_EXACT (exact model only, full cube: split-bf16
+ *          split-bf16 hi+lo complex products on MFMA, FP32 accumulation;
+ *          the moving paths as one complex GEMM where its padding, 256
+ *          channels, 64 samples and 96 paths, leaves it the cheaper form;
+ *          relative error bar 1e-3), RR_GEMM_EXACT (exact model only, full cube: split-bf16
  *          complex products on the matrix cores of FP64-reduced leg phases,
  *          held to the exact model's 1e-4 bar; either one (Tx x paths) by
  *          (paths x Rx) product per (chirp, sample) in square tiles of 16,
@@ -340,7 +344,7 @@ int rr_synthesize(rr_ctx *ctx, int32_t model, int32_t engine, void *cube_dev, in
  * data (one synthesis record per path and the path range of each transmitter
  * group) live in a fixed scratch area of the library: at most
  * RR_NOALLOC_MAX_PATHS paths and RR_NOALLOC_MAX_TX transmitters (per-element
- * launch), about 13.7 MB that every GPU the library runs on holds from the
+ * launch), about 14.1 MB that every GPU the library runs on holds from the
  * first rr_create on it until the process ends.  Inputs are the context's
  * paths, array, chirp and object velocities; cube_dev (caller-owned,
  * complex64 [n_ch][n_chirps][n_samples], cube_elems complex elements) is

@@ -26,6 +26,13 @@
 // hi*hi + hi*lo + lo*hi, FP32 accumulation (as the separable GEMM).  Several
 // path splits write partial tiles that a second kernel adds in split order
 // (deterministic).
+//
+// The paths at rest add the same to every chirp: they are summed once, as one
+// chirp, and the moving paths' products are added to that sum as each chirp
+// is stored (traced streets hold 0.05-4 % moving paths: the street's 12 x 16
+// per-element cube of 2.6e5 paths, 128 chirps x 256 samples, 9.0 -> 0.24 ms).
+// The separable model runs here too, with its own legs (X: f0 and the sample
+// phase over the phase-centre length, Y: the receiver offset at f0).
 #include "rr_internal.h"
 
 namespace {
@@ -57,32 +64,14 @@ __device__ __forceinline__ double dist3(const double *a, const double *b)
     return sqrt(dx * dx + dy * dy + dz * dz);
 }
 
-// The paths of a synthesis: n records from `paths`, or, with rng_lo given,
-// the records *rng_lo .. *rng_hi of `paths`, read on the device (a batched
-// launch knows its scenes' path ranges only there), at most Ppad of them (the
-// caller checks the count against its capacity afterwards).
-struct PathRange {
-    const SynPath *paths;
-    int64_t n;
-    const int64_t *rng_lo, *rng_hi;
-};
-
-// the path records and count of a synthesis, and the padded count the
-// product reads (a multiple of FQ_PAD; table entries beyond it are not needed)
-__device__ __forceinline__ void path_range(const PathRange &R, int64_t Ppad, const SynPath *&p,
-                                           int64_t &n, int64_t &used)
+// the path records and count of a synthesis, read on the device, and the
+// padded count the product reads (a multiple of FQ_PAD; table entries beyond
+// it are not needed)
+__device__ __forceinline__ int64_t path_count(const int64_t *lo, const int64_t *hi, int64_t Ppad)
 {
-    if (R.rng_lo) {
-        const int64_t lo = *R.rng_lo, hi = *R.rng_hi;
-        p = R.paths + lo;
-        n = min(max(hi - lo, (int64_t)0), Ppad);
-        used = (n + FQ_PAD - 1) / FQ_PAD * FQ_PAD;
-    } else {
-        p = R.paths;
-        n = R.n;
-        used = Ppad;
-    }
+    return min(max(*hi - *lo, (int64_t)0), Ppad);
 }
+__device__ __forceinline__ int64_t pad_count(int64_t n) { return (n + FQ_PAD - 1) / FQ_PAD * FQ_PAD; }
 
 // Leg tables, one thread per path over a share of the chirps: the first and
 // last hit point at chirp time and the length between them, then per element
@@ -91,17 +80,17 @@ __device__ __forceinline__ void path_range(const PathRange &R, int64_t Ppad, con
 // the amplitude (0 beyond the path count) and source.  OWN_TX (per-element
 // launch, sample split): the channels of transmitter t read only the paths of
 // t's group, so only each path's own transmitter word is kept, xt[m][0][p].
-template <bool OWN_TX>
-__global__ __launch_bounds__(256) void k_freq_legs(PathRange PR, int64_t Ppad, int M, double t_rep,
-                                                   const double *tx, int T, const double *rx,
-                                                   int R, double f0c, double dfc, uint2 *xt,
-                                                   uint2 *yt, float *amp, int32_t *src)
+// SEP (separable model): beta of X is f0 (D(m) + dT_t) / c and its gamma that
+// of D(m), the length through the phase centres; Y is the receiver offset
+// f0 dR_r / c alone, both offsets at chirp 0.
+template <bool OWN_TX, bool SEP>
+__global__ __launch_bounds__(256) void k_freq_legs(FreqLegs A, int64_t Ppad, uint2 *xt, uint2 *yt,
+                                                   float *amp, int32_t *src)
 {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const SynPath *paths;
-    int64_t n, used;
-    path_range(PR, Ppad, paths, n, used);
-    if (p >= used) return;
+    const int64_t n = path_count(A.rng_lo, A.rng_hi, Ppad);
+    if (p >= pad_count(n)) return;
+    const int M = A.M, R = A.R, T = A.T;
     const int XR = OWN_TX ? 1 : T;
     if (p >= n) {
         for (int m = blockIdx.y; m < M; m += gridDim.y) {
@@ -114,10 +103,11 @@ __global__ __launch_bounds__(256) void k_freq_legs(PathRange PR, int64_t Ppad, i
         }
         return;
     }
-    const SynPath &P = paths[p];
+    const SynPath &P = A.paths[*A.rng_lo + p];
     const int K = P.K;
     const int t_own = OWN_TX ? min(max(P.src, 0), T - 1) : 0;
     double h[RR_KMAX][3], v[RR_KMAX][3];   // the path's points, held over the chirps
+    double os[3], e0 = 0.0, ek = 0.0;      // SEP: source, its and oR's chirp-0 legs
 #pragma unroll
     for (int j = 0; j < RR_KMAX; j++)
 #pragma unroll
@@ -125,8 +115,13 @@ __global__ __launch_bounds__(256) void k_freq_legs(PathRange PR, int64_t Ppad, i
             h[j][a] = j < K ? P.P[j][a] : 0.0;
             v[j][a] = j < K ? P.V[j][a] : 0.0;
         }
+    if (SEP) {
+        for (int a = 0; a < 3; a++) os[a] = P.src >= 0 ? A.tx[3 * P.src + a] : A.oT[a];
+        e0 = dist3(h[0], os);
+        ek = dist3(A.oR, P.P[K - 1]);
+    }
     for (int m = blockIdx.y; m < M; m += gridDim.y) {
-        const double tau = (double)m * t_rep;
+        const double tau = (double)m * A.t_rep;
         double q1[3], qk[3], inner = 0.0;
         for (int a = 0; a < 3; a++) q1[a] = h[0][a] + v[0][a] * tau;
         for (int a = 0; a < 3; a++) qk[a] = q1[a];
@@ -138,15 +133,17 @@ __global__ __launch_bounds__(256) void k_freq_legs(PathRange PR, int64_t Ppad, i
             inner += dist3(q, qk);
             for (int a = 0; a < 3; a++) qk[a] = q[a];
         }
+        const double D = SEP ? dist3(q1, os) + inner + dist3(A.oR, qk) : 0.0;
         uint2 *xo = xt + (int64_t)m * XR * Ppad + p;
         for (int i = 0; i < XR; i++) {
-            const double d = dist3(q1, tx + 3 * (OWN_TX ? t_own : i)) + inner;
-            xo[(int64_t)i * Ppad] = make_uint2(turns_u32(d * f0c), turns_u32(d * dfc));
+            const double *e = A.tx + 3 * (OWN_TX ? t_own : i);
+            const double d = SEP ? D + (dist3(h[0], e) - e0) : dist3(q1, e) + inner;
+            xo[(int64_t)i * Ppad] = make_uint2(turns_u32(d * A.f0c), turns_u32((SEP ? D : d) * A.dfc));
         }
         uint2 *yo = yt + (int64_t)m * R * Ppad + p;
         for (int i = 0; i < R; i++) {
-            const double d = dist3(rx + 3 * i, qk);
-            yo[(int64_t)i * Ppad] = make_uint2(turns_u32(d * f0c), turns_u32(d * dfc));
+            const double d = SEP ? dist3(A.rx + 3 * i, P.P[K - 1]) - ek : dist3(A.rx + 3 * i, qk);
+            yo[(int64_t)i * Ppad] = make_uint2(turns_u32(d * A.f0c), SEP ? 0u : turns_u32(d * A.dfc));
         }
     }
     if (blockIdx.y == 0) {
@@ -285,12 +282,15 @@ struct FreqArgs {
     int tt, rt;               // Tx and Rx tiles
     int kg;                   // groups of FQ_G samples
     int n_split;
-    int64_t split_len;        // paths per split (multiple of FQ_PAD)
-    float2 *out;              // cube (one split) or partial tiles [split][m][k][T][R]
+    // cube (one split), or partial sums: tiles [split][m][k][T][R], sample
+    // split [split][channel][m][k]
+    float2 *out;
     int partial;
-    // with rng_lo: the path count is *rng_hi - *rng_lo (at most Ppad), read
-    // on the device, and the splits divide its padded count evenly
+    const float2 *rest;       // cube only: [channel][k] added to every chirp, or NULL
+    // the path count is *rng_hi - *rng_lo (at most Ppad), read on the device;
+    // the splits divide its padded count evenly
     const int64_t *rng_lo, *rng_hi;
+    int64_t gate_lo, gate_hi; // nothing is done unless gate_lo < count <= gate_hi
     // sample split (one channel per wavefront): k = k1 S + k2, S = 2^S_log2
     int S, S_log2;
     int64_t n_waves;
@@ -330,6 +330,10 @@ void k_freq_gemm(FreqArgs A)
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // the sample group fastest: the workgroups that share one split's tables
     // run together
+    const int64_t n = path_count(A.rng_lo, A.rng_hi, A.Ppad);
+    if (n <= A.gate_lo || n > A.gate_hi) return;
+    const int64_t used = pad_count(n);
+    const int64_t split_len = pad_count((used + A.n_split - 1) / A.n_split);
     int64_t id = blockIdx.x;
     const int kq = (int)(id % A.kg);
     id /= A.kg;
@@ -342,12 +346,6 @@ void k_freq_gemm(FreqArgs A)
     const int kw = kq * FQ_G + w;
     const bool kv = kw < A.K;
     const unsigned ku = (unsigned)(kv ? kw : A.K - 1);
-    int64_t used = A.Ppad, split_len = A.split_len;
-    if (A.rng_lo) {
-        const int64_t n = min(max(*A.rng_hi - *A.rng_lo, (int64_t)0), A.Ppad);
-        used = (n + FQ_PAD - 1) / FQ_PAD * FQ_PAD;
-        split_len = ((used + A.n_split - 1) / A.n_split + FQ_PAD - 1) / FQ_PAD * FQ_PAD;
-    }
     const int64_t pstart = (int64_t)s * split_len;
     const int64_t nsteps = max(min(used, pstart + split_len) - pstart, (int64_t)0) / STEP;
     // an empty split still writes its (zero) tile; its loads stay at path 0
@@ -472,10 +470,13 @@ void k_freq_gemm(FreqArgs A)
                 const int ro = r0 + BS * j + lrow;
                 if (to < A.T && ro < A.R) {
                     const float2 v = make_float2(sr[i][j][e], si[i][j][e]);
-                    if (A.partial)
+                    const int64_t c = (int64_t)to * A.R + ro;
+                    if (A.partial) {
                         A.out[((((int64_t)s * A.M + m) * A.K + kw) * A.T + to) * A.R + ro] = v;
-                    else
-                        A.out[(((int64_t)to * A.R + ro) * A.M + m) * A.K + kw] = v;
+                    } else {
+                        const float2 b = A.rest ? A.rest[c * A.K + kw] : make_float2(0.0f, 0.0f);
+                        A.out[(c * A.M + m) * A.K + kw] = make_float2(v.x + b.x, v.y + b.y);
+                    }
                 }
             }
 }
@@ -512,12 +513,10 @@ __global__ __launch_bounds__(FQ_G * 64, (!PER_EL && QB * SB == 1) ? 3 : 2) void 
     const int m = (int)(id % A.M);
     const int s = (int)(id / A.M);
     const int t = c / A.R, r = c - t * A.R;
-    int64_t used = A.Ppad, split_len = A.split_len;
-    if (A.rng_lo) {
-        const int64_t n = min(max(*A.rng_hi - *A.rng_lo, (int64_t)0), A.Ppad);
-        used = (n + FQ_PAD - 1) / FQ_PAD * FQ_PAD;
-        split_len = ((used + A.n_split - 1) / A.n_split + FQ_PAD - 1) / FQ_PAD * FQ_PAD;
-    }
+    const int64_t n = path_count(A.rng_lo, A.rng_hi, A.Ppad);
+    if (n <= A.gate_lo || n > A.gate_hi) return;
+    const int64_t used = pad_count(n);
+    int64_t split_len = pad_count((used + A.n_split - 1) / A.n_split);
     // the paths this channel reads: all, or (per-element) its transmitter's
     // group widened to whole 32-path steps (the paths of neighbouring groups
     // in the edge steps are masked by their source below)
@@ -658,34 +657,91 @@ __global__ __launch_bounds__(FQ_G * 64, (!PER_EL && QB * SB == 1) ? 3 : 2) void 
                 const int k = kk1 * A.S + kk2;
                 if (kk2 >= A.S || k >= A.K) continue;
                 const float2 v = make_float2(sr[i][j][e], si[i][j][e]);
-                if (A.partial)
-                    A.out[((((int64_t)s * A.M + m) * A.K + k) * A.T + t) * A.R + r] = v;
-                else
-                    A.out[((int64_t)c * A.M + m) * A.K + k] = v;
+                if (A.partial) {
+                    A.out[(((int64_t)s * C + c) * A.M + m) * A.K + k] = v;
+                } else {
+                    const float2 b = A.rest ? A.rest[(int64_t)c * A.K + k] : make_float2(0.0f, 0.0f);
+                    A.out[((int64_t)c * A.M + m) * A.K + k] = make_float2(v.x + b.x, v.y + b.y);
+                }
             }
 }
 
-// cube[(t R + r) M + m][k] = sum over splits, in split order
-__global__ void k_freq_reduce(const float2 *part, int n_split, int T, int R, int M, int K,
-                              float2 *cube)
+// the launch whose partial sums a reduction adds did its work (see FreqArgs)
+__device__ __forceinline__ bool gated(const FreqArgs &A)
+{
+    const int64_t n = path_count(A.rng_lo, A.rng_hi, A.Ppad);
+    return n <= A.gate_lo || n > A.gate_hi;
+}
+
+// tiles: cube[c][m][k] = rest[c][k] + sum over splits, in split order, of
+// part[split][m][k][c].  The partial sums run over channels, the cube over
+// samples: 32 x 32 entries pass through LDS so that both sides are read and
+// written in whole 256-byte runs (one entry per lane and 8-byte stores a
+// sweep apart took 76 us for the hand's 8 836 x 128 cube).
+__global__ __launch_bounds__(256) void k_freq_reduce(FreqArgs A, float2 *cube)
+{
+    __shared__ float2 sh[32][33];
+    if (gated(A)) return;
+    const int C = A.T * A.R;
+    const int cb = (C + 31) / 32, kb = (A.K + 31) / 32;
+    int64_t id = blockIdx.x;
+    const int c0 = (int)(id % cb) * 32;
+    id /= cb;
+    const int k0 = (int)(id % kb) * 32, m = (int)(id / kb);
+    const int x = threadIdx.x & 31, y = threadIdx.x >> 5;
+    const int64_t per = (int64_t)A.M * A.K * C;
+    const float2 *part = A.out;
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        const int k = k0 + y + 8 * q, c = c0 + x;
+        float2 v = make_float2(0.0f, 0.0f);
+        if (k < A.K && c < C) {
+            const float2 *p = part + ((int64_t)m * A.K + k) * C + c;
+#pragma unroll 8
+            for (int s = 0; s < A.n_split; s++) {
+                const float2 u = p[s * per];
+                v.x += u.x;
+                v.y += u.y;
+            }
+        }
+        sh[y + 8 * q][x] = v;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        const int c = c0 + y + 8 * q, k = k0 + x;
+        if (k < A.K && c < C) {
+            float2 v = sh[x][y + 8 * q];
+            if (A.rest) {
+                const float2 b = A.rest[(int64_t)c * A.K + k];
+                v.x += b.x;
+                v.y += b.y;
+            }
+            cube[((int64_t)c * A.M + m) * A.K + k] = v;
+        }
+    }
+}
+
+// sample split: the same with part[split][c][m][k], entry by entry
+__global__ __launch_bounds__(256) void k_freq_sum(FreqArgs A, float2 *cube)
 {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t per = (int64_t)M * K * T * R;
-    if (g >= per) return;
-    // g enumerates (m, k, t, r) with r fastest: coalesced partial reads
-    const int r = (int)(g % R);
-    int64_t q = g / R;
-    const int t = (int)(q % T);
-    q /= T;
-    const int k = (int)(q % K);
-    const int m = (int)(q / K);
-    float re = 0.0f, im = 0.0f;
-    for (int s = 0; s < n_split; s++) {
-        const float2 v = part[(int64_t)s * per + g];
-        re += v.x;
-        im += v.y;
+    const int64_t per = (int64_t)A.T * A.R * A.M * A.K;
+    if (g >= per || gated(A)) return;
+    const float2 *part = A.out;
+    float2 v = make_float2(0.0f, 0.0f);
+#pragma unroll 8
+    for (int s = 0; s < A.n_split; s++) {
+        const float2 u = part[s * per + g];
+        v.x += u.x;
+        v.y += u.y;
     }
-    cube[(((int64_t)t * R + r) * M + m) * K + k] = make_float2(re, im);
+    if (A.rest) {
+        const float2 b = A.rest[g / ((int64_t)A.M * A.K) * A.K + g % A.K];
+        v.x += b.x;
+        v.y += b.y;
+    }
+    cube[g] = v;
 }
 
 }  // namespace
@@ -693,25 +749,24 @@ __global__ void k_freq_reduce(const float2 *part, int n_split, int T, int R, int
 int freq_k_step() { return FQ_PAD; }
 int freq_k_group() { return FQ_G; }
 
-hipError_t launch_freq_prep(const SynPath *paths, int64_t n, const int64_t *rng_lo,
-                            const int64_t *rng_hi, int64_t Ppad, int M, double t_rep,
-                            const double *tx, int T, bool own_tx, const double *rx, int R,
-                            double f0c, double dfc, uint2 *xt, uint2 *yt, float *amp, int32_t *src,
-                            hipStream_t s)
+hipError_t launch_freq_prep(const FreqLegs &L, int64_t Ppad, bool own_tx, uint2 *xt, uint2 *yt,
+                            float *amp, int32_t *src, hipStream_t s)
 {
-    if (M <= 0 || Ppad <= 0) return hipSuccess;
-    PathRange PR{paths, n, rng_lo, rng_hi};
+    if (L.M <= 0 || Ppad <= 0) return hipSuccess;
     // one thread per path; the chirps shared over enough workgroups to fill
     // the chip (each thread keeps its path's points over its chirps)
     const int64_t bx = (Ppad + 255) / 256;
-    const int by = (int)std::min<int64_t>(M, std::max<int64_t>(1, (4096 + bx - 1) / bx));
+    const int by = (int)std::min<int64_t>(L.M, std::max<int64_t>(1, (4096 + bx - 1) / bx));
     const dim3 g((unsigned)bx, (unsigned)by);
-    if (own_tx)
-        hipLaunchKernelGGL(k_freq_legs<true>, g, dim3(256), 0, s, PR, Ppad, M, t_rep, tx, T, rx, R,
-                           f0c, dfc, xt, yt, amp, src);
-    else
-        hipLaunchKernelGGL(k_freq_legs<false>, g, dim3(256), 0, s, PR, Ppad, M, t_rep, tx, T, rx, R,
-                           f0c, dfc, xt, yt, amp, src);
+#define LEGS(O, S) hipLaunchKernelGGL((k_freq_legs<O, S>), g, dim3(256), 0, s, L, Ppad, xt, yt, amp, src)
+    if (L.sep) {
+        if (own_tx) LEGS(true, true);
+        else LEGS(false, true);
+    } else {
+        if (own_tx) LEGS(true, false);
+        else LEGS(false, false);
+    }
+#undef LEGS
     return hipGetLastError();
 }
 
@@ -801,55 +856,56 @@ int64_t freq_table_entries(int T, int R, int M, int64_t Ppad, bool own_tx)
     return (int64_t)M * ((own_tx ? 1 : T) + R) * Ppad;
 }
 
-void freq_splits(int tile, int T, int R, int M, int K, int64_t Ppad, int &n_split, int64_t &split_len)
+// Path splits, by the shape alone (a batched launch does not know its path
+// counts): enough workgroups to fill the chip, which the many chirps of
+// moving paths do by themselves.
+int freq_splits(int tile, int T, int R, int M, int K)
 {
-    // enough workgroups to fill the chip four times over (one per CU at a
-    // time), at least 16 steps of paths each
-    int64_t groups;
     if (tile == 1) {
-        groups = ((int64_t)M * T * R + FQ_G - 1) / FQ_G;
-    } else {
-        const int64_t kg = (K + FQ_G - 1) / FQ_G;
-        groups = (int64_t)M * kg * ((T + tile - 1) / tile) * ((R + tile - 1) / tile);
+        const int64_t groups = ((int64_t)M * T * R + FQ_G - 1) / FQ_G;
+        const int64_t want = M == 1 ? 2048 : 256;
+        return (int)std::min<int64_t>(128, std::max<int64_t>(1, (want + groups - 1) / groups));
     }
-    int64_t ns = std::max<int64_t>(1, (1024 + groups - 1) / groups);
-    ns = std::min<int64_t>(ns, std::max<int64_t>(1, Ppad / (16 * FQ_PAD)));
-    int64_t len = (Ppad + ns - 1) / ns;
-    len = (len + FQ_PAD - 1) / FQ_PAD * FQ_PAD;
-    n_split = (int)((Ppad + len - 1) / len);
-    split_len = len;
+    const int64_t kg = (K + FQ_G - 1) / FQ_G;
+    const int64_t groups = (int64_t)M * kg * ((T + tile - 1) / tile) * ((R + tile - 1) / tile);
+    return (int)std::min<int64_t>(128, std::max<int64_t>(1, (1024 + groups - 1) / groups));
 }
 
-hipError_t launch_freq_gemm(const uint2 *xt, const uint2 *yt, const float *amp, const int32_t *src,
-                            int T, int R, int M, int K, int64_t Ppad, int n_split, int64_t split_len,
-                            int per_element, int tile, const int64_t *rng_lo, const int64_t *rng_hi,
-                            const int64_t *groups, float2 *partial, float2 *cube, hipStream_t s)
+int freq_mov_tile(int tile, int K, bool per_element)
 {
-    if ((int64_t)n_split * split_len < Ppad || split_len % FQ_PAD || Ppad % FQ_PAD || Ppad <= 0)
-        return hipErrorInvalidValue;
+    return !per_element && K <= FQ_KS_KMAX ? 1 : tile;
+}
+
+hipError_t launch_freq_gemm(const FreqSum &q, hipStream_t s)
+{
+    const int tile = q.tile, T = q.T, R = q.R, M = q.M, K = q.K;
+    if (q.Ppad % FQ_PAD || q.Ppad <= 0 || !q.rng_lo || !q.rng_hi) return hipErrorInvalidValue;
     if (tile != 1 && tile != 16 && tile != 32 && tile != 48 && tile != 64 && tile != 96)
         return hipErrorInvalidValue;
     if (tile == 1 && K > FQ_KS_KMAX) return hipErrorInvalidValue;
+    const int n_split = freq_splits(tile, T, R, M, K);
     FreqArgs A;
-    A.xt = xt;
-    A.yt = yt;
-    A.amp = amp;
-    A.src = src;
+    A.xt = q.xt;
+    A.yt = q.yt;
+    A.amp = q.amp;
+    A.src = q.src;
     A.T = T;
     A.R = R;
     A.M = M;
     A.K = K;
-    A.Ppad = Ppad;
+    A.Ppad = q.Ppad;
     A.tt = (T + tile - 1) / tile;
     A.rt = (R + tile - 1) / tile;
     A.kg = (K + FQ_G - 1) / FQ_G;
     A.n_split = n_split;
-    A.split_len = split_len;
     A.partial = n_split > 1;
-    A.out = n_split > 1 ? partial : cube;
-    A.rng_lo = rng_lo;
-    A.rng_hi = rng_hi;
-    A.groups = tile == 1 && per_element ? groups : nullptr;
+    A.out = n_split > 1 ? q.partial : q.cube;
+    A.rest = q.rest;
+    A.rng_lo = q.rng_lo;
+    A.rng_hi = q.rng_hi;
+    A.gate_lo = q.gate_lo;
+    A.gate_hi = q.gate_hi;
+    A.groups = tile == 1 && q.per_element ? q.groups : nullptr;
     int qb = 1, sb = 1;
     ks_shape(K, qb, sb, A.S, A.S_log2);
     A.n_waves = (int64_t)n_split * M * T * R;
@@ -857,7 +913,7 @@ hipError_t launch_freq_gemm(const uint2 *xt, const uint2 *yt, const float *amp, 
                                      : (int64_t)n_split * M * A.tt * A.rt * A.kg;
     if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
     const dim3 g((unsigned)blocks), t(FQ_G * 64);
-    const bool pe = per_element != 0;
+    const bool pe = q.per_element != 0;
 #define KS_LAUNCH(QB, SB)                                                                         \
     do {                                                                                          \
         if (pe) hipLaunchKernelGGL((k_freq_ks<true, QB, SB>), g, t, 0, s, A);                     \
@@ -882,10 +938,12 @@ hipError_t launch_freq_gemm(const uint2 *xt, const uint2 *yt, const float *amp, 
     }
 #undef FQ_LAUNCH
 #undef KS_LAUNCH
-    if (n_split > 1) {
+    if (n_split > 1 && tile == 1) {
         const int64_t per = (int64_t)M * K * T * R;
-        hipLaunchKernelGGL(k_freq_reduce, dim3((unsigned)((per + 255) / 256)), dim3(256), 0, s,
-                           partial, n_split, T, R, M, K, cube);
+        hipLaunchKernelGGL(k_freq_sum, dim3((unsigned)((per + 255) / 256)), dim3(256), 0, s, A, q.cube);
+    } else if (n_split > 1) {
+        const int64_t nb = (int64_t)((T * R + 31) / 32) * ((K + 31) / 32) * M;
+        hipLaunchKernelGGL(k_freq_reduce, dim3((unsigned)nb), dim3(256), 0, s, A, q.cube);
     }
     return hipGetLastError();
 }

@@ -243,7 +243,9 @@ __device__ __forceinline__ bf16x8 as_bf(uint4 v) { return __builtin_bit_cast(bf1
 __global__ __launch_bounds__(GM_THREADS, 1) void k_gemm(const uint4 *__restrict__ Af,
                                                         const uint4 *__restrict__ Bp, int RB,
                                                         int KB, int Ppad, int C, int M, int K,
-                                                        int n_col_tiles, float2 *__restrict__ cube)
+                                                        int n_col_tiles,
+                                                        const float2 *__restrict__ rest,
+                                                        float2 *__restrict__ cube)
 {
     // B: three buffers x 6 planes x column blocks, each fragment 64 lanes x
     // 16 B with 64 B of padding after lane 31, so that the generator's
@@ -460,8 +462,11 @@ __global__ __launch_bounds__(GM_THREADS, 1) void k_gemm(const uint4 *__restrict_
                 const int row = (rb0 + i) * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
                 const int k = k0 + j * 32 + (lane & 31);
                 const float a = p1[i][j][e], b = p2[i][j][e];
-                if (row < C && k < K)
-                    cube[((int64_t)row * M + m) * K + k] = make_float2(a - b, p3[i][j][e] - a - b);
+                if (row < C && k < K) {
+                    const float2 z = rest ? rest[(int64_t)row * K + k] : make_float2(0.0f, 0.0f);
+                    cube[((int64_t)row * M + m) * K + k] =
+                        make_float2(z.x + (a - b), z.y + (p3[i][j][e] - a - b));
+                }
             }
 }
 
@@ -502,7 +507,7 @@ hipError_t launch_gemm_prep_b(const SynthArgs &a, int Ppad, uint4 *Bp, hipStream
 }
 
 hipError_t launch_gemm_main(const uint4 *Af, const uint4 *Bp, int Cpad, int Ppad, int C, int M,
-                            int K, float2 *cube, hipStream_t s)
+                            int K, const float2 *rest, float2 *cube, hipStream_t s)
 {
     const int RB = Cpad / 32, KB = Ppad / GM_KS;
     const int64_t n_col_tiles = (int64_t)M * ((K + GM_TN - 1) / GM_TN);
@@ -510,6 +515,6 @@ hipError_t launch_gemm_main(const uint4 *Af, const uint4 *Bp, int Cpad, int Ppad
     if (n_col_tiles > INT32_MAX || blocks > UINT32_MAX) return hipErrorInvalidValue;
     if (blocks <= 0 || KB <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_gemm, dim3((unsigned)blocks), dim3(GM_THREADS), 0, s, Af, Bp, RB, KB, Ppad,
-                       C, M, K, (int)n_col_tiles, cube);
+                       C, M, K, (int)n_col_tiles, rest, cube);
     return hipGetLastError();
 }

@@ -10,9 +10,15 @@
 // both as 32-bit fixed-point turns in an LDS table.  A lane then forms the
 // start phase of its run exactly in integer arithmetic (beta + k0 gamma modulo
 // 2^32), takes the hardware sin/cos of it and of the step (input in turns),
-// and walks the run by complex rotation, accumulating in FP32 registers.  A
-// second kernel evaluates individual cube entries fully in FP64 for checks at
-// sizes where the whole cube is not needed.
+// and walks the run by complex rotation, accumulating in FP32 registers.
+//
+// A path whose every hit rests adds the same to every chirp, so the records
+// come in two parts (paths at rest, moving paths): the first part is summed
+// once, into chirp 0 of the cube (k_synth_rest), and the sum over the moving
+// paths is added to it chirp by chirp (k_synth_direct).  On the street, where
+// 99.8 % of the paths lie on the static ground, that is 1/128 of the work.
+// A further kernel evaluates individual cube entries fully in FP64 for checks
+// at sizes where the whole cube is not needed.
 #include <algorithm>
 
 #include "rr_internal.h"
@@ -88,10 +94,13 @@ __device__ __forceinline__ float turns_f32(unsigned u)
     return (float)(int)u * 2.3283064365386963e-10f;
 }
 
-// One workgroup tile: rows rb * RPB .. of group g (a Tx in the per-element
-// mode, everything in the shared mode), every sample of those rows.
+// One workgroup tile of the moving paths: rows rb * RPB .. of group g (a Tx in
+// the per-element mode, everything in the shared mode), every sample of those
+// rows, row = (m - m0) RC + channel of the group; chirp 0 of the cube, the sum
+// over the paths at rest, is added.  Chirp 0 itself is a launch of its own
+// (m0 = 0, one row per channel) after every other chirp has read it.
 template <int KR>
-__device__ void synth_block(const SynthArgs &A, int g, int rb, int rows_per_group, int RC,
+__device__ void synth_block(const SynthArgs &A, int g, int rb, int rows_per_group, int RC, int m0,
                             SynPath *sp, uint2 *tab)
 {
     const int TPR = A.K / KR;
@@ -105,8 +114,8 @@ __device__ void synth_block(const SynthArgs &A, int g, int rb, int rows_per_grou
     float are[KR], aim[KR];
 #pragma unroll
     for (int k = 0; k < KR; k++) { are[k] = 0.0f; aim[k] = 0.0f; }
-    const int64_t p0 = A.ranges[g];
-    const int64_t p1 = A.p_limit > 0 ? min(A.ranges[g + 1], p0 + A.p_limit) : A.ranges[g + 1];
+    const int64_t p0 = A.mranges[g];
+    const int64_t p1 = A.p_limit > 0 ? min(A.mranges[g + 1], p0 + A.p_limit) : A.mranges[g + 1];
     const int chunk = min(SYN_CHUNK, SYN_TAB / RPB);
     for (int64_t base = p0; base < p1; base += chunk) {
         const int cnt = (int)min((int64_t)chunk, p1 - base);
@@ -124,7 +133,7 @@ __device__ void synth_block(const SynthArgs &A, int g, int rb, int rows_per_grou
             const int rw = rb * RPB + l;
             uint2 v = make_uint2(0u, 0u);
             if (rw < rows_per_group) {
-                const int m = rw / RC, cc = rw - (rw / RC) * RC;
+                const int m = m0 + rw / RC, cc = rw - (rw / RC) * RC;
                 const int c = A.shared ? cc : g * A.nrx + cc;
                 const int t = c / A.nrx, r = c - (c / A.nrx) * A.nrx;
                 const double tx[3] = {A.tx[3 * t], A.tx[3 * t + 1], A.tx[3 * t + 2]};
@@ -157,66 +166,202 @@ __device__ void synth_block(const SynthArgs &A, int g, int rb, int rows_per_grou
         }
     }
     if (!valid) return;
-    const int m = row / RC, cc = row - (row / RC) * RC;
+    const int m = m0 + row / RC, cc = row - (row / RC) * RC;
     const int c = A.shared ? cc : g * A.nrx + cc;
+    const float2 *rest = A.cube + (int64_t)c * A.M * A.K + k0;
     float2 *out = A.cube + ((int64_t)c * A.M + m) * A.K + k0;
 #pragma unroll
-    for (int k = 0; k < KR; k++) out[k] = make_float2(are[k], aim[k]);
+    for (int k = 0; k < KR; k++) {
+        const float2 b = rest[k];
+        out[k] = make_float2(b.x + are[k], b.y + aim[k]);
+    }
+}
+
+// Chirp 0 of channel c: the sum over the paths at rest of its group, by one
+// workgroup.  TPR lanes (a power of two) cover the samples, KR each; the other
+// lanes take the same samples of every (REST_T / TPR)-th path, so that a few
+// channels of many paths still fill a compute unit's lanes (the tiny scene's
+// 4 channels of 2 400 paths and 16 chirps: 20 us here and 2 x 9 us for the
+// moving part, against 1.47 ms for the sum of all paths chirp by chirp), and the lanes' sums are added in a fixed order: across the
+// wavefront, then over the wavefronts through LDS.
+#define REST_T 512
+struct RestLds {
+    uint2 tab[REST_T];        // (beta, gamma) of the chunk's paths
+    float amp[REST_T];
+    float2 red[REST_T * 8];   // partial sums, eight samples a lane at a time
+};
+template <int KR>
+__device__ void rest_block(const SynthArgs &A, int c, int TPR, RestLds &L)
+{
+    const int tid = threadIdx.x;
+    const int t = c / A.nrx, r = c - t * A.nrx;
+    const int g = A.shared ? 0 : t;
+    const int pos = tid & (TPR - 1), sub = tid / TPR, G = REST_T / TPR;
+    const unsigned k0 = (unsigned)(pos * KR);
+    const double f0c = A.f0 * A.inv_c;
+    const double bkc = A.bw / (double)A.K * A.inv_c;
+    const double tx[3] = {A.tx[3 * t], A.tx[3 * t + 1], A.tx[3 * t + 2]};
+    const double rx[3] = {A.rx[3 * r], A.rx[3 * r + 1], A.rx[3 * r + 2]};
+    const int64_t p0 = A.ranges[g];
+    const int64_t p1 = A.p_limit > 0 ? min(A.ranges[g + 1], p0 + A.p_limit) : A.ranges[g + 1];
+    float are[KR], aim[KR];
+#pragma unroll
+    for (int k = 0; k < KR; k++) { are[k] = 0.0f; aim[k] = 0.0f; }
+    for (int64_t base = p0; base < p1; base += REST_T) {
+        const int cnt = (int)min((int64_t)REST_T, p1 - base);
+        __syncthreads();
+        if (tid < cnt) {
+            const SynPath &P = A.paths[base + tid];
+            double db, ds;
+            path_lengths(A, P, 0.0, tx, rx, db, ds);
+            L.tab[tid] = make_uint2(turns_u32(db * f0c), turns_u32(ds * bkc));
+            L.amp[tid] = (float)P.amp;
+        }
+        __syncthreads();
+        for (int q = sub; q < cnt; q += G) {
+            const uint2 ph = L.tab[q];
+            const float a = L.amp[q];
+            const float u0 = turns_f32(ph.x + k0 * ph.y);
+            const float u1 = turns_f32(ph.y);
+            float pr = a * __builtin_amdgcn_cosf(u0), pi = -a * __builtin_amdgcn_sinf(u0);
+            const float rr = __builtin_amdgcn_cosf(u1), ri = -__builtin_amdgcn_sinf(u1);
+#pragma unroll
+            for (int k = 0; k < KR; k++) {
+                are[k] += pr;
+                aim[k] += pi;
+                const float nr = pr * rr - pi * ri;
+                const float ni = pr * ri + pi * rr;
+                pr = nr;
+                pi = ni;
+            }
+        }
+    }
+    for (int off = TPR; off < 64; off <<= 1)
+#pragma unroll
+        for (int k = 0; k < KR; k++) {
+            are[k] += __shfl_xor(are[k], off);
+            aim[k] += __shfl_xor(aim[k], off);
+        }
+    // wavefront w now holds samples of positions (w % wps) 64 + lane
+    const int wps = TPR > 64 ? TPR / 64 : 1, np = REST_T / 64 / wps;
+    const int lane = tid & 63, w = tid >> 6;
+    float2 *out = A.cube + (int64_t)c * A.M * A.K;
+    for (int h = 0; h < KR; h += 8) {
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < KR; k++)
+            if (lane < TPR && k >= h && k < h + 8) L.red[(w * 64 + lane) * 8 + k - h] = make_float2(are[k], aim[k]);
+        __syncthreads();
+        for (int o = tid; o < TPR * 8; o += REST_T) {
+            const int ps = o >> 3, kk = h + (o & 7), k = ps * KR + kk;
+            if (kk >= KR || k >= A.K) continue;
+            float2 v = make_float2(0.0f, 0.0f);
+            for (int j = 0; j < np; j++) {
+                const float2 x = L.red[((j * wps + (ps >> 6)) * 64 + (ps & 63)) * 8 + (o & 7)];
+                v.x += x.x;
+                v.y += x.y;
+            }
+            out[k] = v;
+        }
+    }
+}
+
+// samples of a channel over the lanes: at most 16 a lane, and as few as the
+// power of two of lanes allows (the samples beyond K are padding)
+__device__ __forceinline__ void rest_tile(const SynthArgs &A, int c, RestLds &L)
+{
+    int TPR = 1;
+    while (TPR * 16 < A.K && TPR < REST_T) TPR <<= 1;
+    const int kr = (A.K + TPR - 1) / TPR;
+    if (kr <= 4) rest_block<4>(A, c, TPR, L);
+    else if (kr <= 8) rest_block<8>(A, c, TPR, L);
+    else if (kr <= 12) rest_block<12>(A, c, TPR, L);
+    else rest_block<16>(A, c, TPR, L);
+}
+
+__global__ __launch_bounds__(REST_T) void k_synth_rest(SynthArgs A)
+{
+    __shared__ RestLds L;
+    rest_tile(A, blockIdx.x, L);
 }
 
 template <int KR>
 __global__ __launch_bounds__(SYN_T) void k_synth_direct(SynthArgs A, int rows_per_group, int RC,
-                                                        int blocks_per_group)
+                                                        int blocks_per_group, int m0)
 {
     __shared__ SynPath sp[SYN_CHUNK];
     __shared__ uint2 tab[SYN_TAB];
     const int g = blockIdx.x / blocks_per_group;
-    synth_block<KR>(A, g, blockIdx.x - g * blocks_per_group, rows_per_group, RC, sp, tab);
+    synth_block<KR>(A, g, blockIdx.x - g * blocks_per_group, rows_per_group, RC, m0, sp, tab);
 }
 
-// Batched, persistent: workgroups pull (scene, tile) items from a device
-// counter; each scene carries its own tile shape (samples per lane KR, chosen
-// by the autotuner) and its path range comes from the batched scan.
+// the next item of a persistent kernel: the same in every lane, kept in
+// scalar registers with the scene it belongs to
+__device__ __forceinline__ bool next_item(long long *slot, unsigned long long *work,
+                                          const int64_t *item_start, int S, int &scene, int &local)
+{
+    __syncthreads();
+    if (threadIdx.x == 0) *slot = (long long)atomicAdd(work, 1ull);
+    __syncthreads();
+    const long long iv = *slot;
+    const int64_t it = (int64_t)(((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane(
+                                      (int)(iv >> 32)) << 32) |
+                                 (unsigned)__builtin_amdgcn_readfirstlane((int)iv));
+    if (it >= item_start[S]) return false;
+    int lo = 0, hi = S - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) / 2;
+        if (item_start[mid] <= it) lo = mid; else hi = mid - 1;
+    }
+    scene = __builtin_amdgcn_readfirstlane(lo);
+    local = (int)(it - item_start[scene]);
+    return true;
+}
+
+// Batched, persistent: workgroups pull (scene, channel) items of the paths at
+// rest, then (scene, tile) items of the moving ones, from a device counter;
+// each scene carries its own tile shape (samples per lane KR, chosen by the
+// autotuner) and its path ranges come from the batched scan.
+__global__ __launch_bounds__(REST_T) void k_batch_rest(const SynthArgs *scenes,
+                                                       const int64_t *item_start, int S,
+                                                       unsigned long long *work)
+{
+    __shared__ RestLds L;
+    __shared__ long long s_item;
+    int scene, local;
+    while (next_item(&s_item, work, item_start, S, scene, local)) {
+        const SynthArgs A = scenes[scene];
+        rest_tile(A, local, L);
+    }
+}
+
+// first: chirp 0 alone (its rest sum is then replaced by the whole), else
+// every other chirp
 __global__ __launch_bounds__(SYN_T) void k_batch_synth(const SynthArgs *scenes,
                                                        const BatchSynthInfo *info,
-                                                       const int64_t *item_start, int S,
+                                                       const int64_t *item_start, int S, int first,
                                                        unsigned long long *work)
 {
     __shared__ SynPath sp[SYN_CHUNK];
     __shared__ uint2 tab[SYN_TAB];
     __shared__ long long s_item;
-    const int64_t n_items = item_start[S];
-    while (true) {
-        __syncthreads();
-        if (threadIdx.x == 0) s_item = (long long)atomicAdd(work, 1ull);
-        __syncthreads();
-        // the item is the same in every lane: keep it, the scene search and
-        // the scene's arguments in scalar registers
-        const long long iv = s_item;
-        const int64_t it = (int64_t)(((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane(
-                                          (int)(iv >> 32)) << 32) |
-                                     (unsigned)__builtin_amdgcn_readfirstlane((int)iv));
-        if (it >= n_items) break;
-        int lo = 0, hi = S - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) / 2;
-            if (item_start[mid] <= it) lo = mid; else hi = mid - 1;
-        }
-        lo = __builtin_amdgcn_readfirstlane(lo);
-        const SynthArgs A = scenes[lo];
-        const BatchSynthInfo I = info[lo];
-        const int local = (int)(it - item_start[lo]);
-        const int g = local / I.bpg;
-        const int rb = local - g * I.bpg;
+    int scene, local;
+    while (next_item(&s_item, work, item_start, S, scene, local)) {
+        const SynthArgs A = scenes[scene];
+        const BatchSynthInfo I = info[scene];
+        const int bpg = first ? I.bpg0 : I.bpg;
+        const int g = local / bpg;
+        const int rb = local - g * bpg;
+        const int rows = first ? I.rc : I.rows_per_group, m0 = first ? 0 : 1;
         switch (I.kr) {
 #if RR_BATCH_MAX_KR >= 32
-        case 32: synth_block<32>(A, g, rb, I.rows_per_group, I.rc, sp, tab); break;
+        case 32: synth_block<32>(A, g, rb, rows, I.rc, m0, sp, tab); break;
 #endif
-        case 16: synth_block<16>(A, g, rb, I.rows_per_group, I.rc, sp, tab); break;
-        case 8: synth_block<8>(A, g, rb, I.rows_per_group, I.rc, sp, tab); break;
-        case 4: synth_block<4>(A, g, rb, I.rows_per_group, I.rc, sp, tab); break;
-        case 2: synth_block<2>(A, g, rb, I.rows_per_group, I.rc, sp, tab); break;
-        default: synth_block<1>(A, g, rb, I.rows_per_group, I.rc, sp, tab); break;
+        case 16: synth_block<16>(A, g, rb, rows, I.rc, m0, sp, tab); break;
+        case 8: synth_block<8>(A, g, rb, rows, I.rc, m0, sp, tab); break;
+        case 4: synth_block<4>(A, g, rb, rows, I.rc, m0, sp, tab); break;
+        case 2: synth_block<2>(A, g, rb, rows, I.rc, m0, sp, tab); break;
+        default: synth_block<1>(A, g, rb, rows, I.rc, m0, sp, tab); break;
         }
     }
 }
@@ -239,9 +384,12 @@ __global__ __launch_bounds__(256) void k_synth_sampled(SynthArgs A, const int64_
     const double rx[3] = {A.rx[3 * r], A.rx[3 * r + 1], A.rx[3 * r + 2]};
     const double tau = (double)m * A.t_rep;
     const double fk = A.f0 + A.bw * (double)k / (double)A.K;
-    const int64_t p0 = A.shared ? 0 : A.ranges[t], p1 = A.shared ? A.n_paths : A.ranges[t + 1];
+    const int g = A.shared ? 0 : t;
+    const int64_t p0 = A.ranges[g], n0 = A.ranges[g + 1] - p0;
+    const int64_t p1 = A.mranges[g], n = n0 + A.mranges[g + 1] - p1;
     double re = 0.0, im = 0.0;
-    for (int64_t p = p0 + threadIdx.x; p < p1; p += 256) {
+    for (int64_t i = threadIdx.x; i < n; i += 256) {
+        const int64_t p = i < n0 ? p0 + i : p1 + (i - n0);
         const SynPath &P = A.paths[p];
         double db, ds;
         path_lengths(A, P, tau, tx, rx, db, ds);
@@ -265,36 +413,122 @@ __global__ __launch_bounds__(256) void k_synth_sampled(SynthArgs A, const int64_
     if (threadIdx.x == 0) A.cube[blockIdx.x] = make_float2((float)sre[0], (float)sim[0]);
 }
 
-__global__ void k_syn_prep(PathSoA P, int64_t n, const double *obj_vel, int nobj,
-                           const double *pt_vel, int npts, SynPath *out)
+// velocity of path i's hit q (NULL: none)
+__device__ __forceinline__ const double *hit_velocity(const PathSoA &P, int q, int64_t i,
+                                                      const BatchVel &bv)
 {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
+    const int vid = P.vid[q * P.cap + i];
+    if (vid >= 0 && vid < bv.nobj) return bv.obj_vel + 3 * vid;
+    if (vid >= bv.nobj && vid < bv.nobj + bv.npts) return bv.pt_vel + 3 * (vid - bv.nobj);
+    return nullptr;
+}
+
+__device__ __forceinline__ bool at_rest(const PathSoA &P, int64_t i, const BatchVel &bv)
+{
+    if (bv.M <= 1) return true;
+    const int K = P.K[i];
+    bool rest = true;
+#pragma unroll
+    for (int q = 0; q < RR_KMAX; q++)
+        if (q < K) {
+            const double *v = hit_velocity(P, q, i, bv);
+            if (v && (v[0] != 0.0 || v[1] != 0.0 || v[2] != 0.0)) rest = false;
+        }
+    return rest;
+}
+
+__device__ __forceinline__ SynPath syn_record(const PathSoA &P, int64_t i, const BatchVel &bv)
+{
     SynPath s;
-    const int64_t cap = P.cap;
 #pragma unroll
     for (int q = 0; q < RR_KMAX; q++) {
-        int vid = P.vid[q * cap + i];
-        const double *v = nullptr;
-        if (vid >= 0 && vid < nobj) v = obj_vel + 3 * vid;
-        else if (vid >= nobj && vid < nobj + npts) v = pt_vel + 3 * (vid - nobj);
+        const double *v = hit_velocity(P, q, i, bv);
 #pragma unroll
         for (int a = 0; a < 3; a++) {
-            s.P[q][a] = P.p[(3 * q + a) * cap + i];
+            s.P[q][a] = P.p[(3 * q + a) * P.cap + i];
             s.V[q][a] = v ? v[a] : 0.0;
         }
     }
     s.amp = P.amp[i];
     s.K = P.K[i];
     s.src = P.src[i];
-    out[i] = s;
+    return s;
 }
 
-// ranges[g] = first path with src >= g (paths sorted by src); g in [0, n_groups]
-// ranges[g] = first path whose source is >= g0 + g, g = 0 .. n_groups (src
-// sorted): per-Tx groups with g0 = 0, the single group of a shared launch
-// (every src = -1) with g0 = -1
-__global__ void k_ranges(const int32_t *src, int64_t n, int n_groups, int g0, int64_t *ranges)
+// The records in two parts, each in path order: a count of the paths at rest
+// per block of PREP_T, then every block adds the counts before it (one pass
+// over a list that is 1/1024 of the paths) and places its own records.
+#define PREP_T 1024
+__global__ __launch_bounds__(PREP_T) void k_rest_count(PathSoA P, int64_t n, BatchVel bv,
+                                                       uint32_t *bsums, int32_t *info)
+{
+    const int64_t i = (int64_t)blockIdx.x * PREP_T + threadIdx.x;
+    const int c = __syncthreads_count(i < n && at_rest(P, i, bv));
+    if (threadIdx.x == 0) {
+        bsums[blockIdx.x] = (uint32_t)c;
+        info[2 + blockIdx.x] = c;
+        if (blockIdx.x == 0) info[0] = P.src[0];
+        if (blockIdx.x == gridDim.x - 1) info[1] = P.src[n - 1];
+    }
+}
+
+// paths at rest before this thread's path, and of all n (nb blocks)
+__device__ __forceinline__ void rest_rank(bool rest, const uint32_t *bsums, int64_t nb,
+                                          uint32_t &before, uint32_t &total)
+{
+    __shared__ uint32_t sh_w[PREP_T / 64], sh_b[PREP_T / 64], sh_t[PREP_T / 64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const unsigned long long m = __ballot(rest);
+    uint32_t b = 0, t = 0;
+    for (int64_t j = threadIdx.x; j < nb; j += PREP_T) {
+        const uint32_t x = bsums[j];
+        t += x;
+        if (j < (int64_t)blockIdx.x) b += x;
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+        b += __shfl_xor(b, off);
+        t += __shfl_xor(t, off);
+    }
+    if (lane == 0) {
+        sh_w[w] = (uint32_t)__popcll(m);
+        sh_b[w] = b;
+        sh_t[w] = t;
+    }
+    __syncthreads();
+    before = (uint32_t)__popcll(m & ((1ull << lane) - 1));
+    total = 0;
+    for (int j = 0; j < PREP_T / 64; j++) {
+        before += sh_b[j] + (j < w ? sh_w[j] : 0u);
+        total += sh_t[j];
+    }
+}
+
+__device__ __forceinline__ void place_record(const PathSoA &P, int64_t i, int64_t n, bool rest,
+                                             uint32_t before, uint32_t total, const BatchVel &bv,
+                                             uint32_t *pre, SynPath *out)
+{
+    if (i >= n) return;
+    pre[i] = before;
+    if (i == n - 1) pre[n] = total;
+    out[rest ? (int64_t)before : (int64_t)total + (i - (int64_t)before)] = syn_record(P, i, bv);
+}
+
+__global__ __launch_bounds__(PREP_T) void k_syn_prep(PathSoA P, int64_t n, BatchVel bv,
+                                                     const uint32_t *bsums, uint32_t *pre,
+                                                     SynPath *out)
+{
+    const int64_t i = (int64_t)blockIdx.x * PREP_T + threadIdx.x;
+    const bool rest = i < n && at_rest(P, i, bv);
+    uint32_t before, total;
+    rest_rank(rest, bsums, gridDim.x, before, total);
+    place_record(P, i, n, rest, before, total, bv, pre, out);
+}
+
+// ranges of group g's paths in the two parts (src sorted; first path whose
+// source is >= g0 + g, g = 0 .. n_groups): per-Tx groups with g0 = 0, the
+// single group of a shared launch (every src = -1) with g0 = -1
+__global__ void k_rest_ranges(const int32_t *src, int64_t n, int n_groups, int g0,
+                              const uint32_t *pre, int64_t *rest, int64_t *mov)
 {
     int g = blockIdx.x * blockDim.x + threadIdx.x;
     if (g > n_groups) return;
@@ -303,62 +537,80 @@ __global__ void k_ranges(const int32_t *src, int64_t n, int n_groups, int g0, in
         int64_t mid = (lo + hi) / 2;
         if (src[mid] < g0 + g) lo = mid + 1; else hi = mid;
     }
-    ranges[g] = lo;
+    const int64_t r = n > 0 ? pre[lo] : 0, all = n > 0 ? pre[n] : 0;
+    rest[g] = r;
+    mov[g] = all + lo - r;
 }
 
-// synthesis records of the batched path pool: the scene of a path follows
-// from its virtual ray id
-__global__ void k_batch_prep(PathSoA P, const unsigned long long *total, int64_t cap,
-                             const int64_t *vr_start, int S, const BatchVel *vel, SynPath *out)
+// the velocity tables of the scene whose virtual rays hold ray v (the paths
+// of the batched pool are in virtual ray order)
+__device__ __forceinline__ const BatchVel &batch_scene(int64_t v, const int64_t *vr_start, int S,
+                                                       const BatchVel *vel)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t n = min((int64_t)*total, cap);
-    if (i >= n) return;
-    const int64_t v = P.ray[i];
     int lo = 0, hi = S - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) / 2;
         if (vr_start[mid] <= v) lo = mid; else hi = mid - 1;
     }
-    const BatchVel &bv = vel[lo];
-    SynPath s;
-    const int64_t c = P.cap;
-#pragma unroll
-    for (int q = 0; q < RR_KMAX; q++) {
-        const int vid = P.vid[q * c + i];
-        const double *vv = nullptr;
-        if (vid >= 0 && vid < bv.nobj) vv = bv.obj_vel + 3 * vid;
-        else if (vid >= bv.nobj && vid < bv.nobj + bv.npts) vv = bv.pt_vel + 3 * (vid - bv.nobj);
-#pragma unroll
-        for (int a = 0; a < 3; a++) {
-            s.P[q][a] = P.p[(3 * q + a) * c + i];
-            s.V[q][a] = vv ? vv[a] : 0.0;
-        }
+    return vel[lo];
+}
+
+__global__ __launch_bounds__(PREP_T) void k_batch_rest_count(PathSoA P,
+                                                             const unsigned long long *total,
+                                                             int64_t cap, const int64_t *vr_start,
+                                                             int S, const BatchVel *vel,
+                                                             uint32_t *bsums)
+{
+    const int64_t i = (int64_t)blockIdx.x * PREP_T + threadIdx.x;
+    const int64_t n = min((int64_t)*total, cap);
+    bool rest = false;
+    if (i < n) rest = at_rest(P, i, batch_scene(P.ray[i], vr_start, S, vel));
+    const int c = __syncthreads_count(rest);
+    if (threadIdx.x == 0) bsums[blockIdx.x] = (uint32_t)c;
+}
+
+// synthesis records of the batched path pool: the scene of a path follows
+// from its virtual ray id
+__global__ __launch_bounds__(PREP_T) void k_batch_prep(PathSoA P, const unsigned long long *total,
+                                                       int64_t cap, const int64_t *vr_start, int S,
+                                                       const BatchVel *vel, const uint32_t *bsums,
+                                                       uint32_t *pre, SynPath *out)
+{
+    const int64_t i = (int64_t)blockIdx.x * PREP_T + threadIdx.x;
+    const int64_t n = min((int64_t)*total, cap);
+    if ((int64_t)blockIdx.x * PREP_T >= n) {
+        if (n == 0 && i == 0) pre[0] = 0;
+        return;
     }
-    s.amp = P.amp[i];
-    s.K = P.K[i];
-    s.src = P.src[i];
-    out[i] = s;
+    const BatchVel &bv = batch_scene(P.ray[min(i, n - 1)], vr_start, S, vel);
+    const bool rest = i < n && at_rest(P, i, bv);
+    uint32_t before, tot;
+    rest_rank(rest, bsums, (n + PREP_T - 1) / PREP_T, before, tot);
+    place_record(P, i, n, rest, before, tot, bv, pre, out);
 }
 
 // per-scene path ranges from the batched exclusive scan: paths of virtual
-// rays [vr0 + t n_vps, ...) start at offsets[vr0 + t n_vps]
+// rays [vr0 + t n_vps, ...) start at offsets[vr0 + t n_vps]; then those of
+// the two parts of the records
 __global__ void k_batch_ranges(const uint32_t *offsets, int64_t V, const unsigned long long *total,
-                               int64_t cap, const BatchRangeInfo *ri, int S, int64_t *ranges)
+                               int64_t cap, const BatchRangeInfo *ri, int S, const uint32_t *pre,
+                               int64_t *rest, int64_t *mov)
 {
     const int s = blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= S) return;
     const BatchRangeInfo &R = ri[s];
     const int64_t tot = min((int64_t)*total, cap);
-    auto off = [&](int64_t v) -> int64_t {
-        const int64_t o = v < V ? (int64_t)offsets[v] : tot;
-        return min(o, tot);
+    auto put = [&](int g, int64_t v) {
+        const int64_t o = min(v < V ? (int64_t)offsets[v] : tot, tot);
+        const int64_t r = pre[o];
+        rest[R.base + g] = r;
+        mov[R.base + g] = (int64_t)pre[tot] + o - r;
     };
     if (R.shared) {
-        ranges[R.base] = off(R.vr0);
-        ranges[R.base + 1] = off(R.vr0 + R.n_vps);
+        put(0, R.vr0);
+        put(1, R.vr0 + R.n_vps);
     } else {
-        for (int g = 0; g <= R.n_groups; g++) ranges[R.base + g] = off(R.vr0 + (int64_t)g * R.n_vps);
+        for (int g = 0; g <= R.n_groups; g++) put(g, R.vr0 + (int64_t)g * R.n_vps);
     }
 }
 
@@ -370,7 +622,7 @@ __global__ void k_fill_u64(unsigned long long *p, int64_t n, unsigned long long 
 
 }  // namespace
 
-hipError_t launch_batch_synth(const SynthArgs *scenes, const BatchSynthInfo *info,
+hipError_t launch_batch_synth(int stage, const SynthArgs *scenes, const BatchSynthInfo *info,
                               const int64_t *item_start, int S, int64_t n_items,
                               unsigned long long *work, hipStream_t s)
 {
@@ -379,27 +631,36 @@ hipError_t launch_batch_synth(const SynthArgs *scenes, const BatchSynthInfo *inf
     (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     const int64_t grid = std::min<int64_t>(n_items, (int64_t)cus * 8);
     if (grid <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_batch_synth, dim3((unsigned)grid), dim3(SYN_T), 0, s, scenes, info,
-                       item_start, S, work);
+    if (stage == 0)
+        hipLaunchKernelGGL(k_batch_rest, dim3((unsigned)grid), dim3(REST_T), 0, s, scenes,
+                           item_start, S, work);
+    else
+        hipLaunchKernelGGL(k_batch_synth, dim3((unsigned)grid), dim3(SYN_T), 0, s, scenes, info,
+                           item_start, S, stage == 2 ? 1 : 0, work);
     return hipGetLastError();
 }
 
+int64_t rest_blocks(int64_t n) { return (n + PREP_T - 1) / PREP_T; }
+
 hipError_t launch_batch_prep(const PathSoA &paths, const unsigned long long *total, int64_t cap,
-                             const int64_t *vr_start, int S, const BatchVel *vel, SynPath *out,
-                             hipStream_t s)
+                             const int64_t *vr_start, int S, const BatchVel *vel, uint32_t *bsums,
+                             uint32_t *pre, SynPath *out, hipStream_t s)
 {
     if (cap <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_batch_prep, dim3((unsigned)((cap + 255) / 256)), dim3(256), 0, s, paths,
-                       total, cap, vr_start, S, vel, out);
+    const dim3 g((unsigned)rest_blocks(cap));
+    hipLaunchKernelGGL(k_batch_rest_count, g, dim3(PREP_T), 0, s, paths, total, cap, vr_start, S,
+                       vel, bsums);
+    hipLaunchKernelGGL(k_batch_prep, g, dim3(PREP_T), 0, s, paths, total, cap, vr_start, S, vel,
+                       bsums, pre, out);
     return hipGetLastError();
 }
 
 hipError_t launch_batch_ranges(const uint32_t *offsets, int64_t V, const unsigned long long *total,
-                               int64_t cap, const BatchRangeInfo *ri, int S, int64_t *ranges,
-                               hipStream_t s)
+                               int64_t cap, const BatchRangeInfo *ri, int S, const uint32_t *pre,
+                               int64_t *rest, int64_t *mov, hipStream_t s)
 {
     hipLaunchKernelGGL(k_batch_ranges, dim3((unsigned)((S + 63) / 64)), dim3(64), 0, s, offsets, V,
-                       total, cap, ri, S, ranges);
+                       total, cap, ri, S, pre, rest, mov);
     return hipGetLastError();
 }
 
@@ -410,33 +671,57 @@ hipError_t launch_fill_u64(unsigned long long *p, int64_t n, unsigned long long 
     return hipGetLastError();
 }
 
-hipError_t launch_syn_prep(const PathSoA &paths, int64_t n, const double *obj_vel, int nobj,
-                           const double *pt_vel, int npts, SynPath *out, hipStream_t s)
+static BatchVel one_scene(const double *obj_vel, int nobj, const double *pt_vel, int npts, int split)
+{
+    BatchVel bv;
+    bv.obj_vel = obj_vel;
+    bv.pt_vel = pt_vel;
+    bv.nobj = nobj;
+    bv.npts = npts;
+    bv.M = split ? 2 : 1;
+    return bv;
+}
+
+hipError_t launch_rest_count(const PathSoA &paths, int64_t n, const double *obj_vel, int nobj,
+                             const double *pt_vel, int npts, int split, uint32_t *bsums,
+                             int32_t *info, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_syn_prep, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, paths, n,
-                       obj_vel, nobj, pt_vel, npts, out);
+    hipLaunchKernelGGL(k_rest_count, dim3((unsigned)rest_blocks(n)), dim3(PREP_T), 0, s, paths, n,
+                       one_scene(obj_vel, nobj, pt_vel, npts, split), bsums, info);
     return hipGetLastError();
 }
 
-hipError_t launch_ranges(const int32_t *src, int64_t n, int n_groups, int g0, int64_t *ranges,
-                         hipStream_t s)
+hipError_t launch_syn_prep(const PathSoA &paths, int64_t n, const double *obj_vel, int nobj,
+                           const double *pt_vel, int npts, int split, const uint32_t *bsums,
+                           uint32_t *pre, SynPath *out, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_ranges, dim3((unsigned)((n_groups + 1 + 255) / 256)), dim3(256), 0, s,
-                       src, n, n_groups, g0, ranges);
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_syn_prep, dim3((unsigned)rest_blocks(n)), dim3(PREP_T), 0, s, paths, n,
+                       one_scene(obj_vel, nobj, pt_vel, npts, split), bsums, pre, out);
     return hipGetLastError();
 }
 
+hipError_t launch_rest_ranges(const int32_t *src, int64_t n, int n_groups, int g0,
+                              const uint32_t *pre, int64_t *rest, int64_t *mov, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_rest_ranges, dim3((unsigned)((n_groups + 1 + 255) / 256)), dim3(256), 0,
+                       s, src, n, n_groups, g0, pre, rest, mov);
+    return hipGetLastError();
+}
+
+// rows of one launch: RC channels of every group for chirps m0 ..
 template <int KR>
-static hipError_t launch_kr(const SynthArgs &a, int n_groups, int rows_per_group, int RC,
+static hipError_t launch_kr(const SynthArgs &a, int n_groups, int rows_per_group, int RC, int m0,
                             hipStream_t s)
 {
     const int TPR = a.K / KR;
     const int RPB = SYN_T / TPR;
     const int bpg = (rows_per_group + RPB - 1) / RPB;
     const int64_t blocks = (int64_t)bpg * n_groups;
+    if (blocks <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_synth_direct<KR>, dim3((unsigned)blocks), dim3(SYN_T), 0, s, a,
-                       rows_per_group, RC, bpg);
+                       rows_per_group, RC, bpg, m0);
     return hipGetLastError();
 }
 
@@ -447,14 +732,22 @@ hipError_t launch_synth_direct(const SynthArgs &a, int n_groups, int rows_per_gr
     int kr = 32;
     while (kr > 1 && a.K % kr != 0) kr >>= 1;
     if (a.K / kr > SYN_T) return hipErrorInvalidValue;
-    switch (kr) {
-    case 32: return launch_kr<32>(a, n_groups, rows_per_group, RC, s);
-    case 16: return launch_kr<16>(a, n_groups, rows_per_group, RC, s);
-    case 8: return launch_kr<8>(a, n_groups, rows_per_group, RC, s);
-    case 4: return launch_kr<4>(a, n_groups, rows_per_group, RC, s);
-    case 2: return launch_kr<2>(a, n_groups, rows_per_group, RC, s);
-    default: return launch_kr<1>(a, n_groups, rows_per_group, RC, s);
+    hipLaunchKernelGGL(k_synth_rest, dim3((unsigned)(a.ntx * a.nrx)), dim3(REST_T), 0, s, a);
+    if (a.M <= 1) return hipGetLastError();
+    for (int m0 = 1; m0 >= 0; m0--) {
+        const int rows = m0 ? rows_per_group - RC : RC;
+        hipError_t e;
+        switch (kr) {
+        case 32: e = launch_kr<32>(a, n_groups, rows, RC, m0, s); break;
+        case 16: e = launch_kr<16>(a, n_groups, rows, RC, m0, s); break;
+        case 8: e = launch_kr<8>(a, n_groups, rows, RC, m0, s); break;
+        case 4: e = launch_kr<4>(a, n_groups, rows, RC, m0, s); break;
+        case 2: e = launch_kr<2>(a, n_groups, rows, RC, m0, s); break;
+        default: e = launch_kr<1>(a, n_groups, rows, RC, m0, s); break;
+        }
+        if (e != hipSuccess) return e;
     }
+    return hipSuccess;
 }
 
 hipError_t launch_synth_sampled(const SynthArgs &a, const int64_t *idx, int64_t n_idx,

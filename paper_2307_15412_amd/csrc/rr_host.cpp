@@ -61,6 +61,16 @@ struct DevBuf {
     template <class T> T *as() const { return static_cast<T *>(p); }
 };
 
+// Tables and partial sums of the exact product engine, and its sum over the
+// paths at rest, [channel][sample].
+struct FreqBufs {
+    DevBuf xt, yt, amp, src, part, rest;
+    void release()
+    {
+        for (DevBuf *b : {&xt, &yt, &amp, &src, &part, &rest}) b->release();
+    }
+};
+
 // Device path list: one allocation, planes carved out of it.
 struct PathStore {
     DevBuf buf;
@@ -112,12 +122,16 @@ bool finite3(const double *p, int64_t n)
 
 // Scratch of rr_synthesize_noalloc: synthesis records of up to
 // RR_NOALLOC_MAX_PATHS paths, then the path ranges of up to RR_NOALLOC_MAX_TX
-// transmitter groups.  Each GPU holds its own copy from module load until the
-// process ends.  Host code reaches it only through the device address that
-// hipGetSymbolAddress returns for the current device (g_scratch_dev), never
-// through the array's name.
+// transmitter groups (paths at rest, moving paths), the counts and the prefix
+// that split the records in those two parts.  Each GPU holds its own copy
+// from module load until the process ends.  Host code reaches it only through
+// the device address that hipGetSymbolAddress returns for the current device
+// (g_scratch_dev), never through the array's name.
 #define NOALLOC_RANGES_OFF (((size_t)RR_NOALLOC_MAX_PATHS * sizeof(SynPath) + 255) / 256 * 256)
-#define NOALLOC_BYTES (NOALLOC_RANGES_OFF + (size_t)(RR_NOALLOC_MAX_TX + 2) * 8)
+#define NOALLOC_MOV_OFF (NOALLOC_RANGES_OFF + (size_t)(RR_NOALLOC_MAX_TX + 2) * 8)
+#define NOALLOC_PRE_OFF (NOALLOC_MOV_OFF + (size_t)(RR_NOALLOC_MAX_TX + 2) * 8)
+#define NOALLOC_SUMS_OFF (NOALLOC_PRE_OFF + ((size_t)RR_NOALLOC_MAX_PATHS + 2) * 4)
+#define NOALLOC_BYTES (NOALLOC_SUMS_OFF + ((size_t)RR_NOALLOC_MAX_PATHS / 256 + 2) * 8)
 static __device__ __align__(256) unsigned char scratch[NOALLOC_BYTES];
 
 namespace {
@@ -180,7 +194,9 @@ struct rr_ctx {
     int n_az = 0, n_el = 0;        // proposal grid (cdf set)
 
     // synthesis scratch
-    DevBuf syn, ranges;
+    DevBuf syn;                 // records, the groups' ranges in both parts, prefix, block counts
+    int32_t *h_info = nullptr;  // pinned: first and last source, counts at rest per block
+    int64_t h_info_n = 0;
     DevBuf gT, gR, gA, gB;     // GEMM operands
 
     // learned proposal
@@ -196,7 +212,7 @@ struct rr_ctx {
     std::vector<float> h_verts;
     // refit of the BVH to moved vertices (rr_scene_update_vertices)
     DevBuf tris_dev, verts_dev, refit_order, ubox;
-    DevBuf fq_xt, fq_yt, fq_amp, fq_src, fq_part;   // exact-model GEMM engine
+    FreqBufs fq;               // exact product engine
     DevBuf order_cells, order_rc, order_idx;   // coherent ray order of a trace
     DevBuf bp_sf;              // cube slices in fragment layout (MFMA back-projection)
     std::vector<double> h_tx, h_rx;
@@ -312,6 +328,22 @@ int resolve_paths(rr_ctx *c)
     return RR_OK;
 }
 
+// pinned host words for the counts a synthesis reads back (written by its
+// kernel, read after a synchronisation)
+int info_room(rr_ctx *c, int64_t n)
+{
+    if (c->h_info_n >= n) return RR_OK;
+    if (c->h_info) (void)hipHostFree(c->h_info);
+    c->h_info = nullptr;
+    c->h_info_n = 0;
+    if (hipHostMalloc((void **)&c->h_info, (size_t)n * 4, hipHostMallocDefault) != hipSuccess) {
+        c->h_info = nullptr;
+        return fail(RR_ENOMEM, "hipHostMalloc(%lld) failed", (long long)n * 4);
+    }
+    c->h_info_n = n;
+    return RR_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -339,7 +371,8 @@ int rr_create(int hip_device, void *hip_stream, rr_ctx **out)
             return fail(RR_EHIP, "hipEventCreate failed");
         }
     }
-    int rc = c->counter.ensure(256);
+    int rc = info_room(c, 1024);
+    if (!rc) rc = c->counter.ensure(256);
     if (!rc) rc = c->total.ensure(256);
     if (!rc) rc = c->err_flag.ensure(256);
     if (rc) {
@@ -360,13 +393,15 @@ void rr_destroy(rr_ctx *c)
     DevBuf *bufs[] = {&c->nodes, &c->ltris, &c->obj_alpha, &c->obj_vel, &c->pt_pos, &c->pt_vel,
                       &c->pt_ap, &c->tx, &c->rx, &c->counts, &c->offsets, &c->bsums,
                       &c->counter, &c->total, &c->err_flag, &c->hits, &c->cdf, &c->syn,
-                      &c->ranges, &c->tmp.buf, &c->paths.buf, &c->gT, &c->gR, &c->gA,
+                      &c->tmp.buf, &c->paths.buf, &c->gT, &c->gR, &c->gA,
                       &c->gB, &c->tri_obj, &c->mlp_p, &c->mlp_m, &c->mlp_v, &c->mlp_g,
                       &c->mlp_acts, &c->mlp_z, &c->mlp_dz, &c->mlp_d, &c->mlp_loss, &c->mlp_part,
                       &c->tr_codes, &c->tr_hist, &c->tr_loss, &c->bp_peak, &c->trace_stats, &c->tri_alpha, &c->pieces_v, &c->pieces_p, &c->tris_dev, &c->verts_dev,
                       &c->refit_order, &c->ubox,
-                      &c->order_cells, &c->order_rc, &c->order_idx, &c->fq_xt, &c->fq_yt, &c->fq_amp, &c->fq_src, &c->fq_part, &c->bp_sf};
+                      &c->order_cells, &c->order_rc, &c->order_idx, &c->bp_sf};
     for (DevBuf *b : bufs) b->release();
+    c->fq.release();
+    if (c->h_info) (void)hipHostFree(c->h_info);
     for (auto &e : c->ev)
         if (e) (void)hipEventDestroy(e);
     delete c;
@@ -1022,9 +1057,9 @@ int rr_set_paths(rr_ctx *c, const rr_paths *s, int64_t n)
     return RR_OK;
 }
 
-// separable model on the matrix cores: operand preparation, then the GEMM
-// (the context's events bracket the GEMM kernel alone)
-static int rr_synth_gemm(rr_ctx *c, const SynthArgs &A)
+// separable model on the matrix cores: operand preparation, then the GEMM over
+// the paths of A, added to rest [channel][sample] (may be NULL)
+static int rr_synth_gemm(rr_ctx *c, const SynthArgs &A, const float2 *rest)
 {
     const int C = c->ntx * c->nrx;
     const int Cpad = (C + gemm_row_pad() - 1) / gemm_row_pad() * gemm_row_pad();
@@ -1041,16 +1076,14 @@ static int rr_synth_gemm(rr_ctx *c, const SynthArgs &A)
     HIPCHK(launch_gemm_prep_a(c->gT.as<const float2>(), c->gR.as<const float2>(), c->nrx, C, Cpad,
                               (int)Ppad, c->gA.as<uint4>(), c->stream));
     HIPCHK(launch_gemm_prep_b(A, (int)Ppad, c->gB.as<uint4>(), c->stream));
-    HIPCHK(hipEventRecord(c->ev[2], c->stream));
     HIPCHK(launch_gemm_main(c->gA.as<const uint4>(), c->gB.as<const uint4>(), Cpad, (int)Ppad, C,
-                            A.M, A.K, A.cube, c->stream));
+                            A.M, A.K, rest, A.cube, c->stream));
     return RR_OK;
 }
 
-// Exact model as one complex product per (chirp, sample): leg tables per
-// (chirp, element, path), then the split-bf16 MFMA kernel over path splits.
 static const int64_t FREQ_TABLE_MAX = (int64_t)16 << 30;   // AUTO's table budget (bytes)
 
+// AUTO's estimate of the leg tables: all n paths as if they moved
 static int64_t freq_table_bytes(const rr_ctx *c, int64_t n)
 {
     const int64_t ks = freq_k_step();
@@ -1060,36 +1093,146 @@ static int64_t freq_table_bytes(const rr_ctx *c, int64_t n)
     return 8 * freq_table_entries(c->ntx, c->nrx, c->chirp.n_chirps, Ppad, own);
 }
 
-static int rr_synth_freq(rr_ctx *c, const SynthArgs &A)
+}  // extern "C"
+
+// One synthesis on the exact product engine: array, chirp and layout, and
+// room for p_rest paths at rest and p_mov moving ones (multiples of
+// freq_k_step()).  In a batched launch both are the scene's capacity.
+struct FreqPlan {
+    int T, R, M, K, tile, per_el;
+    int64_t p_rest, p_mov;
+};
+
+static int64_t freq_pad(int64_t n)
 {
-    const int64_t n = A.n_paths;
     const int64_t ks = freq_k_step();
-    const int64_t Ppad = std::max<int64_t>((n + ks - 1) / ks * ks, ks);
-    const int T = c->ntx, R = c->nrx, M = A.M, K = A.K;
-    const bool per_el = c->mode != RR_TX_SHARED;
-    const int tile = freq_tile(T, R, K, per_el);
-    int n_split = 1;
-    int64_t split_len = Ppad;
-    freq_splits(tile, T, R, M, K, Ppad, n_split, split_len);
-    const bool own = freq_own_tx(tile, per_el, A.ranges != nullptr);
+    return std::max<int64_t>((n + ks - 1) / ks * ks, ks);
+}
+
+// modelled time per chirp of n moving paths on the product engine and on the
+// separable GEMM, in the units of freq_tile_cost (1e12 complex multiply-adds/s
+// on one MI355X; the GEMM's 71 over its padded sizes)
+static double freq_cost(const FreqPlan &q, int64_t n)
+{
+    const int few = freq_mov_tile(q.tile, q.K, q.per_el);
+    return (double)freq_pad(n) *
+           freq_tile_cost(q.T, q.R, q.K, n <= FREQ_MOV_KS ? few : q.tile, q.per_el);
+}
+static double gemm_cost(int64_t C, int64_t K, int64_t n)
+{
+    const int64_t rp = gemm_row_pad(), ct = gemm_col_tile(), ks = gemm_k_step();
+    return (double)((C + rp - 1) / rp * rp) * ((K + ct - 1) / ct * ct) *
+           std::max<int64_t>((n + ks - 1) / ks * ks, ks) / 71.0;
+}
+
+// grow the buffers to a plan's needs
+static int freq_ensure(FreqBufs &b, const FreqPlan &q)
+{
+    const int64_t C = (int64_t)q.T * q.R;
+    size_t xt = 0, yt = 0, part = 0;
+    auto need = [&](int tile, int M, int64_t P) {
+        const bool own = freq_own_tx(tile, q.per_el, true);
+        xt = std::max(xt, (size_t)M * (own ? 1 : q.T) * P * 8);
+        yt = std::max(yt, (size_t)M * q.R * P * 8);
+        const int ns = freq_splits(tile, q.T, q.R, M, q.K);
+        if (ns > 1) part = std::max(part, (size_t)ns * M * q.K * C * 8);
+    };
+    if (q.p_rest) need(q.tile, 1, q.p_rest);
+    if (q.p_mov) {
+        need(q.tile, q.M, q.p_mov);
+        need(freq_mov_tile(q.tile, q.K, q.per_el), q.M, q.p_mov);
+    }
+    const size_t pp = (size_t)std::max(q.p_rest, q.p_mov) * 4;
     int rc;
-    if ((rc = c->fq_xt.ensure((size_t)M * (own ? 1 : T) * Ppad * 8))) return rc;
-    if ((rc = c->fq_yt.ensure((size_t)M * R * Ppad * 8))) return rc;
-    if ((rc = c->fq_amp.ensure((size_t)Ppad * 4))) return rc;
-    if ((rc = c->fq_src.ensure((size_t)Ppad * 4))) return rc;
-    if (n_split > 1 && (rc = c->fq_part.ensure((size_t)n_split * M * K * T * R * 8))) return rc;
-    HIPCHK(hipEventRecord(c->ev[2], c->stream));
-    HIPCHK(launch_freq_prep(A.paths, n, nullptr, nullptr, Ppad, M, A.t_rep, A.tx, T, own, A.rx, R,
-                            A.f0 * A.inv_c, A.bw / (double)K * A.inv_c, c->fq_xt.as<uint2>(),
-                            c->fq_yt.as<uint2>(), c->fq_amp.as<float>(), c->fq_src.as<int32_t>(),
-                            c->stream));
-    HIPCHK(launch_freq_gemm(c->fq_xt.as<const uint2>(), c->fq_yt.as<const uint2>(),
-                            c->fq_amp.as<const float>(), c->fq_src.as<const int32_t>(), T, R, M, K,
-                            Ppad, (int)n_split, split_len, per_el, tile, nullptr, nullptr,
-                            per_el ? A.ranges : nullptr, c->fq_part.as<float2>(), A.cube,
-                            c->stream));
+    if ((rc = b.xt.ensure(xt)) || (rc = b.yt.ensure(yt)) || (rc = b.amp.ensure(pp)) ||
+        (rc = b.src.ensure(pp)) || (part && (rc = b.part.ensure(part))))
+        return rc;
+    return q.M > 1 ? b.rest.ensure((size_t)C * q.K * 8) : RR_OK;
+}
+
+// Sum over one part of the records (paths at rest: one chirp) on a layout,
+// leg tables first; the count is read on the device from rng[0], rng[n_rng],
+// the ranges of the part's groups.
+static hipError_t freq_legs(const FreqBufs &b, const FreqPlan &q, const SynthArgs &A, int tile,
+                            int M, int64_t P, const int64_t *rng, int n_rng, hipStream_t st)
+{
+    FreqLegs L{};
+    L.paths = A.paths;
+    L.rng_lo = rng;
+    L.rng_hi = rng + n_rng;
+    L.tx = A.tx;
+    L.rx = A.rx;
+    L.T = q.T;
+    L.R = q.R;
+    L.M = M;
+    L.t_rep = A.t_rep;
+    L.f0c = A.f0 * A.inv_c;
+    L.dfc = A.bw / (double)q.K * A.inv_c;
+    L.sep = A.model == RR_SEPARABLE;
+    for (int a = 0; a < 3; a++) {
+        L.oT[a] = A.oT[a];
+        L.oR[a] = A.oR[a];
+    }
+    return launch_freq_prep(L, P, freq_own_tx(tile, q.per_el, true), b.xt.as<uint2>(),
+                            b.yt.as<uint2>(), b.amp.as<float>(), b.src.as<int32_t>(), st);
+}
+
+static hipError_t freq_sum(const FreqBufs &b, const FreqPlan &q, int tile, int M, int64_t P,
+                           const int64_t *rng, int n_rng, int64_t gate_lo, int64_t gate_hi,
+                           const float2 *rest, float2 *out, hipStream_t st)
+{
+    FreqSum f{};
+    f.xt = b.xt.as<const uint2>();
+    f.yt = b.yt.as<const uint2>();
+    f.amp = b.amp.as<const float>();
+    f.src = b.src.as<const int32_t>();
+    f.T = q.T;
+    f.R = q.R;
+    f.M = M;
+    f.K = q.K;
+    f.Ppad = P;
+    f.per_element = q.per_el;
+    f.tile = tile;
+    f.rng_lo = rng;
+    f.rng_hi = rng + n_rng;
+    f.groups = rng;
+    f.gate_lo = gate_lo;
+    f.gate_hi = gate_hi;
+    f.rest = rest;
+    f.partial = b.part.as<float2>();
+    f.cube = out;
+    return launch_freq_gemm(f, st);
+}
+
+// the paths at rest: into the rest buffer, or the cube of a single chirp
+static int freq_rest(const FreqBufs &b, const FreqPlan &q, const SynthArgs &A, hipStream_t st)
+{
+    const int n_rng = q.per_el ? q.T : 1;
+    HIPCHK(freq_legs(b, q, A, q.tile, 1, q.p_rest, A.ranges, n_rng, st));
+    HIPCHK(freq_sum(b, q, q.tile, 1, q.p_rest, A.ranges, n_rng, -1, INT64_MAX, nullptr,
+                    q.M > 1 ? b.rest.as<float2>() : A.cube, st));
     return RR_OK;
 }
+
+// The moving paths on top of the rest buffer.  n_mov: their number, or -1
+// (known on the device only: both layouts are enqueued, one of them works).
+static int freq_moving(const FreqBufs &b, const FreqPlan &q, const SynthArgs &A, int64_t n_mov,
+                       hipStream_t st)
+{
+    const int n_rng = q.per_el ? q.T : 1;
+    const int few = freq_mov_tile(q.tile, q.K, q.per_el);   // same tables as q.tile's
+    HIPCHK(freq_legs(b, q, A, q.tile, q.M, q.p_mov, A.mranges, n_rng, st));
+    const int64_t gate = few == q.tile ? INT64_MAX : FREQ_MOV_KS;
+    if (n_mov <= gate)
+        HIPCHK(freq_sum(b, q, few, q.M, q.p_mov, A.mranges, n_rng, -1, gate,
+                        b.rest.as<const float2>(), A.cube, st));
+    if (few != q.tile && (n_mov < 0 || n_mov > gate))
+        HIPCHK(freq_sum(b, q, q.tile, q.M, q.p_mov, A.mranges, n_rng, gate, INT64_MAX,
+                        b.rest.as<const float2>(), A.cube, st));
+    return RR_OK;
+}
+
+extern "C" {
 
 int rr_synthesize(rr_ctx *c, int32_t model, int32_t engine, void *cube, int64_t cube_elems,
                   const int64_t *idx, int64_t n_idx)
@@ -1137,33 +1280,39 @@ int rr_synthesize(rr_ctx *c, int32_t model, int32_t engine, void *cube, int64_t 
     const int shared = c->mode == RR_TX_SHARED;
     const int n_groups = shared ? 1 : c->ntx;
     int rc;
-    if ((rc = c->syn.ensure((size_t)std::max<int64_t>(n, 1) * sizeof(SynPath)))) return rc;
-    if ((rc = c->ranges.ensure((size_t)(n_groups + 2) * 8))) return rc;
+    const int64_t nb = rest_blocks(n);
+    const size_t rec = (size_t)std::max<int64_t>(n, 1) * sizeof(SynPath);
+    const size_t rng = (size_t)(n_groups + 2) * 8;
+    if ((rc = c->syn.ensure(rec + 2 * rng + (size_t)(n + nb + 2) * 4))) return rc;
     if (!c->has_scene) return fail(RR_ESTATE, "scene must be set (velocities)");
+    if ((rc = info_room(c, nb + 2))) return rc;
+    int64_t *rr = reinterpret_cast<int64_t *>(c->syn.as<char>() + rec), *rm = rr + n_groups + 2;
+    uint32_t *pre = reinterpret_cast<uint32_t *>(rm + n_groups + 2), *sums = pre + n + 1;
+    SynPath *sp = c->syn.as<SynPath>();
+    const int split = M > 1;
+    int64_t n_rest = 0;
     if (n > 0) {
-        // src must match the launch mode: all -1 (shared) or sorted within [0, n_tx)
-        int32_t ends[2] = {0, 0};
-        HIPCHK(hipMemcpyAsync(&ends[0], c->paths.soa.src, 4, hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(hipMemcpyAsync(&ends[1], c->paths.soa.src + (n - 1), 4, hipMemcpyDeviceToHost,
-                              c->stream));
+        // src must match the launch mode: all -1 (shared) or sorted within
+        // [0, n_tx); the counts size the engines' buffers
+        HIPCHK(launch_rest_count(c->paths.soa, n, c->obj_vel.as<const double>(), c->nobj,
+                                 c->pt_vel.as<const double>(), c->npts, split, sums, c->h_info,
+                                 c->stream));
         HIPCHK(hipStreamSynchronize(c->stream));
+        const int32_t *ends = c->h_info;
         if (shared ? (ends[0] != -1 || ends[1] != -1) : (ends[0] < 0 || ends[1] >= c->ntx))
             return fail(RR_EINVAL, "path sources do not match the array's launch mode");
+        for (int64_t i = 0; i < nb; i++) n_rest += c->h_info[2 + i];
     }
-    SynPath *sp = c->syn.as<SynPath>();
+    const int64_t n_mov = n - n_rest;
     HIPCHK(launch_syn_prep(c->paths.soa, n, c->obj_vel.as<const double>(), c->nobj,
-                           c->pt_vel.as<const double>(), c->npts, sp, c->stream));
+                           c->pt_vel.as<const double>(), c->npts, split, sums, pre, sp, c->stream));
     // shared paths carry src = -1: one group over all paths
-    if (shared) {
-        int64_t r[2] = {0, n};
-        HIPCHK(hipMemcpyAsync(c->ranges.p, r, 16, hipMemcpyHostToDevice, c->stream));
-        HIPCHK(hipStreamSynchronize(c->stream));
-    } else {
-        HIPCHK(launch_ranges(c->paths.soa.src, n, n_groups, 0, c->ranges.as<int64_t>(), c->stream));
-    }
+    HIPCHK(launch_rest_ranges(c->paths.soa.src, n, n_groups, shared ? -1 : 0, pre, rr, rm,
+                              c->stream));
     SynthArgs A{};
     A.paths = sp;
-    A.ranges = c->ranges.as<const int64_t>();
+    A.ranges = rr;
+    A.mranges = rm;
     A.n_paths = n;
     A.tx = c->tx.as<const double>();
     A.rx = c->rx.as<const double>();
@@ -1182,12 +1331,25 @@ int rr_synthesize(rr_ctx *c, int32_t model, int32_t engine, void *cube, int64_t 
     A.M = (int)M;
     A.K = (int)K;
     A.cube = static_cast<float2 *>(cube);
-    if (engine == RR_GEMM_BF16X3) {
-        rc = rr_synth_gemm(c, A);
-        if (rc) return rc;
-    } else if (engine == RR_GEMM_EXACT) {
-        rc = rr_synth_freq(c, A);
-        if (rc) return rc;
+    if (engine == RR_GEMM_BF16X3 || engine == RR_GEMM_EXACT) {
+        HIPCHK(hipEventRecord(c->ev[2], c->stream));
+        FreqPlan q{c->ntx, c->nrx, (int)M, (int)K, 0, !shared, freq_pad(n_rest), freq_pad(n_mov)};
+        q.tile = freq_tile(q.T, q.R, q.K, q.per_el);
+        // the moving paths of the separable model: the GEMM, where its padding
+        // (256 channels, 64 samples, 96 paths) leaves it the cheaper engine
+        const bool gemm = model == RR_SEPARABLE && M > 1 &&
+                          gemm_cost(q.T * q.R, q.K, n_mov) < freq_cost(q, n_mov);
+        if (M == 1 || gemm) q.p_mov = 0;
+        if ((rc = freq_ensure(c->fq, q))) return rc;
+        if ((rc = freq_rest(c->fq, q, A, c->stream))) return rc;
+        if (gemm) {
+            SynthArgs G = A;
+            G.paths = sp + n_rest;
+            G.n_paths = n_mov;
+            if ((rc = rr_synth_gemm(c, G, c->fq.rest.as<const float2>()))) return rc;
+        } else if (M > 1 && (rc = freq_moving(c->fq, q, A, n_mov, c->stream))) {
+            return rc;
+        }
     } else if (idx) {
         HIPCHK(hipEventRecord(c->ev[2], c->stream));
         HIPCHK(launch_synth_sampled(A, idx, n_idx, c->stream));
@@ -1235,12 +1397,23 @@ int rr_synthesize_noalloc(rr_ctx *c, int32_t model, void *cube, int64_t cube_ele
     if (!base) return fail(RR_ESTATE, "scratch not initialised on device %d", c->device);
     SynPath *sp = reinterpret_cast<SynPath *>(base);
     int64_t *ranges = reinterpret_cast<int64_t *>(base + NOALLOC_RANGES_OFF);
+    int64_t *mranges = reinterpret_cast<int64_t *>(base + NOALLOC_MOV_OFF);
+    uint32_t *pre = reinterpret_cast<uint32_t *>(base + NOALLOC_PRE_OFF);
+    uint32_t *sums = reinterpret_cast<uint32_t *>(base + NOALLOC_SUMS_OFF);
+    const int split = M > 1;
+    // the second half of the counts' room takes the copy that rr_synthesize reads
+    HIPCHK(launch_rest_count(c->paths.soa, n, c->obj_vel.as<const double>(), c->nobj,
+                             c->pt_vel.as<const double>(), c->npts, split, sums,
+                             reinterpret_cast<int32_t *>(sums + RR_NOALLOC_MAX_PATHS / 256),
+                             c->stream));
     HIPCHK(launch_syn_prep(c->paths.soa, n, c->obj_vel.as<const double>(), c->nobj,
-                           c->pt_vel.as<const double>(), c->npts, sp, c->stream));
-    HIPCHK(launch_ranges(c->paths.soa.src, n, n_groups, shared ? -1 : 0, ranges, c->stream));
+                           c->pt_vel.as<const double>(), c->npts, split, sums, pre, sp, c->stream));
+    HIPCHK(launch_rest_ranges(c->paths.soa.src, n, n_groups, shared ? -1 : 0, pre, ranges, mranges,
+                              c->stream));
     SynthArgs A{};
     A.paths = sp;
     A.ranges = ranges;
+    A.mranges = mranges;
     A.n_paths = n;
     A.tx = c->tx.as<const double>();
     A.rx = c->rx.as<const double>();
@@ -1725,8 +1898,7 @@ struct BatchScene {
     bool use_freq = false;
     int tile = 0;                         // exact engine: product tile
     int64_t fq_cap = 0;                   // exact engine: leg table capacity (paths)
-    int fq_split = 1;
-    int64_t fq_ppad = 0, fq_split_len = 0;  // table stride and split length of the graph
+    int64_t fq_ppad = 0;                  // exact engine: table stride of the graph
     int64_t n_last = -1;                  // path count of the last launch
     void release()
     {
@@ -1750,13 +1922,15 @@ struct rr_batch {
     std::vector<BatchScene> sc;
     hipStream_t st = nullptr;
     hipEvent_t ev[6] = {};
-    DevBuf d_targs, d_sargs, d_info, d_chunk, d_items, d_vr, d_vel, d_rinfo, d_ranges;
+    DevBuf d_targs, d_sargs, d_info, d_chunk, d_items, d_vr, d_vel, d_rinfo, d_ranges, d_items_rest, d_items0, rest_pre, rest_sums;
     DevBuf counts, offsets, bsums, total, counter, work;
     PathStore tmp, fin;
     DevBuf syn, alpha_tmp;
-    DevBuf fq_xt, fq_yt, fq_amp, fq_src, fq_part;   // exact engine, shared by its scenes
-    int64_t cap = 0, V_total = 0, n_chunks = 0, n_items = 0, n_ranges = 0, nb = 0;
+    FreqBufs fq;                          // exact engine, shared by its scenes
+    int64_t cap = 0, V_total = 0, n_chunks = 0, n_ranges = 0, nb = 0;
+    int64_t n_items = 0, n_items_rest = 0, n_items0 = 0;   // direct engine's work
     std::vector<char> synth_on;           // scenes the synthesis stage computes
+    std::vector<SynthArgs> h_sargs;       // their arguments, as uploaded to d_sargs
     std::vector<int64_t> range_base;
     std::vector<void *> cubes;
     hipGraph_t graph = nullptr;
@@ -1823,6 +1997,12 @@ void batch_plan(BatchScene &x)
     x.tile = tile;
 }
 
+FreqPlan batch_freq_plan(const BatchScene &x)
+{
+    return FreqPlan{x.ntx, x.nrx, x.chirp.n_chirps, x.chirp.n_samples, x.tile, x.mode != RR_TX_SHARED,
+                    x.fq_ppad, x.chirp.n_chirps > 1 ? x.fq_ppad : 0};
+}
+
 // per-scene tables and global buffers for the current scene set and cubes;
 // only_K > 0 gives synthesis work to the scenes with that sample count alone,
 // only_scene >= 0 to that scene alone, and p_limit > 0 caps the paths of each
@@ -1836,6 +2016,7 @@ int batch_prepare(rr_batch *b, int only_K = 0, int64_t p_limit = 0, int only_sce
     std::vector<BatchVel> vel(S);
     std::vector<BatchRangeInfo> ri(S);
     std::vector<int64_t> chunk(S + 1, 0), items(S + 1, 0), vr(S + 1, 0);
+    std::vector<int64_t> items_rest(S + 1, 0), items0(S + 1, 0);
     b->range_base.assign(S + 1, 0);
     b->synth_on.assign(S, 0);
     int64_t V = 0, est = 0;
@@ -1858,16 +2039,20 @@ int batch_prepare(rr_batch *b, int only_K = 0, int64_t p_limit = 0, int only_sce
         if (x.kr <= 0) return fail(RR_EUNSUPPORTED, "scene %d: n_samples too large", s);
         const int n_groups = shared ? 1 : x.ntx;
         const int RC = shared ? x.ntx * x.nrx : x.nrx;
-        const int rows = RC * M;
+        const int rows = RC * (M - 1);        // of the chirps after the first
         const int RPB = 256 / (K / x.kr);
         info[s].kr = x.kr;
         info[s].rows_per_group = rows;
         info[s].rc = RC;
         info[s].bpg = (rows + RPB - 1) / RPB;
+        info[s].bpg0 = M > 1 ? (RC + RPB - 1) / RPB : 0;
         batch_plan(x);
         const bool synth = (only_K <= 0 || K == only_K) && (only_scene < 0 || s == only_scene);
         b->synth_on[s] = synth;
-        items[s + 1] = items[s] + (synth && !x.use_freq ? (int64_t)info[s].bpg * n_groups : 0);
+        const bool direct = synth && !x.use_freq;
+        items_rest[s + 1] = items_rest[s] + (direct ? (int64_t)x.ntx * x.nrx : 0);
+        items[s + 1] = items[s] + (direct ? (int64_t)info[s].bpg * n_groups : 0);
+        items0[s + 1] = items0[s] + (direct ? (int64_t)info[s].bpg0 * n_groups : 0);
         b->range_base[s + 1] = b->range_base[s] + (shared ? 2 : n_groups + 1);
     }
     vr[S] = V;
@@ -1876,6 +2061,8 @@ int batch_prepare(rr_batch *b, int only_K = 0, int64_t p_limit = 0, int only_sce
     b->V_total = V;
     b->n_chunks = chunk[S];
     b->n_items = items[S];
+    b->n_items_rest = items_rest[S];
+    b->n_items0 = items0[S];
     b->n_ranges = b->range_base[S];
     b->nb = scan_u8_blocks(V);
     int rc;
@@ -1895,35 +2082,21 @@ int batch_prepare(rr_batch *b, int only_K = 0, int64_t p_limit = 0, int only_sce
     if ((rc = b->d_rinfo.ensure(sizeof(BatchRangeInfo) * S))) return rc;
     if ((rc = b->d_chunk.ensure(8 * (S + 1)))) return rc;
     if ((rc = b->d_items.ensure(8 * (S + 1)))) return rc;
+    if ((rc = b->d_items_rest.ensure(8 * (S + 1)))) return rc;
+    if ((rc = b->d_items0.ensure(8 * (S + 1)))) return rc;
+    if ((rc = b->rest_pre.ensure((size_t)(b->cap + 1) * 4))) return rc;
+    if ((rc = b->rest_sums.ensure((size_t)(rest_blocks(b->cap) + 1) * 4))) return rc;
     if ((rc = b->d_vr.ensure(8 * (S + 1)))) return rc;
-    if ((rc = b->d_ranges.ensure(8 * (b->n_ranges + 1)))) return rc;
-    // exact engine: per scene the table stride (capacity, or the timing cap)
-    // and path splits; one set of tables serves its scenes in turn
-    {
-        const int64_t ks = freq_k_step();
-        size_t xt = 0, yt = 0, pp = 0, part = 0;
-        for (int s = 0; s < S; s++) {
-            BatchScene &x = b->sc[s];
-            if (!x.use_freq || !b->synth_on[s]) continue;
-            int64_t P = x.fq_cap;
-            if (p_limit > 0) P = std::min<int64_t>(P, std::max<int64_t>((p_limit + ks - 1) / ks * ks, ks));
-            x.fq_ppad = P;
-            const int M = x.chirp.n_chirps, K = x.chirp.n_samples;
-            freq_splits(x.tile, x.ntx, x.nrx, M, K, P, x.fq_split, x.fq_split_len);
-            const bool own = freq_own_tx(x.tile, x.mode != RR_TX_SHARED, true);
-            xt = std::max(xt, (size_t)M * (own ? 1 : x.ntx) * P * 8);
-            yt = std::max(yt, (size_t)M * x.nrx * P * 8);
-            pp = std::max(pp, (size_t)P * 4);
-            if (x.fq_split > 1)
-                part = std::max(part, (size_t)x.fq_split * M * K * x.ntx * x.nrx * 8);
-        }
-        if (pp) {
-            if ((rc = b->fq_xt.ensure(xt))) return rc;
-            if ((rc = b->fq_yt.ensure(yt))) return rc;
-            if ((rc = b->fq_amp.ensure(pp))) return rc;
-            if ((rc = b->fq_src.ensure(pp))) return rc;
-            if (part && (rc = b->fq_part.ensure(part))) return rc;
-        }
+    // the groups' ranges among the paths at rest, then among the moving paths
+    if ((rc = b->d_ranges.ensure(16 * (b->n_ranges + 1)))) return rc;
+    // exact engine: per scene the table stride (capacity, or the timing cap);
+    // one set of tables serves its scenes in turn
+    for (int s = 0; s < S; s++) {
+        BatchScene &x = b->sc[s];
+        if (!x.use_freq || !b->synth_on[s]) continue;
+        x.fq_ppad = x.fq_cap;
+        if (p_limit > 0) x.fq_ppad = std::min<int64_t>(x.fq_ppad, freq_pad(p_limit));
+        if ((rc = freq_ensure(b->fq, batch_freq_plan(x)))) return rc;
     }
     const double INV_2PI = 0.15915494309189535;
     for (int s = 0; s < S; s++) {
@@ -1965,6 +2138,7 @@ int batch_prepare(rr_batch *b, int only_K = 0, int64_t p_limit = 0, int only_sce
         Y = SynthArgs{};
         Y.paths = b->syn.as<const SynPath>();
         Y.ranges = b->d_ranges.as<const int64_t>() + b->range_base[s];
+        Y.mranges = Y.ranges + b->n_ranges;
         Y.n_paths = 0;
         Y.tx = x.tx.as<const double>();
         Y.rx = x.rx.as<const double>();
@@ -1988,12 +2162,14 @@ int batch_prepare(rr_batch *b, int only_K = 0, int64_t p_limit = 0, int only_sce
         vel[s].pt_vel = x.pt_vel.as<const double>();
         vel[s].nobj = x.nobj;
         vel[s].npts = x.npts;
+        vel[s].M = x.chirp.n_chirps;
         ri[s].vr0 = vr[s];
         ri[s].n_vps = x.n_vps;
         ri[s].base = b->range_base[s];
         ri[s].n_groups = (int)x.n_src;
         ri[s].shared = x.mode == RR_TX_SHARED;
     }
+    b->h_sargs = sa;
     hipStream_t st = b->st;
     HIPCHK(hipMemcpyAsync(b->d_targs.p, ta.data(), sizeof(TraceArgs) * S, hipMemcpyHostToDevice, st));
     HIPCHK(hipMemcpyAsync(b->d_sargs.p, sa.data(), sizeof(SynthArgs) * S, hipMemcpyHostToDevice, st));
@@ -2002,6 +2178,8 @@ int batch_prepare(rr_batch *b, int only_K = 0, int64_t p_limit = 0, int only_sce
     HIPCHK(hipMemcpyAsync(b->d_rinfo.p, ri.data(), sizeof(BatchRangeInfo) * S, hipMemcpyHostToDevice, st));
     HIPCHK(hipMemcpyAsync(b->d_chunk.p, chunk.data(), 8 * (S + 1), hipMemcpyHostToDevice, st));
     HIPCHK(hipMemcpyAsync(b->d_items.p, items.data(), 8 * (S + 1), hipMemcpyHostToDevice, st));
+    HIPCHK(hipMemcpyAsync(b->d_items_rest.p, items_rest.data(), 8 * (S + 1), hipMemcpyHostToDevice, st));
+    HIPCHK(hipMemcpyAsync(b->d_items0.p, items0.data(), 8 * (S + 1), hipMemcpyHostToDevice, st));
     HIPCHK(hipMemcpyAsync(b->d_vr.p, vr.data(), 8 * (S + 1), hipMemcpyHostToDevice, st));
     HIPCHK(hipStreamSynchronize(st));
     return RR_OK;
@@ -2024,11 +2202,13 @@ int batch_enqueue_trace(rr_batch *b, bool timed)
                           b->offsets.as<const uint32_t>(), b->fin.soa, b->cap, st));
     HIPCHK(launch_batch_prep(b->fin.soa, b->total.as<const unsigned long long>(), b->cap,
                              b->d_vr.as<const int64_t>(), b->S, b->d_vel.as<const BatchVel>(),
+                             b->rest_sums.as<uint32_t>(), b->rest_pre.as<uint32_t>(),
                              b->syn.as<SynPath>(), st));
     HIPCHK(launch_batch_ranges(b->offsets.as<const uint32_t>(), b->V_total,
                                b->total.as<const unsigned long long>(), b->cap,
-                               b->d_rinfo.as<const BatchRangeInfo>(), b->S, b->d_ranges.as<int64_t>(),
-                               st));
+                               b->d_rinfo.as<const BatchRangeInfo>(), b->S,
+                               b->rest_pre.as<const uint32_t>(), b->d_ranges.as<int64_t>(),
+                               b->d_ranges.as<int64_t>() + b->n_ranges, st));
     if (timed) HIPCHK(hipEventRecord(b->ev[1], st));
     return RR_OK;
 }
@@ -2037,31 +2217,24 @@ int batch_enqueue_synth(rr_batch *b, bool timed)
 {
     hipStream_t st = b->st;
     unsigned long long *work = b->work.as<unsigned long long>();
-    HIPCHK(launch_fill_u64(work + 1, 1, 0ull, st));
+    HIPCHK(launch_fill_u64(work + 1, 3, 0ull, st));
     if (timed) HIPCHK(hipEventRecord(b->ev[2], st));
-    HIPCHK(launch_batch_synth(b->d_sargs.as<const SynthArgs>(), b->d_info.as<const BatchSynthInfo>(),
-                              b->d_items.as<const int64_t>(), b->S, b->n_items, work + 1, st));
+    const DevBuf *items[3] = {&b->d_items_rest, &b->d_items, &b->d_items0};
+    const int64_t n_items[3] = {b->n_items_rest, b->n_items, b->n_items0};
+    for (int g = 0; g < 3; g++)
+        HIPCHK(launch_batch_synth(g, b->d_sargs.as<const SynthArgs>(),
+                                  b->d_info.as<const BatchSynthInfo>(),
+                                  items[g]->as<const int64_t>(), b->S, n_items[g], work + 1 + g, st));
     // the exact product engine's scenes, one after the other on the shared
-    // tables; each reads its path range from the device
-    const int64_t *rg = b->d_ranges.as<const int64_t>();
+    // tables; each reads its path ranges from the device
     for (int s = 0; s < b->S; s++) {
         const BatchScene &x = b->sc[s];
         if (!x.use_freq || !b->synth_on[s]) continue;
-        const int64_t *lo = rg + b->range_base[s], *hi = rg + b->range_base[s + 1] - 1;
-        const int M = x.chirp.n_chirps, K = x.chirp.n_samples;
-        const double inv_c = 1.0 / 299792458.0;
-        HIPCHK(launch_freq_prep(b->syn.as<const SynPath>(), 0, lo, hi, x.fq_ppad, M, x.chirp.t_rep,
-                                x.tx.as<const double>(), x.ntx,
-                                freq_own_tx(x.tile, x.mode != RR_TX_SHARED, true),
-                                x.rx.as<const double>(), x.nrx, x.chirp.f0 * inv_c,
-                                x.chirp.bandwidth / (double)K * inv_c, b->fq_xt.as<uint2>(),
-                                b->fq_yt.as<uint2>(),
-                                b->fq_amp.as<float>(), b->fq_src.as<int32_t>(), st));
-        HIPCHK(launch_freq_gemm(b->fq_xt.as<const uint2>(), b->fq_yt.as<const uint2>(),
-                                b->fq_amp.as<const float>(), b->fq_src.as<const int32_t>(), x.ntx,
-                                x.nrx, M, K, x.fq_ppad, x.fq_split, x.fq_split_len,
-                                x.mode != RR_TX_SHARED, x.tile, lo, hi, lo, b->fq_part.as<float2>(),
-                                static_cast<float2 *>(b->cubes[s]), st));
+        const FreqPlan q = batch_freq_plan(x);
+        const SynthArgs &A = b->h_sargs[s];
+        if (int rc = freq_rest(b->fq, q, A, st)) return rc;
+        if (q.M > 1)
+            if (int rc = freq_moving(b->fq, q, A, -1, st)) return rc;
     }
     if (timed) HIPCHK(hipEventRecord(b->ev[3], st));
     return RR_OK;
@@ -2073,10 +2246,10 @@ int batch_enqueue_synth(rr_batch *b, bool timed)
 int batch_check(rr_batch *b, bool *overflow)
 {
     unsigned long long cnt = 0, tot = 0;
-    std::vector<int64_t> r(b->n_ranges + 1);
+    std::vector<int64_t> r(2 * b->n_ranges + 1);
     HIPCHK(hipMemcpyAsync(&cnt, b->counter.p, 8, hipMemcpyDeviceToHost, b->st));
     HIPCHK(hipMemcpyAsync(&tot, b->total.p, 8, hipMemcpyDeviceToHost, b->st));
-    HIPCHK(hipMemcpyAsync(r.data(), b->d_ranges.p, 8 * b->n_ranges, hipMemcpyDeviceToHost, b->st));
+    HIPCHK(hipMemcpyAsync(r.data(), b->d_ranges.p, 16 * b->n_ranges, hipMemcpyDeviceToHost, b->st));
     HIPCHK(hipStreamSynchronize(b->st));
     *overflow = (int64_t)cnt > b->cap;
     if (*overflow) b->cap = (int64_t)cnt + (int64_t)cnt / 4 + 4096;
@@ -2084,7 +2257,8 @@ int batch_check(rr_batch *b, bool *overflow)
     if (*overflow) return RR_OK;   // counts are cut short: re-run first
     for (int s = 0; s < b->S; s++) {
         BatchScene &x = b->sc[s];
-        const int64_t n = r[b->range_base[s + 1] - 1] - r[b->range_base[s]];
+        const int64_t g0 = b->range_base[s], g1 = b->range_base[s + 1] - 1;
+        const int64_t n = r[g1] - r[g0] + r[b->n_ranges + g1] - r[b->n_ranges + g0];
         x.n_last = n;
         if (x.use_freq && b->synth_on[s] && n > x.fq_ppad) {
             x.fq_cap = n + n / 4 + 1024;
@@ -2133,8 +2307,9 @@ void rr_batch_destroy(rr_batch *b)
     DevBuf *bufs[] = {&b->d_targs, &b->d_sargs, &b->d_info, &b->d_chunk, &b->d_items, &b->d_vr,
                       &b->d_vel, &b->d_rinfo, &b->d_ranges, &b->counts, &b->offsets, &b->bsums,
                       &b->total, &b->counter, &b->work, &b->syn, &b->alpha_tmp, &b->tmp.buf,
-                      &b->fin.buf};
+                      &b->fin.buf, &b->d_items_rest, &b->d_items0, &b->rest_pre, &b->rest_sums};
     for (DevBuf *x : bufs) x->release();
+    b->fq.release();
     for (auto &e : b->ev)
         if (e) (void)hipEventDestroy(e);
     if (b->st) (void)hipStreamDestroy(b->st);

@@ -114,9 +114,13 @@ struct SynPath {
     int32_t src;
 };
 
+// The records of a synthesis are split in two, each part in path order: the
+// paths at rest (every hit on an object of zero velocity), whose sum is the
+// same for every chirp and is formed once, then the moving ones.
 struct SynthArgs {
     const SynPath *paths;
-    const int64_t *ranges;    // [n_groups + 1] path range of each group
+    const int64_t *ranges;    // [n_groups + 1] paths at rest of each group
+    const int64_t *mranges;   // [n_groups + 1] moving paths of each group
     int64_t n_paths;
     const double *tx, *rx;    // device [n][3]
     int ntx, nrx;
@@ -154,12 +158,14 @@ struct BatchSynthInfo {
     int kr;                   // samples per lane (tile shape)
     int rows_per_group;
     int rc;                   // channels per group
-    int bpg;                  // workgroups per group
+    int bpg;                  // workgroups per group for the chirps after the first
+    int bpg0;                 // workgroups per group for the first chirp
 };
 struct BatchVel {
     const double *obj_vel;
     const double *pt_vel;
     int nobj, npts;
+    int M;                    // chirps: with one, every path counts as at rest
 };
 struct BatchRangeInfo {
     int64_t vr0;              // first virtual ray of the scene
@@ -192,14 +198,21 @@ hipError_t launch_bp_mfma(const float2 *cube, int64_t stride, const double *tx, 
 int64_t bp_mfma_frag_bytes(int K);
 int freq_k_step();
 int freq_k_group();   // samples per exact-GEMM workgroup
-// leg tables of n paths, or (rng_lo != NULL) of the records *rng_lo ..
-// *rng_hi of `paths` read on the device, at most Ppad of them; own_tx: one X
-// row per chirp, each path's own transmitter (see freq_own_tx)
-hipError_t launch_freq_prep(const SynPath *paths, int64_t n, const int64_t *rng_lo,
-                            const int64_t *rng_hi, int64_t Ppad, int M, double t_rep,
-                            const double *tx, int T, bool own_tx, const double *rx, int R,
-                            double f0c, double dfc, uint2 *xt, uint2 *yt, float *amp, int32_t *src,
-                            hipStream_t s);
+// leg tables of the records *rng_lo .. *rng_hi of `paths` (read on the device,
+// at most Ppad of them); own_tx: one X row per chirp, each path's own
+// transmitter (see freq_own_tx); sep: the separable model's legs, from the
+// phase centres oT, oR
+struct FreqLegs {
+    const SynPath *paths;
+    const int64_t *rng_lo, *rng_hi;
+    const double *tx, *rx;
+    int T, R, M;
+    double t_rep, f0c, dfc;
+    int sep;
+    double oT[3], oR[3];
+};
+hipError_t launch_freq_prep(const FreqLegs &L, int64_t Ppad, bool own_tx, uint2 *xt, uint2 *yt,
+                            float *amp, int32_t *src, hipStream_t s);
 // the X table keeps one row per chirp (each path's own transmitter) for a
 // per-element launch on the sample split with transmitter groups, else one
 // per (chirp, transmitter); entries (8 bytes each) of both tables
@@ -210,18 +223,33 @@ int64_t freq_table_entries(int T, int R, int M, int64_t Ppad, bool own_tx);
 // the modelled time (relative) of one, and the path splits of a launch
 int freq_tile(int T, int R, int K, bool per_element);
 double freq_tile_cost(int T, int R, int K, int tile, bool per_element);
-void freq_splits(int tile, int T, int R, int M, int K, int64_t Ppad, int &n_split, int64_t &split_len);
+int freq_splits(int tile, int T, int R, int M, int K);
 // the exact model's AUTO rule: the best product layout is modelled at least
 // 1.5x the direct engine's throughput
 bool freq_pays(int T, int R, int K, bool per_element);
-// rng_lo / rng_hi (may be NULL): the path count read on the device, as for
-// launch_freq_prep; the splits then divide that count evenly.  groups (may be
-// NULL; per-element launch, tile 1): [T + 1] path range of each transmitter
-// in the list the tables were built from (offset by groups[0])
-hipError_t launch_freq_gemm(const uint2 *xt, const uint2 *yt, const float *amp, const int32_t *src,
-                            int T, int R, int M, int K, int64_t Ppad, int n_split, int64_t split_len,
-                            int per_element, int tile, const int64_t *rng_lo, const int64_t *rng_hi,
-                            const int64_t *groups, float2 *partial, float2 *cube, hipStream_t s);
+// The layout of the moving paths of a launch on layout `tile`: up to
+// FREQ_MOV_KS of them run as the sample split, whose wavefronts write whole
+// runs of samples (the tiles store 8 bytes per channel and sample).
+#define FREQ_MOV_KS 1024
+int freq_mov_tile(int tile, int K, bool per_element);
+// cube[c][m][k] = rest[c][k] (if given) + the sum over the paths of the
+// tables, whose count is read on the device (*rng_hi - *rng_lo, at most Ppad)
+// and divided evenly over the splits.  groups (may be NULL; per-element
+// launch, tile 1): [T + 1] path range of each transmitter, offset by
+// groups[0].  The launch does its work only if gate_lo < count <= gate_hi.
+struct FreqSum {
+    const uint2 *xt, *yt;
+    const float *amp;
+    const int32_t *src;
+    int T, R, M, K;
+    int64_t Ppad;
+    int per_element, tile;
+    const int64_t *rng_lo, *rng_hi, *groups;
+    int64_t gate_lo, gate_hi;
+    const float2 *rest;
+    float2 *partial, *cube;
+};
+hipError_t launch_freq_gemm(const FreqSum &q, hipStream_t s);
 hipError_t launch_refit(float4 *nodes, float *ubox, const int32_t *order,
                         const int64_t *level_start, int n_levels, float4 *ltris, int64_t n_tris,
                         const int32_t *tris, const float *verts, double pad, hipStream_t s);
@@ -236,10 +264,23 @@ hipError_t launch_scatter(const PathSoA &tmp, const unsigned long long *counter,
                           const uint32_t *offsets, const PathSoA &dst, int64_t keep,
                           hipStream_t s);
 
+// Synthesis records in two parts (see SynthArgs): rest_blocks(n) block counts
+// and n + 1 prefix entries of scratch.  split = 0 keeps every path in the
+// first part.  launch_rest_ranges then gives the ranges of every group in
+// both parts from the ranges `all` in the path list (may be the `rest` table
+// itself), or from the sorted sources of one scene when all is NULL.
+int64_t rest_blocks(int64_t n);
+hipError_t launch_rest_count(const PathSoA &paths, int64_t n, const double *obj_vel, int nobj,
+                             const double *pt_vel, int npts, int split, uint32_t *bsums,
+                             int32_t *info, hipStream_t s);
 hipError_t launch_syn_prep(const PathSoA &paths, int64_t n, const double *obj_vel, int nobj,
-                           const double *pt_vel, int npts, SynPath *out, hipStream_t s);
-hipError_t launch_ranges(const int32_t *src, int64_t n, int n_groups, int g0, int64_t *ranges,
-                         hipStream_t s);
+                           const double *pt_vel, int npts, int split, const uint32_t *bsums,
+                           uint32_t *pre, SynPath *out, hipStream_t s);
+hipError_t launch_rest_ranges(const int32_t *src, int64_t n, int n_groups, int g0,
+                              const uint32_t *pre, int64_t *rest, int64_t *mov, hipStream_t s);
+// direct engine: the paths at rest into chirp 0 of every channel, then that
+// row plus the moving paths into every other chirp, then the moving paths
+// into chirp 0
 hipError_t launch_synth_direct(const SynthArgs &a, int n_groups, int rows_per_group,
                                hipStream_t s);
 hipError_t launch_synth_sampled(const SynthArgs &a, const int64_t *idx, int64_t n_idx,
@@ -255,7 +296,7 @@ hipError_t launch_gemm_prep_a(const float2 *T, const float2 *R, int nrx, int C, 
                               uint4 *Af, hipStream_t s);
 hipError_t launch_gemm_prep_b(const SynthArgs &a, int Ppad, uint4 *Bp, hipStream_t s);
 hipError_t launch_gemm_main(const uint4 *Af, const uint4 *Bp, int Cpad, int Ppad, int C, int M,
-                            int K, float2 *cube, hipStream_t s);
+                            int K, const float2 *rest, float2 *cube, hipStream_t s);
 
 // learned proposal (k_trace.hip: probe and histogram; k_mlp.hip: network)
 hipError_t launch_probe(const TraceArgs &a, float *code, hipStream_t s);
@@ -279,13 +320,16 @@ hipError_t launch_build_cdf(const float *z, float beta, float power, float kappa
                             hipStream_t s);
 hipError_t launch_batch_trace(const TraceArgs *scenes, const int64_t *chunk_start, int S,
                               int64_t n_chunks, unsigned long long *work, hipStream_t s);
-hipError_t launch_batch_synth(const SynthArgs *scenes, const BatchSynthInfo *info,
+// stage 0: paths at rest into chirp 0 (items: channels), 1: the other chirps,
+// 2: moving paths into chirp 0
+hipError_t launch_batch_synth(int stage, const SynthArgs *scenes, const BatchSynthInfo *info,
                               const int64_t *item_start, int S, int64_t n_items,
                               unsigned long long *work, hipStream_t s);
 hipError_t launch_batch_prep(const PathSoA &paths, const unsigned long long *total, int64_t cap,
-                             const int64_t *vr_start, int S, const BatchVel *vel, SynPath *out,
-                             hipStream_t s);
+                             const int64_t *vr_start, int S, const BatchVel *vel, uint32_t *bsums,
+                             uint32_t *pre, SynPath *out, hipStream_t s);
+// rest / mov: ranges of every scene's groups in the two parts of the records
 hipError_t launch_batch_ranges(const uint32_t *offsets, int64_t V, const unsigned long long *total,
-                               int64_t cap, const BatchRangeInfo *ri, int S, int64_t *ranges,
-                               hipStream_t s);
+                               int64_t cap, const BatchRangeInfo *ri, int S, const uint32_t *pre,
+                               int64_t *rest, int64_t *mov, hipStream_t s);
 hipError_t launch_fill_u64(unsigned long long *p, int64_t n, unsigned long long v, hipStream_t s);
