@@ -27,6 +27,7 @@ SOURCES = {
     "rr_host.cpp": [],
     "rr_bvh.cpp": [],
     "rr_pieces.cpp": ["-ffp-contract=off"],
+    "rr_bands.cpp": [],
     "k_trace.hip": ["-ffp-contract=off"],
     "k_synth.hip": [],
     "k_gemm.hip": [],
@@ -34,6 +35,7 @@ SOURCES = {
     "k_image.hip": [],
     "k_refit.hip": ["-ffp-contract=off"],
     "k_freq.hip": [],
+    "k_band.hip": [],
     "k_bpmfma.hip": [],
 }
 

@@ -89,10 +89,11 @@ __global__ __launch_bounds__(256) void k_freq_legs(FreqLegs A, int64_t Ppad, uin
 {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t n = path_count(A.rng_lo, A.rng_hi, Ppad);
-    if (p >= pad_count(n)) return;
+    if (p >= (A.perm ? (int64_t)*A.used : pad_count(n))) return;
+    const int64_t rec = A.perm ? (int64_t)A.perm[p] : p < n ? p : -1;
     const int M = A.M, R = A.R, T = A.T;
     const int XR = OWN_TX ? 1 : T;
-    if (p >= n) {
+    if (rec < 0) {
         for (int m = blockIdx.y; m < M; m += gridDim.y) {
             for (int i = 0; i < XR; i++) xt[((int64_t)m * XR + i) * Ppad + p] = make_uint2(0u, 0u);
             for (int i = 0; i < R; i++) yt[((int64_t)m * R + i) * Ppad + p] = make_uint2(0u, 0u);
@@ -103,7 +104,7 @@ __global__ __launch_bounds__(256) void k_freq_legs(FreqLegs A, int64_t Ppad, uin
         }
         return;
     }
-    const SynPath &P = A.paths[*A.rng_lo + p];
+    const SynPath &P = A.paths[*A.rng_lo + rec];
     const int K = P.K;
     const int t_own = OWN_TX ? min(max(P.src, 0), T - 1) : 0;
     double h[RR_KMAX][3], v[RR_KMAX][3];   // the path's points, held over the chirps
@@ -278,6 +279,7 @@ struct FreqArgs {
     const float *amp;
     const int32_t *src;
     int T, R, M, K;
+    int m0, m_all;            // chirps m0 .. m0 + M - 1 of m_all (tile layouts; else all)
     int64_t Ppad;
     int tt, rt;               // Tx and Rx tiles
     int kg;                   // groups of FQ_G samples
@@ -286,11 +288,18 @@ struct FreqArgs {
     // split [split][channel][m][k]
     float2 *out;
     int partial;
-    const float2 *rest;       // cube only: [channel][k] added to every chirp, or NULL
+    // [channel][k] added to every chirp, or NULL (tile layouts: by the
+    // reduction, the products being partial sums then)
+    const float2 *rest;
     // the path count is *rng_hi - *rng_lo (at most Ppad), read on the device;
     // the splits divide its padded count evenly
     const int64_t *rng_lo, *rng_hi;
     int64_t gate_lo, gate_hi; // nothing is done unless gate_lo < count <= gate_hi
+    // bands (one chirp): work items of the plan's segments, samples at the
+    // nodes of their class, partial sums to out[slot][channel]
+    BandPlan *plan;
+    const BandSeg *segs;
+    const int32_t *nodes;
     // sample split (one channel per wavefront): k = k1 S + k2, S = 2^S_log2
     int S, S_log2;
     int64_t n_waves;
@@ -313,7 +322,10 @@ struct FreqArgs {
 // lane order so that every read is a contiguous 1 KiB.  Each wavefront
 // generates its own X and Y fragments for its sample.  Rows beyond the
 // array's Tx and Rx counts read row 0's words and are never stored.
-template <bool PER_EL, int BS, int NB>
+// BANDS: the workgroups pull the items of a band plan (a segment's paths at
+// four nodes of its class) from its counter until none is left; the tables
+// are sorted by band.
+template <bool PER_EL, int BS, int NB, bool BANDS>
 __global__ __launch_bounds__(FQ_G * 64, BS == 16 ? (NB == 1 ? 4 : 2)
                                                  : (NB == 3 || (NB == 2 && PER_EL) ? 1 : (NB == 2 ? 2 : 4)))
 void k_freq_gemm(FreqArgs A)
@@ -328,26 +340,61 @@ void k_freq_gemm(FreqArgs A)
     __shared__ uint4 Ls[2][CH + 1][64];
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // the sample group fastest: the workgroups that share one split's tables
-    // run together
-    const int64_t n = path_count(A.rng_lo, A.rng_hi, A.Ppad);
-    if (n <= A.gate_lo || n > A.gate_hi) return;
-    const int64_t used = pad_count(n);
-    const int64_t split_len = pad_count((used + A.n_split - 1) / A.n_split);
-    int64_t id = blockIdx.x;
-    const int kq = (int)(id % A.kg);
-    id /= A.kg;
-    const int ri = (int)(id % A.rt);
-    id /= A.rt;
-    const int ti = (int)(id % A.tt);
-    id /= A.tt;
-    const int m = (int)(id % A.M);
-    const int s = (int)(id / A.M);
-    const int kw = kq * FQ_G + w;
-    const bool kv = kw < A.K;
-    const unsigned ku = (unsigned)(kv ? kw : A.K - 1);
-    const int64_t pstart = (int64_t)s * split_len;
-    const int64_t nsteps = max(min(used, pstart + split_len) - pstart, (int64_t)0) / STEP;
+    __shared__ int next_s;
+    const int items = BANDS ? A.plan->n_items * A.tt * A.rt : 0;
+    do {
+    int ri, ti, m = 0, s = 0, kw;
+    bool kv;
+    unsigned ku;
+    int64_t pstart, nsteps, slot = 0;
+    if (BANDS) {
+        // the next item: which workgroup takes it changes nothing in the sums
+        if (threadIdx.x == 0) next_s = atomicAdd(&A.plan->next, 1);
+        __syncthreads();
+        const int it = __builtin_amdgcn_readfirstlane(next_s);
+        __syncthreads();
+        if (it >= items) return;
+        const int tiles = A.tt * A.rt;
+        const int item = it / tiles;
+        const int tile = it - item * tiles;
+        ri = tile % A.rt;
+        ti = tile / A.rt;
+        int lo = 0, hi = A.plan->n_segs - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) / 2;
+            if (A.segs[mid].item0 <= item) lo = mid; else hi = mid - 1;
+        }
+        const BandSeg q = A.segs[lo];
+        const int g = item - q.item0;
+        kw = g * FQ_G + w;
+        slot = (int64_t)q.slot0 + kw;
+        kv = q.cls >= 0 || kw < A.K;
+        ku = q.cls >= 0 ? (unsigned)A.nodes[q.cls * RR_BAND_NMAX + kw]
+                        : (unsigned)(kv ? kw : A.K - 1);
+        pstart = q.p0;
+        nsteps = q.np / STEP;
+    } else {
+        // the sample group fastest: the workgroups that share one split's
+        // tables run together
+        const int64_t n = path_count(A.rng_lo, A.rng_hi, A.Ppad);
+        if (n <= A.gate_lo || n > A.gate_hi) return;
+        const int64_t used = pad_count(n);
+        const int64_t split_len = pad_count((used + A.n_split - 1) / A.n_split);
+        int64_t id = blockIdx.x;
+        const int kq = (int)(id % A.kg);
+        id /= A.kg;
+        ri = (int)(id % A.rt);
+        id /= A.rt;
+        ti = (int)(id % A.tt);
+        id /= A.tt;
+        m = (int)(id % A.M);
+        s = (int)(id / A.M);
+        kw = kq * FQ_G + w;
+        kv = kw < A.K;
+        ku = (unsigned)(kv ? kw : A.K - 1);
+        pstart = (int64_t)s * split_len;
+        nsteps = max(min(used, pstart + split_len) - pstart, (int64_t)0) / STEP;
+    }
     // an empty split still writes its (zero) tile; its loads stay at path 0
     const int64_t pbeg = nsteps > 0 ? pstart : 0;
     const int t0 = ti * TILE, r0 = ri * TILE;
@@ -364,8 +411,8 @@ void k_freq_gemm(FreqArgs A)
         const int tab = q / (4 * NB), blk = (q % (4 * NB)) >> 2, c = q & 3;
         int row = (tab ? r0 : t0) + BS * blk + lrow;
         if (row >= (tab ? A.R : A.T)) row = 0;    // any valid row: masked later
-        const uint2 *base = tab ? A.yt + ((int64_t)m * A.R + row) * A.Ppad
-                                : A.xt + ((int64_t)m * A.T + row) * A.Ppad;
+        const uint2 *base = tab ? A.yt + ((int64_t)(A.m0 + m) * A.R + row) * A.Ppad
+                                : A.xt + ((int64_t)(A.m0 + m) * A.T + row) * A.Ppad;
         lp[j] = reinterpret_cast<const u32x4 *>(base + 8 * grp + 2 * c);
     }
     // amplitudes and sources of a step: wavefront 0, lanes 0 .. STEP/4 - 1
@@ -458,7 +505,7 @@ void k_freq_gemm(FreqArgs A)
 #undef FQ_STASH
     // D layout: register e of lane l is row 8 (e / 4) + 4 (l / 32) + e % 4
     // (BS = 32) or 4 (l / 16) + e (BS = 16) of the block, column l % BS
-    if (!kv) return;
+    if (kv)
 #pragma unroll
     for (int i = 0; i < NB; i++)
 #pragma unroll
@@ -470,15 +517,15 @@ void k_freq_gemm(FreqArgs A)
                 const int ro = r0 + BS * j + lrow;
                 if (to < A.T && ro < A.R) {
                     const float2 v = make_float2(sr[i][j][e], si[i][j][e]);
-                    const int64_t c = (int64_t)to * A.R + ro;
-                    if (A.partial) {
+                    if (BANDS)
+                        A.out[(slot * A.T + to) * A.R + ro] = v;
+                    else if (A.partial)
                         A.out[((((int64_t)s * A.M + m) * A.K + kw) * A.T + to) * A.R + ro] = v;
-                    } else {
-                        const float2 b = A.rest ? A.rest[c * A.K + kw] : make_float2(0.0f, 0.0f);
-                        A.out[(c * A.M + m) * A.K + kw] = make_float2(v.x + b.x, v.y + b.y);
-                    }
+                    else
+                        A.out[(((int64_t)to * A.R + ro) * A.M + m) * A.K + kw] = v;
                 }
             }
+    } while (BANDS);
 }
 
 // One wavefront per (path split, chirp, channel): the channel's samples as a
@@ -717,7 +764,7 @@ __global__ __launch_bounds__(256) void k_freq_reduce(FreqArgs A, float2 *cube)
                 v.x += b.x;
                 v.y += b.y;
             }
-            cube[((int64_t)c * A.M + m) * A.K + k] = v;
+            cube[((int64_t)c * A.m_all + A.m0 + m) * A.K + k] = v;
         }
     }
 }
@@ -871,6 +918,27 @@ int freq_splits(int tile, int T, int R, int M, int K)
     return (int)std::min<int64_t>(128, std::max<int64_t>(1, (1024 + groups - 1) / groups));
 }
 
+// Chirps of one launch: the tile layouts' products of several chirps are
+// partial sums [m][k][channel] that the reduction turns into the cube's order,
+// about 128 MiB of them at a time (they stay in the last-level cache).
+int freq_chirps(int tile, int T, int R, int M, int K)
+{
+    if (tile == 1 || M == 1) return M;
+    return (int)std::min<int64_t>(M, std::max<int64_t>(1, ((int64_t)1 << 27) / ((int64_t)T * R * K * 8)));
+}
+
+// bytes of partial sums
+int64_t freq_partial(int tile, int T, int R, int M, int K)
+{
+    const int step = freq_chirps(tile, T, R, M, K);
+    int64_t most = 0;
+    for (int m : {step, M % step}) {
+        const int ns = m ? freq_splits(tile, T, R, m, K) : 0;
+        if (ns > 1 || (ns && tile != 1 && M > 1)) most = std::max(most, (int64_t)ns * m * K * T * R * 8);
+    }
+    return most;
+}
+
 int freq_mov_tile(int tile, int K, bool per_element)
 {
     return !per_element && K <= FQ_KS_KMAX ? 1 : tile;
@@ -883,23 +951,19 @@ hipError_t launch_freq_gemm(const FreqSum &q, hipStream_t s)
     if (tile != 1 && tile != 16 && tile != 32 && tile != 48 && tile != 64 && tile != 96)
         return hipErrorInvalidValue;
     if (tile == 1 && K > FQ_KS_KMAX) return hipErrorInvalidValue;
-    const int n_split = freq_splits(tile, T, R, M, K);
-    FreqArgs A;
+    FreqArgs A{};
     A.xt = q.xt;
     A.yt = q.yt;
     A.amp = q.amp;
     A.src = q.src;
     A.T = T;
     A.R = R;
-    A.M = M;
     A.K = K;
+    A.m_all = M;
     A.Ppad = q.Ppad;
     A.tt = (T + tile - 1) / tile;
     A.rt = (R + tile - 1) / tile;
     A.kg = (K + FQ_G - 1) / FQ_G;
-    A.n_split = n_split;
-    A.partial = n_split > 1;
-    A.out = n_split > 1 ? q.partial : q.cube;
     A.rest = q.rest;
     A.rng_lo = q.rng_lo;
     A.rng_hi = q.rng_hi;
@@ -908,12 +972,18 @@ hipError_t launch_freq_gemm(const FreqSum &q, hipStream_t s)
     A.groups = tile == 1 && q.per_element ? q.groups : nullptr;
     int qb = 1, sb = 1;
     ks_shape(K, qb, sb, A.S, A.S_log2);
-    A.n_waves = (int64_t)n_split * M * T * R;
-    const int64_t blocks = tile == 1 ? (A.n_waves + FQ_G - 1) / FQ_G
-                                     : (int64_t)n_split * M * A.tt * A.rt * A.kg;
-    if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
-    const dim3 g((unsigned)blocks), t(FQ_G * 64);
     const bool pe = q.per_element != 0;
+    const int step = freq_chirps(tile, T, R, M, K);
+    for (A.m0 = 0; A.m0 < M; A.m0 += step) {
+        A.M = std::min(step, M - A.m0);
+        A.n_split = freq_splits(tile, T, R, A.M, K);
+        A.partial = A.n_split > 1 || (tile != 1 && q.rest);
+        A.out = A.partial ? q.partial : q.cube;
+        A.n_waves = (int64_t)A.n_split * A.M * T * R;
+        const int64_t blocks = tile == 1 ? (A.n_waves + FQ_G - 1) / FQ_G
+                                         : (int64_t)A.n_split * A.M * A.tt * A.rt * A.kg;
+        if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+        const dim3 g((unsigned)blocks), t(FQ_G * 64);
 #define KS_LAUNCH(QB, SB)                                                                         \
     do {                                                                                          \
         if (pe) hipLaunchKernelGGL((k_freq_ks<true, QB, SB>), g, t, 0, s, A);                     \
@@ -921,29 +991,64 @@ hipError_t launch_freq_gemm(const FreqSum &q, hipStream_t s)
     } while (0)
 #define FQ_LAUNCH(BS, NB)                                                                         \
     do {                                                                                          \
-        if (pe) hipLaunchKernelGGL((k_freq_gemm<true, BS, NB>), g, t, 0, s, A);                   \
-        else hipLaunchKernelGGL((k_freq_gemm<false, BS, NB>), g, t, 0, s, A);                     \
+        if (pe) hipLaunchKernelGGL((k_freq_gemm<true, BS, NB, false>), g, t, 0, s, A);            \
+        else hipLaunchKernelGGL((k_freq_gemm<false, BS, NB, false>), g, t, 0, s, A);              \
     } while (0)
-    switch (tile) {
-    case 1:
-        if (qb == 1 && sb == 1) KS_LAUNCH(1, 1);
-        else if (qb == 1) KS_LAUNCH(1, 2);
-        else KS_LAUNCH(2, 2);
-        break;
-    case 16: FQ_LAUNCH(16, 1); break;
-    case 48: FQ_LAUNCH(16, 3); break;
-    case 32: FQ_LAUNCH(32, 1); break;
-    case 64: FQ_LAUNCH(32, 2); break;
-    default: FQ_LAUNCH(32, 3); break;
-    }
+        switch (tile) {
+        case 1:
+            if (qb == 1 && sb == 1) KS_LAUNCH(1, 1);
+            else if (qb == 1) KS_LAUNCH(1, 2);
+            else KS_LAUNCH(2, 2);
+            break;
+        case 16: FQ_LAUNCH(16, 1); break;
+        case 48: FQ_LAUNCH(16, 3); break;
+        case 32: FQ_LAUNCH(32, 1); break;
+        case 64: FQ_LAUNCH(32, 2); break;
+        default: FQ_LAUNCH(32, 3); break;
+        }
 #undef FQ_LAUNCH
 #undef KS_LAUNCH
-    if (n_split > 1 && tile == 1) {
-        const int64_t per = (int64_t)M * K * T * R;
-        hipLaunchKernelGGL(k_freq_sum, dim3((unsigned)((per + 255) / 256)), dim3(256), 0, s, A, q.cube);
-    } else if (n_split > 1) {
-        const int64_t nb = (int64_t)((T * R + 31) / 32) * ((K + 31) / 32) * M;
-        hipLaunchKernelGGL(k_freq_reduce, dim3((unsigned)nb), dim3(256), 0, s, A, q.cube);
+        if (A.partial && tile == 1) {
+            const int64_t per = (int64_t)A.M * K * T * R;
+            hipLaunchKernelGGL(k_freq_sum, dim3((unsigned)((per + 255) / 256)), dim3(256), 0, s, A, q.cube);
+        } else if (A.partial) {
+            const int64_t nb = (int64_t)((T * R + 31) / 32) * ((K + 31) / 32) * A.M;
+            hipLaunchKernelGGL(k_freq_reduce, dim3((unsigned)nb), dim3(256), 0, s, A, q.cube);
+        }
+    }
+    return hipGetLastError();
+}
+
+int freq_band_fit(int tile) { return 256 * (tile == 96 ? 1 : tile == 64 || tile == 48 ? 2 : 4); }
+
+hipError_t launch_freq_bands(const FreqSum &q, const BandArgs &B, int64_t max_items, hipStream_t s)
+{
+    const int tile = q.tile;
+    if (q.Ppad % FQ_PAD || q.Ppad <= 0 || q.per_element || q.M != 1) return hipErrorInvalidValue;
+    FreqArgs A{};
+    A.xt = q.xt;
+    A.yt = q.yt;
+    A.amp = q.amp;
+    A.src = q.src;
+    A.T = q.T;
+    A.R = q.R;
+    A.M = 1;
+    A.K = q.K;
+    A.Ppad = q.Ppad;
+    A.tt = (q.T + tile - 1) / tile;
+    A.rt = (q.R + tile - 1) / tile;
+    A.out = q.partial;
+    A.plan = B.plan;
+    A.segs = B.segs;
+    A.nodes = B.nodes;
+    const dim3 g((unsigned)std::min<int64_t>(freq_band_fit(tile), max_items * A.tt * A.rt)), t(FQ_G * 64);
+    switch (tile) {
+    case 16: hipLaunchKernelGGL((k_freq_gemm<false, 16, 1, true>), g, t, 0, s, A); break;
+    case 48: hipLaunchKernelGGL((k_freq_gemm<false, 16, 3, true>), g, t, 0, s, A); break;
+    case 32: hipLaunchKernelGGL((k_freq_gemm<false, 32, 1, true>), g, t, 0, s, A); break;
+    case 64: hipLaunchKernelGGL((k_freq_gemm<false, 32, 2, true>), g, t, 0, s, A); break;
+    case 96: hipLaunchKernelGGL((k_freq_gemm<false, 32, 3, true>), g, t, 0, s, A); break;
+    default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }

@@ -65,9 +65,22 @@ struct DevBuf {
 // paths at rest, [channel][sample].
 struct FreqBufs {
     DevBuf xt, yt, amp, src, part, rest;
+    DevBuf band;               // keys, histograms, order and plan of the bands
+    struct Classes {           // node classes of one sample count
+        int K;
+        BandClasses cls;
+        DevBuf tab;            // nodes, then coefficients
+    };
+    std::vector<Classes> classes;
+    void drop_classes()
+    {
+        for (auto &x : classes) x.tab.release();
+        classes.clear();
+    }
     void release()
     {
-        for (DevBuf *b : {&xt, &yt, &amp, &src, &part, &rest}) b->release();
+        for (DevBuf *b : {&xt, &yt, &amp, &src, &part, &rest, &band}) b->release();
+        drop_classes();
     }
 };
 
@@ -110,6 +123,18 @@ struct PathStore {
         return RR_OK;
     }
 };
+
+// least and greatest coordinates of n points
+void bounds3(const double *p, int64_t n, double *lo, double *hi)
+{
+    for (int a = 0; a < 3; a++) {
+        lo[a] = hi[a] = p[a];
+        for (int64_t i = 1; i < n; i++) {
+            lo[a] = std::min(lo[a], p[3 * i + a]);
+            hi[a] = std::max(hi[a], p[3 * i + a]);
+        }
+    }
+}
 
 bool finite3(const double *p, int64_t n)
 {
@@ -175,6 +200,7 @@ struct rr_ctx {
     double rx_radius = 0.25;
     std::vector<double> tx_h, rx_h;
     double oT[3] = {0, 0, 0}, oR[3] = {0, 0, 0};
+    double box[12];            // bounds of the Tx, then of the Rx elements
     DevBuf tx, rx;
 
     // chirp
@@ -702,6 +728,8 @@ int rr_set_array(rr_ctx *c, const double *tx, int32_t n_tx, const double *rx, in
         for (int i = 0; i < n_rx; i++) s += rx[3 * i + a];
         c->oR[a] = s / (double)n_rx;
     }
+    bounds3(tx, n_tx, c->box, c->box + 3);
+    bounds3(rx, n_rx, c->box + 6, c->box + 9);
     c->ntx = n_tx;
     c->nrx = n_rx;
     c->rx_radius = rx_radius;
@@ -1101,6 +1129,7 @@ static int64_t freq_table_bytes(const rr_ctx *c, int64_t n)
 struct FreqPlan {
     int T, R, M, K, tile, per_el;
     int64_t p_rest, p_mov;
+    const double *box;         // least and greatest coordinates of the Tx, then of the Rx
 };
 
 static int64_t freq_pad(int64_t n)
@@ -1125,8 +1154,64 @@ static double gemm_cost(int64_t C, int64_t K, int64_t n)
            std::max<int64_t>((n + ks - 1) / ks * ks, ks) / 71.0;
 }
 
+// The paths at rest in bands (k_band.hip): for the tile layouts, whose cost is
+// per sample (the sample split already shares its phasors among sqrt(K)
+// samples, and its launches are small), where K takes the smallest class.
+static bool freq_bands(const FreqPlan &q) { return !q.per_el && q.tile >= 16 && q.K >= 40; }
+
+// room of a band plan of at most n nodes a band: work items (chunks of paths x four nodes) for about three rounds of the
+// chip's workgroups (six: the hand's products take the same 2.0 ms and their
+// partial sums 91 instead of 43 us)
+struct BandRoom {
+    int target;
+    int64_t items, perm, blocks;
+    size_t o_hist, o_extent, o_perm, o_plan, o_segs, bytes;
+};
+static BandRoom band_room(const FreqPlan &q, int n)
+{
+    BandRoom r;
+    const int64_t tiles = (int64_t)((q.T + q.tile - 1) / q.tile) * ((q.R + q.tile - 1) / q.tile);
+    r.target = (int)std::max<int64_t>(32, 3 * freq_band_fit(q.tile) / tiles);
+    r.items = r.target + RR_BANDS * (n / 4) + (q.K + 3) / 4;
+    r.perm = q.p_rest + 32 * (RR_BANDS + 1);
+    r.blocks = band_blocks(q.p_rest);
+    auto up = [](size_t n) { return (n + 255) & ~size_t(255); };
+    r.o_hist = up((size_t)q.p_rest * 2);
+    r.o_extent = r.o_hist + up((size_t)r.blocks * (RR_BANDS + 1) * 4);
+    r.o_perm = r.o_extent + up((size_t)r.blocks * (RR_BANDS + 1) * 8);
+    r.o_plan = r.o_perm + up((size_t)r.perm * 4);
+    r.o_segs = r.o_plan + up(sizeof(BandPlan));
+    r.bytes = r.o_segs + up((size_t)r.items * sizeof(BandSeg));
+    return r;
+}
+
+// node classes of K samples (built on the host the first time; a handle keeps
+// those of its last 16 sample counts, a batch has them dropped between its
+// preparations)
+static int band_classes(FreqBufs &b, int K, hipStream_t st, BandClasses &out)
+{
+    for (const auto &x : b.classes)
+        if (x.K == K) {
+            out = x.cls;
+            return RR_OK;
+        }
+    std::vector<int32_t> nodes;
+    std::vector<float> coef;
+    FreqBufs::Classes x;
+    x.K = K;
+    x.cls = rr_band_classes(K, nodes, coef);
+    if (int rc = x.tab.ensure(nodes.size() * 4 + coef.size() * 4)) return rc;
+    HIPCHK(hipMemcpyAsync(x.tab.p, nodes.data(), nodes.size() * 4, hipMemcpyHostToDevice, st));
+    HIPCHK(hipMemcpyAsync(x.tab.as<char>() + nodes.size() * 4, coef.data(), coef.size() * 4,
+                          hipMemcpyHostToDevice, st));
+    HIPCHK(hipStreamSynchronize(st));
+    b.classes.push_back(x);
+    out = x.cls;
+    return RR_OK;
+}
+
 // grow the buffers to a plan's needs
-static int freq_ensure(FreqBufs &b, const FreqPlan &q)
+static int freq_ensure(FreqBufs &b, const FreqPlan &q, hipStream_t st)
 {
     const int64_t C = (int64_t)q.T * q.R;
     size_t xt = 0, yt = 0, part = 0;
@@ -1134,16 +1219,27 @@ static int freq_ensure(FreqBufs &b, const FreqPlan &q)
         const bool own = freq_own_tx(tile, q.per_el, true);
         xt = std::max(xt, (size_t)M * (own ? 1 : q.T) * P * 8);
         yt = std::max(yt, (size_t)M * q.R * P * 8);
-        const int ns = freq_splits(tile, q.T, q.R, M, q.K);
-        if (ns > 1) part = std::max(part, (size_t)ns * M * q.K * C * 8);
+        part = std::max(part, (size_t)freq_partial(tile, q.T, q.R, M, q.K));
     };
-    if (q.p_rest) need(q.tile, 1, q.p_rest);
+    int64_t p_rest = q.p_rest;
+    int rc;
+    if (freq_bands(q)) {
+        BandClasses cls;
+        if ((rc = band_classes(b, q.K, st, cls))) return rc;
+        const BandRoom r = band_room(q, cls.n[cls.count - 1]);
+        p_rest = r.perm;
+        xt = (size_t)q.T * p_rest * 8;
+        yt = (size_t)q.R * p_rest * 8;
+        part = (size_t)r.items * 4 * C * 8;
+        if ((rc = b.band.ensure(r.bytes))) return rc;
+    } else {
+        need(q.tile, 1, q.p_rest);
+    }
     if (q.p_mov) {
         need(q.tile, q.M, q.p_mov);
         need(freq_mov_tile(q.tile, q.K, q.per_el), q.M, q.p_mov);
     }
-    const size_t pp = (size_t)std::max(q.p_rest, q.p_mov) * 4;
-    int rc;
+    const size_t pp = (size_t)std::max(p_rest, q.p_mov) * 4;
     if ((rc = b.xt.ensure(xt)) || (rc = b.yt.ensure(yt)) || (rc = b.amp.ensure(pp)) ||
         (rc = b.src.ensure(pp)) || (part && (rc = b.part.ensure(part))))
         return rc;
@@ -1153,8 +1249,7 @@ static int freq_ensure(FreqBufs &b, const FreqPlan &q)
 // Sum over one part of the records (paths at rest: one chirp) on a layout,
 // leg tables first; the count is read on the device from rng[0], rng[n_rng],
 // the ranges of the part's groups.
-static hipError_t freq_legs(const FreqBufs &b, const FreqPlan &q, const SynthArgs &A, int tile,
-                            int M, int64_t P, const int64_t *rng, int n_rng, hipStream_t st)
+static FreqLegs leg_args(const FreqPlan &q, const SynthArgs &A, int M, const int64_t *rng, int n_rng)
 {
     FreqLegs L{};
     L.paths = A.paths;
@@ -1173,13 +1268,18 @@ static hipError_t freq_legs(const FreqBufs &b, const FreqPlan &q, const SynthArg
         L.oT[a] = A.oT[a];
         L.oR[a] = A.oR[a];
     }
+    return L;
+}
+
+static hipError_t freq_legs(const FreqBufs &b, const FreqPlan &q, const FreqLegs &L, int tile,
+                            int64_t P, hipStream_t st)
+{
     return launch_freq_prep(L, P, freq_own_tx(tile, q.per_el, true), b.xt.as<uint2>(),
                             b.yt.as<uint2>(), b.amp.as<float>(), b.src.as<int32_t>(), st);
 }
 
-static hipError_t freq_sum(const FreqBufs &b, const FreqPlan &q, int tile, int M, int64_t P,
-                           const int64_t *rng, int n_rng, int64_t gate_lo, int64_t gate_hi,
-                           const float2 *rest, float2 *out, hipStream_t st)
+static FreqSum sum_args(const FreqBufs &b, const FreqPlan &q, int tile, int M, int64_t P,
+                        const int64_t *rng, int n_rng, float2 *out)
 {
     FreqSum f{};
     f.xt = b.xt.as<const uint2>();
@@ -1196,21 +1296,58 @@ static hipError_t freq_sum(const FreqBufs &b, const FreqPlan &q, int tile, int M
     f.rng_lo = rng;
     f.rng_hi = rng + n_rng;
     f.groups = rng;
-    f.gate_lo = gate_lo;
-    f.gate_hi = gate_hi;
-    f.rest = rest;
+    f.gate_lo = -1;
+    f.gate_hi = INT64_MAX;
     f.partial = b.part.as<float2>();
     f.cube = out;
-    return launch_freq_gemm(f, st);
+    return f;
 }
 
 // the paths at rest: into the rest buffer, or the cube of a single chirp
 static int freq_rest(const FreqBufs &b, const FreqPlan &q, const SynthArgs &A, hipStream_t st)
 {
     const int n_rng = q.per_el ? q.T : 1;
-    HIPCHK(freq_legs(b, q, A, q.tile, 1, q.p_rest, A.ranges, n_rng, st));
-    HIPCHK(freq_sum(b, q, q.tile, 1, q.p_rest, A.ranges, n_rng, -1, INT64_MAX, nullptr,
-                    q.M > 1 ? b.rest.as<float2>() : A.cube, st));
+    float2 *out = q.M > 1 ? b.rest.as<float2>() : A.cube;
+    FreqLegs L = leg_args(q, A, 1, A.ranges, n_rng);
+    if (!freq_bands(q)) {
+        HIPCHK(freq_legs(b, q, L, q.tile, q.p_rest, st));
+        HIPCHK(launch_freq_gemm(sum_args(b, q, q.tile, 1, q.p_rest, A.ranges, n_rng, out), st));
+        return RR_OK;
+    }
+    const FreqBufs::Classes *cl = nullptr;
+    for (const auto &x : b.classes)
+        if (x.K == q.K) cl = &x;
+    if (!cl) return fail(RR_ESTATE, "node classes of %d samples missing", q.K);
+    const BandRoom r = band_room(q, cl->cls.n[cl->cls.count - 1]);
+    char *w = b.band.as<char>();
+    BandArgs B{};
+    B.plan = reinterpret_cast<BandPlan *>(w + r.o_plan);
+    B.perm = reinterpret_cast<int32_t *>(w + r.o_perm);
+    B.L = L;
+    B.Ppad = q.p_rest;
+    B.perm_cap = r.perm;
+    B.K = q.K;
+    B.bins_per_m = std::fabs(A.bw) * A.inv_c;
+    for (int a = 0; a < 3; a++) {
+        B.tx_lo[a] = q.box[a];
+        B.tx_hi[a] = q.box[3 + a];
+        B.rx_lo[a] = q.box[6 + a];
+        B.rx_hi[a] = q.box[9 + a];
+    }
+    B.cls = cl->cls;
+    B.nodes = cl->tab.as<const int32_t>();
+    B.coef = reinterpret_cast<const float *>(cl->tab.as<const int32_t>() + cl->cls.count * RR_BAND_NMAX);
+    B.target = r.target;
+    B.keys = reinterpret_cast<uint16_t *>(w);
+    B.hist = reinterpret_cast<uint32_t *>(w + r.o_hist);
+    B.extent = reinterpret_cast<uint2 *>(w + r.o_extent);
+    B.segs = reinterpret_cast<BandSeg *>(w + r.o_segs);
+    HIPCHK(launch_band_plan(B, st));
+    L.perm = B.perm;
+    L.used = &B.plan->used;
+    HIPCHK(freq_legs(b, q, L, q.tile, r.perm, st));
+    HIPCHK(launch_freq_bands(sum_args(b, q, q.tile, 1, r.perm, A.ranges, n_rng, nullptr), B, r.items, st));
+    HIPCHK(launch_band_expand(B, b.part.as<float2>(), q.T * q.R, out, st));
     return RR_OK;
 }
 
@@ -1221,14 +1358,15 @@ static int freq_moving(const FreqBufs &b, const FreqPlan &q, const SynthArgs &A,
 {
     const int n_rng = q.per_el ? q.T : 1;
     const int few = freq_mov_tile(q.tile, q.K, q.per_el);   // same tables as q.tile's
-    HIPCHK(freq_legs(b, q, A, q.tile, q.M, q.p_mov, A.mranges, n_rng, st));
+    HIPCHK(freq_legs(b, q, leg_args(q, A, q.M, A.mranges, n_rng), q.tile, q.p_mov, st));
     const int64_t gate = few == q.tile ? INT64_MAX : FREQ_MOV_KS;
-    if (n_mov <= gate)
-        HIPCHK(freq_sum(b, q, few, q.M, q.p_mov, A.mranges, n_rng, -1, gate,
-                        b.rest.as<const float2>(), A.cube, st));
-    if (few != q.tile && (n_mov < 0 || n_mov > gate))
-        HIPCHK(freq_sum(b, q, q.tile, q.M, q.p_mov, A.mranges, n_rng, gate, INT64_MAX,
-                        b.rest.as<const float2>(), A.cube, st));
+    for (int tile : {few, q.tile}) {
+        FreqSum f = sum_args(b, q, tile, q.M, q.p_mov, A.mranges, n_rng, A.cube);
+        f.rest = b.rest.as<const float2>();
+        (tile == few ? f.gate_hi : f.gate_lo) = gate;
+        if (n_mov < 0 || (n_mov > f.gate_lo && n_mov <= f.gate_hi)) HIPCHK(launch_freq_gemm(f, st));
+        if (few == q.tile) break;
+    }
     return RR_OK;
 }
 
@@ -1333,14 +1471,19 @@ int rr_synthesize(rr_ctx *c, int32_t model, int32_t engine, void *cube, int64_t 
     A.cube = static_cast<float2 *>(cube);
     if (engine == RR_GEMM_BF16X3 || engine == RR_GEMM_EXACT) {
         HIPCHK(hipEventRecord(c->ev[2], c->stream));
-        FreqPlan q{c->ntx, c->nrx, (int)M, (int)K, 0, !shared, freq_pad(n_rest), freq_pad(n_mov)};
+        FreqPlan q{c->ntx, c->nrx, (int)M, (int)K, 0, !shared, freq_pad(n_rest), freq_pad(n_mov),
+                   c->box};
         q.tile = freq_tile(q.T, q.R, q.K, q.per_el);
         // the moving paths of the separable model: the GEMM, where its padding
         // (256 channels, 64 samples, 96 paths) leaves it the cheaper engine
         const bool gemm = model == RR_SEPARABLE && M > 1 &&
                           gemm_cost(q.T * q.R, q.K, n_mov) < freq_cost(q, n_mov);
         if (M == 1 || gemm) q.p_mov = 0;
-        if ((rc = freq_ensure(c->fq, q))) return rc;
+        if (c->fq.classes.size() >= 16) {
+            HIPCHK(hipStreamSynchronize(c->stream));
+            c->fq.drop_classes();
+        }
+        if ((rc = freq_ensure(c->fq, q, c->stream))) return rc;
         if ((rc = freq_rest(c->fq, q, A, c->stream))) return rc;
         if (gemm) {
             SynthArgs G = A;
@@ -1884,6 +2027,7 @@ struct BatchScene {
     int64_t n_tris = 0;
     int nobj = 0, npts = 0, ntx = 0, nrx = 0, mode = 0;
     double rx_radius = 0.25, oT[3] = {0, 0, 0}, oR[3] = {0, 0, 0};
+    double box[12];                       // bounds of the Tx, then of the Rx elements
     DevBuf nodes, ltris, obj_alpha, obj_vel, pt_pos, pt_vel, pt_ap, tx, rx;
     rr_chirp chirp{};
     rr_trace_params tp{};
@@ -2000,7 +2144,7 @@ void batch_plan(BatchScene &x)
 FreqPlan batch_freq_plan(const BatchScene &x)
 {
     return FreqPlan{x.ntx, x.nrx, x.chirp.n_chirps, x.chirp.n_samples, x.tile, x.mode != RR_TX_SHARED,
-                    x.fq_ppad, x.chirp.n_chirps > 1 ? x.fq_ppad : 0};
+                    x.fq_ppad, x.chirp.n_chirps > 1 ? x.fq_ppad : 0, x.box};
 }
 
 // per-scene tables and global buffers for the current scene set and cubes;
@@ -2090,13 +2234,15 @@ int batch_prepare(rr_batch *b, int only_K = 0, int64_t p_limit = 0, int only_sce
     // the groups' ranges among the paths at rest, then among the moving paths
     if ((rc = b->d_ranges.ensure(16 * (b->n_ranges + 1)))) return rc;
     // exact engine: per scene the table stride (capacity, or the timing cap);
+    // the last graph is dropped whenever its plan is prepared anew
+    if (b->fq.classes.size() >= 64) b->fq.drop_classes();
     // one set of tables serves its scenes in turn
     for (int s = 0; s < S; s++) {
         BatchScene &x = b->sc[s];
         if (!x.use_freq || !b->synth_on[s]) continue;
         x.fq_ppad = x.fq_cap;
         if (p_limit > 0) x.fq_ppad = std::min<int64_t>(x.fq_ppad, freq_pad(p_limit));
-        if ((rc = freq_ensure(b->fq, batch_freq_plan(x)))) return rc;
+        if ((rc = freq_ensure(b->fq, batch_freq_plan(x), b->st))) return rc;
     }
     const double INV_2PI = 0.15915494309189535;
     for (int s = 0; s < S; s++) {
@@ -2388,6 +2534,8 @@ int rr_batch_set_scene(rr_batch *b, int32_t slot, const float *verts, int64_t n_
         x.oT[a] = st / (double)n_tx;
         x.oR[a] = sr / (double)n_rx;
     }
+    bounds3(tx, n_tx, x.box, x.box + 3);
+    bounds3(rx, n_rx, x.box + 6, x.box + 9);
     x.n_tris = n_tris;
     x.nobj = n_obj;
     x.npts = n_pts;

@@ -210,6 +210,8 @@ struct FreqLegs {
     double t_rep, f0c, dfc;
     int sep;
     double oT[3], oR[3];
+    // bands: the tables hold *used entries, entry p of record perm[p] (-1: none)
+    const int32_t *perm, *used;
 };
 hipError_t launch_freq_prep(const FreqLegs &L, int64_t Ppad, bool own_tx, uint2 *xt, uint2 *yt,
                             float *amp, int32_t *src, hipStream_t s);
@@ -224,6 +226,8 @@ int64_t freq_table_entries(int T, int R, int M, int64_t Ppad, bool own_tx);
 int freq_tile(int T, int R, int K, bool per_element);
 double freq_tile_cost(int T, int R, int K, int tile, bool per_element);
 int freq_splits(int tile, int T, int R, int M, int K);
+int freq_chirps(int tile, int T, int R, int M, int K);
+int64_t freq_partial(int tile, int T, int R, int M, int K);
 // the exact model's AUTO rule: the best product layout is modelled at least
 // 1.5x the direct engine's throughput
 bool freq_pays(int T, int R, int K, bool per_element);
@@ -250,6 +254,67 @@ struct FreqSum {
     float2 *partial, *cube;
 };
 hipError_t launch_freq_gemm(const FreqSum &q, hipStream_t s);
+struct BandArgs;
+// the products of a band plan (tile layouts), partial sums [slot][channel];
+// at most max_items work items
+int freq_band_fit(int tile);   // workgroups the chip holds at a time
+hipError_t launch_freq_bands(const FreqSum &q, const BandArgs &B, int64_t max_items, hipStream_t s);
+// Bands of path lengths (k_band.hip): classes of node counts for K samples,
+// by rising reach z (half the phase that the band's edge gathers over the
+// chirp); nodes [class][RR_BAND_NMAX] sample indices, coef from coef[class]:
+// [node][sample]
+#define RR_BAND_NMAX 32
+#define RR_BAND_CLASSES 7
+struct BandClasses {
+    int32_t count;
+    int32_t n[RR_BAND_CLASSES];
+    float z[RR_BAND_CLASSES];
+    int32_t coef[RR_BAND_CLASSES];
+};
+BandClasses rr_band_classes(int K, std::vector<int32_t> &nodes, std::vector<float> &coef);
+#define RR_BANDS 256          // bands (k_band.hip); longer paths go to the last list
+struct BandSeg {              // at most one chunk of a list's paths
+    int32_t p0, np;           // places in the sorted tables (multiples of 32)
+    int32_t cls;              // class of nodes, -1: every sample
+    int32_t groups;           // work items: four nodes (samples) each
+    int32_t item0, slot0;     // first work item, first partial sum ([slot][channel])
+};
+struct BandOut {              // one list as the expansion reads it
+    int32_t cls, n;           // n partial sums per chunk
+    int32_t chunks, slot0;
+    int32_t row0;             // first of its n rows among the lists of several chunks
+    uint32_t gamma;           // centre, turns per sample
+};
+struct BandPlan {
+    int32_t used, n_segs, n_items, n_out;
+    int32_t n_rows;           // partial sums to add over chunks
+    int32_t next;             // work item counter of the products
+    int32_t base[RR_BANDS + 1];
+    BandOut out[RR_BANDS + 1];
+};
+// the paths at rest of a shared launch in bands; at most `target` +
+// RR_BANDS n / 4 + K / 4 + 1 work items (n the largest class; as many
+// segments), four partial sums each
+struct BandArgs {
+    FreqLegs L;               // one chirp
+    int64_t Ppad, perm_cap;   // capacity in paths, in table entries
+    int K;
+    double bins_per_m;        // B / c
+    double tx_lo[3], tx_hi[3], rx_lo[3], rx_hi[3];
+    BandClasses cls;
+    const int32_t *nodes;
+    const float *coef;
+    int target;
+    uint16_t *keys;           // [Ppad]
+    uint32_t *hist;           // [blocks][RR_BANDS + 1]
+    uint2 *extent;            // [blocks][RR_BANDS + 1]
+    int32_t *perm;            // [perm_cap]
+    BandPlan *plan;
+    BandSeg *segs;
+};
+int64_t band_blocks(int64_t Ppad);
+hipError_t launch_band_plan(const BandArgs &A, hipStream_t s);
+hipError_t launch_band_expand(const BandArgs &A, float2 *part, int C, float2 *out, hipStream_t s);
 hipError_t launch_refit(float4 *nodes, float *ubox, const int32_t *order,
                         const int64_t *level_start, int n_levels, float4 *ltris, int64_t n_tris,
                         const int32_t *tris, const float *verts, double pad, hipStream_t s);
