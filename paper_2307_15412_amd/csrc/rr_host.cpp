@@ -1674,10 +1674,44 @@ int rr_backproject(rr_ctx *c, const void *cube, int64_t cube_elems, const rr_vol
     A.image = static_cast<float2 *>(image);
     HIPCHK(hipEventRecord(c->ev[4], c->stream));
     if (engine == RR_GEMM_EXACT) {
+        BpGrid G{};
+        const double lo[3] = {vol->x0, vol->y0, vol->z0};
+        const int32_t n[3] = {vol->nx, vol->ny, vol->nz};
+        for (int a = 0; a < 3; a++) {
+            G.lo[a] = lo[a];
+            G.hi[a] = lo[a] + (n[a] - 1) * vol->step;
+            G.n[a] = n[a];
+        }
+        G.step = vol->step;
+        G.T = c->ntx;
+        G.R = c->nrx;
+        G.K = (int)K;
+        G.f0 = A.f0;
+        G.df = A.df;
+        G.inv_c = A.inv_c;
+        G.box = c->box;
         int rc;
-        if ((rc = c->bp_sf.ensure((size_t)bp_mfma_frag_bytes((int)K)))) return rc;
-        HIPCHK(launch_bp_mfma(A.cube, A.stride, A.tx, c->ntx, A.rx, c->nrx, (int)K, A.f0, A.df,
-                              A.inv_c, A.x0, A.y0, A.z0, A.step, A.nx, A.ny, A.nz,
+        BandClasses cls{};
+        if (K >= 40) {
+            if (c->fq.classes.size() >= 16) {
+                HIPCHK(hipStreamSynchronize(c->stream));
+                c->fq.drop_classes();
+            }
+            if ((rc = band_classes(c->fq, (int)K, c->stream, cls))) return rc;
+        }
+        const BpPlan P = bp_plan(G, cls);
+        const int32_t *nodes = nullptr;
+        const float *coef = nullptr;
+        if (P.cls >= 0)
+            for (const auto &x : c->fq.classes)
+                if (x.K == (int)K) {
+                    nodes = x.tab.as<const int32_t>() + P.cls * RR_BAND_NMAX;
+                    coef = reinterpret_cast<const float *>(x.tab.as<const int32_t>() + cls.count * RR_BAND_NMAX) +
+                           cls.coef[P.cls];
+                }
+        if ((rc = c->bp_sf.ensure((size_t)(P.frag_bytes + P.turn_bytes)))) return rc;
+        HIPCHK(launch_bp_mfma(G, P, A.cube, A.stride, A.tx, A.rx, nodes, coef,
+                              reinterpret_cast<float2 *>(c->bp_sf.as<char>() + P.frag_bytes),
                               c->bp_sf.as<uint4>(), A.image, c->stream));
     } else {
         HIPCHK(launch_backproject(A, c->stream));

@@ -191,11 +191,6 @@ hipError_t launch_trace_count(const TraceArgs &a, int64_t n_traced, unsigned lon
 hipError_t launch_trace_user(const TraceArgs &a, const UserRays &u, hipStream_t s);
 hipError_t launch_set_alpha(float4 *ltris, int64_t n_tris, const float *tri_alpha,
                             const float *obj_alpha, hipStream_t s);
-hipError_t launch_bp_mfma(const float2 *cube, int64_t stride, const double *tx, int T,
-                          const double *rx, int R, int K, double f0, double df, double inv_c,
-                          double x0, double y0, double z0, double step, int nx, int ny, int nz,
-                          uint4 *Sf, float2 *image, hipStream_t s);
-int64_t bp_mfma_frag_bytes(int K);
 int freq_k_step();
 int freq_k_group();   // samples per exact-GEMM workgroup
 // leg tables of the records *rng_lo .. *rng_hi of `paths` (read on the device,
@@ -273,6 +268,26 @@ struct BandClasses {
 };
 BandClasses rr_band_classes(int K, std::vector<int32_t> &nodes, std::vector<float> &coef);
 #define RR_BANDS 256          // bands (k_band.hip); longer paths go to the last list
+// back-projection on the matrix cores: the volume, array and sweep; a plan
+// (blocks of voxels per axis, workgroups per block, n nodes of class cls, or
+// cls = -1: every sample over the whole volume) with the bytes of its slices
+// and of the transposed cube
+struct BpGrid {
+    double lo[3], hi[3], step;
+    int n[3];
+    int T, R, K;
+    double f0, df, inv_c;
+    const double *box;        // bounds of the Tx, then of the Rx elements
+};
+struct BpPlan {
+    int cls, n;
+    int nb[3], wgs;
+    int64_t frag_bytes, turn_bytes;
+};
+BpPlan bp_plan(const BpGrid &G, const BandClasses &cls);
+hipError_t launch_bp_mfma(const BpGrid &G, const BpPlan &P, const float2 *cube, int64_t stride,
+                          const double *tx, const double *rx, const int32_t *nodes, const float *coef,
+                          float2 *turned, uint4 *Sf, float2 *image, hipStream_t s);
 struct BandSeg {              // at most one chunk of a list's paths
     int32_t p0, np;           // places in the sorted tables (multiples of 32)
     int32_t cls;              // class of nodes, -1: every sample
