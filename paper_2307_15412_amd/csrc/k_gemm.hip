@@ -331,6 +331,11 @@ __global__ __launch_bounds__(GM_THREADS, 1) void k_gemm(const uint4 *__restrict_
     // uniform (scalar registers), the lane adds its own 16 bytes
     const uint4 *arow = Af + (int64_t)rb0 * KB * (GM_PL * 64);
 
+    // Re = P1 - P2 and Im = P3 - P1 - P2 start from the sum over the paths at
+    // rest, loaded while the first operands are (added as the tile was stored,
+    // the large-MIMO cube with 160 moving paths took 3.4 instead of 2.3 ms:
+    // its 12 steps are too short to hide those loads; a 128-row tile with two
+    // workgroups on a compute unit was 3-9 % slower than this one throughout)
     f32x16 p1[GM_WR][GM_NCB], p2[GM_WR][GM_NCB], p3[GM_WR][GM_NCB];
 #pragma unroll
     for (int i = 0; i < GM_WR; i++)
@@ -338,9 +343,13 @@ __global__ __launch_bounds__(GM_THREADS, 1) void k_gemm(const uint4 *__restrict_
         for (int j = 0; j < GM_NCB; j++)
 #pragma unroll
             for (int e = 0; e < 16; e++) {
-                p1[i][j][e] = 0.0f;
+                const int row = (rb0 + i) * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+                const int k = k0 + j * 32 + (lane & 31);
+                float2 z = make_float2(0.0f, 0.0f);
+                if (rest && row < C && k < K) z = rest[(int64_t)row * K + k];
+                p1[i][j][e] = z.x;
                 p2[i][j][e] = 0.0f;
-                p3[i][j][e] = 0.0f;
+                p3[i][j][e] = z.y + z.x;
             }
 
     struct ARow {
@@ -462,11 +471,8 @@ __global__ __launch_bounds__(GM_THREADS, 1) void k_gemm(const uint4 *__restrict_
                 const int row = (rb0 + i) * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
                 const int k = k0 + j * 32 + (lane & 31);
                 const float a = p1[i][j][e], b = p2[i][j][e];
-                if (row < C && k < K) {
-                    const float2 z = rest ? rest[(int64_t)row * K + k] : make_float2(0.0f, 0.0f);
-                    cube[((int64_t)row * M + m) * K + k] =
-                        make_float2(z.x + (a - b), z.y + (p3[i][j][e] - a - b));
-                }
+                if (row < C && k < K)
+                    cube[((int64_t)row * M + m) * K + k] = make_float2(a - b, p3[i][j][e] - a - b);
             }
 }
 
