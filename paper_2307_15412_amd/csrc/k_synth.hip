@@ -590,10 +590,10 @@ __global__ __launch_bounds__(PREP_T) void k_batch_prep(PathSoA P, const unsigned
 }
 
 // per-scene path ranges from the batched exclusive scan: paths of virtual
-// rays [vr0 + t n_vps, ...) start at offsets[vr0 + t n_vps]; then those of
+// rays [vr0 + t n_vps, ...) start at the prefix of vr0 + t n_vps; then those of
 // the two parts of the records
-__global__ void k_batch_ranges(const uint32_t *offsets, int64_t V, const unsigned long long *total,
-                               int64_t cap, const BatchRangeInfo *ri, int S, const uint32_t *pre,
+__global__ void k_batch_ranges(const uint8_t *counts, const uint32_t *bsums, int64_t V,
+                               const unsigned long long *total, int64_t cap, const BatchRangeInfo *ri, int S, const uint32_t *pre,
                                int64_t *rest, int64_t *mov)
 {
     const int s = blockIdx.x * blockDim.x + threadIdx.x;
@@ -601,7 +601,7 @@ __global__ void k_batch_ranges(const uint32_t *offsets, int64_t V, const unsigne
     const BatchRangeInfo &R = ri[s];
     const int64_t tot = min((int64_t)*total, cap);
     auto put = [&](int g, int64_t v) {
-        const int64_t o = min(v < V ? (int64_t)offsets[v] : tot, tot);
+        const int64_t o = min(v < V ? (int64_t)count_prefix(counts, bsums, v) : tot, tot);
         const int64_t r = pre[o];
         rest[R.base + g] = r;
         mov[R.base + g] = (int64_t)pre[tot] + o - r;
@@ -655,11 +655,11 @@ hipError_t launch_batch_prep(const PathSoA &paths, const unsigned long long *tot
     return hipGetLastError();
 }
 
-hipError_t launch_batch_ranges(const uint32_t *offsets, int64_t V, const unsigned long long *total,
-                               int64_t cap, const BatchRangeInfo *ri, int S, const uint32_t *pre,
+hipError_t launch_batch_ranges(const uint8_t *counts, const uint32_t *bsums, int64_t V,
+                               const unsigned long long *total, int64_t cap, const BatchRangeInfo *ri, int S, const uint32_t *pre,
                                int64_t *rest, int64_t *mov, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_batch_ranges, dim3((unsigned)((S + 63) / 64)), dim3(64), 0, s, offsets, V,
+    hipLaunchKernelGGL(k_batch_ranges, dim3((unsigned)((S + 63) / 64)), dim3(64), 0, s, counts, bsums, V,
                        total, cap, ri, S, pre, rest, mov);
     return hipGetLastError();
 }

@@ -51,8 +51,11 @@ __device__ __forceinline__ void philox(uint64_t i, uint64_t src, uint64_t stage,
             k1 += 0xBB67AE8584CAA73Bull;
         }
         const uint64_t M0 = 0xD2E7470EE14C6C93ull, M1 = 0xCA5A826395121157ull;
-        uint64_t hi0 = __umul64hi(M0, c0), lo0 = M0 * c0;
-        uint64_t hi1 = __umul64hi(M1, c2), lo1 = M1 * c2;
+        // (a 128-bit product is 4 quarter-rate multiplies; the high and the low
+        // half asked for apart were 6)
+        const unsigned __int128 w0 = (unsigned __int128)M0 * c0, w1 = (unsigned __int128)M1 * c2;
+        const uint64_t hi0 = (uint64_t)(w0 >> 64), lo0 = (uint64_t)w0;
+        const uint64_t hi1 = (uint64_t)(w1 >> 64), lo1 = (uint64_t)w1;
         uint64_t n0 = hi1 ^ c1 ^ k0;
         uint64_t n2 = hi0 ^ c3 ^ k1;
         c0 = n0; c1 = lo1; c2 = n2; c3 = lo0;
@@ -135,7 +138,7 @@ struct TraceCount {
 // and its position in the leaf-ordered triangle array.  CNT: also count the
 // work into *cn.
 template <bool CNT>
-__device__ int closest_hit_t(const TraceArgs &A, d3 o, d3 d, int skip, double &tbest, int &lbest,
+__device__ __forceinline__ int closest_hit_t(const TraceArgs &A, d3 o, d3 d, int skip, double &tbest, int &lbest,
                              int *stk, TraceCount *cn)
 {
     if (CNT) cn->queries++;
@@ -149,9 +152,17 @@ __device__ int closest_hit_t(const TraceArgs &A, d3 o, d3 d, int skip, double &t
     float tmax = __builtin_huge_valf();
     int sp = 0;
     int ref = 0;
+    // Inner nodes until every lane holds a leaf or has nothing left, then the
+    // leaves: the wavefront's lanes do the same kind of work at a time.  A
+    // step on a node has no branches: the farther child is written to the
+    // stack's free place whether it is kept or not, and the stack's top is
+    // read ahead for the lanes that hit neither child.
+    bool over = false;
     while (true) {
-        if (ref >= 0) {
+        bool more = true;
+        while (more && ref >= 0) {
             if (CNT) cn->nodes++;
+            const int top = stk[max(sp - 1, 0) * RR_TRACE_BLOCK];
             const float4 *N = A.nodes + 4 * (int64_t)ref;
             float4 n0 = N[0], n1 = N[1], n2 = N[2], n3 = N[3];
             float a0 = fmaf(n0.x, ix, -oix), a1 = fmaf(n0.w, ix, -oix);
@@ -164,47 +175,44 @@ __device__ int closest_hit_t(const TraceArgs &A, d3 o, d3 d, int skip, double &t
             c0 = fmaf(n2.x, iz, -oiz); c1 = fmaf(n2.w, iz, -oiz);
             float tn1 = fmaxf(fmaxf(fminf(a0, a1), fminf(b0, b1)), fmaxf(fminf(c0, c1), 0.0f));
             float tf1 = fminf(fminf(fmaxf(a0, a1), fmaxf(b0, b1)), fminf(fmaxf(c0, c1), tmax));
-            bool h0 = tn0 <= tf0, h1 = tn1 <= tf1;
-            int r0 = __float_as_int(n3.x), r1 = __float_as_int(n3.y);
-            if (h0 && h1) {
-                bool first0 = tn0 <= tn1;
-                int nearr = first0 ? r0 : r1, farr = first0 ? r1 : r0;
-                if (sp < RR_STACK) {
-                    stk[sp * RR_TRACE_BLOCK] = farr;
-                    sp++;
-                } else {
-                    atomicOr(A.err_flag, 1);
-                }
-                ref = nearr;
-                continue;
-            }
-            if (h0) { ref = r0; continue; }
-            if (h1) { ref = r1; continue; }
-        } else {
-            int x = ~ref;
-            int first = x >> 3, cnt = (x & 7) + 1;
-            if (CNT) cn->tris += (unsigned)cnt;
-            for (int k = 0; k < cnt; k++) {
-                const float4 *T = A.ltris + 3 * (int64_t)(first + k);
-                float4 t0 = T[0], t1 = T[1], t2 = T[2];
-                int id = __float_as_int(t2.y);
-                if (id == skip) continue;
-                d3 v0 = mk3(t0.x, t0.y, t0.z), v1 = mk3(t0.w, t1.x, t1.y), v2 = mk3(t1.z, t1.w, t2.x);
-                double th;
-                if (mt_hit(o, d, v0, v1, v2, th) && (th < tbest || (th == tbest && id < best))) {
-                    tbest = th;
-                    best = id;
-                    lbest = first + k;
-                    float tf = (float)th;
-                    if ((double)tf < th) tf = nextafterf(tf, __builtin_huge_valf());
-                    tmax = tf;
-                }
+            const bool h0 = tn0 <= tf0, h1 = tn1 <= tf1;
+            const bool both = h0 & h1, none = !(h0 | h1);
+            const int r0 = __float_as_int(n3.x), r1 = __float_as_int(n3.y);
+            const bool take0 = h0 & (!h1 | (tn0 <= tn1));
+            stk[sp * RR_TRACE_BLOCK] = take0 ? r1 : r0;
+            const bool full = sp == A.stack;
+            over |= both & full;
+            ref = none ? top : take0 ? r0 : r1;
+            more = !none | (sp > 0);
+            sp += (both & !full) ? 1 : none ? -1 : 0;
+        }
+        if (!more) break;
+        const int x = ~ref;
+        const int first = x >> 3, cnt = (x & 7) + 1;
+        if (CNT) cn->tris += (unsigned)cnt;
+        for (int k = 0; k < cnt; k++) {
+            const float4 *T = A.ltris + 3 * (int64_t)(first + k);
+            const float4 t0 = T[0], t1 = T[1], t2 = T[2];
+            const int id = __float_as_int(t2.y);
+            const d3 v0 = mk3(t0.x, t0.y, t0.z), v1 = mk3(t0.w, t1.x, t1.y), v2 = mk3(t1.z, t1.w, t2.x);
+            double th;
+            // (the record is loaded whole: testing its id first would wait for
+            // a load of its own)
+            const bool hit = mt_hit(o, d, v0, v1, v2, th);
+            if (hit & (id != skip) && (th < tbest || (th == tbest && id < best))) {
+                tbest = th;
+                best = id;
+                lbest = first + k;
+                float tf = (float)th;
+                if ((double)tf < th) tf = nextafterf(tf, __builtin_huge_valf());
+                tmax = tf;
             }
         }
         if (sp == 0) break;
         sp--;
         ref = stk[sp * RR_TRACE_BLOCK];
     }
+    if (over) atomicOr(A.err_flag, 1);
     return best;
 }
 
@@ -244,10 +252,13 @@ __device__ __forceinline__ int cdf_bin(const double *cdf, int nb, double u)
     return lo;
 }
 
+// The hits of one ray so far, kept in scratch memory (volatile: the compiler
+// would hold them in 32 registers through every traversal, and spill others,
+// for the few rays that return); written once a hit, read when a path is.
 struct Rec {
-    d3 P[RR_KMAX];
-    int tri[RR_KMAX];
-    int vid[RR_KMAX];
+    volatile double P[3 * RR_KMAX];
+    volatile int tri[RR_KMAX];
+    volatile int vid[RR_KMAX];
 };
 
 // one atomic per wavefront; every active lane must call this
@@ -270,24 +281,93 @@ __device__ __forceinline__ void append(const TraceArgs &A, bool rec, int32_t src
     T.K[slot] = K;
     T.ray[slot] = v;
     T.loc[slot] = loc;
-#pragma unroll
+#pragma unroll 1
     for (int q = 0; q < RR_KMAX; q++) {
-        bool u = q < K;
+        const bool u = q < K;
         T.tri[q * cap + slot] = u ? R.tri[q] : -1;
         T.vid[q * cap + slot] = u ? R.vid[q] : -1;
-        T.p[(3 * q + 0) * cap + slot] = u ? R.P[q].x : 0.0;
-        T.p[(3 * q + 1) * cap + slot] = u ? R.P[q].y : 0.0;
-        T.p[(3 * q + 2) * cap + slot] = u ? R.P[q].z : 0.0;
+        for (int a = 0; a < 3; a++) T.p[(3 * q + a) * cap + slot] = u ? R.P[3 * q + a] : 0.0;
     }
     T.L[slot] = L;
     T.amp[slot] = amp;
 }
 
-// one launched ray g (source-major) through all of its bounces
-template <bool CNT = false>
-__device__ __forceinline__ void trace_from(const TraceArgs &A, d3 src, d3 dir, int64_t i, int64_t t, int64_t v,
-                           double amp, int32_t srcid, int32_t *hrow, int *stk, int64_t target,
-                           TraceCount *cn = nullptr);
+// The bounces of one ray from o along the unit vector dir: closest hit,
+// reception of every segment that follows a hit, the direction of Eqs. 1-3
+// at each hit with the random numbers of counter (i, t, j + 1); paths carry
+// source srcid, virtual ray v and amplitude amp.  target >= 0: the ray is
+// dropped (hit row all -1, no paths) unless its first hit is that triangle.
+template <bool CNT>
+__device__ __forceinline__ void trace_from(const TraceArgs &A, d3 o, d3 dir, int64_t i, int64_t t,
+                                           int64_t v, double amp, int32_t srcid, int32_t *hrow,
+                                           int *stk, int64_t target, TraceCount *cn)
+{
+    Rec R;
+    double L = 0.0;
+    int prev = -1;
+    int n_emit = 0;
+    int j = 0;
+    int h = -1, lidx = 0;
+    double th = 0.0;
+    while (true) {
+        // reception: the segment passes the antenna's sphere before its end
+        double ts = 0.0;
+        bool rec = false;
+        if (j >= 1) {
+            d3 w2 = sub3(mk3(A.oR[0], A.oR[1], A.oR[2]), o);
+            ts = dot3(w2, dir);
+            if (ts > 0.0) {
+                double cx = (o.x + ts * dir.x) - A.oR[0];
+                double cy = (o.y + ts * dir.y) - A.oR[1];
+                double cz = (o.z + ts * dir.z) - A.oR[2];
+                rec = cx * cx + cy * cy + cz * cz <= A.r2;
+            }
+        }
+        // the hit of the last segment matters only to what is received on
+        // it (and to a recorded hit list)
+        const bool last = j == A.bmax;
+        if (CNT || hrow || !last || rec) {
+            h = closest_hit_t<CNT>(A, o, dir, prev, th, lidx, stk, cn);
+            rec = rec && ts < th;
+        } else {
+            h = -1;
+        }
+        if (j == 0 && target >= 0 && h != target) {
+            // cast towards a triangle that is not its first hit: not counted
+            if (hrow)
+                for (int q = 0; q <= A.bmax; q++) hrow[q] = -1;
+            return;
+        }
+        if (hrow) hrow[j] = h;
+        append(A, rec, srcid, j, v, n_emit, R, L, amp);
+        n_emit += rec ? 1 : 0;
+        if (h < 0 || last) break;
+        d3 p = mk3(o.x + th * dir.x, o.y + th * dir.y, o.z + th * dir.z);
+        L += th;
+        const float4 *T = A.ltris + 3 * (int64_t)lidx;
+        float4 t0 = T[0], t1 = T[1], t2 = T[2];
+        d3 v0 = mk3(t0.x, t0.y, t0.z), v1 = mk3(t0.w, t1.x, t1.y), v2 = mk3(t1.z, t1.w, t2.x);
+        d3 n = cross3(sub3(v1, v0), sub3(v2, v0));
+        n = div3(n, sqrt(dot3(n, n)));
+        if (dot3(n, dir) > 0.0) n = mk3(-n.x, -n.y, -n.z);
+        R.P[3 * j] = p.x;
+        R.P[3 * j + 1] = p.y;
+        R.P[3 * j + 2] = p.z;
+        R.tri[j] = h;
+        R.vid[j] = __float_as_int(t2.z);
+        j++;
+        uint64_t rb[4];
+        philox((uint64_t)i, (uint64_t)t, (uint64_t)j, A.seed, rb);
+        dir = bounce_dir(dir, n, (double)t2.w, u01(rb[0]), u01(rb[1]));
+        o = p;
+        prev = h;
+    }
+    if (hrow)
+        for (int q = j + 1; q <= A.bmax; q++) hrow[q] = -1;
+    // (zeroed before the launch: a byte per ray in coherent order is a cache
+    // line per ray, and 97 % of them are zero)
+    if (n_emit) A.counts[v] = (uint8_t)n_emit;
+}
 
 // Per-triangle casting: ray i of a source aims at piece f = i / g^2 (a
 // triangle, or part of one cut by the host's subdivision), at a point drawn
@@ -298,7 +378,7 @@ __device__ __forceinline__ void trace_from(const TraceArgs &A, d3 src, d3 dir, i
 // rays inside the field of view are traced, and they count only when the
 // piece's triangle is their first hit.
 template <bool CNT = false>
-__device__ void trace_tri(const TraceArgs &A, int64_t g, int64_t t, int64_t i, int64_t v, d3 src,
+__device__ __forceinline__ void trace_tri(const TraceArgs &A, int64_t g, int64_t t, int64_t i, int64_t v, d3 src,
                           int *stk, TraceCount *cn = nullptr)
 {
     const int64_t gs = A.tri_g, gg = gs * gs;
@@ -326,7 +406,6 @@ __device__ void trace_tri(const TraceArgs &A, int64_t g, int64_t t, int64_t i, i
     if (!ok) {
         if (hrow)
             for (int q = 0; q <= A.bmax; q++) hrow[q] = -1;
-        A.counts[v] = 0;
         return;
     }
     trace_from<CNT>(A, src, d, i, t, v, w / (double)gg, A.shared ? -1 : (int32_t)t, hrow, stk,
@@ -356,15 +435,28 @@ __device__ __forceinline__ void primary_draw(const TraceArgs &A, int64_t t, int6
     }
 }
 
-template <bool CNT = false>
-__device__ void trace_ray(const TraceArgs &A, int64_t g, int *stk, TraceCount *cn = nullptr)
+// source of ray g: g / n_per_src by the FP64 reciprocal (g < 2^32, so the
+// quotient is off by at most one before the correction)
+__device__ __forceinline__ int64_t ray_source(const TraceArgs &A, int64_t g)
 {
-    int64_t t = g / A.n_per_src;
-    int64_t i = g - t * A.n_per_src;
+    if (A.shared) return 0;
+    int64_t t = (int64_t)((double)g * A.inv_per_src);
+    if (t * A.n_per_src > g) t--;
+    else if ((t + 1) * A.n_per_src <= g) t++;
+    return t;
+}
+
+// TRI: the per-triangle sampler, a kernel of its own (its ray generation
+// would cost the others registers)
+template <bool TRI, bool CNT = false>
+__device__ __forceinline__ void trace_ray(const TraceArgs &A, int64_t g, int *stk, TraceCount *cn = nullptr)
+{
+    const int64_t t = ray_source(A, g);
+    const int64_t i = g - t * A.n_per_src;
     int64_t v = A.vbase + t * A.n_virt_per_src + i;
     d3 src = A.shared ? mk3(A.oT[0], A.oT[1], A.oT[2])
                       : mk3(A.tx[3 * t], A.tx[3 * t + 1], A.tx[3 * t + 2]);
-    if (A.sampler == RR_PER_TRIANGLE) {
+    if (TRI) {
         trace_tri<CNT>(A, g, t, i, v, src, stk, cn);
         return;
     }
@@ -385,7 +477,7 @@ __device__ void trace_ray(const TraceArgs &A, int64_t g, int *stk, TraceCount *c
 // Caller-supplied ray g: origin, direction (normalised here), amplitude and
 // source from U; its bounce random numbers use the ray's index within its
 // source's run of rays, so that the launch's own rays reproduce k_trace.
-__device__ void trace_user(const TraceArgs &A, const UserRays &U, int64_t g, int *stk)
+__device__ __forceinline__ void trace_user(const TraceArgs &A, const UserRays &U, int64_t g, int *stk)
 {
     const int32_t srcid = U.src[g];
     int64_t lo = 0, hi = g;
@@ -397,91 +489,13 @@ __device__ void trace_user(const TraceArgs &A, const UserRays &U, int64_t g, int
     d3 d = mk3(U.dir[3 * g], U.dir[3 * g + 1], U.dir[3 * g + 2]);
     d = div3(d, sqrt(dot3(d, d)));
     int32_t *hrow = A.hits ? A.hits + g * (A.bmax + 1) : nullptr;
-    trace_from(A, o, d, g - lo, srcid > 0 ? srcid : 0, A.vbase + g, U.amp[g], srcid, hrow, stk, -1);
-}
-
-// The bounces of one ray from o along the unit vector dir: closest hit,
-// reception of every segment that follows a hit, the direction of Eqs. 1-3
-// at each hit with the random numbers of counter (i, t, j + 1); paths carry
-// source srcid, virtual ray v and amplitude amp.  target >= 0: the ray is
-// dropped (hit row all -1, no paths) unless its first hit is that triangle.
-template <bool CNT>
-__device__ __forceinline__ void trace_from(const TraceArgs &A, d3 src, d3 dir, int64_t i, int64_t t, int64_t v,
-                           double amp, int32_t srcid, int32_t *hrow, int *stk, int64_t target,
-                           TraceCount *cn)
-{
-    Rec R;
-#pragma unroll
-    for (int q = 0; q < RR_KMAX; q++) {
-        R.P[q] = mk3(0.0, 0.0, 0.0);
-        R.tri[q] = -1;
-        R.vid[q] = -1;
-    }
-    d3 o = src;
-    double L = 0.0;
-    int prev = -1;
-    int n_emit = 0;
-    int jlast = A.bmax;
-    for (int j = 0; j <= A.bmax; j++) {
-        double th;
-        int lidx;
-        int h = closest_hit_t<CNT>(A, o, dir, prev, th, lidx, stk, cn);
-        if (j == 0 && target >= 0 && h != target) {
-            // cast towards a triangle that is not its first hit: not counted
-            if (hrow)
-                for (int q = 0; q <= A.bmax; q++) hrow[q] = -1;
-            A.counts[v] = 0;
-            return;
-        }
-        if (hrow) hrow[j] = h;
-        bool rec = false;
-        if (j >= 1) {
-            d3 w2 = sub3(mk3(A.oR[0], A.oR[1], A.oR[2]), o);
-            double ts = dot3(w2, dir);
-            if (ts > 0.0 && ts < th) {
-                double cx = (o.x + ts * dir.x) - A.oR[0];
-                double cy = (o.y + ts * dir.y) - A.oR[1];
-                double cz = (o.z + ts * dir.z) - A.oR[2];
-                rec = cx * cx + cy * cy + cz * cz <= A.r2;
-            }
-        }
-        append(A, rec, srcid, j, v, n_emit, R, L, amp);
-        n_emit += rec ? 1 : 0;
-        if (h < 0 || j == A.bmax) {
-            jlast = j;
-            break;
-        }
-        d3 p = mk3(o.x + th * dir.x, o.y + th * dir.y, o.z + th * dir.z);
-        L += th;
-        const float4 *T = A.ltris + 3 * (int64_t)lidx;
-        float4 t0 = T[0], t1 = T[1], t2 = T[2];
-        d3 v0 = mk3(t0.x, t0.y, t0.z), v1 = mk3(t0.w, t1.x, t1.y), v2 = mk3(t1.z, t1.w, t2.x);
-        d3 n = cross3(sub3(v1, v0), sub3(v2, v0));
-        n = div3(n, sqrt(dot3(n, n)));
-        if (dot3(n, dir) > 0.0) n = mk3(-n.x, -n.y, -n.z);
-        int obj = __float_as_int(t2.z);
-#pragma unroll
-        for (int q = 0; q < RR_KMAX; q++) {
-            if (q == j) {
-                R.P[q] = p;
-                R.tri[q] = h;
-                R.vid[q] = obj;
-            }
-        }
-        uint64_t rb[4];
-        philox((uint64_t)i, (uint64_t)t, (uint64_t)(j + 1), A.seed, rb);
-        dir = bounce_dir(dir, n, (double)t2.w, u01(rb[0]), u01(rb[1]));
-        o = p;
-        prev = h;
-    }
-    if (hrow)
-        for (int j = jlast + 1; j <= A.bmax; j++) hrow[j] = -1;
-    A.counts[v] = (uint8_t)n_emit;
+    trace_from<false>(A, o, d, g - lo, srcid > 0 ? srcid : 0, A.vbase + g, U.amp[g], srcid, hrow, stk,
+                      -1, nullptr);
 }
 
 // Point reflectors: one single-bounce path per (source, point) when both the
 // source-to-point and point-to-receiver legs are unobstructed.
-__device__ void trace_point(const TraceArgs &A, int64_t g, int *stk)
+__device__ __forceinline__ void trace_point(const TraceArgs &A, int64_t g, int *stk)
 {
     int64_t t = g / A.npts, q = g - t * A.npts;
     int64_t v = A.vbase + t * A.n_virt_per_src + A.n_per_src + q;
@@ -500,31 +514,31 @@ __device__ void trace_point(const TraceArgs &A, int64_t g, int *stk)
     closest_hit(A, Q, div3(b, lb), -1, th, lidx, stk);
     vis = vis && !(th < lb);
     Rec R;
-#pragma unroll
-    for (int k = 0; k < RR_KMAX; k++) {
-        R.P[k] = mk3(0.0, 0.0, 0.0);
-        R.tri[k] = -1;
-        R.vid[k] = -1;
-    }
-    R.P[0] = Q;
+    R.P[0] = Q.x;
+    R.P[1] = Q.y;
+    R.P[2] = Q.z;
+    R.tri[0] = -1;
     R.vid[0] = A.nobj + (int)q;
     append(A, vis, A.shared ? -1 : (int32_t)t, 1, v, 0, R, la, A.pt_ap[q] / (la * la * A.omega));
-    A.counts[v] = vis ? 1 : 0;
+    if (vis) A.counts[v] = 1;
 }
 
-// Tracing kernels ask for four wavefronts per SIMD (at most 128 VGPRs): the
-// traversal is bound by the latency of dependent node fetches, and a fourth
-// wavefront hides more of it than the ~20 registers the compiler then keeps
-// in scratch memory cost (street, 1e7 rays: 4.38 against 4.79 ms with three
-// wavefronts and no spills; five wavefronts spill ~145 registers and lose).
-#define RR_TRACE_WAVES 4
+// Tracing kernels ask for five wavefronts per SIMD (at most 96 VGPRs): the
+// traversal is bound by its own instructions and by the latency of dependent
+// node fetches, and a fifth wavefront hides more of that than the ~10
+// registers the compiler then keeps in scratch memory cost (street, 1e7 rays,
+// 3 bounces, with its ordering: 1.60 against 1.73 ms with four; six spill 35
+// and take 1.74).  The
+// stacks leave room for five: a lane's has the tree's depth, not the bound's.
+#define RR_TRACE_WAVES 5
 
 // lane g traces ray order[g] when a coherent order is given, else ray g
+template <bool TRI>
 __global__ __launch_bounds__(RR_TRACE_BLOCK, RR_TRACE_WAVES) void k_trace(TraceArgs A, int64_t n_traced)
 {
-    __shared__ int lds_stack[RR_STACK * RR_TRACE_BLOCK];
+    extern __shared__ int lds_stack[];
     const int64_t g = (int64_t)blockIdx.x * RR_TRACE_BLOCK + threadIdx.x;
-    if (g < n_traced) trace_ray(A, A.order ? (int64_t)A.order[g] : g, lds_stack + threadIdx.x);
+    if (g < n_traced) trace_ray<TRI>(A, A.order ? (int64_t)A.order[g] : g, lds_stack + threadIdx.x);
 }
 
 // k_trace with work counters: the same rays, hits and paths, plus the sums
@@ -533,10 +547,14 @@ __global__ __launch_bounds__(RR_TRACE_BLOCK, RR_TRACE_WAVES) void k_trace(TraceA
 __global__ __launch_bounds__(RR_TRACE_BLOCK) void k_trace_count(TraceArgs A, int64_t n_traced,
                                                                 unsigned long long *stats)
 {
-    __shared__ int lds_stack[RR_STACK * RR_TRACE_BLOCK];
+    extern __shared__ int lds_stack[];
     const int64_t g = (int64_t)blockIdx.x * RR_TRACE_BLOCK + threadIdx.x;
     TraceCount cn = {0u, 0u, 0u};
-    if (g < n_traced) trace_ray<true>(A, A.order ? (int64_t)A.order[g] : g, lds_stack + threadIdx.x, &cn);
+    if (g < n_traced) {
+        const int64_t r = A.order ? (int64_t)A.order[g] : g;
+        if (A.sampler == RR_PER_TRIANGLE) trace_ray<true, true>(A, r, lds_stack + threadIdx.x, &cn);
+        else trace_ray<false, true>(A, r, lds_stack + threadIdx.x, &cn);
+    }
     unsigned long long a = cn.nodes, b = cn.tris, q = cn.queries;
     for (int off = 32; off > 0; off >>= 1) {
         a += __shfl_xor(a, off);
@@ -552,7 +570,7 @@ __global__ __launch_bounds__(RR_TRACE_BLOCK) void k_trace_count(TraceArgs A, int
 
 __global__ __launch_bounds__(RR_TRACE_BLOCK, RR_TRACE_WAVES) void k_trace_user(TraceArgs A, UserRays U)
 {
-    __shared__ int lds_stack[RR_STACK * RR_TRACE_BLOCK];
+    extern __shared__ int lds_stack[];
     const int64_t g = (int64_t)blockIdx.x * RR_TRACE_BLOCK + threadIdx.x;
     if (g < U.n) trace_user(A, U, g, lds_stack + threadIdx.x);
 }
@@ -576,7 +594,7 @@ __global__ void k_check_user(UserRays U, int shared, int ntx, int *flag)
 
 __global__ __launch_bounds__(RR_TRACE_BLOCK) void k_points(TraceArgs A)
 {
-    __shared__ int lds_stack[RR_STACK * RR_TRACE_BLOCK];
+    extern __shared__ int lds_stack[];
     const int64_t g = (int64_t)blockIdx.x * RR_TRACE_BLOCK + threadIdx.x;
     if (g < A.n_src * (int64_t)A.npts) trace_point(A, g, lds_stack + threadIdx.x);
 }
@@ -590,7 +608,7 @@ __global__ __launch_bounds__(RR_TRACE_BLOCK, RR_TRACE_WAVES) void k_batch_trace(
                                                                 const int64_t *chunk_start, int S,
                                                                 unsigned long long *work)
 {
-    __shared__ int lds_stack[RR_STACK * RR_TRACE_BLOCK];
+    extern __shared__ int lds_stack[];
     __shared__ long long s_chunk;
     const int64_t n_chunks = chunk_start[S];
     while (true) {
@@ -610,7 +628,7 @@ __global__ __launch_bounds__(RR_TRACE_BLOCK, RR_TRACE_WAVES) void k_batch_trace(
         const int64_t ray_chunks = (n_traced + RR_TRACE_BLOCK - 1) / RR_TRACE_BLOCK;
         if (c < ray_chunks) {
             const int64_t g = c * RR_TRACE_BLOCK + threadIdx.x;
-            if (g < n_traced) trace_ray(A, g, lds_stack + threadIdx.x);
+            if (g < n_traced) trace_ray<false>(A, g, lds_stack + threadIdx.x);
         } else {
             const int64_t g = (c - ray_chunks) * RR_TRACE_BLOCK + threadIdx.x;
             if (g < A.n_src * (int64_t)A.npts) trace_point(A, g, lds_stack + threadIdx.x);
@@ -624,7 +642,7 @@ __global__ __launch_bounds__(RR_TRACE_BLOCK, RR_TRACE_WAVES) void k_batch_trace(
 // sector's rays of exp(-t / 10 m) for hits on objects other than object 0.
 __global__ __launch_bounds__(RR_TRACE_BLOCK) void k_probe(TraceArgs A, float *code)
 {
-    __shared__ int lds_stack[RR_STACK * RR_TRACE_BLOCK];
+    extern __shared__ int lds_stack[];
     __shared__ double vals[128];
     int *stk = lds_stack + threadIdx.x;
     const int t = threadIdx.x;
@@ -683,99 +701,93 @@ __global__ void k_hist_finish(float *H, int nb)
 }
 
 // ---------------------------------------------------------------------------
-// exclusive scan of uint8 counts -> uint32 offsets (three passes)
+// places of the received paths: an exclusive scan over the rays' counts
 // ---------------------------------------------------------------------------
+// Sums of tiles of RR_SCAN_TILE counts, 16 lanes a tile, and their exclusive
+// scan; a reader adds the counts between its tile's start and its ray
+// (count_prefix): 3 % of the rays or fewer are read, so an offset for every
+// ray was mostly written for nothing (1e7 rays: sums, scan and offsets took 80 us,
+// the sums and their scan take 15).
 #define SCAN_T 256
-#define SCAN_PER 16
-#define SCAN_TILE (SCAN_T * SCAN_PER)
+#define TOP_T 1024
 
-__device__ __forceinline__ uint32_t load16_sum(const uint8_t *c, int64_t base, int64_t n, uint32_t v[16])
+__global__ __launch_bounds__(SCAN_T) void k_scan_reduce(const uint8_t *c, int64_t n16, int64_t nb,
+                                                        uint32_t *bsums)
 {
+    const int64_t i = (int64_t)blockIdx.x * SCAN_T + threadIdx.x;
     uint32_t s = 0;
+    if (i < n16) s = sum_counts(reinterpret_cast<const uint4 *>(c)[i]);
+    for (int off = RR_SCAN_TILE / 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+    const int64_t b = i / (RR_SCAN_TILE / 16);
+    if (i % (RR_SCAN_TILE / 16) == 0 && b < nb) bsums[b] = s;
+}
+
+// One workgroup, four tiles a thread at a time.  host != null: the trace's
+// outcome for the host (pinned): records appended, error flag.
+__global__ __launch_bounds__(TOP_T) void k_scan_top(uint32_t *bsums, int64_t nb,
+                                                    unsigned long long *total,
+                                                    const unsigned long long *counter,
+                                                    const int *err_flag, unsigned long long *host)
+{
+    __shared__ uint32_t part[2][TOP_T / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    uint32_t carry = 0;
+    int turn = 0;
+    for (int64_t b0 = 0; b0 < nb; b0 += 4 * TOP_T, turn ^= 1) {
+        uint4 *p = reinterpret_cast<uint4 *>(bsums + b0) + tid;
+        const int64_t left = nb - (b0 + 4 * tid);
+        uint4 x = make_uint4(0u, 0u, 0u, 0u);
+        if (left > 0) x = *p;            // (room for whole vectors)
+        if (left < 4) x.w = 0u;
+        if (left < 3) x.z = 0u;
+        if (left < 2) x.y = 0u;
+        const uint32_t own = x.x + x.y + x.z + x.w;
+        uint32_t s = own;
 #pragma unroll
-    for (int k = 0; k < 16; k++) {
-        int64_t idx = base + k;
-        v[k] = idx < n ? c[idx] : 0u;
-        s += v[k];
-    }
-    return s;
-}
-
-__device__ uint32_t block_excl_scan(uint32_t x, uint32_t *sh, uint32_t &total)
-{
-    // Hillis-Steele over the block in LDS (SCAN_T threads)
-    int t = threadIdx.x;
-    sh[t] = x;
-    __syncthreads();
-    for (int off = 1; off < SCAN_T; off <<= 1) {
-        uint32_t y = t >= off ? sh[t - off] : 0u;
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t v = __shfl_up(s, off);
+            if (lane >= off) s += v;
+        }
+        if (lane == 63) part[turn][wave] = s;
         __syncthreads();
-        sh[t] += y;
-        __syncthreads();
-    }
-    uint32_t incl = sh[t];
-    total = sh[SCAN_T - 1];
-    __syncthreads();
-    return incl - x;
-}
-
-__global__ __launch_bounds__(SCAN_T) void k_scan_reduce(const uint8_t *c, int64_t n, uint32_t *bsums)
-{
-    __shared__ uint32_t sh[SCAN_T];
-    int64_t base = (int64_t)blockIdx.x * SCAN_TILE + (int64_t)threadIdx.x * SCAN_PER;
-    uint32_t v[16];
-    uint32_t s = load16_sum(c, base, n, v);
-    uint32_t tot;
-    block_excl_scan(s, sh, tot);
-    if (threadIdx.x == 0) bsums[blockIdx.x] = tot;
-}
-
-__global__ __launch_bounds__(SCAN_T) void k_scan_top(uint32_t *bsums, int64_t nb,
-                                                     unsigned long long *total)
-{
-    __shared__ uint32_t sh[SCAN_T];
-    unsigned long long carry = 0;
-    for (int64_t b0 = 0; b0 < nb; b0 += SCAN_T) {
-        int64_t b = b0 + threadIdx.x;
-        uint32_t x = b < nb ? bsums[b] : 0u;
-        uint32_t tot;
-        uint32_t ex = block_excl_scan(x, sh, tot);
-        if (b < nb) bsums[b] = (uint32_t)(carry + ex);
-        carry += tot;
-    }
-    if (threadIdx.x == 0) *total = carry;
-}
-
-__global__ __launch_bounds__(SCAN_T) void k_scan_apply(const uint8_t *c, int64_t n,
-                                                       const uint32_t *boffs, uint32_t *offs)
-{
-    __shared__ uint32_t sh[SCAN_T];
-    int64_t base = (int64_t)blockIdx.x * SCAN_TILE + (int64_t)threadIdx.x * SCAN_PER;
-    uint32_t v[16];
-    uint32_t s = load16_sum(c, base, n, v);
-    uint32_t tot;
-    uint32_t run = boffs[blockIdx.x] + block_excl_scan(s, sh, tot);
+        uint32_t before = carry, all = 0;
 #pragma unroll
-    for (int k = 0; k < 16; k++) {
-        int64_t idx = base + k;
-        if (idx < n) offs[idx] = run;
-        run += v[k];
+        for (int w = 0; w < TOP_T / 64; w++) {
+            const uint32_t v = part[turn][w];
+            if (w < wave) before += v;
+            all += v;
+        }
+        carry += all;
+        uint4 y;
+        y.x = before + s - own;
+        y.y = y.x + x.x;
+        y.z = y.y + x.y;
+        y.w = y.z + x.z;
+        if (left > 0) *p = y;
+    }
+    if (tid == 0) {
+        *total = carry;
+        if (host) {
+            host[0] = *counter;
+            host[1] = (unsigned long long)*err_flag;
+        }
     }
 }
 
 __global__ void k_scatter(PathSoA tmp, const unsigned long long *counter, int64_t tmp_cap,
-                          const uint32_t *offs, PathSoA dst, int64_t keep)
+                          const uint8_t *counts, const uint32_t *bsums, PathSoA dst, int64_t keep)
 {
     int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     int64_t n = (int64_t)*counter;
     if (n > tmp_cap) n = tmp_cap;
     if (s >= n) return;
-    int64_t d = (int64_t)offs[tmp.ray[s]] + tmp.loc[s];
+    const int64_t ray = tmp.ray[s];
+    int64_t d = (int64_t)count_prefix(counts, bsums, ray) + tmp.loc[s];
     if (d >= keep) return;
     const int64_t sc = tmp.cap, dc = dst.cap;
     dst.src[d] = tmp.src[s];
     dst.K[d] = tmp.K[s];
-    dst.ray[d] = tmp.ray[s];
+    dst.ray[d] = ray;
 #pragma unroll
     for (int q = 0; q < RR_KMAX; q++) {
         dst.tri[q * dc + d] = tmp.tri[q * sc + s];
@@ -785,6 +797,41 @@ __global__ void k_scatter(PathSoA tmp, const unsigned long long *counter, int64_
     for (int q = 0; q < 3 * RR_KMAX; q++) dst.p[q * dc + d] = tmp.p[q * sc + s];
     dst.L[d] = tmp.L[s];
     dst.amp[d] = tmp.amp[s];
+}
+
+// A path list into the caller's planes, one launch instead of a strided copy
+// a plane (2e3 paths: 8 copies of 2 us and their gaps against one of 2-3 us).
+__global__ void k_copy_paths(PathSoA src, int64_t n, PathSoA dst)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const int64_t sc = src.cap, dc = dst.cap;
+    if (dst.src) dst.src[i] = src.src[i];
+    if (dst.K) dst.K[i] = src.K[i];
+    if (dst.ray) dst.ray[i] = src.ray[i];
+#pragma unroll
+    for (int q = 0; q < RR_KMAX; q++) {
+        if (dst.tri) dst.tri[q * dc + i] = src.tri[q * sc + i];
+        if (dst.vid) dst.vid[q * dc + i] = src.vid[q * sc + i];
+    }
+    if (dst.p) {
+#pragma unroll
+        for (int q = 0; q < 3 * RR_KMAX; q++) dst.p[q * dc + i] = src.p[q * sc + i];
+    }
+    if (dst.L) dst.L[i] = src.L[i];
+    if (dst.amp) dst.amp[i] = src.amp[i];
+}
+
+// what a trace starts from: every ray's count, the path counter, the error
+// flag and the order's cell counts are zero (one launch for all)
+__global__ void k_trace_clear(uint4 *counts, int64_t n16, unsigned long long *counter, int *err_flag,
+                              unsigned *cells, int64_t nk)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i == 0) *counter = 0ull;
+    if (i == 1 && err_flag) *err_flag = 0;
+    if (i < n16) counts[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (i < nk) cells[i] = 0u;
 }
 
 // Material mix of every leaf triangle (word 11 of its 12-word record): the
@@ -840,9 +887,15 @@ __device__ __forceinline__ void order_chunk(const TraceArgs &A, int64_t chunk, i
 }
 
 #define RR_ORDER_T 512
+#define RR_ORDER_MAXBITS 7
+static_assert(RR_ORDER_T == 512 && RR_ORDER_MAXBITS <= 7, "cell counts must fit 64 KiB of LDS, cell and rank 32 bits");
 
+// ray_cells[ray] = its cell and its rank among its chunk's rays of that cell
+// (cell below 2^14, rank below the chunk's 2^16 rays); first[chunk][cell] =
+// the chunk's first place within the cell
 __global__ __launch_bounds__(RR_ORDER_T) void k_order_count(TraceArgs A, int bits, int64_t chunk,
-                                                            uint16_t *cells, unsigned *cnt)
+                                                            unsigned *ray_cells, unsigned *cnt,
+                                                            unsigned *first)
 {
     extern __shared__ unsigned hist[];
     const int nb = 1 << (2 * bits);
@@ -852,12 +905,12 @@ __global__ __launch_bounds__(RR_ORDER_T) void k_order_count(TraceArgs A, int bit
     __syncthreads();
     for (int64_t i = lo + threadIdx.x; i < hi; i += RR_ORDER_T) {
         const unsigned c = ray_cell(A, t, i, bits);
-        cells[t * A.n_per_src + i] = (uint16_t)c;
-        atomicAdd(&hist[c], 1u);
+        ray_cells[t * A.n_per_src + i] = c | (atomicAdd(&hist[c], 1u) << (2 * RR_ORDER_MAXBITS));
     }
     __syncthreads();
+    first += (int64_t)blockIdx.x * nb;
     for (int b = threadIdx.x; b < nb; b += RR_ORDER_T)
-        if (hist[b]) atomicAdd(cnt + t * nb + b, hist[b]);
+        if (hist[b]) first[b] = atomicAdd(cnt + t * nb + b, hist[b]);
 }
 
 // exclusive scan in place of source blockIdx.x's nb cell counts, offset by
@@ -888,27 +941,29 @@ __global__ __launch_bounds__(1024) void k_order_scan(unsigned *cells, int64_t nb
     }
 }
 
-__global__ __launch_bounds__(RR_ORDER_T) void k_order_place(TraceArgs A, int bits, int64_t chunk,
-                                                            const uint16_t *cells, unsigned *cur,
-                                                            int32_t *order)
+// order[] from every ray's cell, chunk (of 2^shift rays) and rank:
+// independent rays, so the places wait on nothing but their own loads.  The
+// workgroups of a chunk run on one XCD (workgroups go round the 8 XCDs in
+// turn), whose L2 then joins the chunk's neighbours in a cell before they are
+// written back (1e7 rays: 73 us, with
+// a chunk's workgroups on all XCDs 107).
+__global__ __launch_bounds__(RR_ORDER_T) void k_order_place(unsigned n_per_src, unsigned chunks,
+                                                            unsigned per, int bits, int shift,
+                                                            const unsigned *ray_cells,
+                                                            const unsigned *start,
+                                                            const unsigned *first, int32_t *order)
 {
-    extern __shared__ unsigned hist[];
-    const int nb = 1 << (2 * bits);
-    int64_t t, lo, hi;
-    order_chunk(A, chunk, t, lo, hi);
-    const uint16_t *cl = cells + t * A.n_per_src;
-    for (int b = threadIdx.x; b < nb; b += RR_ORDER_T) hist[b] = 0u;
-    __syncthreads();
-    for (int64_t i = lo + threadIdx.x; i < hi; i += RR_ORDER_T) atomicAdd(&hist[cl[i]], 1u);
-    __syncthreads();
-    // this chunk's range of every cell it holds
-    for (int b = threadIdx.x; b < nb; b += RR_ORDER_T) {
-        const unsigned v = hist[b];
-        hist[b] = v ? atomicAdd(cur + t * nb + b, v) : 0u;
-    }
-    __syncthreads();
-    for (int64_t i = lo + threadIdx.x; i < hi; i += RR_ORDER_T)
-        order[atomicAdd(&hist[cl[i]], 1u)] = (int32_t)(t * A.n_per_src + i);
+    const unsigned parts = 1u << (shift - 9);
+    const unsigned group = blockIdx.x / (8 * parts), in = blockIdx.x - group * 8 * parts;
+    const unsigned ch = group * 8 + (in & 7);
+    if (ch >= chunks) return;
+    const unsigned t = ch / per, i = ((ch - t * per) << shift) + (in >> 3) * RR_ORDER_T + threadIdx.x;
+    if (i >= n_per_src) return;
+    const unsigned ray = t * n_per_src + i;
+    const unsigned w = ray_cells[ray];
+    const unsigned c = w & ((1u << (2 * RR_ORDER_MAXBITS)) - 1u);
+    order[start[(t << (2 * bits)) + c] + first[((int64_t)ch << (2 * bits)) + c] +
+          (w >> (2 * RR_ORDER_MAXBITS))] = (int32_t)ray;
 }
 
 }  // namespace
@@ -927,9 +982,8 @@ hipError_t launch_set_alpha(float4 *ltris, int64_t n_tris, const float *tri_alph
 // cells per source: 4^b with about 128-512 rays a cell (a sweep of cell sizes
 // found ~200 best for 8e5 and 4e6 rays per source), at most 128 x 128 (the
 // LDS counts of a workgroup, 64 KiB; cell numbers fit 16 bits)
-#define RR_ORDER_MAXBITS 7
 #define RR_ORDER_CELL 128
-static_assert(RR_ORDER_MAXBITS <= 7, "cell counts must fit 64 KiB of LDS");
+static int order_shift(int bits) { return std::max(2 * bits + 2, 9); }
 int trace_order_bits(int64_t n_per_src)
 {
     int bits = 0;
@@ -937,30 +991,47 @@ int trace_order_bits(int64_t n_per_src)
     return bits;
 }
 
+// chunks of one source's rays: four rays a cell, at least a workgroup's
+int64_t trace_order_chunks(int64_t n_src, int64_t n_per_src, int bits)
+{
+    const int64_t chunk = (int64_t)1 << order_shift(bits);
+    return n_src * ((n_per_src + chunk - 1) / chunk);
+}
+
 hipError_t launch_trace_order(const TraceArgs &a, int64_t n_traced, int bits, unsigned *cells,
-                              uint16_t *ray_cells, int32_t *order, hipStream_t s)
+                              unsigned *ray_cells, unsigned *first, int32_t *order, hipStream_t s)
 {
     if (n_traced <= 0) return hipSuccess;
-    if (bits > RR_ORDER_MAXBITS || n_traced != a.n_src * a.n_per_src) return hipErrorInvalidValue;
-    const int64_t nb = (int64_t)1 << (2 * bits), nk = a.n_src * nb;
-    hipError_t e = hipMemsetAsync(cells, 0, (size_t)nk * 4, s);
-    if (e != hipSuccess) return e;
-    const int64_t chunk = 4 * nb;
-    const int64_t blocks = a.n_src * ((a.n_per_src + chunk - 1) / chunk);
+    if (bits > RR_ORDER_MAXBITS || n_traced != a.n_src * a.n_per_src || n_traced >= ((int64_t)1 << 31))
+        return hipErrorInvalidValue;
+    const int64_t nb = (int64_t)1 << (2 * bits);
+    const int shift = order_shift(bits);
+    const int64_t chunk = (int64_t)1 << shift;
+    const int64_t blocks = trace_order_chunks(a.n_src, a.n_per_src, bits);
     const size_t lds = (size_t)nb * 4;
     hipLaunchKernelGGL(k_order_count, dim3((unsigned)blocks), dim3(RR_ORDER_T), lds, s, a, bits, chunk,
-                       ray_cells, cells);
+                       ray_cells, cells, first);
     hipLaunchKernelGGL(k_order_scan, dim3((unsigned)a.n_src), dim3(1024), 0, s, cells, nb, a.n_per_src);
-    hipLaunchKernelGGL(k_order_place, dim3((unsigned)blocks), dim3(RR_ORDER_T), lds, s, a, bits, chunk,
-                       ray_cells, cells, order);
+    hipLaunchKernelGGL(k_order_place, dim3((unsigned)((((blocks + 7) & ~(int64_t)7) * chunk) / RR_ORDER_T)),
+                       dim3(RR_ORDER_T), 0, s, (unsigned)a.n_per_src, (unsigned)blocks,
+                       (unsigned)(blocks / a.n_src), bits, shift, ray_cells, cells, first, order);
     return hipGetLastError();
+}
+
+// LDS of a workgroup's stacks: a.stack entries and a spare one a lane
+static size_t stack_bytes(const TraceArgs &a)
+{
+    return (size_t)(a.stack + 1) * RR_TRACE_BLOCK * sizeof(int);
 }
 
 hipError_t launch_trace(const TraceArgs &a, int64_t n_traced, hipStream_t s)
 {
     if (n_traced <= 0) return hipSuccess;
     int64_t blocks = (n_traced + RR_TRACE_BLOCK - 1) / RR_TRACE_BLOCK;
-    hipLaunchKernelGGL(k_trace, dim3((unsigned)blocks), dim3(RR_TRACE_BLOCK), 0, s, a, n_traced);
+    if (a.sampler == RR_PER_TRIANGLE)
+        hipLaunchKernelGGL(k_trace<true>, dim3((unsigned)blocks), dim3(RR_TRACE_BLOCK), stack_bytes(a), s, a, n_traced);
+    else
+        hipLaunchKernelGGL(k_trace<false>, dim3((unsigned)blocks), dim3(RR_TRACE_BLOCK), stack_bytes(a), s, a, n_traced);
     return hipGetLastError();
 }
 
@@ -969,7 +1040,7 @@ hipError_t launch_trace_count(const TraceArgs &a, int64_t n_traced, unsigned lon
 {
     if (n_traced <= 0) return hipSuccess;
     int64_t blocks = (n_traced + RR_TRACE_BLOCK - 1) / RR_TRACE_BLOCK;
-    hipLaunchKernelGGL(k_trace_count, dim3((unsigned)blocks), dim3(RR_TRACE_BLOCK), 0, s, a, n_traced,
+    hipLaunchKernelGGL(k_trace_count, dim3((unsigned)blocks), dim3(RR_TRACE_BLOCK), stack_bytes(a), s, a, n_traced,
                        stats);
     return hipGetLastError();
 }
@@ -978,7 +1049,7 @@ hipError_t launch_trace_user(const TraceArgs &a, const UserRays &u, hipStream_t 
 {
     if (u.n <= 0) return hipSuccess;
     int64_t blocks = (u.n + RR_TRACE_BLOCK - 1) / RR_TRACE_BLOCK;
-    hipLaunchKernelGGL(k_trace_user, dim3((unsigned)blocks), dim3(RR_TRACE_BLOCK), 0, s, a, u);
+    hipLaunchKernelGGL(k_trace_user, dim3((unsigned)blocks), dim3(RR_TRACE_BLOCK), stack_bytes(a), s, a, u);
     return hipGetLastError();
 }
 
@@ -995,11 +1066,11 @@ hipError_t launch_points(const TraceArgs &a, hipStream_t s)
     int64_t n = a.n_src * (int64_t)a.npts;
     if (n <= 0) return hipSuccess;
     int64_t blocks = (n + RR_TRACE_BLOCK - 1) / RR_TRACE_BLOCK;
-    hipLaunchKernelGGL(k_points, dim3((unsigned)blocks), dim3(RR_TRACE_BLOCK), 0, s, a);
+    hipLaunchKernelGGL(k_points, dim3((unsigned)blocks), dim3(RR_TRACE_BLOCK), stack_bytes(a), s, a);
     return hipGetLastError();
 }
 
-hipError_t launch_batch_trace(const TraceArgs *scenes, const int64_t *chunk_start, int S,
+hipError_t launch_batch_trace(const TraceArgs *scenes, const int64_t *chunk_start, int S, int stack,
                               int64_t n_chunks, unsigned long long *work, hipStream_t s)
 {
     int dev = 0, cus = 256;
@@ -1007,14 +1078,15 @@ hipError_t launch_batch_trace(const TraceArgs *scenes, const int64_t *chunk_star
     (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     const int64_t grid = std::min<int64_t>(n_chunks, (int64_t)cus * 16);
     if (grid <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_batch_trace, dim3((unsigned)grid), dim3(RR_TRACE_BLOCK), 0, s, scenes,
+    const size_t lds = (size_t)(stack + 1) * RR_TRACE_BLOCK * sizeof(int);
+    hipLaunchKernelGGL(k_batch_trace, dim3((unsigned)grid), dim3(RR_TRACE_BLOCK), lds, s, scenes,
                        chunk_start, S, work);
     return hipGetLastError();
 }
 
 hipError_t launch_probe(const TraceArgs &a, float *code, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_probe, dim3(1), dim3(RR_TRACE_BLOCK), 0, s, a, code);
+    hipLaunchKernelGGL(k_probe, dim3(1), dim3(RR_TRACE_BLOCK), stack_bytes(a), s, a, code);
     return hipGetLastError();
 }
 
@@ -1029,31 +1101,45 @@ hipError_t launch_hist(const TraceArgs &a, int64_t n_traced, const int32_t *hits
     return hipGetLastError();
 }
 
-int64_t scan_u8_blocks(int64_t n) { return (n + SCAN_TILE - 1) / SCAN_TILE; }
-
-hipError_t launch_scan_u8(const uint8_t *counts, int64_t n, uint32_t *offsets, uint32_t *bsums,
-                          int64_t nb_cap, unsigned long long *total, hipStream_t s)
+hipError_t launch_copy_paths(const PathSoA &src, int64_t n, const PathSoA &dst, hipStream_t s)
 {
-    int64_t nb = scan_u8_blocks(n);
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_copy_paths, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, src, n, dst);
+    return hipGetLastError();
+}
+
+hipError_t launch_trace_clear(uint8_t *counts, int64_t V, unsigned long long *counter, int *err_flag,
+                              unsigned *cells, int64_t nk, hipStream_t s)
+{
+    const int64_t n16 = (V + 15) / 16;
+    const int64_t n = std::max<int64_t>(std::max(n16, nk), 2);
+    hipLaunchKernelGGL(k_trace_clear, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
+                       reinterpret_cast<uint4 *>(counts), n16, counter, err_flag, cells, nk);
+    return hipGetLastError();
+}
+
+int64_t scan_u8_blocks(int64_t n) { return (n + RR_SCAN_TILE - 1) / RR_SCAN_TILE; }
+
+hipError_t launch_scan_u8(const uint8_t *counts, int64_t n, uint32_t *bsums, int64_t nb_cap,
+                          unsigned long long *total, const unsigned long long *counter,
+                          const int *err_flag, unsigned long long *host, hipStream_t s)
+{
+    const int64_t nb = scan_u8_blocks(n), n16 = (n + 15) / 16;
     if (nb > nb_cap) return hipErrorInvalidValue;
-    if (nb == 0) {
-        hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(SCAN_T), 0, s, bsums, (int64_t)0, total);
-        return hipGetLastError();
-    }
-    hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nb), dim3(SCAN_T), 0, s, counts, n, bsums);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(SCAN_T), 0, s, bsums, nb, total);
-    hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)nb), dim3(SCAN_T), 0, s, counts, n, bsums,
-                       offsets);
+    if (nb > 0)
+        hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)((n16 + SCAN_T - 1) / SCAN_T)), dim3(SCAN_T), 0,
+                           s, counts, n16, nb, bsums);
+    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(TOP_T), 0, s, bsums, nb, total, counter, err_flag, host);
     return hipGetLastError();
 }
 
 hipError_t launch_scatter(const PathSoA &tmp, const unsigned long long *counter, int64_t tmp_cap,
-                          const uint32_t *offsets, const PathSoA &dst, int64_t keep,
-                          hipStream_t s)
+                          const uint8_t *counts, const uint32_t *bsums, const PathSoA &dst,
+                          int64_t keep, hipStream_t s)
 {
     if (tmp_cap <= 0 || keep <= 0) return hipSuccess;
     int64_t blocks = (tmp_cap + 255) / 256;
     hipLaunchKernelGGL(k_scatter, dim3((unsigned)blocks), dim3(256), 0, s, tmp, counter, tmp_cap,
-                       offsets, dst, keep);
+                       counts, bsums, dst, keep);
     return hipGetLastError();
 }

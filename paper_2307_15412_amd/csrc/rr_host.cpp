@@ -208,7 +208,7 @@ struct rr_ctx {
     rr_chirp chirp{};
 
     // trace state
-    DevBuf counts, offsets, bsums, counter, total, err_flag, hits, cdf;
+    DevBuf counts, bsums, counter, total, err_flag, hits, cdf;
     PathStore tmp;
     int64_t tmp_cap = 0;
     PathStore paths;
@@ -221,6 +221,7 @@ struct rr_ctx {
 
     // synthesis scratch
     DevBuf syn;                 // records, the groups' ranges in both parts, prefix, block counts
+    unsigned long long *h_trace = nullptr;   // pinned: records and error flag of the last trace
     int32_t *h_info = nullptr;  // pinned: first and last source, counts at rest per block
     int64_t h_info_n = 0;
     DevBuf gT, gR, gA, gB;     // GEMM operands
@@ -239,7 +240,7 @@ struct rr_ctx {
     // refit of the BVH to moved vertices (rr_scene_update_vertices)
     DevBuf tris_dev, verts_dev, refit_order, ubox;
     FreqBufs fq;               // exact product engine
-    DevBuf order_cells, order_rc, order_idx;   // coherent ray order of a trace
+    DevBuf order_cells, order_rc, order_first, order_idx;   // coherent ray order of a trace
     DevBuf bp_sf;              // cube slices in fragment layout (MFMA back-projection)
     std::vector<double> h_tx, h_rx;
     std::vector<int64_t> refit_levels;   // starts of the levels in refit_order, deepest first
@@ -258,6 +259,11 @@ struct rr_ctx {
 
 namespace {
 
+// A lane pushes at most one child an inner node on its way to the deepest
+// leaf: stacks of the tree's own depth take less LDS than those of the
+// deepest tree, and five wavefronts fit a SIMD (street, depth 19: 4.5 before).
+int trace_stack(int depth) { return std::min(RR_STACK, depth + 1); }
+
 // The trace stage of rr_trace / rr_trace_rays: tracing kernels, scan of the
 // per-ray counts, scatter into (ray, bounce) order; grows the temporary
 // buffer and re-runs once if it overflowed.
@@ -265,24 +271,25 @@ namespace {
 // path count on the device and keeps at most min(path_cap, buffer) paths;
 // resolve_paths reads the count back when the host first needs it.
 template <class Kernels>
-int run_trace(rr_ctx *c, TraceArgs &A, int64_t V, int64_t nb, int64_t path_cap, Kernels kernels,
-              int64_t *n_paths_out)
+int run_trace(rr_ctx *c, TraceArgs &A, int64_t V, int64_t nb, int64_t n_cells, int64_t path_cap,
+              Kernels kernels, int64_t *n_paths_out)
 {
     int rc;
     c->paths_pending = false;
     if (!n_paths_out) {
         A.tmp = c->tmp.soa;
-        HIPCHK(hipMemsetAsync(c->counter.p, 0, 8, c->stream));
-        HIPCHK(hipMemsetAsync(c->err_flag.p, 0, 4, c->stream));
         HIPCHK(hipEventRecord(c->ev[0], c->stream));
+        HIPCHK(launch_trace_clear(A.counts, V, A.counter, A.err_flag, c->order_cells.as<unsigned>(),
+                                  n_cells, c->stream));
         HIPCHK(kernels(A));
         HIPCHK(hipEventRecord(c->ev[6], c->stream));
-        HIPCHK(launch_scan_u8(A.counts, V, c->offsets.as<uint32_t>(), c->bsums.as<uint32_t>(),
-                              nb + 1, c->total.as<unsigned long long>(), c->stream));
+        HIPCHK(launch_scan_u8(A.counts, V, c->bsums.as<uint32_t>(), nb + 1,
+                              c->total.as<unsigned long long>(), A.counter, A.err_flag, c->h_trace,
+                              c->stream));
         const int64_t keep = path_cap > 0 ? std::min(path_cap, c->tmp_cap) : c->tmp_cap;
         if ((rc = c->paths.alloc(std::max<int64_t>(keep, 1)))) return rc;
-        HIPCHK(launch_scatter(c->tmp.soa, A.counter, c->tmp_cap, c->offsets.as<uint32_t>(),
-                              c->paths.soa, keep, c->stream));
+        HIPCHK(launch_scatter(c->tmp.soa, A.counter, c->tmp_cap, A.counts,
+                              c->bsums.as<uint32_t>(), c->paths.soa, keep, c->stream));
         HIPCHK(hipEventRecord(c->ev[1], c->stream));
         c->n_paths = -1;
         c->paths_pending = true;
@@ -294,19 +301,17 @@ int run_trace(rr_ctx *c, TraceArgs &A, int64_t V, int64_t nb, int64_t path_cap, 
     }
     for (int attempt = 0; attempt < 2; attempt++) {
         A.tmp = c->tmp.soa;
-        HIPCHK(hipMemsetAsync(c->counter.p, 0, 8, c->stream));
-        HIPCHK(hipMemsetAsync(c->err_flag.p, 0, 4, c->stream));
         HIPCHK(hipEventRecord(c->ev[0], c->stream));
+        HIPCHK(launch_trace_clear(A.counts, V, A.counter, A.err_flag, c->order_cells.as<unsigned>(),
+                                  n_cells, c->stream));
         HIPCHK(kernels(A));
         HIPCHK(hipEventRecord(c->ev[6], c->stream));
-        HIPCHK(launch_scan_u8(A.counts, V, c->offsets.as<uint32_t>(), c->bsums.as<uint32_t>(),
-                              nb + 1, c->total.as<unsigned long long>(), c->stream));
-        unsigned long long cnt = 0;
-        int errf = 0;
-        HIPCHK(hipMemcpyAsync(&cnt, c->counter.p, 8, hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(hipMemcpyAsync(&errf, c->err_flag.p, 4, hipMemcpyDeviceToHost, c->stream));
+        HIPCHK(launch_scan_u8(A.counts, V, c->bsums.as<uint32_t>(), nb + 1,
+                              c->total.as<unsigned long long>(), A.counter, A.err_flag, c->h_trace,
+                              c->stream));
         HIPCHK(hipStreamSynchronize(c->stream));
-        if (errf)
+        const unsigned long long cnt = c->h_trace[0];
+        if (c->h_trace[1])
             return fail(RR_EUNSUPPORTED, "traversal stack overflow (BVH depth %d)", c->bvh_depth);
         if ((int64_t)cnt > c->tmp_cap) {
             c->tmp_cap = (int64_t)cnt + cnt / 4 + 1024;
@@ -316,8 +321,8 @@ int run_trace(rr_ctx *c, TraceArgs &A, int64_t V, int64_t nb, int64_t path_cap, 
         int64_t keep = (int64_t)cnt;
         if (path_cap > 0 && keep > path_cap) keep = path_cap;
         if ((rc = c->paths.alloc(std::max<int64_t>(keep, 1)))) return rc;
-        HIPCHK(launch_scatter(c->tmp.soa, A.counter, c->tmp_cap, c->offsets.as<uint32_t>(),
-                              c->paths.soa, keep, c->stream));
+        HIPCHK(launch_scatter(c->tmp.soa, A.counter, c->tmp_cap, A.counts,
+                              c->bsums.as<uint32_t>(), c->paths.soa, keep, c->stream));
         HIPCHK(hipEventRecord(c->ev[1], c->stream));
         c->n_paths = keep;
         c->trace_timed = true;
@@ -337,12 +342,9 @@ int resolve_paths(rr_ctx *c)
     if (!c->paths_pending) return RR_OK;
     c->paths_pending = false;
     HIPCHK(hipSetDevice(c->device));
-    unsigned long long cnt = 0;
-    int errf = 0;
-    HIPCHK(hipMemcpyAsync(&cnt, c->counter.p, 8, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipMemcpyAsync(&errf, c->err_flag.p, 4, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
-    if (errf)
+    const unsigned long long cnt = c->h_trace[0];
+    if (c->h_trace[1])
         return fail(RR_EUNSUPPORTED, "traversal stack overflow (BVH depth %d)", c->bvh_depth);
     if ((int64_t)cnt > c->tmp_cap) {
         const int64_t need = (int64_t)cnt;
@@ -398,6 +400,10 @@ int rr_create(int hip_device, void *hip_stream, rr_ctx **out)
         }
     }
     int rc = info_room(c, 1024);
+    if (!rc && hipHostMalloc((void **)&c->h_trace, 64, hipHostMallocDefault) != hipSuccess) {
+        c->h_trace = nullptr;
+        rc = fail(RR_ENOMEM, "hipHostMalloc failed");
+    }
     if (!rc) rc = c->counter.ensure(256);
     if (!rc) rc = c->total.ensure(256);
     if (!rc) rc = c->err_flag.ensure(256);
@@ -417,17 +423,18 @@ void rr_destroy(rr_ctx *c)
     if (c->stream) (void)hipStreamSynchronize(c->stream);
     else (void)hipDeviceSynchronize();
     DevBuf *bufs[] = {&c->nodes, &c->ltris, &c->obj_alpha, &c->obj_vel, &c->pt_pos, &c->pt_vel,
-                      &c->pt_ap, &c->tx, &c->rx, &c->counts, &c->offsets, &c->bsums,
+                      &c->pt_ap, &c->tx, &c->rx, &c->counts, &c->bsums,
                       &c->counter, &c->total, &c->err_flag, &c->hits, &c->cdf, &c->syn,
                       &c->tmp.buf, &c->paths.buf, &c->gT, &c->gR, &c->gA,
                       &c->gB, &c->tri_obj, &c->mlp_p, &c->mlp_m, &c->mlp_v, &c->mlp_g,
                       &c->mlp_acts, &c->mlp_z, &c->mlp_dz, &c->mlp_d, &c->mlp_loss, &c->mlp_part,
                       &c->tr_codes, &c->tr_hist, &c->tr_loss, &c->bp_peak, &c->trace_stats, &c->tri_alpha, &c->pieces_v, &c->pieces_p, &c->tris_dev, &c->verts_dev,
                       &c->refit_order, &c->ubox,
-                      &c->order_cells, &c->order_rc, &c->order_idx, &c->bp_sf};
+                      &c->order_cells, &c->order_rc, &c->order_first, &c->order_idx, &c->bp_sf};
     for (DevBuf *b : bufs) b->release();
     c->fq.release();
     if (c->h_info) (void)hipHostFree(c->h_info);
+    if (c->h_trace) (void)hipHostFree(c->h_trace);
     for (auto &e : c->ev)
         if (e) (void)hipEventDestroy(e);
     delete c;
@@ -800,9 +807,8 @@ static int trace_impl(rr_ctx *c, const rr_trace_params *tp, int64_t *n_paths_out
 
     int rc;
     if ((rc = c->counts.ensure((size_t)V + 64))) return rc;
-    if ((rc = c->offsets.ensure((size_t)V * 4 + 64))) return rc;
     const int64_t nb = scan_u8_blocks(V);
-    if ((rc = c->bsums.ensure((size_t)(nb + 1) * 4))) return rc;
+    if ((rc = c->bsums.ensure((size_t)(nb + 4) * 4))) return rc;
     if (tp->record_hits) {
         if ((rc = c->hits.ensure((size_t)n_traced * (bmax + 1) * 4 + 64))) return rc;
         c->hits_elems = n_traced * (bmax + 1);
@@ -817,10 +823,14 @@ static int trace_impl(rr_ctx *c, const rr_trace_params *tp, int64_t *n_paths_out
     // (sorted by source and first-direction cell; results do not depend on it)
     const bool coherent = !tri_g && n_per_src >= 4096 && n_traced < ((int64_t)1 << 31);
     const int obits = coherent ? trace_order_bits(n_per_src) : 0;
+    const int64_t n_cells = coherent ? n_src << (2 * obits) : 0;
     if (coherent) {
         if ((rc = c->order_idx.ensure((size_t)n_traced * 4))) return rc;
-        if ((rc = c->order_rc.ensure((size_t)n_traced * 2))) return rc;
-        if ((rc = c->order_cells.ensure((size_t)(n_src << (2 * obits)) * 4))) return rc;
+        if ((rc = c->order_rc.ensure((size_t)n_traced * 4))) return rc;
+        if ((rc = c->order_cells.ensure((size_t)n_cells * 4))) return rc;
+        if ((rc = c->order_first.ensure(
+                 (size_t)(trace_order_chunks(n_src, n_per_src, obits) << (2 * obits)) * 4)))
+            return rc;
     }
 
     TraceArgs A{};
@@ -841,6 +851,7 @@ static int trace_impl(rr_ctx *c, const rr_trace_params *tp, int64_t *n_paths_out
     A.n_src = n_src;
     A.n_per_src = n_per_src;
     A.n_virt_per_src = n_vps;
+    A.inv_per_src = n_per_src > 0 ? 1.0 / (double)n_per_src : 0.0;
     const double INV_2PI = 0.15915494309189535;
     A.at = tp->az_min * INV_2PI;
     A.bt = tp->az_max * INV_2PI;
@@ -864,14 +875,15 @@ static int trace_impl(rr_ctx *c, const rr_trace_params *tp, int64_t *n_paths_out
     A.counts = c->counts.as<uint8_t>();
     A.counter = c->counter.as<unsigned long long>();
     A.err_flag = c->err_flag.as<int>();
+    A.stack = trace_stack(c->bvh_depth);
 
     auto kernels = [&](const TraceArgs &a) -> hipError_t {
         hipError_t e = hipSuccess;
         TraceArgs b = a;
         if (coherent) {
             e = launch_trace_order(a, n_traced, obits, c->order_cells.as<unsigned>(),
-                                   c->order_rc.as<uint16_t>(), c->order_idx.as<int32_t>(),
-                                   c->stream);
+                                   c->order_rc.as<unsigned>(), c->order_first.as<unsigned>(),
+                                   c->order_idx.as<int32_t>(), c->stream);
             b.order = c->order_idx.as<const int32_t>();
         }
         if (e == hipSuccess && stats) {
@@ -882,7 +894,7 @@ static int trace_impl(rr_ctx *c, const rr_trace_params *tp, int64_t *n_paths_out
         }
         return e == hipSuccess ? launch_points(a, c->stream) : e;
     };
-    int rc2 = run_trace(c, A, V, nb, tp->path_cap, kernels, n_paths_out);
+    int rc2 = run_trace(c, A, V, nb, n_cells, tp->path_cap, kernels, n_paths_out);
     if (rc2) return rc2;
     c->last_traced = n_traced;
     c->last_sampler = tp->record_hits ? tp->sampler : -1;
@@ -940,9 +952,8 @@ int rr_trace_rays(rr_ctx *c, const double *orig, const double *dir, const double
     }
     const int64_t V = n;
     if ((rc = c->counts.ensure((size_t)V + 64))) return rc;
-    if ((rc = c->offsets.ensure((size_t)V * 4 + 64))) return rc;
     const int64_t nb = scan_u8_blocks(V);
-    if ((rc = c->bsums.ensure((size_t)(nb + 1) * 4))) return rc;
+    if ((rc = c->bsums.ensure((size_t)(nb + 4) * 4))) return rc;
     if (record_hits) {
         if ((rc = c->hits.ensure((size_t)n * (max_bounces + 1) * 4 + 64))) return rc;
         c->hits_elems = n * (max_bounces + 1);
@@ -977,10 +988,11 @@ int rr_trace_rays(rr_ctx *c, const double *orig, const double *dir, const double
     A.counts = c->counts.as<uint8_t>();
     A.counter = c->counter.as<unsigned long long>();
     A.err_flag = c->err_flag.as<int>();
+    A.stack = trace_stack(c->bvh_depth);
     auto kernels = [&](const TraceArgs &a) -> hipError_t {
         return launch_trace_user(a, U, c->stream);
     };
-    if ((rc = run_trace(c, A, V, nb, 0, kernels, n_paths_out))) return rc;
+    if ((rc = run_trace(c, A, V, nb, 0, 0, kernels, n_paths_out))) return rc;
     c->last_traced = n;
     c->last_sampler = -1;
     return RR_OK;
@@ -1031,14 +1043,17 @@ int rr_get_paths(rr_ctx *c, const rr_paths *d, int64_t *n_out)
     HIPCHK(hipSetDevice(c->device));
     const PathSoA &s = c->paths.soa;
     hipStream_t st = c->stream;
-    if (d->src) HIPCHK(copy_planes(d->src, d->stride, s.src, s.cap, n, 1, 4, st));
-    if (d->K) HIPCHK(copy_planes(d->K, d->stride, s.K, s.cap, n, 1, 4, st));
-    if (d->ray) HIPCHK(copy_planes(d->ray, d->stride, s.ray, s.cap, n, 1, 8, st));
-    if (d->tri) HIPCHK(copy_planes(d->tri, d->stride, s.tri, s.cap, n, RR_KMAX, 4, st));
-    if (d->vid) HIPCHK(copy_planes(d->vid, d->stride, s.vid, s.cap, n, RR_KMAX, 4, st));
-    if (d->p) HIPCHK(copy_planes(d->p, d->stride, s.p, s.cap, n, 3 * RR_KMAX, 8, st));
-    if (d->L) HIPCHK(copy_planes(d->L, d->stride, s.L, s.cap, n, 1, 8, st));
-    if (d->amp) HIPCHK(copy_planes(d->amp, d->stride, s.amp, s.cap, n, 1, 8, st));
+    PathSoA o;
+    o.cap = d->stride;
+    o.src = d->src;
+    o.K = d->K;
+    o.ray = d->ray;
+    o.tri = d->tri;
+    o.vid = d->vid;
+    o.p = d->p;
+    o.L = d->L;
+    o.amp = d->amp;
+    HIPCHK(launch_copy_paths(s, n, o, st));
     HIPCHK(hipStreamSynchronize(st));
     return RR_OK;
 }
@@ -1790,6 +1805,7 @@ int rr_proposal_probe(rr_ctx *c, double az_min, double az_max, float *code16)
     A.at = az_min * INV_2PI;
     A.bt = az_max * INV_2PI;
     A.err_flag = c->err_flag.as<int>();
+    A.stack = trace_stack(c->bvh_depth);
     HIPCHK(launch_probe(A, code16, c->stream));
     return RR_OK;
 }
@@ -2059,6 +2075,7 @@ namespace {
 struct BatchScene {
     bool set = false;
     int64_t n_tris = 0;
+    int bvh_depth = 0;
     int nobj = 0, npts = 0, ntx = 0, nrx = 0, mode = 0;
     double rx_radius = 0.25, oT[3] = {0, 0, 0}, oR[3] = {0, 0, 0};
     double box[12];                       // bounds of the Tx, then of the Rx elements
@@ -2101,7 +2118,8 @@ struct rr_batch {
     hipStream_t st = nullptr;
     hipEvent_t ev[6] = {};
     DevBuf d_targs, d_sargs, d_info, d_chunk, d_items, d_vr, d_vel, d_rinfo, d_ranges, d_items_rest, d_items0, rest_pre, rest_sums;
-    DevBuf counts, offsets, bsums, total, counter, work;
+    int stack = 0;            // the deepest scene's
+    DevBuf counts, bsums, total, counter, work;
     PathStore tmp, fin;
     DevBuf syn, alpha_tmp;
     FreqBufs fq;                          // exact engine, shared by its scenes
@@ -2245,8 +2263,7 @@ int batch_prepare(rr_batch *b, int only_K = 0, int64_t p_limit = 0, int only_sce
     b->nb = scan_u8_blocks(V);
     int rc;
     if ((rc = b->counts.ensure((size_t)V + 64))) return rc;
-    if ((rc = b->offsets.ensure((size_t)V * 4 + 64))) return rc;
-    if ((rc = b->bsums.ensure((size_t)(b->nb + 1) * 4))) return rc;
+    if ((rc = b->bsums.ensure((size_t)(b->nb + 4) * 4))) return rc;
     if ((rc = b->total.ensure(256))) return rc;
     if ((rc = b->counter.ensure(256))) return rc;
     if ((rc = b->work.ensure(256))) return rc;
@@ -2300,6 +2317,7 @@ int batch_prepare(rr_batch *b, int only_K = 0, int64_t p_limit = 0, int only_sce
         A.n_src = x.n_src;
         A.n_per_src = x.n_per_src;
         A.n_virt_per_src = x.n_vps;
+        A.inv_per_src = x.n_per_src > 0 ? 1.0 / (double)x.n_per_src : 0.0;
         A.at = x.tp.az_min * INV_2PI;
         A.bt = x.tp.az_max * INV_2PI;
         A.slo = std::sin(x.tp.el_min);
@@ -2314,6 +2332,8 @@ int batch_prepare(rr_batch *b, int only_K = 0, int64_t p_limit = 0, int only_sce
         A.tmp = b->tmp.soa;
         A.counter = b->counter.as<unsigned long long>();
         A.err_flag = b->c->err_flag.as<int>();
+        A.stack = trace_stack(x.bvh_depth);
+        b->stack = std::max(b->stack, A.stack);
         SynthArgs &Y = sa[s];
         Y = SynthArgs{};
         Y.paths = b->syn.as<const SynPath>();
@@ -2372,19 +2392,21 @@ int batch_enqueue_trace(rr_batch *b, bool timed)
     hipStream_t st = b->st;
     unsigned long long *work = b->work.as<unsigned long long>();
     HIPCHK(launch_fill_u64(work, 2, 0ull, st));
-    HIPCHK(launch_fill_u64(b->counter.as<unsigned long long>(), 1, 0ull, st));
     if (timed) HIPCHK(hipEventRecord(b->ev[0], st));
+    HIPCHK(launch_trace_clear(b->counts.as<uint8_t>(), b->V_total, b->counter.as<unsigned long long>(),
+                              nullptr, nullptr, 0, st));
     HIPCHK(launch_batch_trace(b->d_targs.as<const TraceArgs>(), b->d_chunk.as<const int64_t>(), b->S,
-                              b->n_chunks, work, st));
-    HIPCHK(launch_scan_u8(b->counts.as<const uint8_t>(), b->V_total, b->offsets.as<uint32_t>(),
-                          b->bsums.as<uint32_t>(), b->nb + 1, b->total.as<unsigned long long>(), st));
+                              b->stack, b->n_chunks, work, st));
+    HIPCHK(launch_scan_u8(b->counts.as<const uint8_t>(), b->V_total, b->bsums.as<uint32_t>(),
+                          b->nb + 1, b->total.as<unsigned long long>(), nullptr, nullptr, nullptr, st));
     HIPCHK(launch_scatter(b->tmp.soa, b->counter.as<const unsigned long long>(), b->cap,
-                          b->offsets.as<const uint32_t>(), b->fin.soa, b->cap, st));
+                          b->counts.as<const uint8_t>(), b->bsums.as<const uint32_t>(), b->fin.soa,
+                          b->cap, st));
     HIPCHK(launch_batch_prep(b->fin.soa, b->total.as<const unsigned long long>(), b->cap,
                              b->d_vr.as<const int64_t>(), b->S, b->d_vel.as<const BatchVel>(),
                              b->rest_sums.as<uint32_t>(), b->rest_pre.as<uint32_t>(),
                              b->syn.as<SynPath>(), st));
-    HIPCHK(launch_batch_ranges(b->offsets.as<const uint32_t>(), b->V_total,
+    HIPCHK(launch_batch_ranges(b->counts.as<const uint8_t>(), b->bsums.as<const uint32_t>(), b->V_total,
                                b->total.as<const unsigned long long>(), b->cap,
                                b->d_rinfo.as<const BatchRangeInfo>(), b->S,
                                b->rest_pre.as<const uint32_t>(), b->d_ranges.as<int64_t>(),
@@ -2485,7 +2507,7 @@ void rr_batch_destroy(rr_batch *b)
     batch_drop_graph(b);
     for (auto &x : b->sc) x.release();
     DevBuf *bufs[] = {&b->d_targs, &b->d_sargs, &b->d_info, &b->d_chunk, &b->d_items, &b->d_vr,
-                      &b->d_vel, &b->d_rinfo, &b->d_ranges, &b->counts, &b->offsets, &b->bsums,
+                      &b->d_vel, &b->d_rinfo, &b->d_ranges, &b->counts, &b->bsums,
                       &b->total, &b->counter, &b->work, &b->syn, &b->alpha_tmp, &b->tmp.buf,
                       &b->fin.buf, &b->d_items_rest, &b->d_items0, &b->rest_pre, &b->rest_sums};
     for (DevBuf *x : bufs) x->release();
@@ -2542,6 +2564,7 @@ int rr_batch_set_scene(rr_batch *b, int32_t slot, const float *verts, int64_t n_
     if (rc) return fail(rc, "BVH build: %s", err.c_str());
     BatchScene &x = b->sc[slot];
     if ((rc = x.nodes.ensure(bvh.nodes.size() * 4 + 64))) return rc;
+    x.bvh_depth = bvh.depth;
     if ((rc = x.ltris.ensure(bvh.tris.size() * 4 + 64))) return rc;
     if ((rc = x.obj_alpha.ensure((size_t)n_obj * 4))) return rc;
     if ((rc = x.obj_vel.ensure((size_t)n_obj * 24))) return rc;

@@ -60,6 +60,35 @@ int rr_build_bvh(const float *verts, int64_t nv, const int32_t *tris, const int3
                  const float *obj_alpha, int64_t nt, HostBvh &out, std::string &err);
 
 // ---------------------------------------------------------------------------
+// prefix of the rays' path counts: sums before every tile, and the tile's own
+// counts up to the ray
+// ---------------------------------------------------------------------------
+#define RR_SCAN_TILE 256
+
+#ifdef __HIP__
+__device__ __forceinline__ uint32_t sum_counts(uint4 v)
+{
+    return __builtin_amdgcn_sad_u8(
+        v.x, 0u, __builtin_amdgcn_sad_u8(
+                     v.y, 0u, __builtin_amdgcn_sad_u8(v.z, 0u, __builtin_amdgcn_sad_u8(v.w, 0u, 0u))));
+}
+
+// paths of the rays before ray v
+__device__ __forceinline__ uint32_t count_prefix(const uint8_t *counts, const uint32_t *bsums, int64_t v)
+{
+    const int64_t b = v / RR_SCAN_TILE;
+    const uint4 *c = reinterpret_cast<const uint4 *>(counts + b * RR_SCAN_TILE);
+    const int in = (int)(v - b * RR_SCAN_TILE), full = in >> 4, part = in & 15;
+    uint32_t s = bsums[b];
+#pragma unroll 8
+    for (int k = 0; k < full; k++) s += sum_counts(c[k]);
+    const uint8_t *t = reinterpret_cast<const uint8_t *>(c + full);
+    for (int k = 0; k < part; k++) s += t[k];
+    return s;
+}
+#endif
+
+// ---------------------------------------------------------------------------
 // trace kernel arguments (by value)
 // ---------------------------------------------------------------------------
 struct TraceArgs {
@@ -74,6 +103,7 @@ struct TraceArgs {
     int shared;
     int nobj, npts;
     int64_t n_src, n_per_src, n_virt_per_src;
+    double inv_per_src;       // 1 / n_per_src
     double at, bt, slo, shi, omega;
     int bmax;
     uint64_t seed;
@@ -88,10 +118,11 @@ struct TraceArgs {
     const int32_t *order;     // [n_traced] ray of each lane (coherent order) or null
     // outputs
     int32_t *hits;            // [n_src*n_per_src][bmax+1] or null
-    uint8_t *counts;          // indexed by vbase + virtual ray
+    uint8_t *counts;          // indexed by vbase + virtual ray; zero before the launch
     PathSoA tmp;
-    unsigned long long *counter;
+    unsigned long long *counter;   // records appended
     int *err_flag;
+    int stack;                // entries of a lane's traversal stack, at most RR_STACK
 };
 
 // caller-supplied rays (device arrays)
@@ -179,10 +210,12 @@ struct BatchRangeInfo {
 hipError_t launch_trace(const TraceArgs &a, int64_t n_traced, hipStream_t s);
 // coherent ray order of a uniform or proposal launch: rays sorted by source
 // and the 2^bits x 2^bits cell of their first direction (cells: n_src 4^bits
-// counters, ray_cells: n_traced cell numbers, order: n_traced ray indices)
+// counters, zero before; ray_cells: n_traced cells and ranks; first: 4^bits
+// places per chunk, trace_order_chunks of them; order: n_traced ray indices)
 int trace_order_bits(int64_t n_per_src);
+int64_t trace_order_chunks(int64_t n_src, int64_t n_per_src, int bits);
 hipError_t launch_trace_order(const TraceArgs &a, int64_t n_traced, int bits, unsigned *cells,
-                              uint16_t *ray_cells, int32_t *order, hipStream_t s);
+                              unsigned *ray_cells, unsigned *first, int32_t *order, hipStream_t s);
 hipError_t launch_points(const TraceArgs &a, hipStream_t s);
 // k_trace plus exact work counters: stats[0] BVH nodes fetched, stats[1] leaf
 // triangle records fetched, stats[2] closest-hit queries (summed, not cleared)
@@ -337,12 +370,21 @@ hipError_t launch_backproject(const BackProjArgs &a, hipStream_t s);
 hipError_t launch_max_projection(const float2 *img, int64_t nx, int64_t nyz, float *out,
                                  float *peak, float floor_db, hipStream_t s);
 hipError_t launch_check_user(const UserRays &u, int shared, int ntx, int *flag, hipStream_t s);
-hipError_t launch_scan_u8(const uint8_t *counts, int64_t n, uint32_t *offsets, uint32_t *bsums,
-                          int64_t nb_cap, unsigned long long *total, hipStream_t s);
+// What every trace starts from: counts (a multiple of 16 bytes allocated),
+// *counter, *err_flag (or null) and nk cell counts zero.
+hipError_t launch_trace_clear(uint8_t *counts, int64_t V, unsigned long long *counter, int *err_flag,
+                              unsigned *cells, int64_t nk, hipStream_t s);
+// bsums[b] = paths of the rays before tile b; *total = their number; host
+// (pinned, or null) = {*counter, *err_flag}
+hipError_t launch_scan_u8(const uint8_t *counts, int64_t n, uint32_t *bsums, int64_t nb_cap,
+                          unsigned long long *total, const unsigned long long *counter,
+                          const int *err_flag, unsigned long long *host, hipStream_t s);
 int64_t scan_u8_blocks(int64_t n);
 hipError_t launch_scatter(const PathSoA &tmp, const unsigned long long *counter, int64_t tmp_cap,
-                          const uint32_t *offsets, const PathSoA &dst, int64_t keep,
-                          hipStream_t s);
+                          const uint8_t *counts, const uint32_t *bsums, const PathSoA &dst,
+                          int64_t keep, hipStream_t s);
+// the first n paths into dst's planes; a null plane is left out
+hipError_t launch_copy_paths(const PathSoA &src, int64_t n, const PathSoA &dst, hipStream_t s);
 
 // Synthesis records in two parts (see SynthArgs): rest_blocks(n) block counts
 // and n + 1 prefix entries of scratch.  split = 0 keeps every path in the
@@ -398,7 +440,7 @@ hipError_t launch_mlp_backward(const float *P, const float *dz, int64_t n, const
 hipError_t launch_adam(float *P, const float *G, float *m, float *v, float lr, int step, hipStream_t s);
 hipError_t launch_build_cdf(const float *z, float beta, float power, float kappa, double *cdf,
                             hipStream_t s);
-hipError_t launch_batch_trace(const TraceArgs *scenes, const int64_t *chunk_start, int S,
+hipError_t launch_batch_trace(const TraceArgs *scenes, const int64_t *chunk_start, int S, int stack,
                               int64_t n_chunks, unsigned long long *work, hipStream_t s);
 // stage 0: paths at rest into chirp 0 (items: channels), 1: the other chirps,
 // 2: moving paths into chirp 0
@@ -409,7 +451,7 @@ hipError_t launch_batch_prep(const PathSoA &paths, const unsigned long long *tot
                              const int64_t *vr_start, int S, const BatchVel *vel, uint32_t *bsums,
                              uint32_t *pre, SynPath *out, hipStream_t s);
 // rest / mov: ranges of every scene's groups in the two parts of the records
-hipError_t launch_batch_ranges(const uint32_t *offsets, int64_t V, const unsigned long long *total,
-                               int64_t cap, const BatchRangeInfo *ri, int S, const uint32_t *pre,
+hipError_t launch_batch_ranges(const uint8_t *counts, const uint32_t *bsums, int64_t V,
+                               const unsigned long long *total, int64_t cap, const BatchRangeInfo *ri, int S, const uint32_t *pre,
                                int64_t *rest, int64_t *mov, hipStream_t s);
 hipError_t launch_fill_u64(unsigned long long *p, int64_t n, unsigned long long v, hipStream_t s);
