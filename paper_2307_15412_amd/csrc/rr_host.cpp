@@ -222,7 +222,7 @@ struct rr_ctx {
     // synthesis scratch
     DevBuf syn;                 // records, the groups' ranges in both parts, prefix, block counts
     unsigned long long *h_trace = nullptr;   // pinned: records and error flag of the last trace
-    int32_t *h_info = nullptr;  // pinned: first and last source, counts at rest per block
+    int32_t *h_info = nullptr;  // pinned, behind h_trace: first and last source, counts at rest per block
     int64_t h_info_n = 0;
     DevBuf gT, gR, gA, gB;     // GEMM operands
 
@@ -249,7 +249,7 @@ struct rr_ctx {
     TraceArgs last{};          // arguments of the last trace (histogram)
     int64_t last_traced = 0;
     int last_sampler = -1;
-    DevBuf mlp_p, mlp_m, mlp_v, mlp_g, mlp_acts, mlp_z, mlp_dz, mlp_d, mlp_loss, mlp_part;
+    DevBuf mlp_p, mlp_m, mlp_v, mlp_g, mlp_acts, mlp_z, mlp_dz, mlp_loss, mlp_part;
     DevBuf tr_codes, tr_hist, tr_loss;   // minibatch staging of rr_proposal_train
     DevBuf bp_peak;                      // peak of the last maximum projection
     DevBuf trace_stats;                  // work counters of rr_trace_work
@@ -361,13 +361,12 @@ int resolve_paths(rr_ctx *c)
 int info_room(rr_ctx *c, int64_t n)
 {
     if (c->h_info_n >= n) return RR_OK;
-    if (c->h_info) (void)hipHostFree(c->h_info);
-    c->h_info = nullptr;
-    c->h_info_n = 0;
-    if (hipHostMalloc((void **)&c->h_info, (size_t)n * 4, hipHostMallocDefault) != hipSuccess) {
-        c->h_info = nullptr;
-        return fail(RR_ENOMEM, "hipHostMalloc(%lld) failed", (long long)n * 4);
-    }
+    unsigned long long *p = nullptr;
+    if (hipHostMalloc((void **)&p, 64 + (size_t)n * 4, hipHostMallocDefault) != hipSuccess)
+        return fail(RR_ENOMEM, "hipHostMalloc(%lld) failed", (long long)n * 4 + 64);
+    if (c->h_trace) (void)hipHostFree(c->h_trace);
+    c->h_trace = p;
+    c->h_info = reinterpret_cast<int32_t *>(c->h_trace + 8);
     c->h_info_n = n;
     return RR_OK;
 }
@@ -400,10 +399,6 @@ int rr_create(int hip_device, void *hip_stream, rr_ctx **out)
         }
     }
     int rc = info_room(c, 1024);
-    if (!rc && hipHostMalloc((void **)&c->h_trace, 64, hipHostMallocDefault) != hipSuccess) {
-        c->h_trace = nullptr;
-        rc = fail(RR_ENOMEM, "hipHostMalloc failed");
-    }
     if (!rc) rc = c->counter.ensure(256);
     if (!rc) rc = c->total.ensure(256);
     if (!rc) rc = c->err_flag.ensure(256);
@@ -427,13 +422,12 @@ void rr_destroy(rr_ctx *c)
                       &c->counter, &c->total, &c->err_flag, &c->hits, &c->cdf, &c->syn,
                       &c->tmp.buf, &c->paths.buf, &c->gT, &c->gR, &c->gA,
                       &c->gB, &c->tri_obj, &c->mlp_p, &c->mlp_m, &c->mlp_v, &c->mlp_g,
-                      &c->mlp_acts, &c->mlp_z, &c->mlp_dz, &c->mlp_d, &c->mlp_loss, &c->mlp_part,
+                      &c->mlp_acts, &c->mlp_z, &c->mlp_dz, &c->mlp_loss, &c->mlp_part,
                       &c->tr_codes, &c->tr_hist, &c->tr_loss, &c->bp_peak, &c->trace_stats, &c->tri_alpha, &c->pieces_v, &c->pieces_p, &c->tris_dev, &c->verts_dev,
                       &c->refit_order, &c->ubox,
                       &c->order_cells, &c->order_rc, &c->order_first, &c->order_idx, &c->bp_sf};
     for (DevBuf *b : bufs) b->release();
     c->fq.release();
-    if (c->h_info) (void)hipHostFree(c->h_info);
     if (c->h_trace) (void)hipHostFree(c->h_trace);
     for (auto &e : c->ev)
         if (e) (void)hipEventDestroy(e);
@@ -1896,7 +1890,6 @@ static int mlp_buffers(rr_ctx *c, int64_t rows, int n_scenes)
     if ((rc = c->mlp_acts.ensure((size_t)rows * 3 * 64 * 2))) return rc;
     if ((rc = c->mlp_z.ensure((size_t)rows * 4))) return rc;
     if ((rc = c->mlp_dz.ensure((size_t)rows * 4))) return rc;
-    if ((rc = c->mlp_d.ensure((size_t)rows * 3 * 64 * 4))) return rc;
     if ((rc = c->mlp_loss.ensure((size_t)n_scenes * 4 + 4))) return rc;
     if ((rc = c->mlp_part.ensure((size_t)mlp_part_rows(rows) * RR_MLP_PARAMS * 4))) return rc;
     return RR_OK;
@@ -1922,22 +1915,19 @@ static int mlp_step(rr_ctx *c, const float *codes, const float *hist, int32_t n_
     int rc = mlp_buffers(c, rows, n_scenes);
     if (rc) return rc;
     __half *acts = c->mlp_acts.as<__half>();
-    float *d = c->mlp_d.as<float>();
     HIPCHK(launch_mlp_forward(c->mlp_p.as<const float>(), codes, rows, acts, c->mlp_z.as<float>(),
                               c->stream));
     HIPCHK(launch_softmax_grad(c->mlp_z.as<const float>(), hist, n_scenes, c->mlp_dz.as<float>(),
                                c->mlp_loss.as<float>(), c->stream));
+    if (lr > 0.0f) c->mlp_step++;
     HIPCHK(launch_mlp_backward(c->mlp_p.as<const float>(), c->mlp_dz.as<const float>(), rows, acts,
-                               d, d + rows * 64, d + 2 * rows * 64, codes, c->mlp_part.as<float>(),
-                               c->mlp_g.as<float>(), c->stream));
+                               codes, c->mlp_part.as<float>(), c->mlp_g.as<float>(),
+                               adam_args(c->mlp_p.as<float>(), c->mlp_m.as<float>(),
+                                         c->mlp_v.as<float>(), lr, c->mlp_step),
+                               c->stream));
     if (grad_out)
         HIPCHK(hipMemcpyAsync(grad_out, c->mlp_g.p, RR_MLP_PARAMS * 4, hipMemcpyDeviceToDevice,
                               c->stream));
-    if (lr > 0.0f) {
-        c->mlp_step++;
-        HIPCHK(launch_adam(c->mlp_p.as<float>(), c->mlp_g.as<const float>(), c->mlp_m.as<float>(),
-                           c->mlp_v.as<float>(), lr, c->mlp_step, c->stream));
-    }
     return RR_OK;
 }
 

@@ -429,15 +429,21 @@ hipError_t launch_mlp_forward(const float *P, const float *codes, int64_t n, __h
                               hipStream_t s);
 hipError_t launch_softmax_grad(const float *z, const float *H, int n_scenes, float *dz, float *loss,
                                hipStream_t s);
-// weight gradients: the rows are split over at most 4 096 blocks, each
-// writing its partial sums into part; two passes then add them in a fixed
-// order (runs of consecutive blocks, then the runs) into grad (every entry
-// written).  part holds mlp_part_rows(n) rows of RR_MLP_PARAMS floats.
+// lr > 0: a step of Adam after the gradient
+struct AdamArgs {
+    float *P, *m, *v;
+    float lr, b1, b2, c1, c2, eps;
+};
+AdamArgs adam_args(float *P, float *m, float *v, float lr, int step);
+// Backward pass, weight gradients and Adam.  The rows (whole scenes) are
+// split over at most 256 workgroups, each writing its partial sums into part;
+// two passes then add them in a fixed order (runs of consecutive workgroups,
+// then the runs) into grad (every entry written).  part holds
+// mlp_part_rows(n) rows of RR_MLP_PARAMS floats.
 int64_t mlp_part_rows(int64_t n);
 hipError_t launch_mlp_backward(const float *P, const float *dz, int64_t n, const __half *acts,
-                               float *d1, float *d2, float *d3, const float *codes, float *part,
-                               float *grad, hipStream_t s);
-hipError_t launch_adam(float *P, const float *G, float *m, float *v, float lr, int step, hipStream_t s);
+                               const float *codes, float *part, float *grad, const AdamArgs &adam,
+                               hipStream_t s);
 hipError_t launch_build_cdf(const float *z, float beta, float power, float kappa, double *cdf,
                             hipStream_t s);
 hipError_t launch_batch_trace(const TraceArgs *scenes, const int64_t *chunk_start, int S, int stack,
