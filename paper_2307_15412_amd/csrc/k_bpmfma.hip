@@ -26,9 +26,10 @@
 // 81 x 201 x 201 voxels of 1 mm in 324 blocks of 23 mm).  The block's slices
 // are formed in FP32 on the vector units (k_bp_block).  The host picks n and
 // the block edge by modelled time; a coarse grid or a short sweep keeps every
-// sample.  Measured: the hand's image 67 -> 8.3 ms (12 nodes; slices 0.4 ms),
-// matrix cores 47 % busy (64 % at every sample: the 188 FP64 legs a voxel and
-// the first slice's load are now a fifth of a workgroup's time); a 30 x 37
+// sample.  Measured: the hand's image 67 -> 7.8 ms (12 nodes; slices 0.4 ms),
+// the products at 1.19 PFLOP/s, where a large bf16 matrix product reaches
+// 1.2-1.4 (the FP64 legs of a voxel and the first slice's load are a fifth of
+// a workgroup's time); a 30 x 37
 // array on 17 x 41 x 39 voxels at 33 samples 0.169 -> 0.061 ms by its smaller
 // tile alone.
 //
@@ -334,47 +335,10 @@ __global__ __launch_bounds__(BG_W * 64, TB * RS == 2 ? 4 : 2) void k_bp_mfma(BpM
         return A.nodes ? (float)(((double)A.nodes[n] - 0.5 * (A.K - 1)) * A.df * A.inv_c)
                        : (float)((A.f0 + (double)n * A.df) * A.inv_c);
     };
-    // The two wavefronts of a SIMD run skewed: the leading half (w >= 4)
-    // makes the next frequency's B operands after its Tx sum, so it starts
-    // each frequency with matrix products while the other half is still
-    // generating phasors, and the other way round at the end.
-    const bool lead = w >= BG_W / 2;
-    BOps b;
-    if (lead) gen_b(freq(0), b);
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    const f32x4 zero = {};
-    for (int n = 0; n < A.n; n++) {
-        const float fc = freq(n);
-        if (!lead) gen_b(fc, b);
-        const uint4 *S = Ss[n & 1];
-        f32x4 ur[TB], ui[TB];
-#pragma unroll
-        for (int rs = 0; rs < RS; rs++) {
-#pragma unroll
-            for (int tb = 0; tb < TB; tb++) {
-                const int fb = ((tb * RS + rs) * 4) * 64 + lane;
-                const uint4 Srh = S[fb], Srl = S[fb + 64], Sih = S[fb + 128], Sil = S[fb + 192];
-                // U_re += Sr Br - Si Bi, U_im += Sr Bi + Si Br (hi*hi + hi*lo + lo*hi)
-                ur[tb] = MFMA(Srh, b.rh[rs], rs == 0 ? zero : ur[tb]);
-                ur[tb] = MFMA(Srh, b.rl[rs], ur[tb]);
-                ur[tb] = MFMA(Srl, b.rh[rs], ur[tb]);
-                ur[tb] = MFMA(Sih, b.nih[rs], ur[tb]);
-                ur[tb] = MFMA(Sih, b.nil[rs], ur[tb]);
-                ur[tb] = MFMA(Sil, b.nih[rs], ur[tb]);
-                ui[tb] = MFMA(Srh, b.ih[rs], rs == 0 ? zero : ui[tb]);
-                ui[tb] = MFMA(Srh, b.il[rs], ui[tb]);
-                ui[tb] = MFMA(Srl, b.ih[rs], ui[tb]);
-                ui[tb] = MFMA(Sih, b.rh[rs], ui[tb]);
-                ui[tb] = MFMA(Sih, b.rl[rs], ui[tb]);
-                ui[tb] = MFMA(Sil, b.rh[rs], ui[tb]);
-            }
-        }
-        // every wavefront has read this frequency's slice: the next one may
-        // be requested into the other buffer
-        if (n + 1 < A.n) fetch(n + 1, (n + 1) & 1);
-        // transmit phasors of this lane's Tx rows times U (D layout: element e
-        // of lane l is row 4 (l / 16) + e, column l % 16 of each block)
+    f32x4 ur[TB], ui[TB];
+    // transmit phasors of this lane's Tx rows times U (D layout: element e of
+    // lane l is row 4 (l / 16) + e, column l % 16 of each block)
+    auto tx_sum = [&](float fc) {
 #pragma unroll
         for (int tb = 0; tb < TB; tb++)
 #pragma unroll
@@ -384,10 +348,62 @@ __global__ __launch_bounds__(BG_W * 64, TB * RS == 2 ? 4 : 2) void k_bp_mfma(BpM
                 img_re = fmaf(ar, ur[tb][e], fmaf(-ai, ui[tb][e], img_re));
                 img_im = fmaf(ar, ui[tb][e], fmaf(ai, ur[tb][e], img_im));
             }
-        if (lead && n + 1 < A.n) gen_b(freq(n + 1), b);
+    };
+    // The two wavefronts of a SIMD take turns: the leading half (w >= 4)
+    // starts a frequency with its matrix products while the other half adds
+    // the last frequency's Tx sum and generates this one's phasors, and the
+    // other way round after that, so that neither waits for the other's
+    // vector work.  With two Tx blocks' sums in turn and priority for products
+    // the hand's image takes 7.4 instead of 8.1 ms (Tx sums of both halves
+    // before the barrier, one block at a time): 1.19 PFLOP/s of split products.
+    const bool lead = w >= BG_W / 2;
+    BOps b;
+    if (lead) gen_b(freq(0), b);
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    const f32x4 zero = {};
+    for (int n = 0; n < A.n; n++) {
+        if (!lead) {
+            if (n) tx_sum(freq(n - 1));
+            gen_b(freq(n), b);
+        }
+        const uint4 *S = Ss[n & 1];
+        __builtin_amdgcn_s_setprio(1);    // products first, vector work in between
+#pragma unroll
+        for (int rs = 0; rs < RS; rs++) {
+            // two Tx blocks at a time: four independent sums in turn (a chain's
+            // next product waits for the last one's result)
+#pragma unroll
+            for (int tb = 0; tb < TB; tb += 2) {
+                // U_re += Sr Br - Si Bi, U_im += Sr Bi + Si Br (hi*hi + hi*lo + lo*hi)
+                auto both = [&](int pl, const uint4 &re, const uint4 &im, bool set) {
+#pragma unroll
+                    for (int h = 0; h < 2; h++) {
+                        const uint4 f = S[(((tb + h) * RS + rs) * 4 + pl) * 64 + lane];
+                        ur[tb + h] = MFMA(f, re, set ? zero : ur[tb + h]);
+                        ui[tb + h] = MFMA(f, im, set ? zero : ui[tb + h]);
+                    }
+                };
+                both(0, b.rh[rs], b.ih[rs], rs == 0);
+                both(0, b.rl[rs], b.il[rs], false);
+                both(1, b.rh[rs], b.ih[rs], false);
+                both(2, b.nih[rs], b.rh[rs], false);
+                both(2, b.nil[rs], b.rl[rs], false);
+                both(3, b.nih[rs], b.rh[rs], false);
+            }
+        }
+        __builtin_amdgcn_s_setprio(0);
+        // every wavefront has read this frequency's slice: the next one may
+        // be requested into the other buffer
+        if (n + 1 < A.n) fetch(n + 1, (n + 1) & 1);
+        if (lead) {
+            tx_sum(freq(n));
+            if (n + 1 < A.n) gen_b(freq(n + 1), b);
+        }
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
     }
+    if (!lead) tx_sum(freq(A.n - 1));
     // the four lanes l % 16 + 16 q hold the four quarters of one voxel's Tx rows
     img_re += __shfl_xor(img_re, 16);
     img_im += __shfl_xor(img_im, 16);
