@@ -599,24 +599,16 @@ __global__ __launch_bounds__(RR_TRACE_BLOCK) void k_points(TraceArgs A)
     if (g < A.n_src * (int64_t)A.npts) trace_point(A, g, lds_stack + threadIdx.x);
 }
 
-// Batched, persistent: the launched rays and the point reflectors of every
-// scene are cut into chunks of one workgroup; workgroups pull chunk indices
-// from a device counter until the queue is empty.  chunk_start[s] is the
-// first chunk of scene s (S + 1 entries); scene s's rays come before its
-// point reflectors.
+// Batched: the launched rays and the point reflectors of every scene are cut
+// into chunks of one workgroup.  chunk_start[s] is the first chunk of scene s
+// (S + 1 entries); scene s's rays come before its point reflectors, in their
+// coherent order where the scene has one (8 scenes of 3e5 rays: 349 us and
+// 61 for the orders; 690 without).
 __global__ __launch_bounds__(RR_TRACE_BLOCK, RR_TRACE_WAVES) void k_batch_trace(const TraceArgs *scenes,
-                                                                const int64_t *chunk_start, int S,
-                                                                unsigned long long *work)
+                                                                const int64_t *chunk_start, int S)
 {
     extern __shared__ int lds_stack[];
-    __shared__ long long s_chunk;
-    const int64_t n_chunks = chunk_start[S];
-    while (true) {
-        __syncthreads();
-        if (threadIdx.x == 0) s_chunk = (long long)atomicAdd(work, 1ull);
-        __syncthreads();
-        const int64_t ch = s_chunk;
-        if (ch >= n_chunks) break;
+    for (int64_t ch = blockIdx.x; ch < chunk_start[S]; ch += gridDim.x) {
         int lo = 0, hi = S - 1;
         while (lo < hi) {
             const int mid = (lo + hi + 1) / 2;
@@ -628,7 +620,8 @@ __global__ __launch_bounds__(RR_TRACE_BLOCK, RR_TRACE_WAVES) void k_batch_trace(
         const int64_t ray_chunks = (n_traced + RR_TRACE_BLOCK - 1) / RR_TRACE_BLOCK;
         if (c < ray_chunks) {
             const int64_t g = c * RR_TRACE_BLOCK + threadIdx.x;
-            if (g < n_traced) trace_ray<false>(A, g, lds_stack + threadIdx.x);
+            if (g < n_traced)
+                trace_ray<false>(A, A.order ? (int64_t)A.order[g] : g, lds_stack + threadIdx.x);
         } else {
             const int64_t g = (c - ray_chunks) * RR_TRACE_BLOCK + threadIdx.x;
             if (g < A.n_src * (int64_t)A.npts) trace_point(A, g, lds_stack + threadIdx.x);
@@ -876,50 +869,40 @@ __device__ __forceinline__ unsigned ray_cell(const TraceArgs &A, int64_t t, int6
     return spread_bits(ca) | (spread_bits(cs) << 1);
 }
 
-// workgroup blockIdx.x: chunk c of source t, rays [lo, hi)
-__device__ __forceinline__ void order_chunk(const TraceArgs &A, int64_t chunk, int64_t &t,
-                                            int64_t &lo, int64_t &hi)
-{
-    const int64_t per = (A.n_per_src + chunk - 1) / chunk;
-    t = blockIdx.x / per;
-    lo = (int64_t)(blockIdx.x - t * per) * chunk;
-    hi = min(lo + chunk, A.n_per_src);
-}
-
 #define RR_ORDER_T 512
 #define RR_ORDER_MAXBITS 7
-static_assert(RR_ORDER_T == 512 && RR_ORDER_MAXBITS <= 7, "cell counts must fit 64 KiB of LDS, cell and rank 32 bits");
+static_assert(RR_ORDER_T == 512 && RR_ORDER_MAXBITS <= 7,
+              "cell counts must fit 64 KiB of LDS, cell and rank 32 bits");
 
-// ray_cells[ray] = its cell and its rank among its chunk's rays of that cell
-// (cell below 2^14, rank below the chunk's 2^16 rays); first[chunk][cell] =
-// the chunk's first place within the cell
-__global__ __launch_bounds__(RR_ORDER_T) void k_order_count(TraceArgs A, int bits, int64_t chunk,
-                                                            unsigned *ray_cells, unsigned *cnt,
-                                                            unsigned *first)
+// Chunk ch (of 2^shift rays of one source): ray_cells[ray] = its cell and its
+// rank among the chunk's rays of that cell (cell below 2^14, rank below the
+// chunk's 2^16 rays); first[chunk][cell] = the chunk's first place within the
+// cell.
+__device__ __forceinline__ void order_count(const TraceArgs &A, const OrderTab &O, unsigned ch,
+                                            unsigned *hist)
 {
-    extern __shared__ unsigned hist[];
-    const int nb = 1 << (2 * bits);
-    int64_t t, lo, hi;
-    order_chunk(A, chunk, t, lo, hi);
+    const int nb = 1 << (2 * O.bits);
+    const int64_t t = ch / O.per, lo = (int64_t)(ch - t * O.per) << O.shift;
+    const int64_t hi = min(lo + ((int64_t)1 << O.shift), A.n_per_src);
     for (int b = threadIdx.x; b < nb; b += RR_ORDER_T) hist[b] = 0u;
     __syncthreads();
     for (int64_t i = lo + threadIdx.x; i < hi; i += RR_ORDER_T) {
-        const unsigned c = ray_cell(A, t, i, bits);
-        ray_cells[t * A.n_per_src + i] = c | (atomicAdd(&hist[c], 1u) << (2 * RR_ORDER_MAXBITS));
+        const unsigned c = ray_cell(A, t, i, O.bits);
+        O.ray_cells[t * A.n_per_src + i] = c | (atomicAdd(&hist[c], 1u) << (2 * RR_ORDER_MAXBITS));
     }
     __syncthreads();
-    first += (int64_t)blockIdx.x * nb;
+    unsigned *first = O.first + ((int64_t)ch << (2 * O.bits));
     for (int b = threadIdx.x; b < nb; b += RR_ORDER_T)
-        if (hist[b]) first[b] = atomicAdd(cnt + t * nb + b, hist[b]);
+        if (hist[b]) first[b] = atomicAdd(O.cells + t * nb + b, hist[b]);
 }
 
-// exclusive scan in place of source blockIdx.x's nb cell counts, offset by
-// the source's first position (every source has n_per_src rays): one
-// workgroup of 1024 threads a source, each over a contiguous run
-__global__ __launch_bounds__(1024) void k_order_scan(unsigned *cells, int64_t nb, int64_t n_per_src)
+// exclusive scan in place of source t's nb cell counts, offset by the
+// source's first position (every source has n_per_src rays): one workgroup of
+// 1024 threads, each over a contiguous run
+__device__ __forceinline__ void order_scan(const OrderTab &O, int64_t t, int64_t n_per_src, unsigned *part)
 {
-    __shared__ unsigned part[1024];
-    unsigned *c = cells + (int64_t)blockIdx.x * nb;
+    const int64_t nb = (int64_t)1 << (2 * O.bits);
+    unsigned *c = O.cells + t * nb;
     const int tid = threadIdx.x;
     const int64_t per = (nb + 1023) / 1024;
     const int64_t lo = min(nb, (int64_t)tid * per), hi = min(nb, lo + per);
@@ -933,7 +916,7 @@ __global__ __launch_bounds__(1024) void k_order_scan(unsigned *cells, int64_t nb
         part[tid] += v;
         __syncthreads();
     }
-    unsigned run = (unsigned)((int64_t)blockIdx.x * n_per_src) + (tid ? part[tid - 1] : 0u);
+    unsigned run = (unsigned)(t * n_per_src) + (tid ? part[tid - 1] : 0u);
     for (int64_t k = lo; k < hi; k++) {
         const unsigned x = c[k];
         c[k] = run;
@@ -941,29 +924,80 @@ __global__ __launch_bounds__(1024) void k_order_scan(unsigned *cells, int64_t nb
     }
 }
 
-// order[] from every ray's cell, chunk (of 2^shift rays) and rank:
-// independent rays, so the places wait on nothing but their own loads.  The
-// workgroups of a chunk run on one XCD (workgroups go round the 8 XCDs in
-// turn), whose L2 then joins the chunk's neighbours in a cell before they are
-// written back (1e7 rays: 73 us, with
-// a chunk's workgroups on all XCDs 107).
-__global__ __launch_bounds__(RR_ORDER_T) void k_order_place(unsigned n_per_src, unsigned chunks,
-                                                            unsigned per, int bits, int shift,
-                                                            const unsigned *ray_cells,
-                                                            const unsigned *start,
-                                                            const unsigned *first, int32_t *order)
+// order[] from the ray's cell, chunk and rank: independent rays, so the
+// places wait on nothing but their own loads
+__device__ __forceinline__ void order_place(const OrderTab &O, unsigned n_per_src, unsigned ch,
+                                            unsigned in_chunk)
 {
-    const unsigned parts = 1u << (shift - 9);
-    const unsigned group = blockIdx.x / (8 * parts), in = blockIdx.x - group * 8 * parts;
-    const unsigned ch = group * 8 + (in & 7);
-    if (ch >= chunks) return;
-    const unsigned t = ch / per, i = ((ch - t * per) << shift) + (in >> 3) * RR_ORDER_T + threadIdx.x;
+    const unsigned t = ch / O.per, i = ((ch - t * O.per) << O.shift) + in_chunk;
     if (i >= n_per_src) return;
     const unsigned ray = t * n_per_src + i;
-    const unsigned w = ray_cells[ray];
+    const unsigned w = O.ray_cells[ray];
     const unsigned c = w & ((1u << (2 * RR_ORDER_MAXBITS)) - 1u);
-    order[start[(t << (2 * bits)) + c] + first[((int64_t)ch << (2 * bits)) + c] +
-          (w >> (2 * RR_ORDER_MAXBITS))] = (int32_t)ray;
+    O.order[O.cells[(t << (2 * O.bits)) + c] + O.first[((int64_t)ch << (2 * O.bits)) + c] +
+            (w >> (2 * RR_ORDER_MAXBITS))] = (int32_t)ray;
+}
+
+__global__ __launch_bounds__(RR_ORDER_T) void k_order_count(TraceArgs A, OrderTab O)
+{
+    extern __shared__ unsigned hist[];
+    order_count(A, O, blockIdx.x, hist);
+}
+
+__global__ __launch_bounds__(1024) void k_order_scan(OrderTab O, int64_t n_per_src)
+{
+    __shared__ unsigned part[1024];
+    order_scan(O, blockIdx.x, n_per_src, part);
+}
+
+// The workgroups of a chunk run on one XCD (workgroups go round the 8 XCDs in
+// turn), whose L2 then joins the chunk's neighbours in a cell before they are
+// written back (1e7 rays: 73 us, with a chunk's workgroups on all XCDs 107).
+__global__ __launch_bounds__(RR_ORDER_T) void k_order_place(OrderTab O, unsigned n_per_src, unsigned chunks)
+{
+    const unsigned parts = 1u << (O.shift - 9);
+    const unsigned group = blockIdx.x / (8 * parts), in = blockIdx.x - group * 8 * parts;
+    const unsigned ch = group * 8 + (in & 7);
+    if (ch < chunks) order_place(O, n_per_src, ch, (in >> 3) * RR_ORDER_T + threadIdx.x);
+}
+
+// the same for every scene of a batch: tabs[s].chunk0 and .src0 are scene s's
+// first chunk and source (a scene in ray order has none); a workgroup a chunk
+// or source
+template <class Key>
+__device__ __forceinline__ int order_scene(const OrderTab *tabs, int S, int64_t k, Key key)
+{
+    int lo = 0, hi = S - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) / 2;
+        if (key(tabs[mid]) <= k) lo = mid; else hi = mid - 1;
+    }
+    return lo;
+}
+
+__global__ __launch_bounds__(RR_ORDER_T) void k_batch_order_count(const TraceArgs *scenes,
+                                                                  const OrderTab *tabs, int S)
+{
+    extern __shared__ unsigned hist[];
+    const int s = order_scene(tabs, S, blockIdx.x, [](const OrderTab &O) { return O.chunk0; });
+    order_count(scenes[s], tabs[s], (unsigned)(blockIdx.x - tabs[s].chunk0), hist);
+}
+
+__global__ __launch_bounds__(1024) void k_batch_order_scan(const TraceArgs *scenes, const OrderTab *tabs,
+                                                           int S)
+{
+    __shared__ unsigned part[1024];
+    const int s = order_scene(tabs, S, blockIdx.x, [](const OrderTab &O) { return O.src0; });
+    order_scan(tabs[s], blockIdx.x - tabs[s].src0, scenes[s].n_per_src, part);
+}
+
+__global__ __launch_bounds__(RR_ORDER_T) void k_batch_order_place(const TraceArgs *scenes,
+                                                                  const OrderTab *tabs, int S)
+{
+    const int s = order_scene(tabs, S, blockIdx.x, [](const OrderTab &O) { return O.chunk0; });
+    const OrderTab &O = tabs[s];
+    for (unsigned i = threadIdx.x; i < 1u << O.shift; i += RR_ORDER_T)
+        order_place(O, (unsigned)scenes[s].n_per_src, (unsigned)(blockIdx.x - O.chunk0), i);
 }
 
 }  // namespace
@@ -983,7 +1017,6 @@ hipError_t launch_set_alpha(float4 *ltris, int64_t n_tris, const float *tri_alph
 // found ~200 best for 8e5 and 4e6 rays per source), at most 128 x 128 (the
 // LDS counts of a workgroup, 64 KiB; cell numbers fit 16 bits)
 #define RR_ORDER_CELL 128
-static int order_shift(int bits) { return std::max(2 * bits + 2, 9); }
 int trace_order_bits(int64_t n_per_src)
 {
     int bits = 0;
@@ -992,29 +1025,38 @@ int trace_order_bits(int64_t n_per_src)
 }
 
 // chunks of one source's rays: four rays a cell, at least a workgroup's
-int64_t trace_order_chunks(int64_t n_src, int64_t n_per_src, int bits)
+OrderTab trace_order_tab(int64_t n_per_src)
 {
-    const int64_t chunk = (int64_t)1 << order_shift(bits);
-    return n_src * ((n_per_src + chunk - 1) / chunk);
+    OrderTab O{};
+    O.bits = trace_order_bits(n_per_src);
+    O.shift = std::max(2 * O.bits + 2, 9);
+    O.per = (unsigned)((n_per_src + ((int64_t)1 << O.shift) - 1) >> O.shift);
+    return O;
 }
 
-hipError_t launch_trace_order(const TraceArgs &a, int64_t n_traced, int bits, unsigned *cells,
-                              unsigned *ray_cells, unsigned *first, int32_t *order, hipStream_t s)
+hipError_t launch_trace_order(const TraceArgs &a, int64_t n_traced, const OrderTab &O, hipStream_t s)
 {
     if (n_traced <= 0) return hipSuccess;
-    if (bits > RR_ORDER_MAXBITS || n_traced != a.n_src * a.n_per_src || n_traced >= ((int64_t)1 << 31))
+    if (O.bits > RR_ORDER_MAXBITS || n_traced != a.n_src * a.n_per_src || n_traced >= ((int64_t)1 << 31))
         return hipErrorInvalidValue;
-    const int64_t nb = (int64_t)1 << (2 * bits);
-    const int shift = order_shift(bits);
-    const int64_t chunk = (int64_t)1 << shift;
-    const int64_t blocks = trace_order_chunks(a.n_src, a.n_per_src, bits);
-    const size_t lds = (size_t)nb * 4;
-    hipLaunchKernelGGL(k_order_count, dim3((unsigned)blocks), dim3(RR_ORDER_T), lds, s, a, bits, chunk,
-                       ray_cells, cells, first);
-    hipLaunchKernelGGL(k_order_scan, dim3((unsigned)a.n_src), dim3(1024), 0, s, cells, nb, a.n_per_src);
-    hipLaunchKernelGGL(k_order_place, dim3((unsigned)((((blocks + 7) & ~(int64_t)7) * chunk) / RR_ORDER_T)),
-                       dim3(RR_ORDER_T), 0, s, (unsigned)a.n_per_src, (unsigned)blocks,
-                       (unsigned)(blocks / a.n_src), bits, shift, ray_cells, cells, first, order);
+    const int64_t chunks = a.n_src * O.per;
+    hipLaunchKernelGGL(k_order_count, dim3((unsigned)chunks), dim3(RR_ORDER_T), (size_t)4 << (2 * O.bits),
+                       s, a, O);
+    hipLaunchKernelGGL(k_order_scan, dim3((unsigned)a.n_src), dim3(1024), 0, s, O, a.n_per_src);
+    hipLaunchKernelGGL(k_order_place, dim3((unsigned)(((chunks + 7) & ~(int64_t)7) << (O.shift - 9))),
+                       dim3(RR_ORDER_T), 0, s, O, (unsigned)a.n_per_src, (unsigned)chunks);
+    return hipGetLastError();
+}
+
+hipError_t launch_batch_order(const TraceArgs *scenes, const OrderTab *tabs, int S, int64_t chunks,
+                              int64_t sources, int bits, hipStream_t s)
+{
+    if (chunks <= 0) return hipSuccess;
+    if (bits > RR_ORDER_MAXBITS) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_batch_order_count, dim3((unsigned)chunks), dim3(RR_ORDER_T),
+                       (size_t)4 << (2 * bits), s, scenes, tabs, S);
+    hipLaunchKernelGGL(k_batch_order_scan, dim3((unsigned)sources), dim3(1024), 0, s, scenes, tabs, S);
+    hipLaunchKernelGGL(k_batch_order_place, dim3((unsigned)chunks), dim3(RR_ORDER_T), 0, s, scenes, tabs, S);
     return hipGetLastError();
 }
 
@@ -1071,16 +1113,13 @@ hipError_t launch_points(const TraceArgs &a, hipStream_t s)
 }
 
 hipError_t launch_batch_trace(const TraceArgs *scenes, const int64_t *chunk_start, int S, int stack,
-                              int64_t n_chunks, unsigned long long *work, hipStream_t s)
+                              int64_t n_chunks, hipStream_t s)
 {
-    int dev = 0, cus = 256;
-    (void)hipGetDevice(&dev);
-    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    const int64_t grid = std::min<int64_t>(n_chunks, (int64_t)cus * 16);
-    if (grid <= 0) return hipSuccess;
+    if (n_chunks <= 0) return hipSuccess;
     const size_t lds = (size_t)(stack + 1) * RR_TRACE_BLOCK * sizeof(int);
+    const int64_t grid = std::min<int64_t>(n_chunks, 1 << 24);   // below 2^32 threads
     hipLaunchKernelGGL(k_batch_trace, dim3((unsigned)grid), dim3(RR_TRACE_BLOCK), lds, s, scenes,
-                       chunk_start, S, work);
+                       chunk_start, S);
     return hipGetLastError();
 }
 

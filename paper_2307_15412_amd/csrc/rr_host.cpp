@@ -264,6 +264,12 @@ namespace {
 // deepest tree, and five wavefronts fit a SIMD (street, depth 19: 4.5 before).
 int trace_stack(int depth) { return std::min(RR_STACK, depth + 1); }
 
+// rays of a source from which their coherent order pays
+bool order_pays(int64_t n_per_src, int64_t n_traced)
+{
+    return n_per_src >= 4096 && n_traced < ((int64_t)1 << 31);
+}
+
 // The trace stage of rr_trace / rr_trace_rays: tracing kernels, scan of the
 // per-ray counts, scatter into (ray, bounce) order; grows the temporary
 // buffer and re-runs once if it overflowed.
@@ -815,16 +821,20 @@ static int trace_impl(rr_ctx *c, const rr_trace_params *tp, int64_t *n_paths_out
     if ((rc = c->tmp.alloc(c->tmp_cap))) return rc;
     // uniform and proposal launches trace their rays in a coherent order
     // (sorted by source and first-direction cell; results do not depend on it)
-    const bool coherent = !tri_g && n_per_src >= 4096 && n_traced < ((int64_t)1 << 31);
-    const int obits = coherent ? trace_order_bits(n_per_src) : 0;
-    const int64_t n_cells = coherent ? n_src << (2 * obits) : 0;
+    const bool coherent = !tri_g && order_pays(n_per_src, n_traced);
+    OrderTab O{};
+    int64_t n_cells = 0;
     if (coherent) {
+        O = trace_order_tab(n_per_src);
+        n_cells = n_src << (2 * O.bits);
         if ((rc = c->order_idx.ensure((size_t)n_traced * 4))) return rc;
         if ((rc = c->order_rc.ensure((size_t)n_traced * 4))) return rc;
         if ((rc = c->order_cells.ensure((size_t)n_cells * 4))) return rc;
-        if ((rc = c->order_first.ensure(
-                 (size_t)(trace_order_chunks(n_src, n_per_src, obits) << (2 * obits)) * 4)))
-            return rc;
+        if ((rc = c->order_first.ensure((size_t)(n_cells * O.per) * 4))) return rc;
+        O.cells = c->order_cells.as<unsigned>();
+        O.ray_cells = c->order_rc.as<unsigned>();
+        O.first = c->order_first.as<unsigned>();
+        O.order = c->order_idx.as<int32_t>();
     }
 
     TraceArgs A{};
@@ -875,9 +885,7 @@ static int trace_impl(rr_ctx *c, const rr_trace_params *tp, int64_t *n_paths_out
         hipError_t e = hipSuccess;
         TraceArgs b = a;
         if (coherent) {
-            e = launch_trace_order(a, n_traced, obits, c->order_cells.as<unsigned>(),
-                                   c->order_rc.as<unsigned>(), c->order_first.as<unsigned>(),
-                                   c->order_idx.as<int32_t>(), c->stream);
+            e = launch_trace_order(a, n_traced, O, c->stream);
             b.order = c->order_idx.as<const int32_t>();
         }
         if (e == hipSuccess && stats) {
@@ -2066,6 +2074,7 @@ struct BatchScene {
     bool set = false;
     int64_t n_tris = 0;
     int bvh_depth = 0;
+    bool ordered = false;     // its rays are traced in their coherent order
     int nobj = 0, npts = 0, ntx = 0, nrx = 0, mode = 0;
     double rx_radius = 0.25, oT[3] = {0, 0, 0}, oR[3] = {0, 0, 0};
     double box[12];                       // bounds of the Tx, then of the Rx elements
@@ -2109,6 +2118,10 @@ struct rr_batch {
     hipEvent_t ev[6] = {};
     DevBuf d_targs, d_sargs, d_info, d_chunk, d_items, d_vr, d_vel, d_rinfo, d_ranges, d_items_rest, d_items0, rest_pre, rest_sums;
     int stack = 0;            // the deepest scene's
+    // coherent orders of the scenes' rays
+    DevBuf d_order, order_cells, order_rc, order_first, order_idx;
+    int64_t n_order_chunks = 0, n_order_src = 0, n_order_cells = 0;
+    int order_bits = 0;
     DevBuf counts, bsums, total, counter, work;
     PathStore tmp, fin;
     DevBuf syn, alpha_tmp;
@@ -2203,6 +2216,9 @@ int batch_prepare(rr_batch *b, int only_K = 0, int64_t p_limit = 0, int only_sce
     std::vector<BatchRangeInfo> ri(S);
     std::vector<int64_t> chunk(S + 1, 0), items(S + 1, 0), vr(S + 1, 0);
     std::vector<int64_t> items_rest(S + 1, 0), items0(S + 1, 0);
+    std::vector<OrderTab> tabs(S);
+    int64_t o_chunks = 0, o_src = 0, o_cells = 0, o_first = 0, o_rays = 0;
+    b->order_bits = 0;
     b->range_base.assign(S + 1, 0);
     b->synth_on.assign(S, 0);
     int64_t V = 0, est = 0;
@@ -2220,6 +2236,20 @@ int batch_prepare(rr_batch *b, int only_K = 0, int64_t p_limit = 0, int only_sce
         const int64_t rchunks = (x.n_src * x.n_per_src + RR_TRACE_BLOCK - 1) / RR_TRACE_BLOCK;
         const int64_t pchunks = (x.n_src * x.npts + RR_TRACE_BLOCK - 1) / RR_TRACE_BLOCK;
         chunk[s + 1] = chunk[s] + rchunks + pchunks;
+        const int64_t n_traced = x.n_src * x.n_per_src;
+        x.ordered = order_pays(x.n_per_src, n_traced);
+        if (x.ordered) tabs[s] = trace_order_tab(x.n_per_src);
+        tabs[s].chunk0 = o_chunks;
+        tabs[s].src0 = o_src;
+        if (x.ordered) {
+            const int64_t cells = x.n_src << (2 * tabs[s].bits);
+            o_chunks += x.n_src * tabs[s].per;
+            o_src += x.n_src;
+            o_cells += cells;
+            o_first += cells * tabs[s].per;
+            o_rays += n_traced;
+            b->order_bits = std::max(b->order_bits, tabs[s].bits);
+        }
         const int K = x.chirp.n_samples, M = x.chirp.n_chirps;
         if (x.kr <= 0) x.kr = largest_kr(K, RR_BATCH_MAX_KR);
         if (x.kr <= 0) return fail(RR_EUNSUPPORTED, "scene %d: n_samples too large", s);
@@ -2251,8 +2281,34 @@ int batch_prepare(rr_batch *b, int only_K = 0, int64_t p_limit = 0, int only_sce
     b->n_items0 = items0[S];
     b->n_ranges = b->range_base[S];
     b->nb = scan_u8_blocks(V);
+    b->n_order_chunks = o_chunks;
+    b->n_order_src = o_src;
+    b->n_order_cells = o_cells;
     int rc;
     if ((rc = b->counts.ensure((size_t)V + 64))) return rc;
+    if ((rc = b->d_order.ensure(sizeof(OrderTab) * S))) return rc;
+    if (o_chunks > 0) {
+        if ((rc = b->order_cells.ensure((size_t)o_cells * 4))) return rc;
+        if ((rc = b->order_first.ensure((size_t)o_first * 4))) return rc;
+        if ((rc = b->order_rc.ensure((size_t)o_rays * 4))) return rc;
+        if ((rc = b->order_idx.ensure((size_t)o_rays * 4))) return rc;
+        unsigned *cells = b->order_cells.as<unsigned>(), *first = b->order_first.as<unsigned>();
+        unsigned *ray_cells = b->order_rc.as<unsigned>();
+        int32_t *order = b->order_idx.as<int32_t>();
+        for (int s = 0; s < S; s++) {
+            const BatchScene &x = b->sc[s];
+            if (!x.ordered) continue;
+            const int64_t nc = x.n_src << (2 * tabs[s].bits);
+            tabs[s].cells = cells;
+            tabs[s].first = first;
+            tabs[s].ray_cells = ray_cells;
+            tabs[s].order = order;
+            cells += nc;
+            first += nc * tabs[s].per;
+            ray_cells += x.n_src * x.n_per_src;
+            order += x.n_src * x.n_per_src;
+        }
+    }
     if ((rc = b->bsums.ensure((size_t)(b->nb + 4) * 4))) return rc;
     if ((rc = b->total.ensure(256))) return rc;
     if ((rc = b->counter.ensure(256))) return rc;
@@ -2317,6 +2373,7 @@ int batch_prepare(rr_batch *b, int only_K = 0, int64_t p_limit = 0, int only_sce
         A.seed = x.tp.seed;
         A.sampler = RR_UNIFORM;
         A.vbase = vr[s];
+        A.order = tabs[s].order;
         A.hits = nullptr;
         A.counts = b->counts.as<uint8_t>();
         A.tmp = b->tmp.soa;
@@ -2362,6 +2419,7 @@ int batch_prepare(rr_batch *b, int only_K = 0, int64_t p_limit = 0, int only_sce
     b->h_sargs = sa;
     hipStream_t st = b->st;
     HIPCHK(hipMemcpyAsync(b->d_targs.p, ta.data(), sizeof(TraceArgs) * S, hipMemcpyHostToDevice, st));
+    HIPCHK(hipMemcpyAsync(b->d_order.p, tabs.data(), sizeof(OrderTab) * S, hipMemcpyHostToDevice, st));
     HIPCHK(hipMemcpyAsync(b->d_sargs.p, sa.data(), sizeof(SynthArgs) * S, hipMemcpyHostToDevice, st));
     HIPCHK(hipMemcpyAsync(b->d_info.p, info.data(), sizeof(BatchSynthInfo) * S, hipMemcpyHostToDevice, st));
     HIPCHK(hipMemcpyAsync(b->d_vel.p, vel.data(), sizeof(BatchVel) * S, hipMemcpyHostToDevice, st));
@@ -2375,18 +2433,18 @@ int batch_prepare(rr_batch *b, int only_K = 0, int64_t p_limit = 0, int only_sce
     return RR_OK;
 }
 
-// the trace stage: zero the queue and path counters (kernel fills, no
-// memset nodes), persistent trace, scan, scatter, synthesis records, ranges
+// the trace stage: counts, counters and cells zeroed (by a kernel: no memset
+// nodes), ray orders, trace, scan, scatter, synthesis records, ranges
 int batch_enqueue_trace(rr_batch *b, bool timed)
 {
     hipStream_t st = b->st;
-    unsigned long long *work = b->work.as<unsigned long long>();
-    HIPCHK(launch_fill_u64(work, 2, 0ull, st));
+    const TraceArgs *ta = b->d_targs.as<const TraceArgs>();
     if (timed) HIPCHK(hipEventRecord(b->ev[0], st));
     HIPCHK(launch_trace_clear(b->counts.as<uint8_t>(), b->V_total, b->counter.as<unsigned long long>(),
-                              nullptr, nullptr, 0, st));
-    HIPCHK(launch_batch_trace(b->d_targs.as<const TraceArgs>(), b->d_chunk.as<const int64_t>(), b->S,
-                              b->stack, b->n_chunks, work, st));
+                              nullptr, b->order_cells.as<unsigned>(), b->n_order_cells, st));
+    HIPCHK(launch_batch_order(ta, b->d_order.as<const OrderTab>(), b->S, b->n_order_chunks,
+                              b->n_order_src, b->order_bits, st));
+    HIPCHK(launch_batch_trace(ta, b->d_chunk.as<const int64_t>(), b->S, b->stack, b->n_chunks, st));
     HIPCHK(launch_scan_u8(b->counts.as<const uint8_t>(), b->V_total, b->bsums.as<uint32_t>(),
                           b->nb + 1, b->total.as<unsigned long long>(), nullptr, nullptr, nullptr, st));
     HIPCHK(launch_scatter(b->tmp.soa, b->counter.as<const unsigned long long>(), b->cap,
@@ -2499,7 +2557,8 @@ void rr_batch_destroy(rr_batch *b)
     DevBuf *bufs[] = {&b->d_targs, &b->d_sargs, &b->d_info, &b->d_chunk, &b->d_items, &b->d_vr,
                       &b->d_vel, &b->d_rinfo, &b->d_ranges, &b->counts, &b->bsums,
                       &b->total, &b->counter, &b->work, &b->syn, &b->alpha_tmp, &b->tmp.buf,
-                      &b->fin.buf, &b->d_items_rest, &b->d_items0, &b->rest_pre, &b->rest_sums};
+                      &b->fin.buf, &b->d_order, &b->order_cells, &b->order_rc, &b->order_first, &b->order_idx,
+                      &b->d_items_rest, &b->d_items0, &b->rest_pre, &b->rest_sums};
     for (DevBuf *x : bufs) x->release();
     b->fq.release();
     for (auto &e : b->ev)

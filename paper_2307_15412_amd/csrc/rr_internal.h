@@ -208,14 +208,23 @@ struct BatchRangeInfo {
 
 // launchers (defined in the .hip files)
 hipError_t launch_trace(const TraceArgs &a, int64_t n_traced, hipStream_t s);
-// coherent ray order of a uniform or proposal launch: rays sorted by source
-// and the 2^bits x 2^bits cell of their first direction (cells: n_src 4^bits
-// counters, zero before; ray_cells: n_traced cells and ranks; first: 4^bits
-// places per chunk, trace_order_chunks of them; order: n_traced ray indices)
-int trace_order_bits(int64_t n_per_src);
-int64_t trace_order_chunks(int64_t n_src, int64_t n_per_src, int bits);
-hipError_t launch_trace_order(const TraceArgs &a, int64_t n_traced, int bits, unsigned *cells,
-                              unsigned *ray_cells, unsigned *first, int32_t *order, hipStream_t s);
+// Coherent ray order of a uniform or proposal launch: rays sorted by source
+// and the 2^bits x 2^bits cell of their first direction, in chunks of 2^shift
+// rays of one source, per of them a source.
+struct OrderTab {
+    int bits, shift;
+    unsigned per;
+    int64_t chunk0, src0;     // batch: the scene's first chunk and source
+    unsigned *cells;          // n_src 4^bits counters, zero before
+    unsigned *ray_cells;      // n_traced cells and ranks
+    unsigned *first;          // n_src per 4^bits places
+    int32_t *order;           // n_traced ray indices
+};
+OrderTab trace_order_tab(int64_t n_per_src);
+hipError_t launch_trace_order(const TraceArgs &a, int64_t n_traced, const OrderTab &O, hipStream_t s);
+// every scene's at once: chunks and sources in total, bits of the largest
+hipError_t launch_batch_order(const TraceArgs *scenes, const OrderTab *tabs, int S, int64_t chunks,
+                              int64_t sources, int bits, hipStream_t s);
 hipError_t launch_points(const TraceArgs &a, hipStream_t s);
 // k_trace plus exact work counters: stats[0] BVH nodes fetched, stats[1] leaf
 // triangle records fetched, stats[2] closest-hit queries (summed, not cleared)
@@ -447,7 +456,7 @@ hipError_t launch_mlp_backward(const float *P, const float *dz, int64_t n, const
 hipError_t launch_build_cdf(const float *z, float beta, float power, float kappa, double *cdf,
                             hipStream_t s);
 hipError_t launch_batch_trace(const TraceArgs *scenes, const int64_t *chunk_start, int S, int stack,
-                              int64_t n_chunks, unsigned long long *work, hipStream_t s);
+                              int64_t n_chunks, hipStream_t s);
 // stage 0: paths at rest into chirp 0 (items: channels), 1: the other chirps,
 // 2: moving paths into chirp 0
 hipError_t launch_batch_synth(int stage, const SynthArgs *scenes, const BatchSynthInfo *info,
