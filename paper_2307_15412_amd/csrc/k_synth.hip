@@ -591,12 +591,18 @@ __global__ __launch_bounds__(PREP_T) void k_batch_prep(PathSoA P, const unsigned
 
 // per-scene path ranges from the batched exclusive scan: paths of virtual
 // rays [vr0 + t n_vps, ...) start at the prefix of vr0 + t n_vps; then those of
-// the two parts of the records
+// the two parts of the records.  host (pinned): records appended, paths, and
+// the groups' starts in the path list.
 __global__ void k_batch_ranges(const uint8_t *counts, const uint32_t *bsums, int64_t V,
-                               const unsigned long long *total, int64_t cap, const BatchRangeInfo *ri, int S, const uint32_t *pre,
-                               int64_t *rest, int64_t *mov)
+                               const unsigned long long *total, const unsigned long long *counter,
+                               int64_t cap, const BatchRangeInfo *ri, int S, const uint32_t *pre,
+                               int64_t *rest, int64_t *mov, int64_t *host)
 {
     const int s = blockIdx.x * blockDim.x + threadIdx.x;
+    if (s == 0) {
+        host[0] = (int64_t)*counter;
+        host[1] = (int64_t)*total;
+    }
     if (s >= S) return;
     const BatchRangeInfo &R = ri[s];
     const int64_t tot = min((int64_t)*total, cap);
@@ -605,6 +611,7 @@ __global__ void k_batch_ranges(const uint8_t *counts, const uint32_t *bsums, int
         const int64_t r = pre[o];
         rest[R.base + g] = r;
         mov[R.base + g] = (int64_t)pre[tot] + o - r;
+        host[2 + R.base + g] = o;
     };
     if (R.shared) {
         put(0, R.vr0);
@@ -656,11 +663,12 @@ hipError_t launch_batch_prep(const PathSoA &paths, const unsigned long long *tot
 }
 
 hipError_t launch_batch_ranges(const uint8_t *counts, const uint32_t *bsums, int64_t V,
-                               const unsigned long long *total, int64_t cap, const BatchRangeInfo *ri, int S, const uint32_t *pre,
-                               int64_t *rest, int64_t *mov, hipStream_t s)
+                               const unsigned long long *total, const unsigned long long *counter,
+                               int64_t cap, const BatchRangeInfo *ri, int S, const uint32_t *pre,
+                               int64_t *rest, int64_t *mov, int64_t *host, hipStream_t s)
 {
     hipLaunchKernelGGL(k_batch_ranges, dim3((unsigned)((S + 63) / 64)), dim3(64), 0, s, counts, bsums, V,
-                       total, cap, ri, S, pre, rest, mov);
+                       total, counter, cap, ri, S, pre, rest, mov, host);
     return hipGetLastError();
 }
 

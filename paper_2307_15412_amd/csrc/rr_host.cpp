@@ -2093,6 +2093,7 @@ struct BatchScene {
     int tile = 0;                         // exact engine: product tile
     int64_t fq_cap = 0;                   // exact engine: leg table capacity (paths)
     int64_t fq_ppad = 0;                  // exact engine: table stride of the graph
+    int lane = 0;                         // exact engine: its stream and tables
     int64_t n_last = -1;                  // path count of the last launch
     void release()
     {
@@ -2110,6 +2111,11 @@ int largest_kr(int K, int limit)
 
 }  // namespace
 
+// Most lanes of a batch's exact engine, and the leg tables they may hold in
+// all: a scene's ten kernels are too small to fill the chip one at a time
+#define RR_BATCH_LANES 4
+const int64_t BATCH_LANE_TABLES = (int64_t)4 << 30;
+
 struct rr_batch {
     rr_ctx *c = nullptr;
     int S = 0;
@@ -2125,12 +2131,19 @@ struct rr_batch {
     DevBuf counts, bsums, total, counter, work;
     PathStore tmp, fin;
     DevBuf syn, alpha_tmp;
-    FreqBufs fq;                          // exact engine, shared by its scenes
+    // exact engine: its scenes run in lanes, each on its own stream (the
+    // first on st) with its own tables, which serve the lane's scenes in turn
+    FreqBufs fq[RR_BATCH_LANES];
+    hipStream_t side[RR_BATCH_LANES] = {};
+    hipEvent_t fork = nullptr, join[RR_BATCH_LANES] = {};
+    int lanes = 1;
     int64_t cap = 0, V_total = 0, n_chunks = 0, n_ranges = 0, nb = 0;
     int64_t n_items = 0, n_items_rest = 0, n_items0 = 0;   // direct engine's work
     std::vector<char> synth_on;           // scenes the synthesis stage computes
     std::vector<SynthArgs> h_sargs;       // their arguments, as uploaded to d_sargs
     std::vector<int64_t> range_base;
+    int64_t *h_out = nullptr;             // pinned: what a launch tells the host (k_batch_ranges)
+    int64_t h_out_n = 0;
     std::vector<void *> cubes;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -2200,6 +2213,51 @@ FreqPlan batch_freq_plan(const BatchScene &x)
 {
     return FreqPlan{x.ntx, x.nrx, x.chirp.n_chirps, x.chirp.n_samples, x.tile, x.mode != RR_TX_SHARED,
                     x.fq_ppad, x.chirp.n_chirps > 1 ? x.fq_ppad : 0, x.box};
+}
+
+// the exact engine's lanes: each scene in the one with the least product work
+// so far (the direct engine's scenes run ahead of lane 0's), and every lane's
+// tables; one lane where more would not fit
+int batch_lanes(rr_batch *b)
+{
+    int64_t table = 1;
+    int n = 0;
+    for (int s = 0; s < b->S; s++) {
+        const BatchScene &x = b->sc[s];
+        if (!x.use_freq || !b->synth_on[s]) continue;
+        table = std::max(table, batch_freq_bytes(x, x.fq_ppad, x.tile));
+        n++;
+    }
+    b->lanes = (int)std::max<int64_t>(1, std::min<int64_t>({RR_BATCH_LANES, n, BATCH_LANE_TABLES / table}));
+    if (b->lanes > 1 && !b->fork) {
+        HIPCHK(hipEventCreateWithFlags(&b->fork, hipEventDisableTiming));
+        for (int k = 1; k < RR_BATCH_LANES; k++) {
+            HIPCHK(hipStreamCreateWithFlags(&b->side[k], hipStreamNonBlocking));
+            HIPCHK(hipEventCreateWithFlags(&b->join[k], hipEventDisableTiming));
+        }
+    }
+    while (true) {
+        double work[RR_BATCH_LANES] = {};
+        for (int s = 0; s < b->S; s++) {
+            const BatchScene &x = b->sc[s];
+            if (!x.use_freq && b->synth_on[s])
+                work[0] += (double)x.ntx * x.nrx * x.chirp.n_samples;
+        }
+        int rc = RR_OK;
+        for (FreqBufs &f : b->fq)
+            if (f.classes.size() >= 64) f.drop_classes();
+        for (int s = 0; s < b->S && !rc; s++) {
+            BatchScene &x = b->sc[s];
+            if (!x.use_freq || !b->synth_on[s]) continue;
+            x.lane = (int)(std::min_element(work, work + b->lanes) - work);
+            work[x.lane] += (double)x.ntx * x.nrx * x.chirp.n_samples;
+            rc = freq_ensure(b->fq[x.lane], batch_freq_plan(x), b->st);
+        }
+        if (!rc || b->lanes == 1) return rc;
+        (void)hipGetLastError();
+        for (FreqBufs &f : b->fq) f.release();
+        b->lanes = 1;
+    }
 }
 
 // per-scene tables and global buffers for the current scene set and cubes;
@@ -2330,17 +2388,25 @@ int batch_prepare(rr_batch *b, int only_K = 0, int64_t p_limit = 0, int only_sce
     if ((rc = b->d_vr.ensure(8 * (S + 1)))) return rc;
     // the groups' ranges among the paths at rest, then among the moving paths
     if ((rc = b->d_ranges.ensure(16 * (b->n_ranges + 1)))) return rc;
+    if (b->h_out_n < b->n_ranges + 2) {
+        if (b->h_out) (void)hipHostFree(b->h_out);
+        b->h_out = nullptr;
+        b->h_out_n = 0;
+        if (hipHostMalloc((void **)&b->h_out, 8 * (b->n_ranges + 2), hipHostMallocDefault) != hipSuccess) {
+            b->h_out = nullptr;
+            return fail(RR_ENOMEM, "hipHostMalloc(%lld) failed", (long long)(8 * (b->n_ranges + 2)));
+        }
+        b->h_out_n = b->n_ranges + 2;
+    }
     // exact engine: per scene the table stride (capacity, or the timing cap);
     // the last graph is dropped whenever its plan is prepared anew
-    if (b->fq.classes.size() >= 64) b->fq.drop_classes();
-    // one set of tables serves its scenes in turn
     for (int s = 0; s < S; s++) {
         BatchScene &x = b->sc[s];
         if (!x.use_freq || !b->synth_on[s]) continue;
         x.fq_ppad = x.fq_cap;
         if (p_limit > 0) x.fq_ppad = std::min<int64_t>(x.fq_ppad, freq_pad(p_limit));
-        if ((rc = freq_ensure(b->fq, batch_freq_plan(x), b->st))) return rc;
     }
+    if ((rc = batch_lanes(b))) return rc;
     const double INV_2PI = 0.15915494309189535;
     for (int s = 0; s < S; s++) {
         BatchScene &x = b->sc[s];
@@ -2455,10 +2521,11 @@ int batch_enqueue_trace(rr_batch *b, bool timed)
                              b->rest_sums.as<uint32_t>(), b->rest_pre.as<uint32_t>(),
                              b->syn.as<SynPath>(), st));
     HIPCHK(launch_batch_ranges(b->counts.as<const uint8_t>(), b->bsums.as<const uint32_t>(), b->V_total,
-                               b->total.as<const unsigned long long>(), b->cap,
+                               b->total.as<const unsigned long long>(),
+                               b->counter.as<const unsigned long long>(), b->cap,
                                b->d_rinfo.as<const BatchRangeInfo>(), b->S,
                                b->rest_pre.as<const uint32_t>(), b->d_ranges.as<int64_t>(),
-                               b->d_ranges.as<int64_t>() + b->n_ranges, st));
+                               b->d_ranges.as<int64_t>() + b->n_ranges, b->h_out, st));
     if (timed) HIPCHK(hipEventRecord(b->ev[1], st));
     return RR_OK;
 }
@@ -2469,23 +2536,34 @@ int batch_enqueue_synth(rr_batch *b, bool timed)
     unsigned long long *work = b->work.as<unsigned long long>();
     HIPCHK(launch_fill_u64(work + 1, 3, 0ull, st));
     if (timed) HIPCHK(hipEventRecord(b->ev[2], st));
+    if (b->lanes > 1) {
+        HIPCHK(hipEventRecord(b->fork, st));
+        for (int k = 1; k < b->lanes; k++) HIPCHK(hipStreamWaitEvent(b->side[k], b->fork, 0));
+    }
     const DevBuf *items[3] = {&b->d_items_rest, &b->d_items, &b->d_items0};
     const int64_t n_items[3] = {b->n_items_rest, b->n_items, b->n_items0};
     for (int g = 0; g < 3; g++)
         HIPCHK(launch_batch_synth(g, b->d_sargs.as<const SynthArgs>(),
                                   b->d_info.as<const BatchSynthInfo>(),
                                   items[g]->as<const int64_t>(), b->S, n_items[g], work + 1 + g, st));
-    // the exact product engine's scenes, one after the other on the shared
-    // tables; each reads its path ranges from the device
-    for (int s = 0; s < b->S; s++) {
+    // the exact product engine's scenes, each lane's one after the other on
+    // its tables; each reads its path ranges from the device
+    int rc = RR_OK;
+    for (int s = 0; s < b->S && !rc; s++) {
         const BatchScene &x = b->sc[s];
         if (!x.use_freq || !b->synth_on[s]) continue;
         const FreqPlan q = batch_freq_plan(x);
         const SynthArgs &A = b->h_sargs[s];
-        if (int rc = freq_rest(b->fq, q, A, st)) return rc;
-        if (q.M > 1)
-            if (int rc = freq_moving(b->fq, q, A, -1, st)) return rc;
+        const hipStream_t ls = x.lane ? b->side[x.lane] : st;
+        rc = freq_rest(b->fq[x.lane], q, A, ls);
+        if (!rc && q.M > 1) rc = freq_moving(b->fq[x.lane], q, A, -1, ls);
     }
+    // (joined whatever happened: a capture ends with its branches)
+    for (int k = 1; k < b->lanes; k++) {
+        HIPCHK(hipEventRecord(b->join[k], b->side[k]));
+        HIPCHK(hipStreamWaitEvent(st, b->join[k], 0));
+    }
+    if (rc) return rc;
     if (timed) HIPCHK(hipEventRecord(b->ev[3], st));
     return RR_OK;
 }
@@ -2495,20 +2573,17 @@ int batch_enqueue_synth(rr_batch *b, bool timed)
 // re-run (*overflow).  Records each scene's path count.
 int batch_check(rr_batch *b, bool *overflow)
 {
-    unsigned long long cnt = 0, tot = 0;
-    std::vector<int64_t> r(2 * b->n_ranges + 1);
-    HIPCHK(hipMemcpyAsync(&cnt, b->counter.p, 8, hipMemcpyDeviceToHost, b->st));
-    HIPCHK(hipMemcpyAsync(&tot, b->total.p, 8, hipMemcpyDeviceToHost, b->st));
-    HIPCHK(hipMemcpyAsync(r.data(), b->d_ranges.p, 16 * b->n_ranges, hipMemcpyDeviceToHost, b->st));
     HIPCHK(hipStreamSynchronize(b->st));
-    *overflow = (int64_t)cnt > b->cap;
-    if (*overflow) b->cap = (int64_t)cnt + (int64_t)cnt / 4 + 4096;
-    b->last_total = (int64_t)tot;
+    const int64_t cnt = b->h_out[0], tot = b->h_out[1];
+    const int64_t *r = b->h_out + 2;
+    *overflow = cnt > b->cap;
+    if (*overflow) b->cap = cnt + cnt / 4 + 4096;
+    b->last_total = tot;
     if (*overflow) return RR_OK;   // counts are cut short: re-run first
     for (int s = 0; s < b->S; s++) {
         BatchScene &x = b->sc[s];
         const int64_t g0 = b->range_base[s], g1 = b->range_base[s + 1] - 1;
-        const int64_t n = r[g1] - r[g0] + r[b->n_ranges + g1] - r[b->n_ranges + g0];
+        const int64_t n = r[g1] - r[g0];
         x.n_last = n;
         if (x.use_freq && b->synth_on[s] && n > x.fq_ppad) {
             x.fq_cap = n + n / 4 + 1024;
@@ -2560,9 +2635,15 @@ void rr_batch_destroy(rr_batch *b)
                       &b->fin.buf, &b->d_order, &b->order_cells, &b->order_rc, &b->order_first, &b->order_idx,
                       &b->d_items_rest, &b->d_items0, &b->rest_pre, &b->rest_sums};
     for (DevBuf *x : bufs) x->release();
-    b->fq.release();
+    for (FreqBufs &f : b->fq) f.release();
+    if (b->h_out) (void)hipHostFree(b->h_out);
     for (auto &e : b->ev)
         if (e) (void)hipEventDestroy(e);
+    if (b->fork) (void)hipEventDestroy(b->fork);
+    for (int k = 1; k < RR_BATCH_LANES; k++) {
+        if (b->join[k]) (void)hipEventDestroy(b->join[k]);
+        if (b->side[k]) (void)hipStreamDestroy(b->side[k]);
+    }
     if (b->st) (void)hipStreamDestroy(b->st);
     delete b;
 }

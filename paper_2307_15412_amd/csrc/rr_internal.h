@@ -465,8 +465,10 @@ hipError_t launch_batch_synth(int stage, const SynthArgs *scenes, const BatchSyn
 hipError_t launch_batch_prep(const PathSoA &paths, const unsigned long long *total, int64_t cap,
                              const int64_t *vr_start, int S, const BatchVel *vel, uint32_t *bsums,
                              uint32_t *pre, SynPath *out, hipStream_t s);
-// rest / mov: ranges of every scene's groups in the two parts of the records
+// rest / mov: ranges of every scene's groups in the two parts of the records;
+// host (pinned): records appended, paths, the groups' starts in the path list
 hipError_t launch_batch_ranges(const uint8_t *counts, const uint32_t *bsums, int64_t V,
-                               const unsigned long long *total, int64_t cap, const BatchRangeInfo *ri, int S, const uint32_t *pre,
-                               int64_t *rest, int64_t *mov, hipStream_t s);
+                               const unsigned long long *total, const unsigned long long *counter,
+                               int64_t cap, const BatchRangeInfo *ri, int S, const uint32_t *pre,
+                               int64_t *rest, int64_t *mov, int64_t *host, hipStream_t s);
 hipError_t launch_fill_u64(unsigned long long *p, int64_t n, unsigned long long v, hipStream_t s);
