@@ -774,45 +774,66 @@ __global__ void k_scatter(PathSoA tmp, const unsigned long long *counter, int64_
     int64_t n = (int64_t)*counter;
     if (n > tmp_cap) n = tmp_cap;
     if (s >= n) return;
-    const int64_t ray = tmp.ray[s];
-    int64_t d = (int64_t)count_prefix(counts, bsums, ray) + tmp.loc[s];
-    if (d >= keep) return;
     const int64_t sc = tmp.cap, dc = dst.cap;
-    dst.src[d] = tmp.src[s];
-    dst.K[d] = tmp.K[s];
+    const int64_t ray = tmp.ray[s];
+    const int64_t d = (int64_t)count_prefix(counts, bsums, ray) + tmp.loc[s];
+    if (d >= keep) return;
+    // (every load first: behind a store each would wait for the one before)
+    const int src = tmp.src[s], K = tmp.K[s];
+    const double L = tmp.L[s], amp = tmp.amp[s];
+    int tri[RR_KMAX], vid[RR_KMAX];
+    double p[3 * RR_KMAX];
+#pragma unroll
+    for (int q = 0; q < RR_KMAX; q++) {
+        tri[q] = tmp.tri[q * sc + s];
+        vid[q] = tmp.vid[q * sc + s];
+    }
+#pragma unroll
+    for (int q = 0; q < 3 * RR_KMAX; q++) p[q] = tmp.p[q * sc + s];
+    dst.src[d] = src;
+    dst.K[d] = K;
     dst.ray[d] = ray;
 #pragma unroll
     for (int q = 0; q < RR_KMAX; q++) {
-        dst.tri[q * dc + d] = tmp.tri[q * sc + s];
-        dst.vid[q * dc + d] = tmp.vid[q * sc + s];
+        dst.tri[q * dc + d] = tri[q];
+        dst.vid[q * dc + d] = vid[q];
     }
 #pragma unroll
-    for (int q = 0; q < 3 * RR_KMAX; q++) dst.p[q * dc + d] = tmp.p[q * sc + s];
-    dst.L[d] = tmp.L[s];
-    dst.amp[d] = tmp.amp[s];
+    for (int q = 0; q < 3 * RR_KMAX; q++) dst.p[q * dc + d] = p[q];
+    dst.L[d] = L;
+    dst.amp[d] = amp;
 }
 
-// A path list into the caller's planes, one launch instead of a strided copy
-// a plane (2e3 paths: 8 copies of 2 us and their gaps against one of 2-3 us).
+// A path list into the caller's planes, plane blockIdx.y of COPY_PLANES: one
+// launch of independent copies instead of a strided copy a plane (2e3 paths:
+// 8 copies of 2 us and their gaps against one launch of 3 us).
+#define COPY_PLANES (5 + 5 * RR_KMAX)
 __global__ void k_copy_paths(PathSoA src, int64_t n, PathSoA dst)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const int64_t sc = src.cap, dc = dst.cap;
-    if (dst.src) dst.src[i] = src.src[i];
-    if (dst.K) dst.K[i] = src.K[i];
-    if (dst.ray) dst.ray[i] = src.ray[i];
-#pragma unroll
-    for (int q = 0; q < RR_KMAX; q++) {
-        if (dst.tri) dst.tri[q * dc + i] = src.tri[q * sc + i];
-        if (dst.vid) dst.vid[q * dc + i] = src.vid[q * sc + i];
+    int y = blockIdx.y;
+    if (y < 3 * RR_KMAX) {
+        if (dst.p) dst.p[y * dc + i] = src.p[y * sc + i];
+        return;
     }
-    if (dst.p) {
-#pragma unroll
-        for (int q = 0; q < 3 * RR_KMAX; q++) dst.p[q * dc + i] = src.p[q * sc + i];
+    y -= 3 * RR_KMAX;
+    if (y < RR_KMAX) {
+        if (dst.tri) dst.tri[y * dc + i] = src.tri[y * sc + i];
+        return;
     }
-    if (dst.L) dst.L[i] = src.L[i];
-    if (dst.amp) dst.amp[i] = src.amp[i];
+    y -= RR_KMAX;
+    if (y < RR_KMAX) {
+        if (dst.vid) dst.vid[y * dc + i] = src.vid[y * sc + i];
+        return;
+    }
+    y -= RR_KMAX;
+    if (y == 0 && dst.src) dst.src[i] = src.src[i];
+    if (y == 1 && dst.K) dst.K[i] = src.K[i];
+    if (y == 2 && dst.ray) dst.ray[i] = src.ray[i];
+    if (y == 3 && dst.L) dst.L[i] = src.L[i];
+    if (y == 4 && dst.amp) dst.amp[i] = src.amp[i];
 }
 
 // what a trace starts from: every ray's count, the path counter, the error
@@ -1143,7 +1164,8 @@ hipError_t launch_hist(const TraceArgs &a, int64_t n_traced, const int32_t *hits
 hipError_t launch_copy_paths(const PathSoA &src, int64_t n, const PathSoA &dst, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_copy_paths, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, src, n, dst);
+    hipLaunchKernelGGL(k_copy_paths, dim3((unsigned)((n + 255) / 256), COPY_PLANES), dim3(256), 0, s, src, n,
+                       dst);
     return hipGetLastError();
 }
 

@@ -261,13 +261,17 @@ namespace {
 
 // A lane pushes at most one child an inner node on its way to the deepest
 // leaf: stacks of the tree's own depth take less LDS than those of the
-// deepest tree, and five wavefronts fit a SIMD (street, depth 19: 4.5 before).
+// bound of 32, of which 4.5 wavefronts fit a SIMD.
 int trace_stack(int depth) { return std::min(RR_STACK, depth + 1); }
 
-// rays of a source from which their coherent order pays
-bool order_pays(int64_t n_per_src, int64_t n_traced)
+// Rays of a source and of the whole launch (or batch) from which a coherent
+// order pays: below a quarter of a million rays the wavefronts fit the chip
+// about once, where the ones with the most work decide and sorted rays make
+// them worse (1e5 rays, call without and with the order: box scene 123, 137
+// us, hand 202, 251; 3e5: tiny scene 165, 153, street 236, 246; 1e6: 272, 215).
+bool order_pays(int64_t n_per_src, int64_t n_traced, int64_t n_launch)
 {
-    return n_per_src >= 4096 && n_traced < ((int64_t)1 << 31);
+    return n_per_src >= 4096 && n_launch >= 1 << 18 && n_traced < ((int64_t)1 << 31);
 }
 
 // The trace stage of rr_trace / rr_trace_rays: tracing kernels, scan of the
@@ -821,7 +825,7 @@ static int trace_impl(rr_ctx *c, const rr_trace_params *tp, int64_t *n_paths_out
     if ((rc = c->tmp.alloc(c->tmp_cap))) return rc;
     // uniform and proposal launches trace their rays in a coherent order
     // (sorted by source and first-direction cell; results do not depend on it)
-    const bool coherent = !tri_g && order_pays(n_per_src, n_traced);
+    const bool coherent = !tri_g && order_pays(n_per_src, n_traced, n_traced);
     OrderTab O{};
     int64_t n_cells = 0;
     if (coherent) {
@@ -2279,7 +2283,8 @@ int batch_prepare(rr_batch *b, int only_K = 0, int64_t p_limit = 0, int only_sce
     b->order_bits = 0;
     b->range_base.assign(S + 1, 0);
     b->synth_on.assign(S, 0);
-    int64_t V = 0, est = 0;
+    int64_t V = 0, est = 0, n_launch = 0;
+    for (const BatchScene &x : b->sc) n_launch += x.tp.n_rays;
     for (int s = 0; s < S; s++) {
         BatchScene &x = b->sc[s];
         if (!x.set) return fail(RR_ESTATE, "batch slot %d is empty", s);
@@ -2295,7 +2300,7 @@ int batch_prepare(rr_batch *b, int only_K = 0, int64_t p_limit = 0, int only_sce
         const int64_t pchunks = (x.n_src * x.npts + RR_TRACE_BLOCK - 1) / RR_TRACE_BLOCK;
         chunk[s + 1] = chunk[s] + rchunks + pchunks;
         const int64_t n_traced = x.n_src * x.n_per_src;
-        x.ordered = order_pays(x.n_per_src, n_traced);
+        x.ordered = order_pays(x.n_per_src, n_traced, n_launch);
         if (x.ordered) tabs[s] = trace_order_tab(x.n_per_src);
         tabs[s].chunk0 = o_chunks;
         tabs[s].src0 = o_src;

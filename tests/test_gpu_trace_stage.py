@@ -1,5 +1,5 @@
 """Edges of the trace stage: ray counts around the tiles of the path-count
-scan (256 rays), the coherent order's threshold (4096 rays a source) and its
+scan (256 rays), the coherent order's threshold (2^18 rays) and its
 chunks, with and without recorded hits.  Paths must be bitwise the oracle's."""
 import pytest
 
@@ -9,7 +9,7 @@ from helpers import assert_paths_equal, gpu_soa_np, oracle_to_soa
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("per_src", [1, 253, 254, 509, 4095, 4096, 4097, 16385])
+@pytest.mark.parametrize("per_src", [1, 253, 254, 509, 4095, 4096, 87381, 87382, 262144])
 @pytest.mark.parametrize("shared", [False, True])
 def test_scan_and_order_edges(gpu, orc, per_src, shared):
     """Three sources (or one, shared) of per_src rays each and three point
