@@ -8,7 +8,8 @@ cube from them.  Inputs are resident in HBM before the timed region (the
 scene, array and chirp are uploaded once; BVH build excluded).
 
 Prints one JSON line: value = path-samples synthesised per second over the
-whole step (P x C x M x K / step time), plus the tracer's Mrays/s, the cube's
+whole step (P x C x M x K / step time: the terms of the cube's definition,
+however few of them are evaluated one by one), plus the tracer's Mrays/s, the cube's
 relative error against the FP64 oracle on sampled entries, the roofline of
 the dominant kernel and the oracle's own throughput on a bounded sample.
 """
@@ -326,14 +327,17 @@ def run_hand(args, sweep=False):
         ctx.set_alpha(list(w.scene.obj_alpha))
     bp_ms = float(np.mean(bp))
     flops = terms * FLOPS_PER_PATH_SAMPLE
-    # the back-projection runs on the matrix cores (split bf16: three products
-    # per real multiply-add are issued; the roofline counts the algorithmic 8)
-    roof = {"bound": "mfma", "achieved": flops / (bp_ms * 1e-3) / 1e12, "peak": BF16_PEAK_TFLOPS,
-            "unit": "TFLOP/s",
-            "traffic": profiled_traffic("paper_2307_15412_amd/csrc/k_bpmfma.hip",
-                                        "profiles/k_bp_mfma_hand.md"),
-            "kernel": "bp_mfma", "flops_per_launch": flops, "issued_flops_per_launch": 3 * flops}
-    roof["frac"] = roof["achieved"] / roof["peak"]
+    # the back-projection's products run on the matrix cores at interpolation
+    # nodes per block of voxels instead of at every step, so the definition's
+    # 8 flops a term are not what is issued: the roofline divides the profiled
+    # launch's matrix flops (split bf16: three products a real multiply-add)
+    bp_src, bp_sum = "paper_2307_15412_amd/csrc/k_bpmfma.hip", "profiles/k_bp_mfma_hand.md"
+    issued = profiled_traffic(bp_src, bp_sum, "matrix_flops_per_launch")
+    roof = {"bound": "mfma", "achieved": issued / (bp_ms * 1e-3) / 1e12 if issued else None,
+            "peak": BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
+            "traffic": profiled_traffic(bp_src, bp_sum), "kernel": "bp_mfma",
+            "definition_flops": flops, "issued_flops_per_launch": issued}
+    roof["frac"] = roof["achieved"] / roof["peak"] if issued else None
 
     cube_rel = img_rel = cpu = None
     if not args.no_check or not args.no_cpu_baseline:
@@ -625,16 +629,16 @@ def street_trace(ctx, scene, args, reps=None):
         raise SystemExit(f"counting trace returned {n2} paths, the timed trace {n}")
     st, kt = float(np.median(stage)), float(np.median(kern))
     alg = work["nodes"] * 64 + work["tris"] * 48 + work["rays"] + n * TRACE_RECORD_BYTES
-    ach = alg / (kt * 1e-3) / 1e9
+    traffic = profiled_traffic("paper_2307_15412_amd/csrc/k_trace.hip", "profiles/k_trace_street.md")
+    ach = traffic / (kt * 1e-3) / 1e9 if traffic is not None else None
     roof = {"bound": "hbm", "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-            "frac": ach / HBM_PEAK_GBS, "kernel": "k_trace",
-            "traffic": profiled_traffic("paper_2307_15412_amd/csrc/k_trace.hip",
-                                        "profiles/k_trace_street.md"),
-            "algorithmic_bytes": alg,
-            "note": "algorithmic bytes count every lane's node and triangle fetch; the rays of a "
-                    "wavefront are traced in a coherent order and share those fetches, and the "
-                    "30 MB BVH stays in L2/MALL, so they can exceed what HBM delivers (the kernel "
-                    "is bound by the latency of dependent node fetches, not by HBM)"}
+            "frac": ach / HBM_PEAK_GBS if ach is not None else None, "kernel": "k_trace",
+            "traffic": traffic, "lane_fetch_bytes": alg,
+            "lane_fetch_gb_per_s": alg / (kt * 1e-3) / 1e9,
+            "note": "achieved: the HBM bytes of the profiled launch over this run's time; "
+                    "lane_fetch_bytes counts every lane's node and triangle fetch, which a "
+                    "coherent wavefront's lanes share and L2/MALL serve.  The kernel is bound by "
+                    "vector issue and the latency of dependent node fetches, not by HBM"}
     # the configuration's cube (exact model, FP32 bar): AUTO's engine (the
     # product engine's per-element sample split) and the direct engine; a
     # path of the per-element launch feeds its own transmitter's 16 channels
@@ -667,9 +671,10 @@ def run_street_trace(args):
     print(json.dumps(street_trace(ctx, None, args, reps=args.steps)))
 
 
-def profiled_traffic(kernel_src: str, summary: str):
-    """HBM bytes per launch recorded in a committed rocprofv3 summary, if that
-    summary was taken on the current source of the kernel (else None)."""
+def profiled_traffic(kernel_src: str, summary: str, key: str = "traffic_bytes_per_launch"):
+    """HBM bytes per launch (or another count, by its key) recorded in a
+    committed rocprofv3 summary, if that summary was taken on the current
+    source of the kernel (else None)."""
     import hashlib
     try:
         src = open(os.path.join(ROOT, kernel_src), "rb").read()
@@ -683,9 +688,21 @@ def profiled_traffic(kernel_src: str, summary: str):
         if ":" in line:
             k, v = line.split(":", 1)
             vals[k.strip()] = v.strip()
-    if vals.get("kernel_source_sha256_16") != sha or "traffic_bytes_per_launch" not in vals:
+    if vals.get("kernel_source_sha256_16") != sha or key not in vals:
         return None
-    return float(vals["traffic_bytes_per_launch"])
+    return float(vals[key])
+
+
+def moving_paths(ctx, scene):
+    """Paths of the context with a hit on an object or point of non-zero
+    velocity: the only ones whose sum differs from chirp to chirp."""
+    p = ctx.paths()
+    vid, K = p["vid"].cpu().numpy(), p["K"].cpu().numpy()
+    vel = np.vstack([np.asarray(scene.obj_vel, float).reshape(-1, 3),
+                     np.asarray(scene.pt_vel, float).reshape(-1, 3)])
+    moves = np.append(np.any(vel != 0.0, axis=1), False)
+    hit = np.arange(vid.shape[0])[:, None] < K[None, :]
+    return int(np.any(moves[np.where(hit, vid, -1)], axis=0).sum())
 
 
 def cpu_model():
@@ -773,8 +790,11 @@ def main():
     tr = float(np.mean(trace_ms))
     sy = float(np.mean(synth_ms))
     eng_name = "gemm_bf16x3" if engine == rr.GEMM_BF16X3 else "direct_fp32"
+    n_mov = moving_paths(ctx, w.scene)
     if sy >= tr:
-        kern_flops = path_samples * FLOPS_PER_PATH_SAMPLE
+        # what the cube cannot do without: a path at rest adds the same to
+        # every chirp (one chirp's multiply-adds), a moving one to each its own
+        kern_flops = (float(P - n_mov) + float(n_mov) * M) * C * K * FLOPS_PER_PATH_SAMPLE
         ach = kern_flops / (sy * 1e-3) / 1e12
         if engine == rr.GEMM_BF16X3:
             roof = {"bound": "mfma", "achieved": ach, "peak": BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
@@ -786,6 +806,11 @@ def main():
                                                 "profiles/k_synth_direct_large_mimo.md")}
         roof["kernel"] = "synth_" + eng_name
         roof["flops_per_launch"] = kern_flops
+        roof["moving_paths"] = n_mov
+        roof["cube_bytes"] = float(C) * M * K * 8
+        roof["cube_gb_per_s"] = roof["cube_bytes"] / (sy * 1e-3) / 1e9
+        roof["note"] = ("flops: paths at rest once, moving paths per chirp; time: the whole "
+                        "synthesis stage (legs, products at rest and moving, cube)")
     else:
         # tracer bytes per segment are counted by the profile; report the rate only
         roof = {"bound": "hbm", "achieved": None, "peak": HBM_PEAK_GBS, "unit": "GB/s",

@@ -315,7 +315,10 @@ int rr_set_paths(rr_ctx *ctx, const rr_paths *src, int64_t n);
  *          (paths x Rx) product per (chirp, sample) in square tiles of 16,
  *          32, 48, 64 or 96, or, per (channel, chirp), one (k1 x paths) by
  *          (paths x k2) product over the samples k = k1 S + k2 (at most 1024
- *          samples); the layout of least modelled time), or
+ *          samples); the layout of least modelled time; in the tile layouts
+ *          the paths at rest are taken in bands of path length and summed at
+ *          8 to 32 nodes a band, from which the samples are interpolated to
+ *          2e-7, where a band has paths enough), or
  *          RR_ENGINE_AUTO: the separable model takes RR_GEMM_BF16X3 when the
  *          64-sample tiling pads a chirp by at most a quarter; the exact model
  *          takes RR_GEMM_EXACT when its best layout is modelled at 1.5x
@@ -488,7 +491,9 @@ int rr_batch_set_alpha(rr_batch *batch, int32_t slot, const float *alpha, int64_
 /* Run the batch: cubes[s] is scene s's complex64 [n_ch][n_chirps][n_samples]
  * device buffer.  The first launch (or the first after a change) captures the
  * pipeline as a hipGraph; later launches replay it (new cube pointers update
- * a device table, or re-capture when a scene uses the product engine).  The
+ * a device table, or re-capture when a scene uses the product engine).
+ * Scenes on the product engine run in up to four lanes, each with tables of
+ * its own (4 GiB in all; one lane beyond that).  The
  * call waits for completion and checks the path pool and the product
  * engine's leg-table capacity of every scene using it (sized from the
  * previous launch's count, else from the ray budget), growing them and
@@ -571,7 +576,7 @@ int rr_max_projection(rr_ctx *ctx, const void *image_dev, const rr_volume *vol, 
 /* Kernel timing of the last rr_trace / rr_synthesize / rr_backproject call,
  * in milliseconds, measured with HIP events on the context stream
  * (synchronises).  which: 0 = trace (all trace kernels, scan and scatter
- * included), 1 = synthesis main kernel, 2 = back-projection, 3 = the tracing
+ * included), 1 = synthesis (after the records: all its kernels), 2 = back-projection, 3 = the tracing
  * kernels of the last trace alone (the coherent ray order, rays and point
  * reflectors, before the scan). */
 int rr_last_kernel_ms(rr_ctx *ctx, int32_t which, double *ms_out);

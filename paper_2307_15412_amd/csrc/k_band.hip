@@ -12,7 +12,7 @@
 // 154 m), so the Tx x Rx products of the product engine run over 12-24 nodes
 // instead of 128-512 samples.  What is left is the expansion, 2 n + 4 FP32
 // multiply-adds per channel, sample and band, and the cube itself.  Measured:
-// the hand's cube (94 x 94 channels, 128 samples, 5.0e5 paths) 13.9 -> 2.6 ms,
+// the hand's cube (94 x 94 channels, 128 samples, 5.0e5 paths) 13.9 -> 2.1 ms,
 // of it the products 2.0 (14.4 at every sample), leg tables 0.25; the resting
 // paths of the large-MIMO cube 5.4 -> 0.4 ms.  The products' vector work (two
 // hardware sin/cos per phasor) still bounds them, as at every sample.

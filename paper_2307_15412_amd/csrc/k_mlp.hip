@@ -249,10 +249,10 @@ __global__ __launch_bounds__(1024) void k_softmax_grad(const float *z, const flo
 // the workgroups' rows of the partial table by two more passes: the gradient
 // is the same bits on every run.
 // One wavefront a SIMD (its sums alone take 128 registers); bound by the 256
-// MFMAs of 64 cycles a tile, 27 us for 131 072 rows at that rate: 65 us,
-// the LDS turns between them and the workgroup's ends being the rest,
-// where a backward kernel that wrote d1-d3 (98) and a kernel a layer that
-// read them again (4 x 34) were bound by those 200 MB and short of wavefronts.
+// MFMAs of 64 cycles a tile, which take 27 us for 131 072 rows, and by the LDS
+// turns between them that one wavefront cannot hide: 65 us.  A backward kernel
+// that wrote d1-d3 (98 us) and one kernel a layer that read them again (4 x 34)
+// were bound by those 200 MB and short of wavefronts.
 #define GR_RS (NH + 1)            // row stride of a gradient tile (floats)
 #define GR_HS (NH + 8)            // of an activation tile (halves)
 #define GR_WGS 256                // most workgroups, one a compute unit

@@ -182,8 +182,9 @@ __device__ void synth_block(const SynthArgs &A, int g, int rb, int rows_per_grou
 // lanes take the same samples of every (REST_T / TPR)-th path, so that a few
 // channels of many paths still fill a compute unit's lanes (the tiny scene's
 // 4 channels of 2 400 paths and 16 chirps: 20 us here and 2 x 9 us for the
-// moving part, against 1.47 ms for the sum of all paths chirp by chirp), and the lanes' sums are added in a fixed order: across the
-// wavefront, then over the wavefronts through LDS.
+// moving part, against 1.47 ms for the sum of all paths chirp by chirp), and
+// the lanes' sums are added in a fixed order: across the wavefront, then over
+// the wavefronts through LDS.
 #define REST_T 512
 struct RestLds {
     uint2 tab[REST_T];        // (beta, gamma) of the chunk's paths
@@ -504,8 +505,8 @@ __device__ __forceinline__ void rest_rank(bool rest, const uint32_t *bsums, int6
 }
 
 // Record i into its place.  The whole record is loaded before the ranks are
-// known, and whether it rests is read from it: loaded after them,
-// behind two more rounds of loads, the hand's 4.96e5 records took 59 instead of 48 us.
+// known, and whether it rests is read from it: loaded after them, behind two
+// more rounds of loads, the hand's 4.96e5 records took 59 instead of 48 us.
 __device__ __forceinline__ void place_record(const PathSoA &P, int64_t i, int64_t n, const BatchVel &bv,
                                              const uint32_t *bsums, int64_t nb, uint32_t *pre,
                                              SynPath *out)

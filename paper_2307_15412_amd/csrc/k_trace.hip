@@ -524,12 +524,14 @@ __device__ __forceinline__ void trace_point(const TraceArgs &A, int64_t g, int *
 }
 
 // Tracing kernels ask for five wavefronts per SIMD (at most 96 VGPRs): the
-// traversal is bound by its own instructions and by the latency of dependent
-// node fetches, and a fifth wavefront hides more of that than the ~10
-// registers the compiler then keeps in scratch memory cost (street, 1e7 rays,
-// 3 bounces, with its ordering: 1.60 against 1.73 ms with four; six spill 35
-// and take 1.74).  The
-// stacks leave room for five: a lane's has the tree's depth, not the bound's.
+// traversal is bound by its own instructions (81 % of the SIMDs' issue cycles
+// on the street's 1e7 rays, nearly half of them Philox products) and by the
+// latency of dependent node fetches, and a fifth wavefront hides more of that
+// than the 4 registers the compiler then keeps in scratch memory cost (street,
+// 1e7 rays, 3 bounces, with its ordering: 1.60 against 1.73 ms with four; six
+// spill 35 and take 1.74).  The stacks leave room for five: a lane's has the
+// tree's depth, not the bound's.  Before the branch-free steps, the 128-bit
+// products and the hit records in scratch the kernel took 1.66 ms alone, now 1.15.
 #define RR_TRACE_WAVES 5
 
 // lane g traces ray order[g] when a coherent order is given, else ray g
