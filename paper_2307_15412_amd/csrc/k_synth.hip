@@ -267,14 +267,20 @@ __device__ void rest_block(const SynthArgs &A, int c, int TPR, RestLds &L)
     }
 }
 
-// samples of a channel over the lanes: at most 16 a lane, and as few as the
-// power of two of lanes allows (the samples beyond K are padding)
+// Samples of a channel over the lanes (those beyond K are padding).  A lane's
+// run is never longer than the moving paths' (the largest power of two that
+// divides K, here at most 16): every rotation of a run adds its rounding, and
+// 195 samples in runs of 13 were 4.3e-7 off the FP64 sum of 64 paths, in runs
+// of one 1.6e-7.
 __device__ __forceinline__ void rest_tile(const SynthArgs &A, int c, RestLds &L)
 {
+    const int run = min(A.K & -A.K, 16);
     int TPR = 1;
-    while (TPR * 16 < A.K && TPR < REST_T) TPR <<= 1;
+    while (TPR * run < A.K && TPR < REST_T) TPR <<= 1;
     const int kr = (A.K + TPR - 1) / TPR;
-    if (kr <= 4) rest_block<4>(A, c, TPR, L);
+    if (kr <= 1) rest_block<1>(A, c, TPR, L);
+    else if (kr <= 2) rest_block<2>(A, c, TPR, L);
+    else if (kr <= 4) rest_block<4>(A, c, TPR, L);
     else if (kr <= 8) rest_block<8>(A, c, TPR, L);
     else if (kr <= 12) rest_block<12>(A, c, TPR, L);
     else rest_block<16>(A, c, TPR, L);

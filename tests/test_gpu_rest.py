@@ -87,3 +87,25 @@ def test_batch_equals_single(gpu, mode, n_tx, n_rx, K, M, speed):
         ref = gpu.synthesize(model=rr.EXACT, engine=engine)
         assert torch.equal(cubes[0], ref), engine
         B.close()
+
+
+@pytest.mark.parametrize("K", [1, 24, 54, 135, 195, 208])
+def test_rest_as_exact_as_moving(gpu, orc, K):
+    """The direct engine's chirp 0, the same paths at rest and moving (which
+    are at the same place there): one run length of the rotations, so the same
+    phasors; the resting sum adds them over the lanes, whose roundings are
+    fewer than those of one lane's chain (a quarter more error is allowed for
+    their chance)."""
+    import paper_2307_15412_amd as rr
+    w = _workload("shared", 3, 4, K, 2)
+    _, op = orc.trace(w.scene, w.array, w.trace, want_hits=False)
+    op = op[np.sort(np.random.default_rng(4).choice(len(op), 200, replace=False))]
+    err = []
+    for which in ("none", "all"):
+        rec = _moving(op, which)
+        gpu.setup(w)
+        gpu.set_paths({k: torch.from_numpy(np.ascontiguousarray(v)) for k, v in oracle_to_soa(rec).items()})
+        got = gpu.synthesize(model=rr.EXACT, engine=rr.DIRECT_FP32).cpu().numpy()[:, 0]
+        ref = orc.synth(rec, w.scene, w.array, w.chirp, model=0)[:, 0]
+        err.append(np.linalg.norm(got - ref) / np.linalg.norm(ref))
+    assert err[0] < 1.25 * err[1] < 1e-5, err
