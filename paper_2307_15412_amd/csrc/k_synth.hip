@@ -177,28 +177,28 @@ __device__ void synth_block(const SynthArgs &A, int g, int rb, int rows_per_grou
     }
 }
 
-// Chirp 0 of channel c: the sum over the paths at rest of its group, by one
-// workgroup.  TPR lanes (a power of two) cover the samples, KR each; the other
-// lanes take the same samples of every (REST_T / TPR)-th path, so that a few
+// Chirp 0 of channel c: the sum over the paths at rest of its group, a part of
+// its samples by one workgroup (rest_shape).  TPR lanes (a power of two) cover
+// the part's samples, KR each; the other lanes take the same samples of every (REST_T / TPR)-th path, so that a few
 // channels of many paths still fill a compute unit's lanes (the tiny scene's
 // 4 channels of 2 400 paths and 16 chirps: 20 us here and 2 x 9 us for the
 // moving part, against 1.47 ms for the sum of all paths chirp by chirp), and
 // the lanes' sums are added in a fixed order: across the wavefront, then over
 // the wavefronts through LDS.
-#define REST_T 512
 struct RestLds {
     uint2 tab[REST_T];        // (beta, gamma) of the chunk's paths
     float amp[REST_T];
     float2 red[REST_T * 8];   // partial sums, eight samples a lane at a time
 };
 template <int KR>
-__device__ void rest_block(const SynthArgs &A, int c, int TPR, RestLds &L)
+__device__ void rest_block(const SynthArgs &A, int c, int part, int TPR, RestLds &L)
 {
     const int tid = threadIdx.x;
     const int t = c / A.nrx, r = c - t * A.nrx;
     const int g = A.shared ? 0 : t;
     const int pos = tid & (TPR - 1), sub = tid / TPR, G = REST_T / TPR;
-    const unsigned k0 = (unsigned)(pos * KR);
+    const int kp = part * TPR * KR;       // the part's first sample
+    const unsigned k0 = (unsigned)(kp + pos * KR);
     const double f0c = A.f0 * A.inv_c;
     const double bkc = A.bw / (double)A.K * A.inv_c;
     const double tx[3] = {A.tx[3 * t], A.tx[3 * t + 1], A.tx[3 * t + 2]};
@@ -254,7 +254,7 @@ __device__ void rest_block(const SynthArgs &A, int c, int TPR, RestLds &L)
             if (lane < TPR && k >= h && k < h + 8) L.red[(w * 64 + lane) * 8 + k - h] = make_float2(are[k], aim[k]);
         __syncthreads();
         for (int o = tid; o < TPR * 8; o += REST_T) {
-            const int ps = o >> 3, kk = h + (o & 7), k = ps * KR + kk;
+            const int ps = o >> 3, kk = h + (o & 7), k = kp + ps * KR + kk;
             if (kk >= KR || k >= A.K) continue;
             float2 v = make_float2(0.0f, 0.0f);
             for (int j = 0; j < np; j++) {
@@ -267,23 +267,19 @@ __device__ void rest_block(const SynthArgs &A, int c, int TPR, RestLds &L)
     }
 }
 
-// Samples of a channel over the lanes (those beyond K are padding).  A lane's
-// run is never longer than the moving paths' (the largest power of two that
-// divides K, here at most 16): every rotation of a run adds its rounding, and
-// 195 samples in runs of 13 were 4.3e-7 off the FP64 sum of 64 paths, in runs
-// of one 1.6e-7.
-__device__ __forceinline__ void rest_tile(const SynthArgs &A, int c, RestLds &L)
+// item: the parts of channel 0, of channel 1, ...
+__device__ __forceinline__ void rest_tile(const SynthArgs &A, int item, RestLds &L)
 {
-    const int run = min(A.K & -A.K, 16);
-    int TPR = 1;
-    while (TPR * run < A.K && TPR < REST_T) TPR <<= 1;
-    const int kr = (A.K + TPR - 1) / TPR;
-    if (kr <= 1) rest_block<1>(A, c, TPR, L);
-    else if (kr <= 2) rest_block<2>(A, c, TPR, L);
-    else if (kr <= 4) rest_block<4>(A, c, TPR, L);
-    else if (kr <= 8) rest_block<8>(A, c, TPR, L);
-    else if (kr <= 12) rest_block<12>(A, c, TPR, L);
-    else rest_block<16>(A, c, TPR, L);
+    const RestShape s = rest_shape(A.K, A.ntx * A.nrx);
+    const int c = item / s.parts, part = item - c * s.parts;
+    switch (s.kr) {
+    case 1: rest_block<1>(A, c, part, s.lanes, L); break;
+    case 2: rest_block<2>(A, c, part, s.lanes, L); break;
+    case 4: rest_block<4>(A, c, part, s.lanes, L); break;
+    case 8: rest_block<8>(A, c, part, s.lanes, L); break;
+    case 12: rest_block<12>(A, c, part, s.lanes, L); break;
+    default: rest_block<16>(A, c, part, s.lanes, L); break;
+    }
 }
 
 __global__ __launch_bounds__(REST_T) void k_synth_rest(SynthArgs A)
@@ -752,7 +748,7 @@ hipError_t launch_synth_direct(const SynthArgs &a, int n_groups, int rows_per_gr
     int kr = 32;
     while (kr > 1 && a.K % kr != 0) kr >>= 1;
     if (a.K / kr > SYN_T) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_synth_rest, dim3((unsigned)(a.ntx * a.nrx)), dim3(REST_T), 0, s, a);
+    hipLaunchKernelGGL(k_synth_rest, dim3((unsigned)rest_items(a.K, a.ntx * a.nrx)), dim3(REST_T), 0, s, a);
     if (a.M <= 1) return hipGetLastError();
     for (int m0 = 1; m0 >= 0; m0--) {
         const int rows = m0 ? rows_per_group - RC : RC;

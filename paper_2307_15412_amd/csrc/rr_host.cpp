@@ -2329,7 +2329,7 @@ int batch_prepare(rr_batch *b, int only_K = 0, int64_t p_limit = 0, int only_sce
         const bool synth = (only_K <= 0 || K == only_K) && (only_scene < 0 || s == only_scene);
         b->synth_on[s] = synth;
         const bool direct = synth && !x.use_freq;
-        items_rest[s + 1] = items_rest[s] + (direct ? (int64_t)x.ntx * x.nrx : 0);
+        items_rest[s + 1] = items_rest[s] + (direct ? rest_items(K, x.ntx * x.nrx) : 0);
         items[s + 1] = items[s] + (direct ? (int64_t)info[s].bpg * n_groups : 0);
         items0[s + 1] = items0[s] + (direct ? (int64_t)info[s].bpg0 * n_groups : 0);
         b->range_base[s + 1] = b->range_base[s] + (shared ? 2 : n_groups + 1);

@@ -184,6 +184,37 @@ struct BackProjArgs {
 #define RR_BATCH_MAX_KR 32
 #endif
 
+// The direct engine's sum over the paths at rest: `parts` workgroups of
+// `lanes` x `kr` samples a channel (the last may be short).  A lane's run is
+// never longer than the moving paths' (the largest power of two that divides
+// K, here at most 16): every rotation of a run adds its rounding, and 195
+// samples in runs of 13 were 4.3e-7 off the FP64 sum of 64 paths, in runs of
+// one 1.3e-7.  The short runs of such counts take many lanes a channel; few
+// channels then give their samples to several workgroups, up to one a compute
+// unit (56 channels x 51 samples, 2.6e5 paths: 3.18 -> 1.87 ms; 4 x 87 and a
+// trace of 2.9e5 rays 272 -> 185 us).  Each part forms the paths' lengths
+// again, so it keeps 16 lanes of work beside them: with one lane of 16 samples
+// a part, 64 x 4 took as long as undivided, and the rest stage of a batch of
+// eight streets, whose channels fill the chip, 137 instead of 68 us.
+#define REST_T 512
+struct RestShape {
+    int kr, lanes, parts;
+};
+static __host__ __device__ inline RestShape rest_shape(int K, int C)
+{
+    RestShape s;
+    const int run = (K & -K) < 16 ? K & -K : 16;
+    s.lanes = 1;
+    while (s.lanes * run < K && s.lanes < REST_T) s.lanes <<= 1;
+    const int kr = (K + s.lanes - 1) / s.lanes;
+    s.kr = kr <= 2 ? kr : kr <= 4 ? 4 : (kr + 3) / 4 * 4;
+    auto parts = [&] { return (K + s.lanes * s.kr - 1) / (s.lanes * s.kr); };
+    while (s.lanes > 16 && (int64_t)C * parts() < 256) s.lanes >>= 1;
+    s.parts = parts();
+    return s;
+}
+inline int64_t rest_items(int K, int C) { return (int64_t)C * rest_shape(K, C).parts; }
+
 // batched launch: per-scene tables read by the persistent kernels
 struct BatchSynthInfo {
     int kr;                   // samples per lane (tile shape)

@@ -109,3 +109,25 @@ def test_rest_as_exact_as_moving(gpu, orc, K):
         ref = orc.synth(rec, w.scene, w.array, w.chirp, model=0)[:, 0]
         err.append(np.linalg.norm(got - ref) / np.linalg.norm(ref))
     assert err[0] < 1.25 * err[1] < 1e-5, err
+
+
+@pytest.mark.parametrize("mode,n_tx,n_rx,K", [("shared", 1, 1, 256), ("per_tx", 1, 4, 87), ("shared", 2, 2, 17),
+                                              ("shared", 7, 8, 51), ("per_tx", 3, 85, 33), ("per_tx", 4, 64, 64)])
+def test_rest_over_workgroups(gpu, orc, mode, n_tx, n_rx, K):
+    """Samples of a channel over several workgroups, the last one short: few
+    channels, as many as the compute units less one and as many; a batch slot
+    equals the single-scene launch bit for bit.  Bar: the direct engine's."""
+    import paper_2307_15412_amd as rr
+    w = _workload(mode, n_tx, n_rx, K, 2, 20_000)
+    gpu.setup(w)
+    assert gpu.trace_workload(w, record_hits=False) > 0
+    got = gpu.synthesize(model=rr.EXACT, engine=rr.DIRECT_FP32)
+    _, op = orc.trace(w.scene, w.array, w.trace, want_hits=False)
+    assert rel_err(got.cpu().numpy(), orc.synth(op, w.scene, w.array, w.chirp, model=0)) < 1e-4
+    B = rr.Batch(gpu, 1)
+    B.set_workload(0, w)
+    B.set_engine(0, rr.DIRECT_FP32)
+    cubes = B.alloc_cubes()
+    B.launch(cubes)
+    assert torch.equal(cubes[0], got)
+    B.close()
