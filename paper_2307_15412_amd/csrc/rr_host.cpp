@@ -274,6 +274,24 @@ bool order_pays(int64_t n_per_src, int64_t n_traced, int64_t n_launch)
     return n_per_src >= 4096 && n_launch >= 1 << 18 && n_traced < ((int64_t)1 << 31);
 }
 
+// Pinned host words for the counts that traces and syntheses read back (written
+// by their kernels, read after a synchronisation), made by the first of them:
+// the allocation is 34 of a handle's 58 us, and imaging and the proposal
+// network need none.
+int info_room(rr_ctx *c, int64_t n)
+{
+    if (c->h_info_n >= n) return RR_OK;
+    n = std::max<int64_t>(n, 1024);
+    unsigned long long *p = nullptr;
+    if (hipHostMalloc((void **)&p, 64 + (size_t)n * 4, hipHostMallocDefault) != hipSuccess)
+        return fail(RR_ENOMEM, "hipHostMalloc(%lld) failed", (long long)n * 4 + 64);
+    if (c->h_trace) (void)hipHostFree(c->h_trace);
+    c->h_trace = p;
+    c->h_info = reinterpret_cast<int32_t *>(c->h_trace + 8);
+    c->h_info_n = n;
+    return RR_OK;
+}
+
 // The trace stage of rr_trace / rr_trace_rays: tracing kernels, scan of the
 // per-ray counts, scatter into (ray, bounce) order; grows the temporary
 // buffer and re-runs once if it overflowed.
@@ -284,7 +302,8 @@ template <class Kernels>
 int run_trace(rr_ctx *c, TraceArgs &A, int64_t V, int64_t nb, int64_t n_cells, int64_t path_cap,
               Kernels kernels, int64_t *n_paths_out)
 {
-    int rc;
+    int rc = info_room(c, 1);
+    if (rc) return rc;
     c->paths_pending = false;
     if (!n_paths_out) {
         A.tmp = c->tmp.soa;
@@ -366,21 +385,6 @@ int resolve_paths(rr_ctx *c)
     return RR_OK;
 }
 
-// pinned host words for the counts a synthesis reads back (written by its
-// kernel, read after a synchronisation)
-int info_room(rr_ctx *c, int64_t n)
-{
-    if (c->h_info_n >= n) return RR_OK;
-    unsigned long long *p = nullptr;
-    if (hipHostMalloc((void **)&p, 64 + (size_t)n * 4, hipHostMallocDefault) != hipSuccess)
-        return fail(RR_ENOMEM, "hipHostMalloc(%lld) failed", (long long)n * 4 + 64);
-    if (c->h_trace) (void)hipHostFree(c->h_trace);
-    c->h_trace = p;
-    c->h_info = reinterpret_cast<int32_t *>(c->h_trace + 8);
-    c->h_info_n = n;
-    return RR_OK;
-}
-
 }  // namespace
 
 extern "C" {
@@ -408,8 +412,7 @@ int rr_create(int hip_device, void *hip_stream, rr_ctx **out)
             return fail(RR_EHIP, "hipEventCreate failed");
         }
     }
-    int rc = info_room(c, 1024);
-    if (!rc) rc = c->counter.ensure(256);
+    int rc = c->counter.ensure(256);
     if (!rc) rc = c->total.ensure(256);
     if (!rc) rc = c->err_flag.ensure(256);
     if (rc) {
