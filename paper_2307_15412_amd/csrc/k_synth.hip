@@ -566,6 +566,16 @@ __device__ __forceinline__ const BatchVel &batch_scene(int64_t v, const int64_t 
     return vel[lo];
 }
 
+// Paths of the batched pool that the synthesis stages read: all of them, or
+// none once rays returned more than the pool holds.  The scatter then leaves
+// places of the pool unwritten (whatever path a dropped record belonged to),
+// so every range is empty and the cubes are zero until the host, which sees
+// the same counter, has grown the pool and run the launch again.
+__device__ __forceinline__ int64_t pool_paths(const unsigned long long *total, int64_t cap)
+{
+    return (int64_t)*total <= cap ? (int64_t)*total : 0;
+}
+
 __global__ __launch_bounds__(PREP_T) void k_batch_rest_count(PathSoA P,
                                                              const unsigned long long *total,
                                                              int64_t cap, const int64_t *vr_start,
@@ -573,7 +583,7 @@ __global__ __launch_bounds__(PREP_T) void k_batch_rest_count(PathSoA P,
                                                              uint32_t *bsums)
 {
     const int64_t i = (int64_t)blockIdx.x * PREP_T + threadIdx.x;
-    const int64_t n = min((int64_t)*total, cap);
+    const int64_t n = pool_paths(total, cap);
     bool rest = false;
     if (i < n) rest = at_rest(P, i, batch_scene(P.ray[i], vr_start, S, vel));
     const int c = __syncthreads_count(rest);
@@ -588,7 +598,7 @@ __global__ __launch_bounds__(PREP_T) void k_batch_prep(PathSoA P, const unsigned
                                                        uint32_t *pre, SynPath *out)
 {
     const int64_t i = (int64_t)blockIdx.x * PREP_T + threadIdx.x;
-    const int64_t n = min((int64_t)*total, cap);
+    const int64_t n = pool_paths(total, cap);
     if ((int64_t)blockIdx.x * PREP_T >= n) {
         if (n == 0 && i == 0) pre[0] = 0;
         return;
@@ -613,7 +623,7 @@ __global__ void k_batch_ranges(const uint8_t *counts, const uint32_t *bsums, int
     }
     if (s >= S) return;
     const BatchRangeInfo &R = ri[s];
-    const int64_t tot = min((int64_t)*total, cap);
+    const int64_t tot = pool_paths(total, cap);
     auto put = [&](int g, int64_t v) {
         const int64_t o = min(v < V ? (int64_t)count_prefix(counts, bsums, v) : tot, tot);
         const int64_t r = pre[o];
