@@ -1133,7 +1133,8 @@ static int rr_synth_gemm(rr_ctx *c, const SynthArgs &A, const float2 *rest)
     return RR_OK;
 }
 
-static const int64_t FREQ_TABLE_MAX = (int64_t)16 << 30;   // AUTO's table budget (bytes)
+// table budget (bytes) of AUTO, and of the separable model's moving paths
+static const int64_t FREQ_TABLE_MAX = (int64_t)16 << 30;
 
 // AUTO's estimate of the leg tables: all n paths as if they moved
 static int64_t freq_table_bytes(const rr_ctx *c, int64_t n)
@@ -1176,6 +1177,12 @@ static double gemm_cost(int64_t C, int64_t K, int64_t n)
     const int64_t rp = gemm_row_pad(), ct = gemm_col_tile(), ks = gemm_k_step();
     return (double)((C + rp - 1) / rp * rp) * ((K + ct - 1) / ct * ct) *
            std::max<int64_t>((n + ks - 1) / ks * ks, ks) / 71.0;
+}
+
+// bytes of the moving paths' leg tables
+static int64_t freq_mov_bytes(const FreqPlan &q)
+{
+    return 8 * freq_table_entries(q.T, q.R, q.M, q.p_mov, freq_own_tx(q.tile, q.per_el, true));
 }
 
 // The paths at rest in bands (k_band.hip): for the tile layouts, whose cost is
@@ -1499,15 +1506,26 @@ int rr_synthesize(rr_ctx *c, int32_t model, int32_t engine, void *cube, int64_t 
                    c->box};
         q.tile = freq_tile(q.T, q.R, q.K, q.per_el);
         // the moving paths of the separable model: the GEMM, where its padding
-        // (256 channels, 64 samples, 96 paths) leaves it the cheaper engine
-        const bool gemm = model == RR_SEPARABLE && M > 1 &&
-                          gemm_cost(q.T * q.R, q.K, n_mov) < freq_cost(q, n_mov);
+        // (256 channels, 64 samples, 96 paths) leaves it the cheaper engine or
+        // the leg tables of every chirp, which its operands do without, would
+        // pass the budget (1 x 60 channels, 256 chirps, 3e5 moving paths: 37 GB
+        // against 2.2) or do not fit the card
+        bool gemm = model == RR_SEPARABLE && M > 1 &&
+                    (gemm_cost(q.T * q.R, q.K, n_mov) < freq_cost(q, n_mov) ||
+                     freq_mov_bytes(q) > FREQ_TABLE_MAX);
         if (M == 1 || gemm) q.p_mov = 0;
         if (c->fq.classes.size() >= 16) {
             HIPCHK(hipStreamSynchronize(c->stream));
             c->fq.drop_classes();
         }
-        if ((rc = freq_ensure(c->fq, q, c->stream))) return rc;
+        rc = freq_ensure(c->fq, q, c->stream);
+        if (rc == RR_ENOMEM && model == RR_SEPARABLE && q.p_mov) {
+            (void)hipGetLastError();
+            gemm = true;
+            q.p_mov = 0;
+            rc = freq_ensure(c->fq, q, c->stream);
+        }
+        if (rc) return rc;
         if ((rc = freq_rest(c->fq, q, A, c->stream))) return rc;
         if (gemm) {
             SynthArgs G = A;
