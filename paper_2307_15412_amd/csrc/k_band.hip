@@ -163,13 +163,9 @@ __global__ __launch_bounds__(512) void k_band_plan(BandArgs A)
             lo = min(lo, e.x);
             hi = max(hi, e.y);
         }
-    // a band costs its sums' expansion, about 1 700 path x four-node products
-    // of 3 072 channels (0.5 us): fewer paths than this are cheaper at every
-    // sample
-    const int thin = 48;
     int cls = -1;
     unsigned gamma = 0u;
-    if (b < RR_BANDS && cnt >= thin) {
+    if (b < RR_BANDS && cnt >= BAND_THIN) {
         const double l = __uint_as_float(lo), h = __uint_as_float(hi);
         const double z = M_PI * (A.K - 1) / A.K * 0.5 * (h - l) * A.bins_per_m;
         for (int q = A.cls.count - 1; q >= 0; q--)

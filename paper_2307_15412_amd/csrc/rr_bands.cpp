@@ -44,6 +44,14 @@ long double sinc_l(long double x)
 }
 }  // namespace
 
+int rr_band_nodes(int K)
+{
+    int n = 0;
+    for (int q = 0; q < N_CLASS; q++)
+        if (K >= 5 * CLASS_N[q]) n = CLASS_N[q];
+    return n;
+}
+
 BandClasses rr_band_classes(int K, std::vector<int32_t> &nodes, std::vector<float> &coef)
 {
     BandClasses c{};

@@ -1155,6 +1155,7 @@ struct FreqPlan {
     int T, R, M, K, tile, per_el;
     int64_t p_rest, p_mov;
     const double *box;         // least and greatest coordinates of the Tx, then of the Rx
+    bool bands;                // the paths at rest in bands (freq_bands, and there is room)
 };
 
 static int64_t freq_pad(int64_t n)
@@ -1185,27 +1186,25 @@ static int64_t freq_mov_bytes(const FreqPlan &q)
     return 8 * freq_table_entries(q.T, q.R, q.M, q.p_mov, freq_own_tx(q.tile, q.per_el, true));
 }
 
-// The paths at rest in bands (k_band.hip): for the tile layouts, whose cost is
-// per sample (the sample split already shares its phasors among sqrt(K)
-// samples, and its launches are small), where K takes the smallest class.
-static bool freq_bands(const FreqPlan &q) { return !q.per_el && q.tile >= 16 && q.K >= 40; }
-
-// room of a band plan of at most n nodes a band: work items (chunks of paths x four nodes) for about three rounds of the
+// room of a band plan: work items (chunks of paths x four nodes) for about three rounds of the
 // chip's workgroups (six: the hand's products take the same 2.0 ms and their
-// partial sums 91 instead of 43 us)
+// partial sums 91 instead of 43 us), and a short last chunk of every list that
+// p_rest paths can make (a band takes BAND_THIN)
 struct BandRoom {
     int target;
-    int64_t items, perm, blocks;
+    int64_t items, perm, blocks, part;
     size_t o_hist, o_extent, o_perm, o_plan, o_segs, bytes;
 };
-static BandRoom band_room(const FreqPlan &q, int n)
+static BandRoom band_room(const FreqPlan &q)
 {
     BandRoom r;
     const int64_t tiles = (int64_t)((q.T + q.tile - 1) / q.tile) * ((q.R + q.tile - 1) / q.tile);
     r.target = (int)std::max<int64_t>(32, 3 * freq_band_fit(q.tile) / tiles);
-    r.items = r.target + RR_BANDS * (n / 4) + (q.K + 3) / 4;
+    r.items = r.target + std::min<int64_t>(RR_BANDS, q.p_rest / BAND_THIN) * (rr_band_nodes(q.K) / 4) +
+              (q.K + 3) / 4;
     r.perm = q.p_rest + 32 * (RR_BANDS + 1);
     r.blocks = band_blocks(q.p_rest);
+    r.part = r.items * 4 * q.T * q.R * 8;
     auto up = [](size_t n) { return (n + 255) & ~size_t(255); };
     r.o_hist = up((size_t)q.p_rest * 2);
     r.o_extent = r.o_hist + up((size_t)r.blocks * (RR_BANDS + 1) * 4);
@@ -1214,6 +1213,22 @@ static BandRoom band_room(const FreqPlan &q, int n)
     r.o_segs = r.o_plan + up(sizeof(BandPlan));
     r.bytes = r.o_segs + up((size_t)r.items * sizeof(BandSeg));
     return r;
+}
+
+// The paths at rest in bands (k_band.hip): for the tile layouts, whose cost is
+// per sample (the sample split already shares its phasors among sqrt(K)
+// samples, and its launches are small), where K takes the smallest class, and
+// where the partial sums of a plan of every band keep to a budget, which a
+// 256 x 256 array of 128 samples does (3.5 GB) and one of 1024 x 1024, which
+// needs 54 GB beside a chirp of 1.1, does not.  By the shape alone, so that a
+// batch and a single launch decide alike.
+static const int64_t BAND_PART_MAX = (int64_t)4 << 30;
+static bool freq_bands(const FreqPlan &q)
+{
+    if (q.per_el || q.tile < 16 || q.K < 40) return false;
+    FreqPlan all = q;
+    all.p_rest = (int64_t)RR_BANDS * BAND_THIN;
+    return band_room(all).part <= BAND_PART_MAX;
 }
 
 // node classes of K samples (built on the host the first time; a handle keeps
@@ -1241,28 +1256,29 @@ static int band_classes(FreqBufs &b, int K, hipStream_t st, BandClasses &out)
     return RR_OK;
 }
 
-// grow the buffers to a plan's needs
-static int freq_ensure(FreqBufs &b, const FreqPlan &q, hipStream_t st)
+// bytes of a plan's buffers
+struct FreqBytes {
+    size_t xt, yt, part, pp, band, rest;
+    int64_t sum() const { return (int64_t)(xt + yt + part + 2 * pp + band + rest); }
+};
+static FreqBytes freq_bytes(const FreqPlan &q)
 {
     const int64_t C = (int64_t)q.T * q.R;
-    size_t xt = 0, yt = 0, part = 0;
+    FreqBytes n{};
     auto need = [&](int tile, int M, int64_t P) {
         const bool own = freq_own_tx(tile, q.per_el, true);
-        xt = std::max(xt, (size_t)M * (own ? 1 : q.T) * P * 8);
-        yt = std::max(yt, (size_t)M * q.R * P * 8);
-        part = std::max(part, (size_t)freq_partial(tile, q.T, q.R, M, q.K));
+        n.xt = std::max(n.xt, (size_t)M * (own ? 1 : q.T) * P * 8);
+        n.yt = std::max(n.yt, (size_t)M * q.R * P * 8);
+        n.part = std::max(n.part, (size_t)freq_partial(tile, q.T, q.R, M, q.K));
     };
     int64_t p_rest = q.p_rest;
-    int rc;
-    if (freq_bands(q)) {
-        BandClasses cls;
-        if ((rc = band_classes(b, q.K, st, cls))) return rc;
-        const BandRoom r = band_room(q, cls.n[cls.count - 1]);
+    if (q.bands) {
+        const BandRoom r = band_room(q);
         p_rest = r.perm;
-        xt = (size_t)q.T * p_rest * 8;
-        yt = (size_t)q.R * p_rest * 8;
-        part = (size_t)r.items * 4 * C * 8;
-        if ((rc = b.band.ensure(r.bytes))) return rc;
+        n.xt = (size_t)q.T * p_rest * 8;
+        n.yt = (size_t)q.R * p_rest * 8;
+        n.part = (size_t)r.part;
+        n.band = r.bytes;
     } else {
         need(q.tile, 1, q.p_rest);
     }
@@ -1270,11 +1286,28 @@ static int freq_ensure(FreqBufs &b, const FreqPlan &q, hipStream_t st)
         need(q.tile, q.M, q.p_mov);
         need(freq_mov_tile(q.tile, q.K, q.per_el), q.M, q.p_mov);
     }
-    const size_t pp = (size_t)std::max(p_rest, q.p_mov) * 4;
-    if ((rc = b.xt.ensure(xt)) || (rc = b.yt.ensure(yt)) || (rc = b.amp.ensure(pp)) ||
-        (rc = b.src.ensure(pp)) || (part && (rc = b.part.ensure(part))))
-        return rc;
-    return q.M > 1 ? b.rest.ensure((size_t)C * q.K * 8) : RR_OK;
+    n.pp = (size_t)std::max(p_rest, q.p_mov) * 4;
+    n.rest = q.M > 1 ? (size_t)C * q.K * 8 : 0;
+    return n;
+}
+
+// grow the buffers to a plan's needs; a plan whose bands do not fit the card
+// takes its paths at rest at every sample
+static int freq_ensure(FreqBufs &b, FreqPlan &q, hipStream_t st)
+{
+    int rc;
+    do {
+        const FreqBytes n = freq_bytes(q);
+        BandClasses cls;
+        rc = q.bands ? band_classes(b, q.K, st, cls) : RR_OK;
+        if (!rc && !(rc = b.xt.ensure(n.xt)) && !(rc = b.yt.ensure(n.yt)) && !(rc = b.amp.ensure(n.pp)) &&
+            !(rc = b.src.ensure(n.pp)) && !(n.part && (rc = b.part.ensure(n.part))) &&
+            !(n.band && (rc = b.band.ensure(n.band))) && !(n.rest && (rc = b.rest.ensure(n.rest))))
+            return RR_OK;
+        if (rc != RR_ENOMEM || !q.bands) return rc;
+        (void)hipGetLastError();
+        q.bands = false;
+    } while (true);
 }
 
 // Sum over one part of the records (paths at rest: one chirp) on a layout,
@@ -1340,7 +1373,7 @@ static int freq_rest(const FreqBufs &b, const FreqPlan &q, const SynthArgs &A, h
     const int n_rng = q.per_el ? q.T : 1;
     float2 *out = q.M > 1 ? b.rest.as<float2>() : A.cube;
     FreqLegs L = leg_args(q, A, 1, A.ranges, n_rng);
-    if (!freq_bands(q)) {
+    if (!q.bands) {
         HIPCHK(freq_legs(b, q, L, q.tile, q.p_rest, st));
         HIPCHK(launch_freq_gemm(sum_args(b, q, q.tile, 1, q.p_rest, A.ranges, n_rng, out), st));
         return RR_OK;
@@ -1349,7 +1382,7 @@ static int freq_rest(const FreqBufs &b, const FreqPlan &q, const SynthArgs &A, h
     for (const auto &x : b.classes)
         if (x.K == q.K) cl = &x;
     if (!cl) return fail(RR_ESTATE, "node classes of %d samples missing", q.K);
-    const BandRoom r = band_room(q, cl->cls.n[cl->cls.count - 1]);
+    const BandRoom r = band_room(q);
     char *w = b.band.as<char>();
     BandArgs B{};
     B.plan = reinterpret_cast<BandPlan *>(w + r.o_plan);
@@ -1503,8 +1536,9 @@ int rr_synthesize(rr_ctx *c, int32_t model, int32_t engine, void *cube, int64_t 
     if (engine == RR_GEMM_BF16X3 || engine == RR_GEMM_EXACT) {
         HIPCHK(hipEventRecord(c->ev[2], c->stream));
         FreqPlan q{c->ntx, c->nrx, (int)M, (int)K, 0, !shared, freq_pad(n_rest), freq_pad(n_mov),
-                   c->box};
+                   c->box, false};
         q.tile = freq_tile(q.T, q.R, q.K, q.per_el);
+        q.bands = freq_bands(q);
         // the moving paths of the separable model: the GEMM, where its padding
         // (256 channels, 64 samples, 96 paths) leaves it the cheaper engine or
         // the leg tables of every chirp, which its operands do without, would
@@ -1523,6 +1557,7 @@ int rr_synthesize(rr_ctx *c, int32_t model, int32_t engine, void *cube, int64_t 
             (void)hipGetLastError();
             gemm = true;
             q.p_mov = 0;
+            q.bands = freq_bands(q);
             rc = freq_ensure(c->fq, q, c->stream);
         }
         if (rc) return rc;
@@ -2118,6 +2153,7 @@ struct BatchScene {
     int tile = 0;                         // exact engine: product tile
     int64_t fq_cap = 0;                   // exact engine: leg table capacity (paths)
     int64_t fq_ppad = 0;                  // exact engine: table stride of the graph
+    bool fq_bands = false;                // exact engine: paths at rest in bands
     int lane = 0;                         // exact engine: its stream and tables
     int64_t n_last = -1;                  // path count of the last launch
     void release()
@@ -2136,8 +2172,8 @@ int largest_kr(int K, int limit)
 
 }  // namespace
 
-// Most lanes of a batch's exact engine, and the leg tables they may hold in
-// all: a scene's ten kernels are too small to fill the chip one at a time
+// Most lanes of a batch's exact engine, and the bytes of tables and partial
+// sums they may hold in all: a scene's ten kernels are too small to fill the chip one at a time
 #define RR_BATCH_LANES 4
 const int64_t BATCH_LANE_TABLES = (int64_t)4 << 30;
 
@@ -2237,7 +2273,7 @@ void batch_plan(BatchScene &x)
 FreqPlan batch_freq_plan(const BatchScene &x)
 {
     return FreqPlan{x.ntx, x.nrx, x.chirp.n_chirps, x.chirp.n_samples, x.tile, x.mode != RR_TX_SHARED,
-                    x.fq_ppad, x.chirp.n_chirps > 1 ? x.fq_ppad : 0, x.box};
+                    x.fq_ppad, x.chirp.n_chirps > 1 ? x.fq_ppad : 0, x.box, x.fq_bands};
 }
 
 // the exact engine's lanes: each scene in the one with the least product work
@@ -2248,9 +2284,10 @@ int batch_lanes(rr_batch *b)
     int64_t table = 1;
     int n = 0;
     for (int s = 0; s < b->S; s++) {
-        const BatchScene &x = b->sc[s];
+        BatchScene &x = b->sc[s];
         if (!x.use_freq || !b->synth_on[s]) continue;
-        table = std::max(table, batch_freq_bytes(x, x.fq_ppad, x.tile));
+        x.fq_bands = freq_bands(batch_freq_plan(x));
+        table = std::max(table, freq_bytes(batch_freq_plan(x)).sum());
         n++;
     }
     b->lanes = (int)std::max<int64_t>(1, std::min<int64_t>({RR_BATCH_LANES, n, BATCH_LANE_TABLES / table}));
@@ -2276,7 +2313,10 @@ int batch_lanes(rr_batch *b)
             if (!x.use_freq || !b->synth_on[s]) continue;
             x.lane = (int)(std::min_element(work, work + b->lanes) - work);
             work[x.lane] += (double)x.ntx * x.nrx * x.chirp.n_samples;
-            rc = freq_ensure(b->fq[x.lane], batch_freq_plan(x), b->st);
+            x.fq_bands = freq_bands(batch_freq_plan(x));
+            FreqPlan q = batch_freq_plan(x);
+            rc = freq_ensure(b->fq[x.lane], q, b->st);
+            x.fq_bands = q.bands;
         }
         if (!rc || b->lanes == 1) return rc;
         (void)hipGetLastError();

@@ -340,7 +340,11 @@ struct BandClasses {
     int32_t coef[RR_BAND_CLASSES];
 };
 BandClasses rr_band_classes(int K, std::vector<int32_t> &nodes, std::vector<float> &coef);
+int rr_band_nodes(int K);     // nodes of the largest class of K samples (0: none)
 #define RR_BANDS 256          // bands (k_band.hip); longer paths go to the last list
+// A band costs its sums' expansion, about 1 700 path x four-node products of
+// 3 072 channels (0.5 us): fewer paths than this are cheaper at every sample.
+#define BAND_THIN 48
 // back-projection on the matrix cores: the volume, array and sweep; a plan
 // (blocks of voxels per axis, workgroups per block, n nodes of class cls, or
 // cls = -1: every sample over the whole volume) with the bytes of its slices
@@ -380,8 +384,8 @@ struct BandPlan {
     int32_t base[RR_BANDS + 1];
     BandOut out[RR_BANDS + 1];
 };
-// the paths at rest of a shared launch in bands; at most `target` +
-// RR_BANDS n / 4 + K / 4 + 1 work items (n the largest class; as many
+// the paths at rest of a shared launch in bands; at most `target` + B n / 4
+// + K / 4 + 1 work items (B bands, n nodes of the largest class; as many
 // segments), four partial sums each
 struct BandArgs {
     FreqLegs L;               // one chirp
