@@ -282,10 +282,10 @@ __device__ __forceinline__ void rest_tile(const SynthArgs &A, int item, RestLds 
     }
 }
 
-__global__ __launch_bounds__(REST_T) void k_synth_rest(SynthArgs A)
+__global__ __launch_bounds__(REST_T) void k_synth_rest(SynthArgs A, int item0)
 {
     __shared__ RestLds L;
-    rest_tile(A, blockIdx.x, L);
+    rest_tile(A, item0 + blockIdx.x, L);
 }
 
 template <int KR>
@@ -758,7 +758,10 @@ hipError_t launch_synth_direct(const SynthArgs &a, int n_groups, int rows_per_gr
     int kr = 32;
     while (kr > 1 && a.K % kr != 0) kr >>= 1;
     if (a.K / kr > SYN_T) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_synth_rest, dim3((unsigned)rest_items(a.K, a.ntx * a.nrx)), dim3(REST_T), 0, s, a);
+    // a launch holds fewer than 2^32 threads: 2^22 channels at a time
+    const int64_t items = rest_items(a.K, a.ntx * a.nrx), step = (int64_t)1 << 22;
+    for (int64_t i = 0; i < items; i += step)
+        hipLaunchKernelGGL(k_synth_rest, dim3((unsigned)std::min(step, items - i)), dim3(REST_T), 0, s, a, (int)i);
     if (a.M <= 1) return hipGetLastError();
     for (int m0 = 1; m0 >= 0; m0--) {
         const int rows = m0 ? rows_per_group - RC : RC;

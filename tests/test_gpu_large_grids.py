@@ -1,0 +1,46 @@
+"""Calls whose launches would pass 2^32 threads where a channel takes a
+workgroup: the direct engine's paths at rest at 2^23 channels and more.  Bars:
+the engines' own."""
+import numpy as np
+import pytest
+import torch
+
+import scenegen as sg
+from helpers import oracle_to_soa, rel_err
+
+pytestmark = pytest.mark.gpu
+
+
+def _array(n_tx, n_rx, rng, mode=sg.MODE_SHARED):
+    n = n_tx + n_rx
+    pos = np.array([0.0, 0.0, 0.5]) + np.stack([np.zeros(n), rng.uniform(-0.2, 0.2, n), rng.uniform(-0.2, 0.2, n)],
+                                               axis=1)
+    return sg.Array(pos[:n_tx], pos[n_tx:], 0.25, mode).checked()
+
+
+@pytest.mark.parametrize("engine,n_tx,n_rx,K,M", [("direct", 2900, 2900, 2, 1), ("direct", 2896, 2897, 1, 2)])
+def test_rows(orc, engine, n_tx, n_rx, K, M):
+    import paper_2307_15412_amd as rr
+    rng = np.random.default_rng(n_rx)
+    w = sg.workload_tiny(6)
+    w.scene.obj_vel = np.array([[0.0, 0.0, 0.0], [5.0, -2.0, 0.5]])
+    w.array = _array(n_tx, n_rx, rng)
+    w.chirp = sg.Chirp(n_samples=K, n_chirps=M)
+    w.trace.n_rays = 20_000
+    _, op = orc.trace(w.scene, w.array, w.trace, want_hits=False)
+    op = op[:40].copy()
+    op["vid"][::4, 0] = 1
+    ctx = rr.Context(0)
+    try:
+        ctx.setup(w)
+        ctx.set_paths({k: torch.from_numpy(np.ascontiguousarray(v)) for k, v in oracle_to_soa(op).items()})
+        eng = rr.DIRECT_FP32 if engine == "direct" else rr.GEMM_EXACT
+        cube = torch.full((n_tx * n_rx, M, K), float("nan"), dtype=torch.complex64, device="cuda:0")
+        ctx.synthesize(model=rr.EXACT, engine=eng, out=cube)
+        flat = cube.reshape(-1)
+        idx = np.concatenate([rng.choice(flat.numel(), 800, replace=False), [0, flat.numel() - 1]])
+        ref = orc.synth(op, w.scene, w.array, w.chirp, model=0, idx=idx)
+        assert rel_err(flat[torch.from_numpy(idx).cuda()].cpu().numpy(), ref) < 1e-4
+        assert not torch.isnan(torch.view_as_real(cube)).any()
+    finally:
+        ctx.close()
