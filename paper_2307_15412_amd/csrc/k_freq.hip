@@ -939,9 +939,10 @@ int64_t freq_partial(int tile, int T, int R, int M, int K)
     return most;
 }
 
-int freq_mov_tile(int tile, int K, bool per_element)
+int freq_mov_tile(int tile, int T, int R, int M, int K, bool per_element)
 {
-    return !per_element && K <= FQ_KS_KMAX ? 1 : tile;
+    // a wavefront a row: a launch holds fewer than 2^32 threads
+    return !per_element && K <= FQ_KS_KMAX && (int64_t)T * R * M < (int64_t)1 << 26 ? 1 : tile;
 }
 
 hipError_t launch_freq_gemm(const FreqSum &q, hipStream_t s)

@@ -1158,6 +1158,11 @@ struct FreqPlan {
     bool bands;                // the paths at rest in bands (freq_bands, and there is room)
 };
 
+static int freq_mov_tile(const FreqPlan &q)
+{
+    return freq_mov_tile(q.tile, q.T, q.R, q.M, q.K, q.per_el);
+}
+
 static int64_t freq_pad(int64_t n)
 {
     const int64_t ks = freq_k_step();
@@ -1169,7 +1174,7 @@ static int64_t freq_pad(int64_t n)
 // on one MI355X; the GEMM's 71 over its padded sizes)
 static double freq_cost(const FreqPlan &q, int64_t n)
 {
-    const int few = freq_mov_tile(q.tile, q.K, q.per_el);
+    const int few = freq_mov_tile(q);
     return (double)freq_pad(n) *
            freq_tile_cost(q.T, q.R, q.K, n <= FREQ_MOV_KS ? few : q.tile, q.per_el);
 }
@@ -1284,7 +1289,7 @@ static FreqBytes freq_bytes(const FreqPlan &q)
     }
     if (q.p_mov) {
         need(q.tile, q.M, q.p_mov);
-        need(freq_mov_tile(q.tile, q.K, q.per_el), q.M, q.p_mov);
+        need(freq_mov_tile(q), q.M, q.p_mov);
     }
     n.pp = (size_t)std::max(p_rest, q.p_mov) * 4;
     n.rest = q.M > 1 ? (size_t)C * q.K * 8 : 0;
@@ -1421,7 +1426,7 @@ static int freq_moving(const FreqBufs &b, const FreqPlan &q, const SynthArgs &A,
                        hipStream_t st)
 {
     const int n_rng = q.per_el ? q.T : 1;
-    const int few = freq_mov_tile(q.tile, q.K, q.per_el);   // same tables as q.tile's
+    const int few = freq_mov_tile(q);   // same tables as q.tile's
     HIPCHK(freq_legs(b, q, leg_args(q, A, q.M, A.mranges, n_rng), q.tile, q.p_mov, st));
     const int64_t gate = few == q.tile ? INT64_MAX : FREQ_MOV_KS;
     for (int tile : {few, q.tile}) {

@@ -1,6 +1,7 @@
 """Calls whose launches would pass 2^32 threads where a channel takes a
-workgroup: the direct engine's paths at rest at 2^23 channels and more.  Bars:
-the engines' own."""
+workgroup or a row (channel and chirp) a wavefront: the direct engine's paths
+at rest at 2^23 channels and more, the product engine's few moving paths at
+2^26 rows and more.  Bars: the engines' own."""
 import numpy as np
 import pytest
 import torch
@@ -18,7 +19,8 @@ def _array(n_tx, n_rx, rng, mode=sg.MODE_SHARED):
     return sg.Array(pos[:n_tx], pos[n_tx:], 0.25, mode).checked()
 
 
-@pytest.mark.parametrize("engine,n_tx,n_rx,K,M", [("direct", 2900, 2900, 2, 1), ("direct", 2896, 2897, 1, 2)])
+@pytest.mark.parametrize("engine,n_tx,n_rx,K,M", [("direct", 2900, 2900, 2, 1), ("direct", 2896, 2897, 1, 2),
+                                                  ("product", 512, 512, 2, 257)])
 def test_rows(orc, engine, n_tx, n_rx, K, M):
     import paper_2307_15412_amd as rr
     rng = np.random.default_rng(n_rx)
