@@ -496,7 +496,9 @@ BpPlan bp_plan(const BpGrid &G, const BandClasses &cls)
             big *= (G.n[a] + p.nb[a] - 1) / p.nb[a];
         }
         p.wgs = (int)((big + BG_W * BG_VW - 1) / (BG_W * BG_VW));
-        if (blocks * p.wgs > 2147483647.0 || blocks * p.n * TB * RS * 4096.0 > 4.0 * (1u << 30)) continue;
+        // fewer than 2^32 threads a launch, at most 4 GiB of slices
+        if (blocks * p.wgs * (BG_W * 64) >= 4294967296.0 || blocks * p.n * TB * RS * 4096.0 > 4.0 * (1u << 30))
+            continue;
         const double t = blocks * p.wgs * BG_W * BG_VW * p.n * rate * rounds(blocks * p.wgs) +
                          blocks * C * G.K * (2.0 * p.n + 16.0) * 2.6e-8 + blocks * C * p.n * 2e-6 + 15.0;
         if (t < cost) {

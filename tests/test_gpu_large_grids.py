@@ -1,7 +1,8 @@
 """Calls whose launches would pass 2^32 threads where a channel takes a
 workgroup or a row (channel and chirp) a wavefront: the direct engine's paths
 at rest at 2^23 channels and more, the product engine's few moving paths at
-2^26 rows and more.  Bars: the engines' own."""
+2^26 rows and more; an image just below 2^30 voxels on the matrix cores, whose
+blocks round up past that.  Bars: the engines' own."""
 import numpy as np
 import pytest
 import torch
@@ -44,5 +45,31 @@ def test_rows(orc, engine, n_tx, n_rx, K, M):
         ref = orc.synth(op, w.scene, w.array, w.chirp, model=0, idx=idx)
         assert rel_err(flat[torch.from_numpy(idx).cuda()].cpu().numpy(), ref) < 1e-4
         assert not torch.isnan(torch.view_as_real(cube)).any()
+    finally:
+        ctx.close()
+
+
+def test_image(orc):
+    import paper_2307_15412_amd as rr
+    rng = np.random.default_rng(3)
+    pos = lambda n: np.stack([np.zeros(n), rng.uniform(-0.02, 0.02, n), rng.uniform(-0.02, 0.02, n)], 1)
+    array = sg.Array(pos(2), pos(2), 0.07, sg.MODE_SHARED).checked()
+    chirp = sg.chirp_sfcw(n_steps=40)
+    dims, step = (1023, 1024, 1024), 2.8e-4
+    grid = ((0.25, -step * 512, -step * 512), step, dims)
+    z = rng.standard_normal((4, 1, 40, 2)).astype(np.float32)
+    cube = torch.view_as_complex(torch.from_numpy(z)).cuda()
+    ctx = rr.Context(0)
+    try:
+        ctx.set_array(array.tx, array.rx, array.rx_radius, array.mode)
+        ctx.set_chirp(chirp.f0, chirp.bandwidth, chirp.t_chirp, chirp.t_rep, 40, 1)
+        image = torch.full(dims, float("nan"), dtype=torch.complex64, device="cuda:0")
+        ctx.backproject(cube, grid, out=image, engine=rr.GEMM_EXACT)
+        sel = np.concatenate([rng.choice(image.numel(), 400, replace=False), [0, image.numel() - 1]])
+        i, j, k = np.unravel_index(sel, dims)
+        vox = np.stack([grid[0][0] + i * step, grid[0][1] + j * step, grid[0][2] + k * step], -1)
+        want = orc.backproject(array, chirp.f0, chirp.bandwidth / 40, cube.cpu().numpy(), vox)
+        got = image.reshape(-1)[torch.from_numpy(sel).cuda()].cpu().numpy()
+        assert np.abs(got - want).max() <= 1e-4 * np.abs(want).max()
     finally:
         ctx.close()
