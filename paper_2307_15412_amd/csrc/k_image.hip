@@ -10,6 +10,8 @@
 //     S = (...((s_{K-1} w + s_{K-2}) w + s_{K-3}) ...) w + s_0,
 // four fused multiply-adds per term, and the channel adds exp(+j 2 pi f0 d/c) S.
 // The cube is staged through LDS in chunks of channels and read as broadcasts.
+#include <algorithm>
+
 #include "rr_internal.h"
 
 namespace {
@@ -118,12 +120,12 @@ __global__ __launch_bounds__(BP_T) void k_backproject(BackProjArgs A)
 // flight, and one atomic of the workgroup goes to the peak (81 x 201 x 201
 // voxels: 13 us; a lane per pixel with an atomic each 39).  The largest
 // square's root is the largest root.
-__global__ __launch_bounds__(256) void k_max_projection(const float2 *img, int64_t nx, int64_t nyz,
+__global__ __launch_bounds__(256) void k_max_projection(const float2 *img, int64_t nx, int64_t nyz, int64_t p0,
                                                         float *out, float *peak)
 {
     __shared__ float part[4][64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int64_t p = (int64_t)blockIdx.x * 64 + lane;
+    const int64_t p = p0 + (int64_t)blockIdx.x * 64 + lane;
     const int64_t per = (nx + 3) / 4, lo = w * per, hi = min(nx, lo + per);
     float m = 0.0f;
     if (p < nyz) {
@@ -168,7 +170,11 @@ hipError_t launch_max_projection(const float2 *img, int64_t nx, int64_t nyz, flo
 {
     if (nyz <= 0) return hipSuccess;
     const unsigned blocks = (unsigned)((nyz + 255) / 256);
-    hipLaunchKernelGGL(k_max_projection, dim3((unsigned)((nyz + 63) / 64)), dim3(256), 0, s, img, nx, nyz, out, peak);
+    // fewer than 2^32 threads a launch: 2^29 pixels at a time
+    const int64_t step = (int64_t)1 << 29;
+    for (int64_t p0 = 0; p0 < nyz; p0 += step)
+        hipLaunchKernelGGL(k_max_projection, dim3((unsigned)((std::min(step, nyz - p0) + 63) / 64)), dim3(256), 0, s,
+                           img, nx, nyz, p0, out, peak);
     hipLaunchKernelGGL(k_to_db, dim3(blocks), dim3(256), 0, s, out, nyz, peak, floor_db);
     return hipGetLastError();
 }

@@ -2,7 +2,8 @@
 workgroup or a row (channel and chirp) a wavefront: the direct engine's paths
 at rest at 2^23 channels and more, the product engine's few moving paths at
 2^26 rows and more; an image just below 2^30 voxels on the matrix cores, whose
-blocks round up past that.  Bars: the engines' own."""
+blocks round up past that, and a projection of 2^30 pixels, a wavefront a
+pixel's quarter.  Bars: the engines' own."""
 import numpy as np
 import pytest
 import torch
@@ -71,5 +72,22 @@ def test_image(orc):
         want = orc.backproject(array, chirp.f0, chirp.bandwidth / 40, cube.cpu().numpy(), vox)
         got = image.reshape(-1)[torch.from_numpy(sel).cuda()].cpu().numpy()
         assert np.abs(got - want).max() <= 1e-4 * np.abs(want).max()
+    finally:
+        ctx.close()
+
+
+def test_projection():
+    import paper_2307_15412_amd as rr
+    side = 1 << 15
+    image = torch.zeros((1, side, side), dtype=torch.complex64, device="cuda:0")
+    flat = image.reshape(-1)
+    at = torch.tensor([5, 1 << 29, (1 << 30) - 1], device="cuda:0")
+    flat[at] = torch.tensor([0.5, 1.0j, -0.8], dtype=torch.complex64, device="cuda:0")
+    ctx = rr.Context(0)
+    try:
+        out = ctx.max_projection(image, ((0.3, 0.0, 0.0), 1e-6, (1, side, side)), floor_db=-60.0).reshape(-1)
+        want = 20.0 * np.log10([0.5, 1.0, 0.8])
+        assert np.abs(out[at].cpu().numpy() - want).max() < 1e-5
+        assert float(out.min()) == -60.0 and int((out > -60.0).sum()) == 3
     finally:
         ctx.close()
