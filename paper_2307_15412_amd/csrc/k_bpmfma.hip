@@ -33,12 +33,13 @@
 // array on 17 x 41 x 39 voxels at 33 samples 0.169 -> 0.061 ms by its smaller
 // tile alone.
 //
-// Leg lengths are formed in FP64 once per voxel and kept in FP32.  At every
-// sample the phase is their FP32 product with f_n / c (below 256 turns in an
-// imaging volume of a few tens of centimetres, good to ~1e-5 turn); at nodes,
-// whose few roundings would not average out, it is their phase at the middle
-// frequency, reduced in FP64, plus the few turns from there.  The hardware
-// sin/cos take turns.
+// Leg lengths are formed in FP64 once per voxel and rounded to FP32, from where
+// every phase starts (below 256 turns in an imaging volume of a few tens of
+// centimetres: the rounding is worth up to 7.6e-6 turn).  At every sample the
+// phase is the FP32 product of the rounded leg with f_n / c, good to ~1e-5
+// turn; at nodes, whose few roundings of that product would not average out,
+// it is the rounded leg's phase at the middle frequency, reduced in FP64, plus
+// the few turns from there.  The hardware sin/cos take turns.
 #include <algorithm>
 #include <cmath>
 
@@ -121,14 +122,20 @@ __device__ __forceinline__ double dist3(double x, double y, double z, const doub
 
 __device__ __forceinline__ double frac(double x) { return x - floor(x); }
 
-// sqrt(v) to ~1e-14: the FP32 root and one Newton step in FP64 (a third of the
-// instructions of the correctly rounded one, which with 188 legs a voxel took
-// a tenth of the kernel at 12 nodes); 0 at 0
-__device__ __forceinline__ double fast_sqrt(double v)
+// sqrt(v) by the FP32 root and two Newton steps in FP64: the first leaves up to
+// 4e-14, the second, with the residual formed exactly, what its own rounding
+// leaves (2e8 values against the correctly rounded root, with the FP32 root
+// and reciprocal each up to a unit off: 862 differ, by one FP64 unit, and no
+// leg after its rounding to FP32; after one step 10 legs).  188 legs a voxel are a
+// tenth of the kernel at 12 nodes: the hand's image takes 8.17 ms with the
+// full root, 7.91 with this one.  0 at 0.
+__device__ __forceinline__ double leg_sqrt(double v)
 {
     const float s = __builtin_amdgcn_sqrtf((float)v);
-    const double d = (double)s;
-    return d + (v - d * d) * (double)(s > 0.0f ? 0.5f * __builtin_amdgcn_rcpf(s) : 0.0f);
+    const double h = (double)(s > 0.0f ? 0.5f * __builtin_amdgcn_rcpf(s) : 0.0f);
+    double d = (double)s;
+    d = fma(fma(-d, d, v), h, d);
+    return fma(fma(-d, d, v), h, d);
 }
 
 // the voxels of an axis in block b of nb: [at, end), sizes differing by one
@@ -286,7 +293,7 @@ __global__ __launch_bounds__(BG_W * 64, TB * RS == 2 ? 4 : 2) void k_bp_mfma(BpM
     __syncthreads();
     auto leg = [&](const double *e, float &d, float &turns) {
         const double ax = x - e[0], ay = y - e[1], az = z - e[2];
-        d = (float)fast_sqrt(ax * ax + ay * ay + az * az);
+        d = (float)leg_sqrt(ax * ax + ay * ay + az * az);
         const double u = (double)d * fmid;
         turns = (float)(u - rint(u));
     };
