@@ -502,8 +502,9 @@ int rr_batch_set_alpha(rr_batch *batch, int32_t slot, const float *alpha, int64_
 int rr_batch_launch(rr_batch *batch, void *const *cubes, int64_t *n_paths_out);
 
 /* Autotune the synthesis: run the batch once into `cubes` for its paths,
- * then, over at most the first 2048 paths of each path group (synthesis time
- * is linear in the path count): for every distinct sample count time each
+ * then, over those paths (of the paths at rest and of the moving ones as many
+ * as take the direct engine some 50 ms each, at least 2048 of every group):
+ * for every distinct sample count time each
  * candidate samples-per-lane value of the direct engine on the scenes with
  * that count and keep the fastest; then per scene left to RR_ENGINE_AUTO
  * time the direct engine against the product engine at every layout (the

@@ -115,7 +115,7 @@ __device__ void synth_block(const SynthArgs &A, int g, int rb, int rows_per_grou
 #pragma unroll
     for (int k = 0; k < KR; k++) { are[k] = 0.0f; aim[k] = 0.0f; }
     const int64_t p0 = A.mranges[g];
-    const int64_t p1 = A.p_limit > 0 ? min(A.mranges[g + 1], p0 + A.p_limit) : A.mranges[g + 1];
+    const int64_t p1 = A.mov_limit > 0 ? min(A.mranges[g + 1], p0 + A.mov_limit) : A.mranges[g + 1];
     const int chunk = min(SYN_CHUNK, SYN_TAB / RPB);
     for (int64_t base = p0; base < p1; base += chunk) {
         const int cnt = (int)min((int64_t)chunk, p1 - base);
@@ -204,7 +204,7 @@ __device__ void rest_block(const SynthArgs &A, int c, int part, int TPR, RestLds
     const double tx[3] = {A.tx[3 * t], A.tx[3 * t + 1], A.tx[3 * t + 2]};
     const double rx[3] = {A.rx[3 * r], A.rx[3 * r + 1], A.rx[3 * r + 2]};
     const int64_t p0 = A.ranges[g];
-    const int64_t p1 = A.p_limit > 0 ? min(A.ranges[g + 1], p0 + A.p_limit) : A.ranges[g + 1];
+    const int64_t p1 = A.rest_limit > 0 ? min(A.ranges[g + 1], p0 + A.rest_limit) : A.ranges[g + 1];
     float are[KR], aim[KR];
 #pragma unroll
     for (int k = 0; k < KR; k++) { are[k] = 0.0f; aim[k] = 0.0f; }

@@ -2135,6 +2135,12 @@ int rr_proposal_build_cost(rr_ctx *c, const float *code16, float beta, float kap
 
 namespace {
 
+// What the autotuner times of one part of a scene's paths: so many of each
+// transmitter group, so many in all (0: every path).
+struct TunePart {
+    int64_t limit = 0, paths = 0;
+};
+
 struct BatchScene {
     bool set = false;
     int64_t n_tris = 0;
@@ -2159,6 +2165,7 @@ struct BatchScene {
     int64_t fq_cap = 0;                   // exact engine: leg table capacity (paths)
     int64_t fq_ppad = 0;                  // exact engine: table stride of the graph
     bool fq_bands = false;                // exact engine: paths at rest in bands
+    TunePart tune_rest, tune_mov;
     int lane = 0;                         // exact engine: its stream and tables
     int64_t n_last = -1;                  // path count of the last launch
     void release()
@@ -2249,8 +2256,9 @@ void batch_plan(BatchScene &x)
     const int64_t est = x.n_src * x.n_per_src / 16 + x.n_src * x.npts;
     const int64_t want = x.n_last >= 0 ? x.n_last + x.n_last / 4 + 1024 : est;
     // start from the estimate; follow the last launch's count down when the
-    // capacity is more than twice what it needs (growth comes from overflow)
-    if (x.fq_cap <= 0 || x.fq_cap > 2 * want) x.fq_cap = want;
+    // capacity is more than twice what it needs, and up when it holds fewer
+    // (a scene on the other engine outgrows it unseen)
+    if (x.fq_cap <= 0 || x.fq_cap > 2 * want || x.fq_cap < x.n_last) x.fq_cap = want;
     x.fq_cap = std::max<int64_t>((x.fq_cap + ks - 1) / ks * ks, ks);
     int eng = x.req_engine, tile = x.req_tile;
     if (x.try_engine >= 0) {
@@ -2277,8 +2285,9 @@ void batch_plan(BatchScene &x)
 
 FreqPlan batch_freq_plan(const BatchScene &x)
 {
+    auto room = [&](const TunePart &t) { return t.paths ? std::min(x.fq_ppad, freq_pad(t.paths)) : x.fq_ppad; };
     return FreqPlan{x.ntx, x.nrx, x.chirp.n_chirps, x.chirp.n_samples, x.tile, x.mode != RR_TX_SHARED,
-                    x.fq_ppad, x.chirp.n_chirps > 1 ? x.fq_ppad : 0, x.box, x.fq_bands};
+                    room(x.tune_rest), x.chirp.n_chirps > 1 ? room(x.tune_mov) : 0, x.box, x.fq_bands};
 }
 
 // the exact engine's lanes: each scene in the one with the least product work
@@ -2332,9 +2341,9 @@ int batch_lanes(rr_batch *b)
 
 // per-scene tables and global buffers for the current scene set and cubes;
 // only_K > 0 gives synthesis work to the scenes with that sample count alone,
-// only_scene >= 0 to that scene alone, and p_limit > 0 caps the paths of each
-// group (all three for the autotuner's timing)
-int batch_prepare(rr_batch *b, int only_K = 0, int64_t p_limit = 0, int only_scene = -1)
+// only_scene >= 0 to that scene alone (both for the autotuner's timing, which
+// may also limit the scenes' paths: tune_rest, tune_mov)
+int batch_prepare(rr_batch *b, int only_K = 0, int only_scene = -1)
 {
     const int S = b->S;
     std::vector<TraceArgs> ta(S);
@@ -2469,14 +2478,9 @@ int batch_prepare(rr_batch *b, int only_K = 0, int64_t p_limit = 0, int only_sce
         }
         b->h_out_n = b->n_ranges + 2;
     }
-    // exact engine: per scene the table stride (capacity, or the timing cap);
-    // the last graph is dropped whenever its plan is prepared anew
-    for (int s = 0; s < S; s++) {
-        BatchScene &x = b->sc[s];
-        if (!x.use_freq || !b->synth_on[s]) continue;
-        x.fq_ppad = x.fq_cap;
-        if (p_limit > 0) x.fq_ppad = std::min<int64_t>(x.fq_ppad, freq_pad(p_limit));
-    }
+    // exact engine: per scene the table stride (capacity); the last graph is
+    // dropped whenever its plan is prepared anew
+    for (BatchScene &x : b->sc) x.fq_ppad = x.fq_cap;
     if ((rc = batch_lanes(b))) return rc;
     const double INV_2PI = 0.15915494309189535;
     for (int s = 0; s < S; s++) {
@@ -2541,7 +2545,8 @@ int batch_prepare(rr_batch *b, int only_K = 0, int64_t p_limit = 0, int only_sce
         Y.M = x.chirp.n_chirps;
         Y.K = x.chirp.n_samples;
         Y.cube = static_cast<float2 *>(s < (int)b->cubes.size() ? b->cubes[s] : nullptr);
-        Y.p_limit = p_limit;
+        Y.rest_limit = x.tune_rest.limit;
+        Y.mov_limit = x.tune_mov.limit;
         vel[s].obj_vel = x.obj_vel.as<const double>();
         vel[s].pt_vel = x.pt_vel.as<const double>();
         vel[s].nobj = x.nobj;
@@ -2881,8 +2886,43 @@ int rr_batch_launch(rr_batch *b, void *const *cubes, int64_t *n_paths_out)
     return RR_OK;
 }
 
-// paths per group timed for each tile candidate
+// What a candidate of the autotuner is timed on: all the paths of the last
+// launch, at rest and moving, up to about this much work of the direct engine
+// for each of the two (path-samples, some 50 ms), at least 2048 paths of every
+// group.  A launch costs less than that either way, and a shorter prefix would
+// not tell the engines apart: their costs that do not depend on the paths
+// (band plan and expansion, both moving layouts, three passes over the cube),
+// and bands too thin to be taken, would decide (32 x 32 channels, 128 samples,
+// 2e5 paths at rest: a launch tuned on 2048 paths took 7.1 ms, on all 0.70).
+static const double TUNE_WORK = 4e11;
 static const int64_t TUNE_PATHS = 2048;
+
+// the limits of every scene, from the ranges of the last launch's paths
+static int tune_limits(rr_batch *b)
+{
+    std::vector<int64_t> r(2 * b->n_ranges);
+    HIPCHK(hipMemcpyAsync(r.data(), b->d_ranges.p, r.size() * 8, hipMemcpyDeviceToHost, b->st));
+    HIPCHK(hipStreamSynchronize(b->st));
+    for (int s = 0; s < b->S; s++) {
+        BatchScene &x = b->sc[s];
+        const int64_t groups = b->range_base[s + 1] - b->range_base[s] - 1;
+        for (int part = 0; part < 2; part++) {
+            const int64_t *g = r.data() + part * b->n_ranges + b->range_base[s];
+            const double per = (double)x.ntx * x.nrx * x.chirp.n_samples * (part ? x.chirp.n_chirps : 1);
+            TunePart t;
+            t.limit = std::max<int64_t>(TUNE_PATHS, (int64_t)(TUNE_WORK / per));
+            int64_t most = 0;
+            for (int64_t k = 0; k < groups; k++) {
+                const int64_t n = g[k + 1] - g[k];
+                most = std::max(most, n);
+                t.paths += std::min(n, t.limit);
+            }
+            if (most <= t.limit) t = TunePart{};
+            (part ? x.tune_mov : x.tune_rest) = t;
+        }
+    }
+    return RR_OK;
+}
 
 int rr_batch_tune(rr_batch *b, void *const *cubes)
 {
@@ -2892,12 +2932,14 @@ int rr_batch_tune(rr_batch *b, void *const *cubes)
     std::vector<int> Ks;
     for (auto &x : b->sc)
         if (std::find(Ks.begin(), Ks.end(), x.chirp.n_samples) == Ks.end()) Ks.push_back(x.chirp.n_samples);
-    // the candidates run eagerly on a bounded prefix of the paths of the last
-    // launch (time is linear in the path count)
+    if ((rc = tune_limits(b))) return rc;
+    // the candidates run eagerly on the paths of the last launch; timed is a
+    // second run (the first loads kernels)
     auto time_synth = [&](int only_K, int only_scene, float *ms) -> int {
-        int r = batch_prepare(b, only_K, TUNE_PATHS, only_scene);
+        int r = batch_prepare(b, only_K, only_scene);
         if (r) return r;
-        if ((r = batch_enqueue_synth(b, true))) return r;
+        for (int rep = 0; rep < 2; rep++)
+            if ((r = batch_enqueue_synth(b, true))) return r;
         HIPCHK(hipStreamSynchronize(b->st));
         HIPCHK(hipEventElapsedTime(ms, b->ev[2], b->ev[3]));
         return RR_OK;
@@ -2946,7 +2988,13 @@ int rr_batch_tune(rr_batch *b, void *const *cubes)
                 x.try_engine = RR_GEMM_EXACT;
                 x.try_tile = tile;
                 float ms = 0.0f;
-                if ((rc = time_synth(0, s, &ms))) break;
+                rc = time_synth(0, s, &ms);
+                if (rc == RR_ENOMEM) {           // a layout that does not fit is none
+                    (void)hipGetLastError();
+                    rc = RR_OK;
+                    continue;
+                }
+                if (rc) break;
                 if (ms * 1.1f + 0.02f < best_ms) {
                     best_ms = ms;
                     best_eng = RR_GEMM_EXACT;
@@ -2957,7 +3005,10 @@ int rr_batch_tune(rr_batch *b, void *const *cubes)
         x.tuned_engine = best_eng;
         x.tuned_tile = best_tile;
     }
-    for (auto &x : b->sc) x.try_engine = -1;
+    for (auto &x : b->sc) {
+        x.try_engine = -1;
+        x.tune_rest = x.tune_mov = TunePart{};
+    }
     batch_drop_graph(b);
     return rc;
 }

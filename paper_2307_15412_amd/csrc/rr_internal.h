@@ -161,7 +161,9 @@ struct SynthArgs {
     double f0, bw, t_rep, inv_c;
     int M, K;
     float2 *cube;
-    int64_t p_limit;          // > 0: at most this many paths of each group (tile timing only)
+// > 0: at most this many paths of each group, at rest and moving (the
+    // autotuner's timings of large scenes)
+    int64_t rest_limit, mov_limit;
 };
 
 // back-projection (imaging): one single-sweep cube onto a voxel grid
