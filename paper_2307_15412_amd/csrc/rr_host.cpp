@@ -222,7 +222,8 @@ struct rr_ctx {
     // synthesis scratch
     DevBuf syn;                 // records, the groups' ranges in both parts, prefix, block counts
     unsigned long long *h_trace = nullptr;   // pinned: records and error flag of the last trace
-    int32_t *h_info = nullptr;  // pinned, behind h_trace: first and last source, counts at rest per block
+    int32_t *h_info = nullptr;  // pinned: first and last source, counts at rest per block
+    int32_t *h_info_own = nullptr;   // its own allocation, when it is not behind h_trace
     int64_t h_info_n = 0;
     DevBuf gT, gR, gA, gB;     // GEMM operands
 
@@ -277,17 +278,27 @@ bool order_pays(int64_t n_per_src, int64_t n_traced, int64_t n_launch)
 // Pinned host words for the counts that traces and syntheses read back (written
 // by their kernels, read after a synchronisation), made by the first of them:
 // the allocation is 34 of a handle's 58 us, and imaging and the proposal
-// network need none.
+// network need none.  The trace's words stay where they are until the handle
+// goes (a captured trace writes to them); a synthesis of many paths takes
+// words of its own.
+#define INFO_WORDS 1024
 int info_room(rr_ctx *c, int64_t n)
 {
     if (c->h_info_n >= n) return RR_OK;
-    n = std::max<int64_t>(n, 1024);
-    unsigned long long *p = nullptr;
-    if (hipHostMalloc((void **)&p, 64 + (size_t)n * 4, hipHostMallocDefault) != hipSuccess)
-        return fail(RR_ENOMEM, "hipHostMalloc(%lld) failed", (long long)n * 4 + 64);
-    if (c->h_trace) (void)hipHostFree(c->h_trace);
-    c->h_trace = p;
-    c->h_info = reinterpret_cast<int32_t *>(c->h_trace + 8);
+    if (!c->h_trace) {
+        if (hipHostMalloc((void **)&c->h_trace, 64 + INFO_WORDS * 4, hipHostMallocDefault) != hipSuccess) {
+            c->h_trace = nullptr;
+            return fail(RR_ENOMEM, "hipHostMalloc(%d) failed", 64 + INFO_WORDS * 4);
+        }
+        c->h_info = reinterpret_cast<int32_t *>(c->h_trace + 8);
+        c->h_info_n = INFO_WORDS;
+        if (c->h_info_n >= n) return RR_OK;
+    }
+    int32_t *p = nullptr;
+    if (hipHostMalloc((void **)&p, (size_t)n * 4, hipHostMallocDefault) != hipSuccess)
+        return fail(RR_ENOMEM, "hipHostMalloc(%lld) failed", (long long)n * 4);
+    if (c->h_info_own) (void)hipHostFree(c->h_info_own);
+    c->h_info = c->h_info_own = p;
     c->h_info_n = n;
     return RR_OK;
 }
@@ -442,6 +453,7 @@ void rr_destroy(rr_ctx *c)
     for (DevBuf *b : bufs) b->release();
     c->fq.release();
     if (c->h_trace) (void)hipHostFree(c->h_trace);
+    if (c->h_info_own) (void)hipHostFree(c->h_info_own);
     for (auto &e : c->ev)
         if (e) (void)hipEventDestroy(e);
     delete c;
