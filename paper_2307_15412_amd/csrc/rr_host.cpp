@@ -1248,9 +1248,22 @@ static bool freq_bands(const FreqPlan &q)
     return band_room(all).part <= BAND_PART_MAX;
 }
 
-// node classes of K samples (built on the host the first time; a handle keeps
-// those of its last 16 sample counts, a batch has them dropped between its
-// preparations)
+// A handle keeps the node classes of 16 sample counts: a new one beyond them
+// drops them all, one of them leaves them alone (and waits for nothing: a
+// captured image reads them).
+static int class_room(FreqBufs &b, int K, hipStream_t st)
+{
+    for (const auto &x : b.classes)
+        if (x.K == K) return RR_OK;
+    if (b.classes.size() >= 16) {
+        HIPCHK(hipStreamSynchronize(st));
+        b.drop_classes();
+    }
+    return RR_OK;
+}
+
+// node classes of K samples (built on the host the first time; a batch has
+// them dropped between its preparations)
 static int band_classes(FreqBufs &b, int K, hipStream_t st, BandClasses &out)
 {
     for (const auto &x : b.classes)
@@ -1565,10 +1578,7 @@ int rr_synthesize(rr_ctx *c, int32_t model, int32_t engine, void *cube, int64_t 
                     (gemm_cost(q.T * q.R, q.K, n_mov) < freq_cost(q, n_mov) ||
                      freq_mov_bytes(q) > FREQ_TABLE_MAX);
         if (M == 1 || gemm) q.p_mov = 0;
-        if (c->fq.classes.size() >= 16) {
-            HIPCHK(hipStreamSynchronize(c->stream));
-            c->fq.drop_classes();
-        }
+        if (q.bands && (rc = class_room(c->fq, q.K, c->stream))) return rc;
         rc = freq_ensure(c->fq, q, c->stream);
         if (rc == RR_ENOMEM && model == RR_SEPARABLE && q.p_mov) {
             (void)hipGetLastError();
@@ -1787,10 +1797,7 @@ int rr_backproject(rr_ctx *c, const void *cube, int64_t cube_elems, const rr_vol
         int rc;
         BandClasses cls{};
         if (K >= 40) {
-            if (c->fq.classes.size() >= 16) {
-                HIPCHK(hipStreamSynchronize(c->stream));
-                c->fq.drop_classes();
-            }
+            if ((rc = class_room(c->fq, (int)K, c->stream))) return rc;
             if ((rc = band_classes(c->fq, (int)K, c->stream, cls))) return rc;
         }
         const BpPlan P = bp_plan(G, cls);
