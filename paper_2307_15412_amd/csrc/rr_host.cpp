@@ -243,6 +243,7 @@ struct rr_ctx {
     FreqBufs fq;               // exact product engine
     DevBuf order_cells, order_rc, order_first, order_idx;   // coherent ray order of a trace
     DevBuf bp_sf;              // cube slices in fragment layout (MFMA back-projection)
+    std::vector<DevBuf> bp_old;      // its smaller predecessors (slice_room)
     std::vector<double> h_tx, h_rx;
     std::vector<int64_t> refit_levels;   // starts of the levels in refit_order, deepest first
     std::vector<int32_t> h_tris;
@@ -451,6 +452,7 @@ void rr_destroy(rr_ctx *c)
                       &c->refit_order, &c->ubox,
                       &c->order_cells, &c->order_rc, &c->order_first, &c->order_idx, &c->bp_sf};
     for (DevBuf *b : bufs) b->release();
+    for (DevBuf &b : c->bp_old) b.release();
     c->fq.release();
     if (c->h_trace) (void)hipHostFree(c->h_trace);
     if (c->h_info_own) (void)hipHostFree(c->h_info_own);
@@ -1248,17 +1250,34 @@ static bool freq_bands(const FreqPlan &q)
     return band_room(all).part <= BAND_PART_MAX;
 }
 
-// A handle keeps the node classes of 16 sample counts: a new one beyond them
-// drops them all, one of them leaves them alone (and waits for nothing: a
-// captured image reads them).
+// A handle keeps the node classes of its sample counts up to 64 MB (72 KB at
+// 128 samples, 0.6 MB at 1024): a new one beyond them drops them all, one of
+// them leaves them alone and waits for nothing (captured images read them).
 static int class_room(FreqBufs &b, int K, hipStream_t st)
 {
-    for (const auto &x : b.classes)
+    size_t bytes = 0;
+    for (const auto &x : b.classes) {
         if (x.K == K) return RR_OK;
-    if (b.classes.size() >= 16) {
+        bytes += x.tab.bytes;
+    }
+    if (bytes > (size_t)64 << 20) {
         HIPCHK(hipStreamSynchronize(st));
         b.drop_classes();
     }
+    return RR_OK;
+}
+
+// Room for n bytes of an image's slices.  They follow the volume, so a larger
+// image must not free those that a captured one of the same sweep writes and
+// reads: the smaller buffer is kept until the handle goes, and growth by half
+// at least keeps all of them together below three times the largest.
+static int slice_room(rr_ctx *c, size_t n)
+{
+    if (n <= c->bp_sf.bytes && c->bp_sf.p) return RR_OK;
+    DevBuf b;
+    if (int rc = b.ensure(std::max(n, c->bp_sf.bytes + c->bp_sf.bytes / 2))) return rc;
+    if (c->bp_sf.p) c->bp_old.push_back(c->bp_sf);
+    c->bp_sf = b;
     return RR_OK;
 }
 
@@ -1810,7 +1829,7 @@ int rr_backproject(rr_ctx *c, const void *cube, int64_t cube_elems, const rr_vol
                     coef = reinterpret_cast<const float *>(x.tab.as<const int32_t>() + cls.count * RR_BAND_NMAX) +
                            cls.coef[P.cls];
                 }
-        if ((rc = c->bp_sf.ensure((size_t)(P.frag_bytes + P.turn_bytes)))) return rc;
+        if ((rc = slice_room(c, (size_t)(P.frag_bytes + P.turn_bytes)))) return rc;
         HIPCHK(launch_bp_mfma(G, P, A.cube, A.stride, A.tx, A.rx, nodes, coef,
                               reinterpret_cast<float2 *>(c->bp_sf.as<char>() + P.frag_bytes),
                               c->bp_sf.as<uint4>(), A.image, c->stream));

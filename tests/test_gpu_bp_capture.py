@@ -1,6 +1,7 @@
-"""An image captured on a handle that holds the nodes of as many sample counts
-as it keeps (16): a sample count among them is captured without a wait, and
-every replay, with eager work between, equals the eager image bit for bit."""
+"""An image captured on a handle that holds the nodes of 16 sample counts: one of
+them is captured without a wait, and every replay equals the eager image bit
+for bit, also after eager images of larger volumes and of other sample counts
+on the same handle (the captured image's slices and node tables stay)."""
 import numpy as np
 import pytest
 import torch
@@ -32,7 +33,12 @@ def test_capture_among_sixteen():
             graph = torch.cuda.CUDAGraph()
             with torch.cuda.graph(graph, stream=stream, capture_error_mode="thread_local"):
                 ctx.backproject(cube, grid, out=image, engine=rr.GEMM_EXACT)
-            for rep in range(3):
+            for rep, (K, dims) in enumerate([(40, (50, 51, 49)), (40, (90, 80, 80)), (90, (60, 60, 60)),
+                                             (57, (20, 20, 20)), (39, (30, 30, 30))]):
+                c = sg.chirp_sfcw(n_steps=K)
+                ctx.set_chirp(c.f0, c.bandwidth, c.t_chirp, c.t_rep, K, 1)
+                other = torch.ones((800, 1, K), dtype=torch.complex64, device="cuda")
+                ctx.backproject(other, (grid[0], 1e-3, dims), engine=rr.GEMM_EXACT)
                 image.fill_(float("nan"))
                 graph.replay()
                 torch.randn(256, 256, device="cuda").matmul(torch.randn(256, 256, device="cuda"))
