@@ -290,12 +290,12 @@ __global__ __launch_bounds__(REST_T) void k_synth_rest(SynthArgs A, int item0)
 
 template <int KR>
 __global__ __launch_bounds__(SYN_T) void k_synth_direct(SynthArgs A, int rows_per_group, int RC,
-                                                        int blocks_per_group, int m0)
+                                                        unsigned blocks_per_group, int m0, unsigned block0)
 {
     __shared__ SynPath sp[SYN_CHUNK];
     __shared__ uint2 tab[SYN_TAB];
-    const int g = blockIdx.x / blocks_per_group;
-    synth_block<KR>(A, g, blockIdx.x - g * blocks_per_group, rows_per_group, RC, m0, sp, tab);
+    const unsigned b = block0 + blockIdx.x, g = b / blocks_per_group;
+    synth_block<KR>(A, (int)g, (int)(b - g * blocks_per_group), rows_per_group, RC, m0, sp, tab);
 }
 
 // the next item of a persistent kernel: the same in every lane, kept in
@@ -744,10 +744,12 @@ static hipError_t launch_kr(const SynthArgs &a, int n_groups, int rows_per_group
     const int TPR = a.K / KR;
     const int RPB = SYN_T / TPR;
     const int bpg = (rows_per_group + RPB - 1) / RPB;
-    const int64_t blocks = (int64_t)bpg * n_groups;
-    if (blocks <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_synth_direct<KR>, dim3((unsigned)blocks), dim3(SYN_T), 0, s, a,
-                       rows_per_group, RC, bpg, m0);
+    // a launch holds fewer than 2^32 threads
+    const int64_t blocks = (int64_t)bpg * n_groups, step = (int64_t)1 << 23;
+    if (blocks >= (int64_t)1 << 32) return hipErrorInvalidValue;
+    for (int64_t b = 0; b < blocks; b += step)
+        hipLaunchKernelGGL(k_synth_direct<KR>, dim3((unsigned)std::min(step, blocks - b)), dim3(SYN_T), 0, s, a,
+                           rows_per_group, RC, (unsigned)bpg, m0, (unsigned)b);
     return hipGetLastError();
 }
 

@@ -91,3 +91,34 @@ def test_projection():
         assert float(out.min()) == -60.0 and int((out > -60.0).sum()) == 3
     finally:
         ctx.close()
+
+
+def test_samples(orc):
+    """The direct engine at 2^32 lanes and more: three samples, a lane each, of
+    1.4e9 rows (some paths at rest, some moving)."""
+    import paper_2307_15412_amd as rr
+    rng = np.random.default_rng(8)
+    M = 350_000
+    w = sg.workload_tiny(6)
+    w.scene.obj_vel = np.array([[0.0, 0.0, 0.0], [0.5, -0.2, 0.0]])
+    w.array = _array(64, 64, rng)
+    w.chirp = sg.Chirp(n_samples=3, n_chirps=M, t_rep=1e-6)
+    w.trace.n_rays = 20_000
+    _, op = orc.trace(w.scene, w.array, w.trace, want_hits=False)
+    op = op[:12].copy()
+    op["vid"][::4, 0] = 1
+    ctx = rr.Context(0)
+    try:
+        ctx.setup(w)
+        ctx.set_paths({k: torch.from_numpy(np.ascontiguousarray(v)) for k, v in oracle_to_soa(op).items()})
+        cube = torch.full((4096, M, 3), float("nan"), dtype=torch.complex64, device="cuda:0")
+        assert cube.numel() > 1 << 32
+        ctx.synthesize(model=rr.EXACT, engine=rr.DIRECT_FP32, out=cube)
+        flat = cube.reshape(-1)
+        idx = np.concatenate([rng.integers(0, flat.numel(), 800), [0, flat.numel() - 1]])
+        ref = orc.synth(op, w.scene, w.array, w.chirp, model=0, idx=idx)
+        assert rel_err(flat[torch.from_numpy(idx).cuda()].cpu().numpy(), ref) < 1e-4
+        for part in torch.view_as_real(cube).split(256):
+            assert not torch.isnan(part).any()
+    finally:
+        ctx.close()
