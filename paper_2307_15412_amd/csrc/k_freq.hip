@@ -279,7 +279,7 @@ struct FreqArgs {
     const float *amp;
     const int32_t *src;
     int T, R, M, K;
-    int m0, m_all;            // chirps m0 .. m0 + M - 1 of m_all (tile layouts; else all)
+    int m0, m_all;            // chirps m0 .. m0 + M - 1 of m_all (the sample split's pointers start there)
     int64_t Ppad;
     int tt, rt;               // Tx and Rx tiles
     int kg;                   // groups of FQ_G samples
@@ -708,7 +708,7 @@ __global__ __launch_bounds__(FQ_G * 64, (!PER_EL && QB * SB == 1) ? 3 : 2) void 
                     A.out[(((int64_t)s * C + c) * A.M + m) * A.K + k] = v;
                 } else {
                     const float2 b = A.rest ? A.rest[(int64_t)c * A.K + k] : make_float2(0.0f, 0.0f);
-                    A.out[((int64_t)c * A.M + m) * A.K + k] = make_float2(v.x + b.x, v.y + b.y);
+                    A.out[((int64_t)c * A.m_all + m) * A.K + k] = make_float2(v.x + b.x, v.y + b.y);
                 }
             }
 }
@@ -920,10 +920,12 @@ int freq_splits(int tile, int T, int R, int M, int K)
 
 // Chirps of one launch: the tile layouts' products of several chirps are
 // partial sums [m][k][channel] that the reduction turns into the cube's order,
-// about 128 MiB of them at a time (they stay in the last-level cache).
+// about 128 MiB of them at a time (they stay in the last-level cache).  The
+// sample split takes a wavefront a row: fewer than 2^32 threads a launch.
 int freq_chirps(int tile, int T, int R, int M, int K)
 {
-    if (tile == 1 || M == 1) return M;
+    if (M == 1) return M;
+    if (tile == 1) return (int)std::min<int64_t>(M, std::max<int64_t>(1, (((int64_t)1 << 26) - FQ_G) / ((int64_t)T * R)));
     return (int)std::min<int64_t>(M, std::max<int64_t>(1, ((int64_t)1 << 27) / ((int64_t)T * R * K * 8)));
 }
 
@@ -933,16 +935,16 @@ int64_t freq_partial(int tile, int T, int R, int M, int K)
     const int step = freq_chirps(tile, T, R, M, K);
     int64_t most = 0;
     for (int m : {step, M % step}) {
-        const int ns = m ? freq_splits(tile, T, R, m, K) : 0;
+        const int ns = m ? freq_splits(tile, T, R, tile == 1 ? M : m, K) : 0;
         if (ns > 1 || (ns && tile != 1 && M > 1)) most = std::max(most, (int64_t)ns * m * K * T * R * 8);
     }
     return most;
 }
 
-int freq_mov_tile(int tile, int T, int R, int M, int K, bool per_element)
+int freq_mov_tile(int tile, int T, int R, int K, bool per_element)
 {
-    // a wavefront a row: a launch holds fewer than 2^32 threads
-    return !per_element && K <= FQ_KS_KMAX && (int64_t)T * R * M < (int64_t)1 << 26 ? 1 : tile;
+    // a wavefront a channel: a launch holds fewer than 2^32 threads
+    return !per_element && K <= FQ_KS_KMAX && (int64_t)T * R <= ((int64_t)1 << 26) - FQ_G ? 1 : tile;
 }
 
 hipError_t launch_freq_gemm(const FreqSum &q, hipStream_t s)
@@ -977,13 +979,20 @@ hipError_t launch_freq_gemm(const FreqSum &q, hipStream_t s)
     const int step = freq_chirps(tile, T, R, M, K);
     for (A.m0 = 0; A.m0 < M; A.m0 += step) {
         A.M = std::min(step, M - A.m0);
-        A.n_split = freq_splits(tile, T, R, A.M, K);
+        A.n_split = freq_splits(tile, T, R, tile == 1 ? M : A.M, K);
         A.partial = A.n_split > 1 || (tile != 1 && q.rest);
         A.out = A.partial ? q.partial : q.cube;
+        if (tile == 1 && A.m0) {
+            // (so many rows are never split: the chunk's tables and cube rows)
+            const int64_t xr = A.groups ? 1 : T;
+            A.xt = q.xt + A.m0 * xr * q.Ppad;
+            A.yt = q.yt + (int64_t)A.m0 * R * q.Ppad;
+            A.out += (int64_t)A.m0 * K;
+        }
         A.n_waves = (int64_t)A.n_split * A.M * T * R;
         const int64_t blocks = tile == 1 ? (A.n_waves + FQ_G - 1) / FQ_G
                                          : (int64_t)A.n_split * A.M * A.tt * A.rt * A.kg;
-        if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+        if (blocks * FQ_G * 64 >= (int64_t)1 << 32) return hipErrorInvalidValue;
         const dim3 g((unsigned)blocks), t(FQ_G * 64);
 #define KS_LAUNCH(QB, SB)                                                                         \
     do {                                                                                          \

@@ -1174,7 +1174,7 @@ struct FreqPlan {
 
 static int freq_mov_tile(const FreqPlan &q)
 {
-    return freq_mov_tile(q.tile, q.T, q.R, q.M, q.K, q.per_el);
+    return freq_mov_tile(q.tile, q.T, q.R, q.K, q.per_el);
 }
 
 static int64_t freq_pad(int64_t n)

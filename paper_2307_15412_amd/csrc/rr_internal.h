@@ -305,7 +305,7 @@ bool freq_pays(int T, int R, int K, bool per_element);
 // FREQ_MOV_KS of them run as the sample split, whose wavefronts write whole
 // runs of samples (the tiles store 8 bytes per channel and sample).
 #define FREQ_MOV_KS 1024
-int freq_mov_tile(int tile, int T, int R, int M, int K, bool per_element);
+int freq_mov_tile(int tile, int T, int R, int K, bool per_element);
 // cube[c][m][k] = rest[c][k] (if given) + the sum over the paths of the
 // tables, whose count is read on the device (*rng_hi - *rng_lo, at most Ppad)
 // and divided evenly over the splits.  groups (may be NULL; per-element

@@ -1,7 +1,8 @@
 """Calls whose launches would pass 2^32 threads where a channel takes a
 workgroup or a row (channel and chirp) a wavefront: the direct engine's paths
-at rest at 2^23 channels and more, the product engine's few moving paths at
-2^26 rows and more; an image just below 2^30 voxels on the matrix cores, whose
+at rest at 2^23 channels and more, the product engine's few moving paths and
+its sample split at 2^26 rows and more (in chunks of chirps, the last a single
+one); an image just below 2^30 voxels on the matrix cores, whose
 blocks round up past that, and a projection of 2^30 pixels, a wavefront a
 pixel's quarter.  Bars: the engines' own."""
 import numpy as np
@@ -22,14 +23,16 @@ def _array(n_tx, n_rx, rng, mode=sg.MODE_SHARED):
 
 
 @pytest.mark.parametrize("engine,n_tx,n_rx,K,M", [("direct", 2900, 2900, 2, 1), ("direct", 2896, 2897, 1, 2),
-                                                  ("product", 512, 512, 2, 257)])
+                                                  ("product", 512, 512, 2, 257),
+                                                  ("product", 4, 4, 24, 4194304),
+                                                  ("product", 512, 512, 2, 256)])
 def test_rows(orc, engine, n_tx, n_rx, K, M):
     import paper_2307_15412_amd as rr
     rng = np.random.default_rng(n_rx)
     w = sg.workload_tiny(6)
     w.scene.obj_vel = np.array([[0.0, 0.0, 0.0], [5.0, -2.0, 0.5]])
     w.array = _array(n_tx, n_rx, rng)
-    w.chirp = sg.Chirp(n_samples=K, n_chirps=M)
+    w.chirp = sg.Chirp(n_samples=K, n_chirps=M, t_rep=1e-6)
     w.trace.n_rays = 20_000
     _, op = orc.trace(w.scene, w.array, w.trace, want_hits=False)
     op = op[:40].copy()
