@@ -600,8 +600,12 @@ def street_trace(ctx, scene, args, reps=None):
     (tracing kernel, scan, scatter), and the tracing kernel's memory roofline
     from the work the counting variant of the kernel reports: BVH nodes
     (64 B) + leaf triangle records (48 B) fetched + one count byte per ray +
-    one appended path record per path.  Then the configuration's exact-model
-    cube from those paths, with AUTO's engine and with the direct engine."""
+    one appended path record per path.  Counted with one bounce fewer, that
+    is without the segment after the last hit: the tracer casts that one only
+    where it passes the receiver's sphere, the counting variant always, so
+    segments and bytes are what the tracer does at least.  Then the
+    configuration's exact-model cube from those paths, with AUTO's engine and
+    with the direct engine."""
     import torch
     import scenegen as sg
     wc = sg.workload_street(0) if scene is None else sg.Workload(
@@ -623,10 +627,12 @@ def street_trace(ctx, scene, args, reps=None):
         stage.append(ctx.kernel_ms(0))
         kern.append(ctx.kernel_ms(3))
     wall = (time.perf_counter() - t0) / reps
-    n2, work = ctx.trace_work(tp.n_rays, tp.max_bounces, tp.seed, tp.az_min, tp.az_max,
-                              tp.el_min, tp.el_max)
+    n2, _ = ctx.trace_work(tp.n_rays, tp.max_bounces, tp.seed, tp.az_min, tp.az_max,
+                           tp.el_min, tp.el_max)
     if n2 != n:
         raise SystemExit(f"counting trace returned {n2} paths, the timed trace {n}")
+    _, work = ctx.trace_work(tp.n_rays, tp.max_bounces - 1, tp.seed, tp.az_min, tp.az_max,
+                             tp.el_min, tp.el_max)
     st, kt = float(np.median(stage)), float(np.median(kern))
     alg = work["nodes"] * 64 + work["tris"] * 48 + work["rays"] + n * TRACE_RECORD_BYTES
     traffic = profiled_traffic("paper_2307_15412_amd/csrc/k_trace.hip", "profiles/k_trace_street.md")
@@ -792,25 +798,29 @@ def main():
     eng_name = "gemm_bf16x3" if engine == rr.GEMM_BF16X3 else "direct_fp32"
     n_mov = moving_paths(ctx, w.scene)
     if sy >= tr:
-        # what the cube cannot do without: a path at rest adds the same to
-        # every chirp (one chirp's multiply-adds), a moving one to each its own
-        kern_flops = (float(P - n_mov) + float(n_mov) * M) * C * K * FLOPS_PER_PATH_SAMPLE
-        ach = kern_flops / (sy * 1e-3) / 1e12
+        cube_bytes = float(C) * M * K * 8
         if engine == rr.GEMM_BF16X3:
-            roof = {"bound": "mfma", "achieved": ach, "peak": BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
+            # what the call cannot do without is the cube's write: the paths at
+            # rest are summed once, at 8 to 32 nodes a band instead of every
+            # sample (how many products that is only the device knows), and
+            # the moving paths' products are few
+            ach = cube_bytes / (sy * 1e-3) / 1e9
+            roof = {"bound": "hbm", "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "traffic": profiled_traffic("paper_2307_15412_amd/csrc/k_gemm.hip",
-                                                "profiles/k_gemm_large_mimo.md")}
+                                                "profiles/k_gemm_large_mimo.md"),
+                    "moving_flops": float(n_mov) * C * M * K * FLOPS_PER_PATH_SAMPLE}
         else:
+            # paths at rest in one chirp, moving ones in every chirp
+            kern_flops = (float(P - n_mov) + float(n_mov) * M) * C * K * FLOPS_PER_PATH_SAMPLE
+            ach = kern_flops / (sy * 1e-3) / 1e12
             roof = {"bound": "alu", "achieved": ach, "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
                     "traffic": profiled_traffic("paper_2307_15412_amd/csrc/k_synth.hip",
-                                                "profiles/k_synth_direct_large_mimo.md")}
+                                                "profiles/k_synth_direct_large_mimo.md"),
+                    "flops_per_launch": kern_flops}
         roof["kernel"] = "synth_" + eng_name
-        roof["flops_per_launch"] = kern_flops
         roof["moving_paths"] = n_mov
-        roof["cube_bytes"] = float(C) * M * K * 8
-        roof["cube_gb_per_s"] = roof["cube_bytes"] / (sy * 1e-3) / 1e9
-        roof["note"] = ("flops: paths at rest once, moving paths per chirp; time: the whole "
-                        "synthesis stage (legs, products at rest and moving, cube)")
+        roof["cube_bytes"] = cube_bytes
+        roof["note"] = "time: the whole synthesis stage (legs, products at rest and moving, cube)"
     else:
         # tracer bytes per segment are counted by the profile; report the rate only
         roof = {"bound": "hbm", "achieved": None, "peak": HBM_PEAK_GBS, "unit": "GB/s",

@@ -186,9 +186,9 @@ typedef struct {
  * rr_synthesize, rr_proposal_histogram) reads it back with one
  * synchronisation; if the paths overflowed the current temporary buffer, that
  * call returns RR_EOVERFLOW, the buffer grows and the trace must be repeated.
- * Uniform and proposal launches of at least 4096 rays per source trace their
- * rays in a coherent order (sorted by source and first-direction cell, which
- * costs n_rays x 6 bytes of device memory); hits, counts and paths are the
+ * Uniform and proposal launches of at least 4096 rays per source and 2^18 in
+ * all trace their rays in a coherent order (sorted by source and
+ * first-direction cell, which costs n_rays x 9 bytes of device memory); hits, counts and paths are the
  * same as in ray order, bit for bit.
  * Errors: RR_ESTATE (no scene or array), RR_EINVAL, RR_ENOMEM, RR_EHIP,
  * RR_EUNSUPPORTED (a BVH deeper than the traversal stack; the builder keeps
@@ -200,7 +200,9 @@ int rr_trace(rr_ctx *ctx, const rr_trace_params *params, int64_t *n_paths_out);
  * tracer's memory roofline (Sec. IV: the tracer's cost grows with the mesh).
  * work_out[0] rays traced (point reflectors excluded), [1] closest-hit
  * queries (segments), [2] BVH nodes fetched (64 B each), [3] leaf triangle
- * records fetched (48 B each).  n_paths_out is required (the call
+ * records fetched (48 B each).  This variant casts every segment; rr_trace
+ * casts the one after a ray's last hit only where it passes the reception
+ * sphere or a hit list is recorded.  n_paths_out is required (the call
  * synchronises).  Errors as rr_trace. */
 int rr_trace_work(rr_ctx *ctx, const rr_trace_params *params, int64_t *n_paths_out,
                   int64_t work_out[4]);
@@ -308,9 +310,10 @@ int rr_set_paths(rr_ctx *ctx, const rr_paths *src, int64_t n);
  *   engine RR_DIRECT_FP32 (either model), RR_GEMM_BF16X3 (separable only:
  *          split-bf16 hi+lo complex products on MFMA, FP32 accumulation;
  *          the moving paths as one complex GEMM where its padding, 256
- *          channels, 64 samples and 96 paths, leaves it the cheaper form;
- *          relative error bar 1e-3), RR_GEMM_EXACT (exact model only, full cube: split-bf16
- *          complex products on the matrix cores of FP64-reduced leg phases,
+ *          channels, 64 samples and 96 paths, leaves it the cheaper form or
+ *          the other form's tables (8 bytes per chirp, path and element)
+ *          would pass 16 GiB; relative error bar 1e-3), RR_GEMM_EXACT
+ *          (exact model only, full cube: split-bf16 complex products on the matrix cores of FP64-reduced leg phases,
  *          held to the exact model's 1e-4 bar; either one (Tx x paths) by
  *          (paths x Rx) product per (chirp, sample) in square tiles of 16,
  *          32, 48, 64 or 96, or, per (channel, chirp), one (k1 x paths) by
@@ -318,7 +321,8 @@ int rr_set_paths(rr_ctx *ctx, const rr_paths *src, int64_t n);
  *          samples); the layout of least modelled time; in the tile layouts
  *          the paths at rest are taken in bands of path length and summed at
  *          8 to 32 nodes a band, from which the samples are interpolated to
- *          2e-7, where a band has paths enough), or
+ *          2e-7, where a band has paths enough and the partial sums of 256
+ *          bands keep to 4 GiB, as up to some 256 x 256 channels do), or
  *          RR_ENGINE_AUTO: the separable model takes RR_GEMM_BF16X3 when the
  *          64-sample tiling pads a chirp by at most a quarter; the exact model
  *          takes RR_GEMM_EXACT when its best layout is modelled at 1.5x
@@ -327,9 +331,10 @@ int rr_set_paths(rr_ctx *ctx, const rr_paths *src, int64_t n);
  *          tiles are modelled at the work they waste, the sample split
  *          reads each transmitter's paths only) and its leg tables (8 bytes
  *          per chirp, path and element; per-element sample split: the
- *          path's own transmitter and every receiver) fit 16 GiB;
- *          everything else, and sampled entries, the direct engine.  AUTO never changes the model, and each engine
- *          it picks meets that model's error bar.
+ *          path's own transmitter and every receiver, as if every path
+ *          moved) fit 16 GiB; everything else, and sampled entries, the
+ *          direct engine.  AUTO never changes the model, and each engine it
+ *          picks meets that model's error bar.
  *   cube_dev complex64 [n_ch][n_chirps][n_samples], cube_elems = its complex
  *          element count; the cube is overwritten.
  *   sample_idx_dev int64 [n_sample] flat entry indices (c*M*K + m*K + k):
@@ -493,7 +498,7 @@ int rr_batch_set_alpha(rr_batch *batch, int32_t slot, const float *alpha, int64_
  * pipeline as a hipGraph; later launches replay it (new cube pointers update
  * a device table, or re-capture when a scene uses the product engine).
  * Scenes on the product engine run in up to four lanes, each with tables of
- * its own (4 GiB in all; one lane beyond that).  The
+ * its own (tables and partial sums 4 GiB in all; one lane beyond that).  The
  * call waits for completion and checks the path pool and the product
  * engine's leg-table capacity of every scene using it (sized from the
  * previous launch's count, else from the ray budget), growing them and

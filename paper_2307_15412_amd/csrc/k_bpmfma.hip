@@ -26,7 +26,7 @@
 // 81 x 201 x 201 voxels of 1 mm in 324 blocks of 23 mm).  The block's slices
 // are formed in FP32 on the vector units (k_bp_block).  The host picks n and
 // the block edge by modelled time; a coarse grid or a short sweep keeps every
-// sample.  Measured: the hand's image 67 -> 7.8 ms (12 nodes; slices 0.4 ms),
+// sample.  Measured: the hand's image 67 -> 7.9 ms (12 nodes; slices 0.4 ms),
 // the products at 1.19 PFLOP/s, where a large bf16 matrix product reaches
 // 1.2-1.4 (the FP64 legs of a voxel and the first slice's load are a fifth of
 // a workgroup's time); a 30 x 37
