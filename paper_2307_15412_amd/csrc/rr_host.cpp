@@ -2886,6 +2886,9 @@ int rr_batch_launch(rr_batch *b, void *const *cubes, int64_t *n_paths_out)
         if (b->dirty || new_cubes) {
             int rc = batch_prepare(b);
             if (rc) return rc;
+            // (a scene that follows the last launch's count to the product
+            // engine: the graph has no kernels for it)
+            if (new_cubes && batch_any_freq(b)) b->dirty = true;
             new_cubes = false;
         }
         if (b->dirty) {
